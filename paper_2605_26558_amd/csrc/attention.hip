@@ -144,7 +144,7 @@ static int launch_attention_group(cas_ctx* ctx, cas_kv* kv, const AttnCall* call
       return CAS_EINVAL;
     AttnSeq& q = b.s[i];
     q.page_row = kv->d_page_table + (size_t)c.seq * g.max_pages_per_seq;
-    q.len = kv->h_len[c.seq];
+    q.len = c.len >= 0 ? c.len : kv->h_len[c.seq];
     q.Q = c.Q; q.ncols = c.ncols;
     q.Knew = c.Knew; q.Vnew = c.Vnew; q.n_new = c.n_new;
     q.qkv = c.qkv; q.slot0 = c.slot0;

@@ -80,17 +80,19 @@ int launch_gemv_draft(cas_ctx*, const cas_wdesc&, const void* spec, const uint16
 int launch_gemv_draft_fused(cas_ctx*, const cas_wdesc&, const void* spec, const uint16_t* x, int batch, float* y,
                             const uint16_t* gain, float eps, int epi, uint16_t* out16);
 int launch_gemm_verify(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X, int ncols, float* Y);
+// wide: the form for the columns of a prompt (any number of them; see wide_shape_ok), same bits
 int launch_gemm_verify_fused(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X,
-                             int ncols, float* Y, int epi, uint16_t* out16);
+                             int ncols, float* Y, int epi, uint16_t* out16, bool wide = false);
+bool gemm_wide_ok(const cas_ctx*, int64_t rows, int64_t cols, int ncols);
 // unary.hip: rows [row0, row0 + nrows) of the raw spec stream (sw words per row) rebuilt from the unary form
 int launch_unary_expand(cas_ctx*, const cas_udesc&, const void* uspec, int64_t row0, int nrows, uint32_t* out);
 int launch_gemm_verify_unary_fused(cas_ctx*, const cas_udesc&, const void* uspec, const void* verif, const uint16_t* X,
-                                   int ncols, float* Y, int epi, uint16_t* out16);
+                                   int ncols, float* Y, int epi, uint16_t* out16, bool wide = false);
 // mx.hip / gemm_verify_mx.hip
 int launch_gemv_draft_mx_fused(cas_ctx*, const cas_mxdesc&, const void* mxspec, const uint16_t* x, float* y,
                                const uint16_t* gain, float eps, int epi, uint16_t* out16);
 int launch_gemm_verify_mx_fused(cas_ctx*, const cas_mxdesc&, const void* mxspec, const void* mxverif, const uint16_t* X,
-                                int ncols, float* Y, int epi, uint16_t* out16);
+                                int ncols, float* Y, int epi, uint16_t* out16, bool wide = false);
 bool mxdesc_ok(const cas_mxdesc*);
 int launch_kv_append(cas_ctx*, cas_kv*, int layer, int seq, const uint16_t* K, const uint16_t* V, int n_tok, int pos0);
 // the same for n_layers consecutive layers in one launch; the vectors of layer layer0 + i start
@@ -100,6 +102,7 @@ int launch_kv_append_layers(cas_ctx*, cas_kv*, int layer0, int n_layers, size_t 
 int launch_kv_read(cas_ctx*, cas_kv*, int layer, int seq, int pos0, int n_tok, int full, uint16_t* K, uint16_t* V);
 struct AttnCall {
   int layer, seq, full;        // full: 0 = speculation data only (draft), 1 = exact reconstruction
+  int len = -1;                // positions read from the cache; -1: the sequence's committed length
   const uint16_t* Q;           // [ncols][n_q_heads][128]
   int ncols, n_q_heads;
   const uint16_t* Knew;        // [n_new][n_kv_heads][128] uncompressed in-flight vectors

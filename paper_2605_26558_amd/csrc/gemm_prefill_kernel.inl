@@ -1,0 +1,284 @@
+// Kernel template and launcher of the wide verification GEMM: the product of the exact matrix with the
+// columns of a long prompt.  The verification GEMM decodes the matrix once per 32 columns at most; here a
+// workgroup decodes 16 RT rows once for 256 columns.  Every output has the bits of the verification GEMM:
+// the parts a row's columns are cut into, the order of the 16-column products within a part and the order
+// in which the parts are added are the same.
+#pragma once
+#include <algorithm>
+#include "gemm_verify_kernel.inl"
+
+namespace cas {
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kWideThreads = 512;
+constexpr int kWideCols = 256;  // columns of X per workgroup
+
+// One workgroup per CU (8 waves of up to 256 registers).  A step takes KB blocks of 128 columns: thread
+// (row r, block, word j) places its 32 values in a tile in LDS, each wave multiplies all rows of the tile
+// with its own columns n and n + 128 of X, which it reads from memory (no other wave of the workgroup needs
+// them).  Two tiles: while one is multiplied the next one is filled, with one barrier per step; the waves
+// w and w + 4, which share a SIMD, take the two halves of a step in opposite order, so that the decode of
+// the one runs under the matrix operations of the other.  Blocks come in the order (part, slab, block of
+// the part), which makes a part one running sum; the counts of kept values in front of every block of
+// every row are made at the start (pre).
+// Bound by the decode (14 lane operations per value and 256 columns) and the 16x16x16 operations (8 K
+// flops in 16 cycles) in about equal parts.
+template <int T, int RT, bool MX>
+__global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a, int Q) {
+  constexpr int ROWS = 16 * RT, KB = 128 / ROWS;
+  static_assert(KB == 2 || KB == 4, "the fragments of X alternate between two sets");
+  constexpr int TILE = KB * ROWS * kTilePitch;  // values of one tile: [block][row][kTilePitch]
+  extern __shared__ uint16_t lds[];
+  uint16_t* pre = lds + 2 * TILE;  // [ROWS][nblk] kept values of the row before each block of 128 columns
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ncb = (a.ncols + kWideCols - 1) / kWideCols;
+  const int cb0 = (int)(blockIdx.x % ncb) * kWideCols, row0 = (int)(blockIdx.x / ncb) * ROWS;
+  const int nblk = (a.bw + 3) >> 2, nslab = (a.bw + 63) >> 6;
+  const int wpl = 16 / Q, per_part = nslab * wpl;  // blocks per part and slab, blocks per part
+  const int nsteps = nslab * 16 / KB;
+
+  // ---- kept values in front of every block
+  {
+    constexpr int RW = ROWS / 8;  // rows per wave
+    uint32_t run[RW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) run[i] = 0;
+    for (int w0 = 0; w0 < a.bw; w0 += 64) {
+      uint32_t m[RW];
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+        const int row = min(row0 + wv * RW + i, a.rows - 1);
+        m[i] = w0 + lane < a.bw ? a.bitmap[(size_t)row * a.bw + w0 + lane] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+        const int cnt = __popc(m[i]), incl = wave_incl_scan(cnt);
+        const int blk = (w0 + lane) >> 2;
+        if ((lane & 3) == 0 && blk < nblk) pre[(wv * RW + i) * nblk + blk] = (uint16_t)(run[i] + (uint32_t)(incl - cnt));
+        run[i] += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+      }
+    }
+    __syncthreads();
+  }
+
+  // first bitmap word of block b in the order of the sums
+  auto block_word = [&](int b) -> int {
+    const int part = b / per_part, rem = b - part * per_part, slab = rem / wpl;
+    return slab * 64 + part * (64 / Q) + 4 * (rem - slab * wpl);
+  };
+
+  // ---- decode role: row r of the tile, block qb of the step (the same for a whole wave), word j of the block
+  const int r = (tid >> 2) & (ROWS - 1), qb = wv * 16 / ROWS, j = lane & 3;
+  const int row = min(row0 + r, a.rows - 1);
+  const uint32_t* bm_row = a.bitmap + (size_t)row * a.bw;
+  const uint32_t* sp_row = a.spec + (size_t)row * a.sw;
+  const uint32_t* lo_row = a.lo + (size_t)row * a.lw;
+  const uint32_t* pr_row = a.pruned + (size_t)row * a.pw;
+  uint16_t* const trow = lds + (qb * ROWS + r) * kTilePitch + j * kGroupPitch + 4;
+  WordWindows<T, true, MX> ww;
+  uint32_t m_next = 0, m_cur = 0;
+  int e_next = 0, e_cur = 0, nvalid = 0;
+  auto load_mask = [&](int st) {
+    m_next = 0;
+    if (st >= nsteps) return;
+    const int w = block_word(st * KB + qb) + j;
+    if (w < a.bw) {
+      m_next = bm_row[w];
+      if constexpr (MX) e_next = (int)a.sexp[(size_t)row * a.ew + w];
+    }
+  };
+  auto issue = [&](int st) {  // windows of the step whose mask came last
+    if (st >= nsteps) return;
+    const int w0 = block_word(st * KB + qb);
+    m_cur = m_next;
+    e_cur = e_next;
+    const int cnt = __popc(m_cur);
+    const int b0 = quad_dpp<0x00>(cnt), b1 = quad_dpp<0x55>(cnt), b2 = quad_dpp<0xAA>(cnt);
+    nvalid = a.cols - (w0 + j) * 32;
+    // words past the end of the row have no fields: keep their (unused) windows in range
+    const uint32_t p = nvalid > 0 ? pre[r * nblk + (w0 >> 2)] + (uint32_t)((j > 0 ? b0 : 0) + (j > 1 ? b1 : 0) + (j > 2 ? b2 : 0)) : 0u;
+    ww.load(p, nvalid > 0 ? (uint32_t)(w0 + j) * 32u - p : 0u, sp_row, lo_row, pr_row);
+  };
+  auto decode = [&](int st) {
+    if (st >= nsteps) return;
+    uint16_t* dst = trow + (st & 1) * TILE;
+    const uint32_t valid = nvalid >= 32 ? 0xFFFFFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
+    if (nvalid < 32) {  // columns past the end are not placed below
+#pragma unroll
+      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(dst + 4 * q) = 0ull;
+    }
+    ww.decode(m_cur, ~m_cur & valid, [&](int pos, uint16_t v) { dst[pos] = v; }, MX ? e_cur : 0);
+    issue(st + 1);
+    load_mask(st + 2);
+  };
+
+  // ---- product role: columns cb0 + 16 wv + mi and 128 further; A[i = lane%16][k = 4*(lane/16)..+3]
+  const int mi = lane & 15, mq = lane >> 4;
+  const bool act0 = cb0 + 16 * wv < a.ncols, act1 = cb0 + 128 + 16 * wv < a.ncols;
+  const int n0 = min(cb0 + 16 * wv + mi, a.ncols - 1), n1 = min(cb0 + 128 + 16 * wv + mi, a.ncols - 1);
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, (int)((int64_t)a.ncols * a.cols * 2), 0x00020000);
+  const int x0 = (n0 * a.cols + 4 * mq) * 2, x1 = (n1 * a.cols + 4 * mq) * 2;
+  f32x4 C[RT][2], S[RT][2];  // running sum of the part, sum of the parts before it
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) C[i][nb] = S[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x2 xa[8][2], xb[8][2];
+  auto load_x = [&](int b, u32x2 (&x)[8][2]) {
+    if (!act0 || b >= nsteps * KB) return;
+    const int c0 = block_word(b) * 32;
+    const bool whole = c0 + 128 <= a.cols;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      // an offset outside the buffer reads as 0: columns past the end (4 columns are inside or outside together)
+      const bool in = whole || c0 + kk * 16 + 4 * mq < a.cols;
+      const int o = (c0 + kk * 16) * 2;
+      x[kk][0] = __builtin_amdgcn_raw_buffer_load_b64(xr, in ? x0 + o : 0x7FFFFFF0, 0, 0);
+      x[kk][1] = __builtin_amdgcn_raw_buffer_load_b64(xr, in ? x1 + o : 0x7FFFFFF0, 0, 0);
+    }
+  };
+  auto flush = [&]() {  // the part is complete
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) {
+        S[i][nb] += C[i][nb];
+        C[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+  auto product = [&](int st) {
+    if (!act0) return;
+    static_for<0, KB>([&](auto J) {
+      constexpr int jb = decltype(J)::value;
+      const int b = st * KB + jb;
+      u32x2 (&x)[8][2] = (jb & 1) ? xb : xa;
+      load_x(b + 1, (jb & 1) ? xa : xb);
+      if (b > per_part - 1 && b % per_part == 0) {
+        if (b == per_part) {
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+              S[i][nb] = C[i][nb];
+              C[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        } else {
+          flush();
+        }
+      }
+      const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 4 * mq;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const int o = (kk >> 1) * kGroupPitch + (kk & 1) * 16;
+        const bf16x4 b0 = __builtin_bit_cast(bf16x4, x[kk][0]), b1 = __builtin_bit_cast(bf16x4, x[kk][1]);
+        bf16x4 av[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) av[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + o);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) C[i][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[i], b0, C[i][0], 0, 0, 0);
+        if (act1) {
+#pragma unroll
+          for (int i = 0; i < RT; ++i) C[i][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[i], b1, C[i][1], 0, 0, 0);
+        }
+      }
+    });
+  };
+
+  load_mask(0);
+  load_x(0, xa);
+  issue(0);
+  load_mask(1);
+  decode(0);
+  __syncthreads();
+  const bool product_first = (wv & 4) != 0;
+  for (int st = 0; st < nsteps; ++st) {
+    if (product_first) product(st);
+    decode(st + 1);
+    if (!product_first) product(st);
+    __syncthreads();
+  }
+  if (!act0) return;
+  flush();
+
+  // ---- S[i][nb][e]: row 16 i + 4 mq + e, column cb0 + 128 nb + 16 wv + mi
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int col = cb0 + 128 * nb + 16 * wv + mi;
+    if (col >= a.ncols) continue;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const int orow = row0 + 16 * i + 4 * mq;
+      const f32x4 s = S[i][nb];
+      if (a.epi == 0) {
+        float* y = a.Y + (size_t)col * a.yld + orow;
+        if (orow + 4 <= a.rows) {
+          __builtin_memcpy(y, &s, 16);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (orow + e < a.rows) y[e] = s[e];
+        }
+      } else if (a.epi == 1) {
+        uint16_t* hp = a.out16 + (size_t)col * a.yld + orow;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (orow + e < a.rows) hp[e] = f32_to_bf16(bf16_to_f32(hp[e]) + round_bf16(s[e]));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          if (orow + e + 1 < a.rows) {
+            const float g = round_bf16(s[e]), u = round_bf16(s[e + 1]);
+            a.out16[(size_t)col * (a.yld >> 1) + ((orow + e) >> 1)] = f32_to_bf16(g / (1.0f + expf(-g)) * u);
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int RT>
+static size_t wide_lds_bytes(int bw) {
+  return sizeof(uint16_t) * (2 * (size_t)128 * kTilePitch + (size_t)16 * RT * ((bw + 3) / 4));
+}
+
+// Whether the wide form takes a matrix of this shape: groups of four columns of X inside or outside a row
+// together and 8-byte aligned, counts of kept values in 16 bits, offsets into X in 31 bits, the LDS.
+static inline bool wide_shape_ok(const cas_ctx* ctx, int64_t rows, int64_t cols, int bw, int ncols) {
+  return rows > 0 && cols % 4 == 0 && cols < 65536 && (int64_t)ncols * cols * 2 < 0x7FFFFF00 &&
+         wide_lds_bytes<4>(bw) <= (size_t)ctx->lds_max;
+}
+
+template <int RT, bool MX>
+static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
+  const size_t lds = wide_lds_bytes<RT>(a.bw);
+  const int64_t grid = (int64_t)((a.rows + 16 * RT - 1) / (16 * RT)) * ((a.ncols + kWideCols - 1) / kWideCols);
+#define CAS_LAUNCH(TV)                                                                                            \
+  case TV: {                                                                                                      \
+    static LdsLimit lim;                                                                                          \
+    const int rc = allow_lds(ctx, (const void*)gemm_prefill_kernel<TV, RT, MX>, lds, lim);                        \
+    if (rc != CAS_OK) return rc;                                                                                  \
+    hipLaunchKernelGGL((gemm_prefill_kernel<TV, RT, MX>), dim3((unsigned)grid), dim3(kWideThreads), lds, ctx->stream, a, q); \
+  } break;
+  switch (t) {
+    CAS_LAUNCH(0) CAS_LAUNCH(1) CAS_LAUNCH(2) CAS_LAUNCH(3) CAS_LAUNCH(4) CAS_LAUNCH(5) CAS_LAUNCH(6) CAS_LAUNCH(7)
+    default: return CAS_EINVAL;
+  }
+#undef CAS_LAUNCH
+  CAS_HIP(ctx, hipGetLastError());
+  return CAS_OK;
+}
+
+// The parts are those the verification GEMM cuts the rows of the WHOLE matrix (a.yld rows) into.  Rows per
+// workgroup: 64, or 32 where 64 would leave a third of the CUs or more without a workgroup.
+template <bool MX>
+static int launch_wide(cas_ctx* ctx, const VerifyArgs& a, int t) {
+  const int groups = (a.yld + 15) / 16;
+  const int q = groups >= kFewGroups ? 4 : a.cols >= 4 * kSlabCols ? 16 : 8;
+  const int64_t wgs = (int64_t)((a.rows + 63) / 64) * ((a.ncols + kWideCols - 1) / kWideCols);
+  if (wgs * 3 < (int64_t)ctx->num_cu * 2) return launch_wide_rt<2, MX>(ctx, a, t, q);
+  return launch_wide_rt<4, MX>(ctx, a, t, q);
+}
+
+}  // namespace cas

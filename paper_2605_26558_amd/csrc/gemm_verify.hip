@@ -23,13 +23,14 @@ int launch_gemm_verify(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const
   return launch_gemm_verify_fused(ctx, d, spec, verif, X, ncols, Y, 0, nullptr);
 }
 
-static int launch_verify_args(cas_ctx* ctx, const VerifyArgs& a, int t) {
+static int launch_verify_args(cas_ctx* ctx, const VerifyArgs& a, int t, bool wide) {
+  if (wide) return launch_gemm_prefill(ctx, a, t);
   if (a.ncols > 8) return launch_gemm_verify_wide(ctx, a, t);
   return verify_narrow<false>(ctx, a, t);
 }
 
 int launch_gemm_verify_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const void* verif,
-                             const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16) {
+                             const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16, bool wide) {
   if (d.rows <= 0) return CAS_OK;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
   VerifyArgs a;
@@ -43,14 +44,14 @@ int launch_gemm_verify_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec,
   a.X = X; a.Y = Y; a.yld = (int)d.rows;
   a.sexp = nullptr; a.ew = 0;
   ProfScope prof(ctx, PROF_GEMM_VERIFY, 4.0 * (double)d.rows * (d.bw + d.sw + d.lw + d.pw));
-  return launch_verify_args(ctx, a, d.t);
+  return launch_verify_args(ctx, a, d.t, wide);
 }
 
 // The same product with the speculation data in the unary form (Sec. 4.2, the lossless
 // configuration): blocks of rows are re-coded into the raw spec stream in the workspace and the
 // kernel above runs on each block, so every output has the bits the raw form gives.
 int launch_gemm_verify_unary_fused(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const void* verif,
-                                   const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16) {
+                                   const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16, bool wide) {
   const cas_wdesc& d = u.base;
   if (d.rows <= 0) return CAS_OK;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
@@ -78,7 +79,7 @@ int launch_gemm_verify_unary_fused(cas_ctx* ctx, const cas_udesc& u, const void*
     a.sexp = nullptr; a.ew = 0;
     a.Y = Y ? Y + r0 : nullptr;
     a.out16 = out16 ? out16 + (epi == 2 ? r0 / 2 : r0) : nullptr;
-    rc = launch_verify_args(ctx, a, d.t);
+    rc = launch_verify_args(ctx, a, d.t, wide);
     if (rc != CAS_OK) return rc;
   }
   return CAS_OK;

@@ -324,5 +324,8 @@ static int verify_wide(cas_ctx* ctx, const VerifyArgs& a, int t) {
 
 // gemm_verify_wide.hip: verify_wide<false> (its own translation unit: the build compiles the files side by side)
 int launch_gemm_verify_wide(cas_ctx* ctx, const VerifyArgs& a, int t);
+// gemm_prefill.hip, gemm_prefill_mx.hip: the form for the columns of a prompt
+int launch_gemm_prefill(cas_ctx* ctx, const VerifyArgs& a, int t);
+int launch_gemm_prefill_mx(cas_ctx* ctx, const VerifyArgs& a, int t);
 
 }  // namespace cas

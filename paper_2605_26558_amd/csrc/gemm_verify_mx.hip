@@ -10,7 +10,7 @@
 namespace cas {
 
 int launch_gemm_verify_mx_fused(cas_ctx* ctx, const cas_mxdesc& x, const void* mxspec, const void* mxverif,
-                                const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16) {
+                                const uint16_t* X, int ncols, float* Y, int epi, uint16_t* out16, bool wide) {
   const cas_wdesc& d = x.base;
   if (d.rows <= 0) return CAS_OK;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
@@ -26,6 +26,7 @@ int launch_gemm_verify_mx_fused(cas_ctx* ctx, const cas_mxdesc& x, const void* m
   a.pruned = (const uint32_t*)((const char*)mxverif + x.off_pruned);
   a.X = X; a.Y = Y; a.yld = (int)d.rows;
   ProfScope prof(ctx, PROF_GEMM_VERIFY, 4.0 * (double)d.rows * (d.bw + x.fw + d.lw + d.pw) + (double)d.rows * x.ew);
+  if (wide) return launch_gemm_prefill_mx(ctx, a, d.t);
   if (ncols > 8) return verify_wide<true>(ctx, a, d.t);
   return verify_narrow<true>(ctx, a, d.t);
 }

@@ -66,3 +66,78 @@ def test_encoder_around_the_sizes_of_its_pieces_and_waves(env, cols, keep, t, ac
     p = O.encode_weight(W, keep, t, a)
     for got, want in zip(_streams(ew), (p.bitmap, p.spec, p.lo, p.pruned)):
         np.testing.assert_array_equal(got, want)
+
+
+WIDE_SHAPES = {  # hidden, query heads, kv heads, feed-forward: 8 parts per row of every matrix; 4 parts (gate/up) and 16 (down)
+    "a": (264, 4, 2, 520, 400 << 10),
+    "b": (200, 14, 2, 8200, 1200 << 10),
+}
+
+
+@pytest.fixture(scope="module")
+def wide_models(env):
+    """(context, model, cache) with a workspace that holds the chunks of a prompt and with one that does not."""
+    from types import SimpleNamespace
+    torch, B, _ = env
+    cache = {}
+
+    def get(shape, form, kv_form, keep, t):
+        key = (shape, form, kv_form, keep, t)
+        if key in cache:
+            return cache[key]
+        hidden, n_q, n_kv, ffn, small = WIDE_SHAPES[shape]
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(17)
+        bits = lambda x: x.to(torch.bfloat16).view(torch.int16)  # noqa: E731
+        rnd = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+        sh = SimpleNamespace(hidden=hidden, n_layers=2, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, ffn=ffn, vocab=301,
+                             rms_eps=1e-5)
+        dims = (("wqkv", (n_q + 2 * n_kv) * 128, hidden), ("wo", hidden, n_q * 128), ("wgu", 2 * ffn, hidden),
+                ("wd", hidden, ffn), ("head", 301, hidden))
+        raw = [{n: bits(rnd(r, c) * c ** -0.5) for n, r, c in dims} for _ in range(2)]
+        gains = [bits(1 + 0.1 * rnd(hidden)) for _ in range(5)]
+        embed = bits(rnd(301, hidden))
+        rope = torch.from_numpy(synth.rope_table(640, 128, 500000.0)).cuda()
+        out = []
+        for ws in (small, 64 << 20):
+            ctx = B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda"))
+            enc = [{n: B.cas_encode_weight(ctx, w, keep, t) for n, w in L.items()} for L in raw]
+            layers = [dict(e, g_attn=gains[2 * i], g_ffn=gains[2 * i + 1]) for i, e in enumerate(enc)]
+            model = B.Model(ctx, sh, layers, enc[0]["head"], embed, gains[4], rope, max_cols=16)
+            if form != "raw":
+                recode, use = (B.cas_mx_encode, model.use_mx) if form == "shared" else (B.cas_unary_encode, model.use_unary)
+                big = B.Context(workspace=torch.empty(8 << 20, dtype=torch.uint8, device="cuda"))
+                for i in range(2):
+                    for which, n in enumerate(("wqkv", "wo", "wgu", "wd")):
+                        use(i, which, recode(big, enc[i][n]))
+            kv = B.KVCache(ctx, 2, n_kv, n_pages=10, max_seqs=1, max_pages_per_seq=10, keep_permille=keep, trunc_bits=t,
+                           exp_mode=B.CAS_EXP_SHARED if kv_form == "shared" else B.CAS_EXP_RAW)
+            out.append((ctx, model, kv))
+        cache[key] = out
+        return out
+
+    return get
+
+
+@pytest.mark.parametrize("shape,form,kv_form,keep,t", [("a", "raw", "raw", 600, 4), ("b", "raw", "raw", 600, 4),
+                                                       ("a", "raw", "raw", 1000, 0), ("b", "shared", "shared", 400, 3),
+                                                       ("a", "shared", "raw", 600, 5), ("b", "unary", "raw", 600, 4)])
+@pytest.mark.parametrize("before,n", [(0, 47), (0, 48), (5, 63), (0, 130), (70, 257), (3, 513)])
+def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, shape, form, kv_form, keep, t, before, n):
+    torch, B, _ = env
+    tokens = torch.from_numpy(synth.token_ids(before + n + 1, 301, seed=3)).cuda()
+    got = []
+    for ctx, model, kv in wide_models(shape, form, kv_form, keep, t):
+        kv.spec_pool.zero_()
+        kv.verif_pool.zero_()
+        B.cas_kv_set_len(kv, 0, 0)
+        if before:
+            B.cas_prefill(ctx, model, kv, 0, tokens[:before])
+        B.cas_prefill(ctx, model, kv, 0, tokens[before:before + n])
+        assert B.cas_kv_len(kv, 0) == before + n
+        logits = torch.empty((1, 301), device="cuda")
+        B.cas_verify_step(ctx, model, kv, 0, tokens[-1:], 0, torch.empty(1, dtype=torch.int32, device="cuda"), logits)
+        assert bool(torch.isfinite(logits).all())
+        got.append((kv.spec_pool.clone(), kv.verif_pool.clone(), logits))
+    for narrow, wide in zip(*got):
+        assert torch.equal(narrow, wide)
