@@ -80,10 +80,13 @@ int launch_gemv_draft(cas_ctx*, const cas_wdesc&, const void* spec, const uint16
 int launch_gemv_draft_fused(cas_ctx*, const cas_wdesc&, const void* spec, const uint16_t* x, int batch, float* y,
                             const uint16_t* gain, float eps, int epi, uint16_t* out16);
 int launch_gemm_verify(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X, int ncols, float* Y);
-// wide: the form for the columns of a prompt (any number of them; see wide_shape_ok), same bits
+// wide: the form for the columns of a prompt (any number of them, X from launch_pack_x), same bits
 int launch_gemm_verify_fused(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X,
                              int ncols, float* Y, int epi, uint16_t* out16, bool wide = false);
-bool gemm_wide_ok(const cas_ctx*, int64_t rows, int64_t cols, int ncols);
+// gemm_prefill.hip: whether the wide form takes a matrix; its packed X [ncols][cols], 16-byte aligned
+bool gemm_wide_ok(const cas_ctx*, int64_t rows, int64_t cols);
+size_t gemm_wide_x_bytes(int64_t cols, int ncols);
+int launch_pack_x(cas_ctx*, const uint16_t* X, int ncols, int cols, void* out);
 // unary.hip: rows [row0, row0 + nrows) of the raw spec stream (sw words per row) rebuilt from the unary form
 int launch_unary_expand(cas_ctx*, const cas_udesc&, const void* uspec, int64_t row0, int nrows, uint32_t* out);
 int launch_gemm_verify_unary_fused(cas_ctx*, const cas_udesc&, const void* uspec, const void* verif, const uint16_t* X,

@@ -116,27 +116,23 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   // ---- product role: columns cb0 + 16 wv + mi and 128 further; A[i = lane%16][k = 4*(lane/16)..+3]
   const int mi = lane & 15, mq = lane >> 4;
   const bool act0 = cb0 + 16 * wv < a.ncols, act1 = cb0 + 128 + 16 * wv < a.ncols;
-  const int n0 = min(cb0 + 16 * wv + mi, a.ncols - 1), n1 = min(cb0 + 128 + 16 * wv + mi, a.ncols - 1);
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, (int)((int64_t)a.ncols * a.cols * 2), 0x00020000);
-  const int x0 = (n0 * a.cols + 4 * mq) * 2, x1 = (n1 * a.cols + 4 * mq) * 2;
+  // X comes packed (pack_x_kernel): the fragments of 16 columns and 32 values of k are one run of 1 KB
+  const size_t xrow = (size_t)nblk * 4 * 512;  // values of a block of 16 columns
+  const uint16_t* const xp0 = a.X + (size_t)((cb0 >> 4) + wv) * xrow + lane * 8;
+  const uint16_t* const xp1 = act1 ? xp0 + 8 * xrow : xp0;
   f32x4 C[RT][2], S[RT][2];  // running sum of the part, sum of the parts before it
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) C[i][nb] = S[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x2 xa[8][2], xb[8][2];
-  auto load_x = [&](int b, u32x2 (&x)[8][2]) {
-    if (!act0 || b >= nsteps * KB) return;
-    const int c0 = block_word(b) * 32;
-    const bool whole = c0 + 128 <= a.cols;
+  uint4 xa[4][2], xb[4][2];
+  auto load_x = [&](int b, uint4 (&x)[4][2]) {
+    const int blk = block_word(b) >> 2;
+    if (!act0 || b >= nsteps * KB || blk >= nblk) return;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      // an offset outside the buffer reads as 0: columns past the end (4 columns are inside or outside together)
-      const bool in = whole || c0 + kk * 16 + 4 * mq < a.cols;
-      const int o = (c0 + kk * 16) * 2;
-      x[kk][0] = __builtin_amdgcn_raw_buffer_load_b64(xr, in ? x0 + o : 0x7FFFFFF0, 0, 0);
-      x[kk][1] = __builtin_amdgcn_raw_buffer_load_b64(xr, in ? x1 + o : 0x7FFFFFF0, 0, 0);
+    for (int kq = 0; kq < 4; ++kq) {
+      x[kq][0] = *reinterpret_cast<const uint4*>(xp0 + (size_t)(blk * 4 + kq) * 512);
+      x[kq][1] = *reinterpret_cast<const uint4*>(xp1 + (size_t)(blk * 4 + kq) * 512);
     }
   };
   auto flush = [&]() {  // the part is complete
@@ -153,7 +149,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
     static_for<0, KB>([&](auto J) {
       constexpr int jb = decltype(J)::value;
       const int b = st * KB + jb;
-      u32x2 (&x)[8][2] = (jb & 1) ? xb : xa;
+      uint4 (&x)[4][2] = (jb & 1) ? xb : xa;
       load_x(b + 1, (jb & 1) ? xa : xb);
       if (b > per_part - 1 && b % per_part == 0) {
         if (b == per_part) {
@@ -168,11 +164,14 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
           flush();
         }
       }
+      if (block_word(b) >= a.bw) return;  // past the end of the rows
       const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 4 * mq;
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         const int o = (kk >> 1) * kGroupPitch + (kk & 1) * 16;
-        const bf16x4 b0 = __builtin_bit_cast(bf16x4, x[kk][0]), b1 = __builtin_bit_cast(bf16x4, x[kk][1]);
+        const uint4 &f0 = x[kk >> 1][0], &f1 = x[kk >> 1][1];
+        const bf16x4 b0 = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f0.z, f0.w} : u32x2{f0.x, f0.y});
+        const bf16x4 b1 = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f1.z, f1.w} : u32x2{f1.x, f1.y});
         bf16x4 av[RT];
 #pragma unroll
         for (int i = 0; i < RT; ++i) av[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + o);
@@ -243,11 +242,9 @@ static size_t wide_lds_bytes(int bw) {
   return sizeof(uint16_t) * (2 * (size_t)128 * kTilePitch + (size_t)16 * RT * ((bw + 3) / 4));
 }
 
-// Whether the wide form takes a matrix of this shape: groups of four columns of X inside or outside a row
-// together and 8-byte aligned, counts of kept values in 16 bits, offsets into X in 31 bits, the LDS.
-static inline bool wide_shape_ok(const cas_ctx* ctx, int64_t rows, int64_t cols, int bw, int ncols) {
-  return rows > 0 && cols % 4 == 0 && cols < 65536 && (int64_t)ncols * cols * 2 < 0x7FFFFF00 &&
-         wide_lds_bytes<4>(bw) <= (size_t)ctx->lds_max;
+// Whether the wide form takes a matrix of this shape: counts of kept values in 16 bits, the LDS.
+static inline bool wide_shape_ok(const cas_ctx* ctx, int64_t rows, int64_t cols, int bw) {
+  return rows > 0 && cols < 65536 && wide_lds_bytes<4>(bw) <= (size_t)ctx->lds_max;
 }
 
 template <int RT, bool MX>

@@ -407,13 +407,13 @@ static ActLayout act_layout(const cas_model_cfg& c) {
 // chunk's keys and values are appended to the cache, and attention runs over runs of `sub` columns, each of
 // which reads the positions before it from the cache and its own uncompressed, exactly as a pass of `sub`
 // columns does.  A chunk therefore leaves the bits in the cache that such passes leave.
-// 8B-shaped, 4 layers, 508 tokens: 7.7 ms (43.4 with passes of 16 columns, whose 32 readings of all weights
+// 8B-shaped, 4 layers, 508 tokens: 5.3 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
 // and 31 unread rows of logits it saves).
 constexpr int kPrefillChunk = 512;
 constexpr int kPrefillMin = 48;  // fewer columns: passes through the narrow kernels are as fast
 
 struct ChunkLayout {
-  size_t h, xn, y, q, ao, k, v, total;  // y: the fp32 projection, then the SwiGLU output
+  size_t h, xn, y, q, ao, k, v, px, total;  // y: the fp32 projection, then the SwiGLU output; px: a layer's packed input
 };
 
 static ChunkLayout chunk_layout(const cas_model_cfg& c, size_t n) {
@@ -427,6 +427,7 @@ static ChunkLayout chunk_layout(const cas_model_cfg& c, size_t n) {
   L.ao = carve(off, n * qd * 2);
   L.k = carve(off, n * kvd * 2);
   L.v = carve(off, n * kvd * 2);
+  L.px = carve(off, gemm_wide_x_bytes(std::max<int64_t>({c.hidden, (int64_t)qd, c.ffn}), (int)n));
   L.total = off;
   return L;
 }
@@ -450,8 +451,7 @@ static int chunk_columns(const cas_ctx* ctx, const cas_model* m, const cas_kv* k
   const int64_t len = kv->h_len[seq];
   if (left < kPrefillMin || len + left > cap || len + left > c.max_pos || !ctx->d_ws) return 0;
   const int qd = c.n_q_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim;
-  if (!gemm_wide_ok(ctx, qd + 2 * kvd, c.hidden, kPrefillChunk) || !gemm_wide_ok(ctx, c.hidden, qd, kPrefillChunk) ||
-      !gemm_wide_ok(ctx, c.hidden, c.ffn, kPrefillChunk))
+  if (!gemm_wide_ok(ctx, qd + 2 * kvd, c.hidden) || !gemm_wide_ok(ctx, c.hidden, qd) || !gemm_wide_ok(ctx, c.hidden, c.ffn))
     return 0;
   size_t rest = 0;  // a block of re-coded rows of a unary matrix: 16 MB of them (or the whole of a smaller one)
   for (size_t i = 0; i + 1 < m->unary.size(); ++i)
@@ -482,13 +482,14 @@ static int prefill_chunk(cas_ctx* ctx, cas_model* m, cas_kv* kv, int seq, const 
   ctx->d_ws = b + L.total;
   ctx->ws_bytes = tail.bytes - (size_t)(b + L.total - (char*)tail.ws);
   uint16_t *h = (uint16_t*)(b + L.h), *xn = (uint16_t*)(b + L.xn), *act = (uint16_t*)(b + L.y), *q = (uint16_t*)(b + L.q),
-           *ao = (uint16_t*)(b + L.ao), *k = (uint16_t*)(b + L.k), *v = (uint16_t*)(b + L.v);
+           *ao = (uint16_t*)(b + L.ao), *k = (uint16_t*)(b + L.k), *v = (uint16_t*)(b + L.v), *px = (uint16_t*)(b + L.px);
   float* y = (float*)(b + L.y);
   auto linear = [&](const cas_tensor& T, const cas_model::UnaryRef& U, const uint16_t* X, float* Y, int epi,
                     uint16_t* out16) -> int {
-    if (U.mx_on) return launch_gemm_verify_mx_fused(ctx, U.mx, U.d_mxspec, U.d_mxverif, X, n, Y, epi, out16, true);
-    if (!U.on) return launch_gemm_verify_fused(ctx, T.desc, T.d_spec, T.d_verif, X, n, Y, epi, out16, true);
-    return launch_gemm_verify_unary_fused(ctx, U.u, U.d_uspec, T.d_verif, X, n, Y, epi, out16, true);
+    CAS_TRY(launch_pack_x(ctx, X, n, (int)T.desc.cols, px));
+    if (U.mx_on) return launch_gemm_verify_mx_fused(ctx, U.mx, U.d_mxspec, U.d_mxverif, px, n, Y, epi, out16, true);
+    if (!U.on) return launch_gemm_verify_fused(ctx, T.desc, T.d_spec, T.d_verif, px, n, Y, epi, out16, true);
+    return launch_gemm_verify_unary_fused(ctx, U.u, U.d_uspec, T.d_verif, px, n, Y, epi, out16, true);
   };
   const int sub = chunk_sub(m, kv), heads = c.n_q_heads + 2 * c.n_kv_heads;
   const int together = (int)std::clamp<size_t>(ctx->ws_bytes / std::max<size_t>(1, chunk_partials(c, std::min(sub, n), len + n)), 1, 4);
