@@ -76,6 +76,8 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) b_base[nb] = Xq + (16 * nb + mi < a.ncols ? 16 * nb + mi : 0) * XQP + 4 * mq;
 
+  const bool xvec = (a.cols & 7) == 0;  // 16-byte pieces of X rows are aligned and never straddle the end
+
   f32x4 C[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) C[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -147,34 +149,44 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
     PrunedWindows pw;
     kw.load(p4[0], sp_row, lo_row);
     // ---- this wave's X columns of the next XST steps (bf16, zero beyond the last column), in pieces
-    // of 8 columns.  A row of X starts at a multiple of 2 bytes only when the matrix has an odd number
-    // of columns: the 16-byte loads assume no more than that.  XB pieces per lane are requested together.
-    // 11003 x 5001 with 20 columns: 59 us; with 2-byte loads for such matrices it took 198 us.
+    // of 8 columns.  Where the number of columns is not a multiple of 8, a row of X starts at any multiple of
+    // 2 bytes and the 16-byte loads assume no more than that; XB pieces per lane are requested together.
+    // 11003 x 5001 with 20 columns: 59 us, with 2-byte loads 198 us.  The plain loop stays for the others: it
+    // is 1 % faster in the passes of four sequences.
     auto stage_x = [&](int s) {
       const int col0 = slab * kSlabCols + part * (WPP * 32) + s * XQ;
-      const int n = a.ncols * (XQ / 8);
-      for (int i0 = lane; i0 < n; i0 += 64 * XB) {
-        uint4 v[XB];
+      if (xvec) {
+        for (int i = lane; i < a.ncols * (XQ / 8); i += 64) {
+          int c = i / (XQ / 8), o = (i - c * (XQ / 8)) * 8;
+          uint4 v = make_uint4(0, 0, 0, 0);
+          if (col0 + o < a.cols) v = *reinterpret_cast<const uint4*>(a.X + (size_t)c * a.cols + col0 + o);
+          *reinterpret_cast<uint4*>(Xq + c * XQP + o) = v;
+        }
+      } else {
+        const int n = a.ncols * (XQ / 8);
+        for (int i0 = lane; i0 < n; i0 += 64 * XB) {
+          uint4 v[XB];
 #pragma unroll
-        for (int q = 0; q < XB; ++q) {
-          const int i = i0 + 64 * q, c = i / (XQ / 8), col = col0 + (i - c * (XQ / 8)) * 8;
-          v[q] = make_uint4(0, 0, 0, 0);
-          if (i < n) {
-            const uint16_t* src = a.X + (size_t)c * a.cols + col;
-            if (col + 8 <= a.cols) {
-              __builtin_memcpy(&v[q], src, 16);
-            } else if (col < a.cols) {  // the ragged end of a row of X
-              uint16_t e[8];
+          for (int q = 0; q < XB; ++q) {
+            const int i = i0 + 64 * q, c = i / (XQ / 8), col = col0 + (i - c * (XQ / 8)) * 8;
+            v[q] = make_uint4(0, 0, 0, 0);
+            if (i < n) {
+              const uint16_t* src = a.X + (size_t)c * a.cols + col;
+              if (col + 8 <= a.cols) {
+                __builtin_memcpy(&v[q], src, 16);
+              } else if (col < a.cols) {  // the ragged end of a row of X
+                uint16_t e[8];
 #pragma unroll
-              for (int k = 0; k < 8; ++k) e[k] = col + k < a.cols ? src[k] : (uint16_t)0;
-              __builtin_memcpy(&v[q], e, 16);
+                for (int k = 0; k < 8; ++k) e[k] = col + k < a.cols ? src[k] : (uint16_t)0;
+                __builtin_memcpy(&v[q], e, 16);
+              }
             }
           }
-        }
 #pragma unroll
-        for (int q = 0; q < XB; ++q) {
-          const int i = i0 + 64 * q, c = i / (XQ / 8), o = (i - c * (XQ / 8)) * 8;
-          if (i < n) *reinterpret_cast<uint4*>(Xq + c * XQP + o) = v[q];
+          for (int q = 0; q < XB; ++q) {
+            const int i = i0 + 64 * q, c = i / (XQ / 8), o = (i - c * (XQ / 8)) * 8;
+            if (i < n) *reinterpret_cast<uint4*>(Xq + c * XQP + o) = v[q];
+          }
         }
       }
     };
