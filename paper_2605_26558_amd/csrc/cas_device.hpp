@@ -112,6 +112,20 @@ __device__ __forceinline__ uint32_t field_at(const uint32_t (&a)[NW]) {
   }
 }
 
+// Field i (compile-time) of `width` bits from a register window, times 2^SCALE (a byte offset into a table).
+template <int WIDTH, int I, int SCALE, int NW>
+__device__ __forceinline__ uint32_t field_scaled(const uint32_t (&a)[NW]) {
+  constexpr int bit = I * WIDTH, w = bit >> 5, sh = bit & 31;
+  constexpr uint32_t mask = ((1u << WIDTH) - 1u) << SCALE;
+  if constexpr (sh + WIDTH > 32) {
+    return __builtin_amdgcn_alignbit(a[w + 1], a[w], sh - SCALE) & mask;
+  } else if constexpr (sh >= SCALE) {
+    return (a[w] >> (sh - SCALE)) & mask;
+  } else {
+    return (a[w] << (SCALE - sh)) & mask;
+  }
+}
+
 // compile-time loop: f(integral_constant<int, I>) for I in [B, E)
 template <int B, int E, class F>
 __device__ __forceinline__ void static_for(F&& f) {

@@ -57,6 +57,8 @@ constexpr int kGemvWaves = kGemvThreads / 64;
 // the lanes are at (with one 33-entry segment per lane they collided at ~3.8 extra cycles per
 // gather, which made the LDS a co-limit of the kernel).
 constexpr int kXRows = 33;
+template <int FW>
+constexpr size_t kMagTabBytes = sizeof(float) << FW;
 template <int NB>
 __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the staged layout
   const int w = col >> 5;
@@ -77,7 +79,11 @@ struct XStage<true> {
 
 // MX = false: fields of 16-T bits, the leading bits of the bf16 word.  MX = true: fields of
 // 9-T bits (sign, 8-T leading magnitude bits) and one shared exponent per bitmap word: the
-// products of a word are summed unscaled and multiplied once by 2^(E + T - 134).
+// products of a word are summed unscaled and multiplied once by 2^(E + T - 134).  The signed
+// magnitude of a field comes from a table of 2^(9-T) floats in LDS, indexed with the field itself: two
+// operations and a gather, where taking it apart and converting it took five in a kernel that is
+// bound by them (8B shape, mean of the launches of a pass: 22.8 us, now 19.5 with the exponents read through a
+// descriptor as well).
 template <int T, int NB, bool MX>
 __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   constexpr int FW = MX ? 9 - T : 16 - T;
@@ -85,7 +91,9 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   using XS = XStage<XH>;
   using XT = typename XS::type;
   extern __shared__ uint8_t xs_raw[];
-  XT* xs = reinterpret_cast<XT*>(xs_raw);
+  // shared-exponent form: the table of signed magnitudes in front of x
+  const uint8_t* const mag_tab = xs_raw;
+  XT* xs = reinterpret_cast<XT*>(xs_raw + (MX ? kMagTabBytes<FW> : 0));
   const int tid = threadIdx.x;
   const int nchunk = (a.bw + 63) >> 6;
   const int nseg = nchunk * 64;
@@ -134,8 +142,9 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 #pragma unroll
     for (int j = (FW + 1) & ~3; j <= FW; ++j) w.d[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4 * j, 0, 0);
     if constexpr (MX) {
-      const int wi = c.chunk * 64 + lane;
-      w.e = wi < a.bw ? a.sexp[(size_t)row * a.ew + wi] : 0u;
+      const __amdgpu_buffer_rsrc_t re = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(a.sexp + (size_t)row * a.ew), 0, a.bw, kRawBufferFlags);  // a byte past the row's words reads as 0
+      w.e = __builtin_amdgcn_raw_buffer_load_b8(re, c.chunk * 64 + lane, 0, 0);
     }
   };
 
@@ -156,17 +165,15 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
       constexpr int i = decltype(I)::value;
       int pos = lowest_bit(m);
       m &= m - 1u;
-      const uint32_t top = field_top<FW, i>(win);
       const XT* xp = xb + pos * (64 * NB);
       if constexpr (MX) {
-        // sign at bit 31, magnitude below it; a lane past its last field reads neighbouring
-        // bits, always a finite number, and multiplies it by the zero entry of the segment
-        const float mag = (float)__builtin_amdgcn_ubfe(top, 32 - FW, FW - 1);
-        const float f = __uint_as_float((top & 0x80000000u) | __float_as_uint(mag));
+        // the field is the index of its signed magnitude; a lane past its last field reads neighbouring
+        // bits, always the index of a finite number, and multiplies it by the zero entry of the segment
+        const float f = *reinterpret_cast<const float*>(mag_tab + field_scaled<FW, i, 2>(win));
 #pragma unroll
         for (int b = 0; b < NB; ++b) accw[b] = fmaf(f, XS::get(xp[b]), accw[b]);
       } else {
-        const float f = __uint_as_float(top);
+        const float f = __uint_as_float(field_top<FW, i>(win));
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[b] = fmaf(f, XS::get(xp[b]), acc[b]);
       }
@@ -234,6 +241,12 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     }
   };
   auto stage_x = [&]() {
+    if constexpr (MX) {
+      if (tid < (1 << FW)) {
+        const float mag = (float)(tid & ((1 << (FW - 1)) - 1));
+        reinterpret_cast<float*>(xs_raw)[tid] = (tid >> (FW - 1)) ? -mag : mag;
+      }
+    }
     for (int sgi = tid; sgi < nseg; sgi += kGemvThreads) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) xs[(((sgi >> 6) * kXRows) * 64 + (sgi & 63)) * NB + b] = XS::put(0.f);
