@@ -32,28 +32,37 @@ int launch_gemv_draft(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const 
   return launch_gemv_draft_fused(ctx, d, spec, x, batch, y, nullptr, 0.f, 0, nullptr);
 }
 
-int launch_gemv_draft_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const uint16_t* x, int batch,
-                            float* y, const uint16_t* gain, float eps, int epi, uint16_t* out16) {
-  if (d.rows <= 0) return CAS_OK;
-  if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
+int launch_gemv_draft_block(cas_ctx* ctx, const cas_wdesc& d, const uint32_t* bitmap, const uint32_t* spec, int nr,
+                            const uint16_t* x, int batch, float* y, const uint16_t* gain, float eps, int epi,
+                            uint16_t* out16) {
   GemvArgs a{};
   a.gain = gain; a.eps = eps; a.epi = epi; a.out16 = out16;
-  a.rows = (int)d.rows; a.cols = (int)d.cols; a.bw = d.bw; a.sw = d.sw;
-  a.bitmap = (const uint32_t*)((const char*)spec + d.off_bitmap);
-  a.spec = (const uint32_t*)((const char*)spec + d.off_spec);
-  a.x = x; a.y = y;
+  a.rows = nr; a.cols = (int)d.cols; a.bw = d.bw; a.sw = d.sw;
+  a.bitmap = bitmap;
+  a.spec = spec;
+  a.x = x; a.y = y; a.yld = (int)d.rows;
   // x: fp32 for one column, bf16 for a batch (see XStage)
   const size_t lds = gemv_lds_bytes(d.bw, batch);
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
-  const int grid = gemv_grid(ctx, epi == 2 ? d.rows / 2 : d.rows);  // a gate/up row pair stays in one wave
+  const int grid = gemv_grid(ctx, epi == 2 ? nr / 2 : nr);  // a gate/up row pair stays in one wave
   a.nwaves = grid * kGemvWaves;
-  ProfScope prof(ctx, PROF_GEMV_DRAFT, 4.0 * (double)d.rows * (d.bw + d.sw));
 #define CAS_T(TV) case TV: return launch_t<TV>(ctx, a, batch, grid, lds);
   switch (d.t) {
     CAS_T(0) CAS_T(1) CAS_T(2) CAS_T(3) CAS_T(4) CAS_T(5) CAS_T(6) CAS_T(7)
   }
 #undef CAS_T
   return CAS_EINVAL;
+}
+
+int launch_gemv_draft_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const uint16_t* x, int batch,
+                            float* y, const uint16_t* gain, float eps, int epi, uint16_t* out16) {
+  if (d.rows <= 0) return CAS_OK;
+  if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
+  if (gemv_lds_bytes(d.bw, batch) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  ProfScope prof(ctx, PROF_GEMV_DRAFT, 4.0 * (double)d.rows * (d.bw + d.sw));
+  return launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)spec + d.off_bitmap),
+                                 (const uint32_t*)((const char*)spec + d.off_spec), (int)d.rows, x, batch, y, gain, eps,
+                                 epi, out16);
 }
 
 }  // namespace cas

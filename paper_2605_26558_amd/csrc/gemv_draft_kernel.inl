@@ -12,12 +12,13 @@ struct GemvArgs {
   const uint32_t* bitmap;
   const uint32_t* spec;
   const uint16_t* x;  // [NB][cols]
-  float* y;           // [NB][rows] (epilogue 0)
+  float* y;           // [NB][yld] (epilogue 0)
+  int yld;            // output rows per column in y / out16 (>= rows: the launch may cover a block of rows)
   // optional fused neighbours of the linear layer
   const uint16_t* gain;  // non-null: x is first RMS-normalised with this gain (rounded to bf16)
   float eps;
   int epi;               // 0: y = W x;  1: h = bf16(h + bf16(W x));  2: act[i] = swiglu(rows 2i, 2i+1)
-  uint16_t* out16;       // h [NB][rows] (epilogue 1) or act [NB][rows/2] (epilogue 2)
+  uint16_t* out16;       // h [NB][yld] (epilogue 1) or act [NB][yld/2] (epilogue 2)
   // shared-exponent form only: one exponent byte per bitmap word, ew bytes per row
   const uint8_t* sexp;
   int ew;
@@ -202,14 +203,14 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
         float s = wave_sum(acc[b]);
         acc[b] = 0.f;
         if (a.epi == 0) {
-          if (lane == 0) a.y[(size_t)b * a.rows + c.row] = s;
+          if (lane == 0) a.y[(size_t)b * a.yld + c.row] = s;
         } else if (a.epi == 1) {
-          uint16_t* hp = a.out16 + (size_t)b * a.rows + c.row;
+          uint16_t* hp = a.out16 + (size_t)b * a.yld + c.row;
           if (lane == 0) *hp = f32_to_bf16(bf16_to_f32(*hp) + round_bf16(s));
         } else {
           if (c.row & 1) {  // up row: the gate row came just before
             const float g = round_bf16(gate[b]), u = round_bf16(s);
-            if (lane == 0) a.out16[(size_t)b * (a.rows >> 1) + (c.row >> 1)] = f32_to_bf16(g / (1.0f + expf(-g)) * u);
+            if (lane == 0) a.out16[(size_t)b * (a.yld >> 1) + (c.row >> 1)] = f32_to_bf16(g / (1.0f + expf(-g)) * u);
           } else {
             gate[b] = s;
           }

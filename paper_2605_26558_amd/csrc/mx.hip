@@ -182,7 +182,7 @@ int launch_gemv_draft_mx_fused(cas_ctx* ctx, const cas_mxdesc& mx, const void* d
   a.spec = (const uint32_t*)((const char*)d_mxspec + mx.off_field);
   a.sexp = (const uint8_t*)d_mxspec + mx.off_sexp;
   a.ew = mx.ew;
-  a.x = d_x; a.y = d_y;
+  a.x = d_x; a.y = d_y; a.yld = (int)d.rows;
   const size_t lds = gemv_lds_bytes(d.bw, 1) + (sizeof(float) << (9 - d.t));  // x, the table of signed magnitudes
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   const int grid = gemv_grid(ctx, epi == 2 ? d.rows / 2 : d.rows);  // a gate/up row pair stays in one wave

@@ -202,43 +202,185 @@ __global__ __launch_bounds__(64) void unary_decode_kernel(UnaryArgs a, uint16_t*
   }
 }
 
-// ---- the raw spec stream of a block of rows, rebuilt from the unary form: one wave per row ------
-// After the row's exponents are in LDS every lane assembles whole output words: word w holds the
-// bits of the (at most four) fields of 16-t bits that overlap it.
-__global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0, uint32_t* __restrict__ out) {
-  extern __shared__ uint8_t lds8[];
-  uint8_t* tab = lds8;         // exp_of_rank
-  uint8_t* exps = lds8 + 256;  // [K]
-  const int lane = threadIdx.x, row = row0 + blockIdx.x;
+// ---- the raw spec stream of a block of rows, rebuilt from the unary form ------------------------
+// One wave per workgroup and R rows.  32 consecutive kept values of a row (a group) fill FW words of the
+// spec stream and take SW words of sign / mantissa fields exactly, so a lane that decodes one group works
+// at fixed positions everywhere but in the code stream, and every lane has the same number of values.
+//   1. The code words of the R rows go to LDS with the running count of their ones.
+//   2. A lane finds the first code of its group by a search in the counts and a search inside the word,
+//      then takes four codes at a time from a window of 64 bits.
+// That holds for rows whose ranks stay below 16 (64 bits then hold four codes) and whose code stream is not
+// unusually long; step 1 looks for both, and the other rows go through unary_row_exponents one by one.
+// Bound by the arithmetic of step 2 (about 13 operations per kept value, 20 with the searches).  Mean of the
+// launches of a verification pass of the 8B shape: 40 us; 68 us when a lane walked the codes that end in one
+// code word and the words of the stream were put together field by field.
+constexpr int kExpandWaves = 3;
+constexpr int kExpandRows = 4;  // most rows of a workgroup
+constexpr int kUnaryPad = 6;    // words of ones behind a row's codes: what the windows of exhausted lanes see
+
+template <int T>
+__global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0, int nrows, int R, int cap,
+                                                          uint32_t* __restrict__ out) {
+  constexpr int mb = 7 - T, SW = 8 - T, FW = 16 - T;
+  extern __shared__ uint32_t lds32[];
+  __shared__ uint32_t etab[16];   // exponent of a rank, in its place in a field
+  __shared__ uint8_t tab[256];    // exp_of_rank
+  uint32_t* const codes = lds32;  // [R][cap]
+  uint16_t* const incl = reinterpret_cast<uint16_t*>(codes + R * cap);  // [R][cap] ones up to and including a word
+  const int lane = threadIdx.x, first = blockIdx.x * R, n = min(R, nrows - first), G = (a.K + 31) >> 5;
   for (int i = lane; i < 256; i += 64) tab[i] = a.table[i];
+  if (lane < 16) etab[lane] = (uint32_t)a.table[lane] << mb;
+  uint32_t slow = 0;  // rows of the workgroup that take the general way
+  // offsets and first code words of all rows are requested together
+  const uint32_t off = a.rowoff[row0 + first + min(lane, n)];
+  uint32_t o0[kExpandRows], c0[kExpandRows][2], c1[kExpandRows][2];
+  int nws[kExpandRows];
+#pragma unroll
+  for (int r = 0; r < kExpandRows; ++r) {
+    o0[r] = (uint32_t)__builtin_amdgcn_readlane((int)off, r);
+    nws[r] = r < n ? __builtin_amdgcn_readlane((int)off, r + 1) - (int)o0[r] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < kExpandRows; ++r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int w = 64 * h + lane;
+      c0[r][h] = w < nws[r] ? a.ue[o0[r] + w] : 0u;
+      c1[r][h] = w + 1 < nws[r] ? a.ue[o0[r] + w + 1] : 0xFFFFFFFFu;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kExpandRows; ++r) {
+    if (r >= n) break;
+    const int nw = nws[r];
+    const uint32_t* ue_row = a.ue + o0[r];
+    if (nw < 1 || nw + kUnaryPad > cap) {
+      slow |= 1u << r;
+      continue;
+    }
+    int run = 0;
+    bool long_run = false;
+    auto chunk = [&](int w0, uint32_t u, uint32_t u1) {
+      const int w = w0 + lane;
+      const int cnt = __popc(u), sum = wave_incl_scan(cnt);
+      if (w < nw) incl[r * cap + w] = (uint16_t)(run + sum);
+      run += __builtin_amdgcn_readlane(sum, 63);
+      if (w == nw - 1 && u) u |= 0xFFFFFFFEu << (31 - __clz(u));  // the bits behind the last code are no zeros of a code
+      if (w >= nw) u = 0xFFFFFFFFu;
+      if (w < nw + kUnaryPad) codes[r * cap + w] = u;
+      uint64_t z = ~(((uint64_t)u1 << 32) | u);  // bit i: 16 zeros from bit i on
+      z &= z >> 1;
+      z &= z >> 2;
+      z &= z >> 4;
+      z &= z >> 8;
+      long_run = long_run || (uint32_t)z != 0u;
+    };
+    chunk(0, c0[r][0], c1[r][0]);
+    if (nw > 64) chunk(64, c0[r][1], c1[r][1]);
+    for (int w0 = 128; w0 < nw; w0 += 64) {
+      const int w = w0 + lane;
+      chunk(w0, w < nw ? ue_row[w] : 0u, w + 1 < nw ? ue_row[w + 1] : 0xFFFFFFFFu);
+    }
+    // the pad of a row that ends close to the last chunk's end
+    for (int w = (nw + 63) / 64 * 64 + lane; w < nw + kUnaryPad; w += 64) codes[r * cap + w] = 0xFFFFFFFFu;
+    if (__builtin_amdgcn_ballot_w64(long_run)) slow |= 1u << r;
+  }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  const uint32_t o0 = a.rowoff[row], o1 = a.rowoff[row + 1];
-  unary_row_exponents(a.ue + o0, (int)(o1 - o0), a.K, tab, exps, lane);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  const int mb = 7 - a.t, SW = 8 - a.t, FW = 16 - a.t;
-  // the row's sign / mantissa fields come through LDS as well: a field is looked at by up to two
-  // output words, and its two words would otherwise be fetched from memory each time
-  uint32_t* sm_row = reinterpret_cast<uint32_t*>(lds8 + 256 + (((size_t)a.K + 3) & ~(size_t)3) + kExpSlack);
-  {
-    const uint32_t* src = a.u_sm + (size_t)row * a.smw;
-    for (int i = lane; i < a.smw; i += 64) sm_row[i] = src[i];
-    if (lane == 0) sm_row[a.smw] = 0u;  // read_field looks one word ahead
+
+  for (int it = lane; it < n * G; it += 64) {
+    const int r = it / G, g = it - r * G, row = row0 + first + r;
+    if ((slow >> r) & 1u) continue;
+    const int nw = (int)(a.rowoff[row + 1] - a.rowoff[row]);
+    uint32_t sm[SW];
+    __builtin_memcpy(sm, a.u_sm + (size_t)row * a.smw + g * SW, 4 * SW);
+    const uint32_t* cw = codes + r * cap;
+    const uint16_t* ic = incl + r * cap;
+    // position of the first bit behind code 32 g - 1
+    uint32_t q = 0;
+    if (g > 0) {
+      const int e0 = 32 * g;
+      int w = 0, len = nw;  // first word that ends e0 or more codes
+      while (len > 0) {
+        const int half = len >> 1;
+        const bool right = ic[w + half] < e0;
+        w = right ? w + half + 1 : w;
+        len = right ? len - half - 1 : half;
+      }
+      uint32_t u = cw[w], pos = 0;
+      int k = e0 - (w > 0 ? ic[w - 1] : 0);  // its k-th one ends code e0 - 1
+#pragma unroll
+      for (int s = 16; s > 0; s >>= 1) {
+        const int c = __popc(u & ((1u << s) - 1u));
+        const bool up = k > c;
+        k = up ? k - c : k;
+        u = up ? u >> s : u;
+        pos = up ? pos + s : pos;
+      }
+      q = 32u * (uint32_t)w + pos + 1u;
+    }
+    uint32_t sp[FW];
+#pragma unroll
+    for (int i = 0; i < FW; ++i) sp[i] = 0;
+    static_for<0, 8>([&](auto Q) {
+      constexpr int i0 = 4 * decltype(Q)::value;
+      const int wi = min((int)(q >> 5), nw + 2);
+      const uint32_t c0 = cw[wi], c1 = cw[wi + 1], c2 = cw[wi + 2];
+      uint32_t lo = __builtin_amdgcn_alignbit(c1, c0, q & 31u), hi = __builtin_amdgcn_alignbit(c2, c1, q & 31u);
+      static_for<0, 4>([&](auto I) {
+        constexpr int i = i0 + decltype(I)::value;
+        const uint32_t z = (uint32_t)lowest_bit(lo), used = z + 1u;  // 16 zeros are not in the window
+        lo = __builtin_amdgcn_alignbit(hi, lo, used);
+        hi >>= used;
+        q += used;
+        const uint32_t f4 = field_at<SW, i>(sm);  // sign, mantissa bits
+        const uint32_t f = (((f4 << 8) | f4) & ((1u << (FW - 1)) | ((1u << mb) - 1u))) | etab[z];
+        constexpr int bit = i * FW, w = bit >> 5, sh = bit & 31;
+        sp[w] |= f << sh;
+        if constexpr (sh + FW > 32) sp[w + 1] |= f >> (32 - sh);
+      });
+    });
+    const int left = a.K - 32 * g;
+    if (left < 32) {  // nothing behind the last value
+#pragma unroll
+      for (int i = 0; i < FW; ++i) {
+        const int nb = left * FW - 32 * i;
+        sp[i] &= nb >= 32 ? 0xFFFFFFFFu : (nb <= 0 ? 0u : (1u << nb) - 1u);
+      }
+    }
+    uint32_t* dst = out + (size_t)(first + r) * a.sw + g * FW;
+    if ((g + 1) * FW <= a.sw) {
+      __builtin_memcpy(dst, sp, 4 * FW);
+    } else {
+#pragma unroll
+      for (int i = 0; i < FW; ++i)
+        if (g * FW + i < a.sw) dst[i] = sp[i];
+    }
+  }
+  if (!slow) return;
+  uint8_t* const exps = reinterpret_cast<uint8_t*>(lds32);  // [K + kExpSlack], over the code words
+  for (int r = 0; r < n; ++r) {
+    if (!((slow >> r) & 1u)) continue;
+    const int row = row0 + first + r;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t o0 = a.rowoff[row], o1 = a.rowoff[row + 1];
+    unary_row_exponents(a.ue + o0, (int)(o1 - o0), a.K, tab, exps, lane);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-  }
-  uint32_t* orow = out + (size_t)blockIdx.x * a.sw;
-  for (int w = lane; w < a.sw; w += 64) {
-    uint32_t word = 0;
-    for (int e = (32 * w) / FW; e < a.K; ++e) {
-      const int bit = e * FW - 32 * w;  // where the field starts, relative to the word (may be negative)
-      if (bit >= 32) break;
-      const uint32_t sm = read_field(sm_row, (uint32_t)e * SW, SW);
-      const uint32_t f = ((sm >> mb) << (mb + 8)) | ((uint32_t)exps[e] << mb) | (sm & ((1u << mb) - 1u));
-      word |= bit >= 0 ? f << bit : f >> (-bit);
+    const uint32_t* sm_row = a.u_sm + (size_t)row * a.smw;
+    uint32_t* orow = out + (size_t)(first + r) * a.sw;
+    for (int w = lane; w < a.sw; w += 64) {
+      uint32_t word = 0;
+      for (int e = (32 * w) / FW; e < a.K; ++e) {
+        const int bit = e * FW - 32 * w;  // where the field starts, relative to the word (may be negative)
+        if (bit >= 32) break;
+        const uint32_t f4 = read_field(sm_row, (uint32_t)e * SW, SW);
+        const uint32_t f = ((f4 >> mb) << (mb + 8)) | ((uint32_t)exps[e] << mb) | (f4 & ((1u << mb) - 1u));
+        word |= bit >= 0 ? f << bit : f >> (-bit);
+      }
+      orow[w] = word;
     }
-    orow[w] = word;
   }
 }
 
@@ -251,6 +393,14 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
 // per chunk whose row 0 is 0.0, so a lane that has run out of set bits multiplies by zero, and
 // a lane reads only its own 4-byte column of the block (no bank conflicts between lanes).
 constexpr int kUnaryWaves = 8;
+constexpr int kUnaryMinBlock = 1024;  // rows of a block that is worth two launches
+
+// LDS of that kernel: codebook, x as fp32, the exponents of a row per wave
+static size_t unary_gemv_lds(const cas_udesc& u) {
+  const cas_wdesc& d = u.base;
+  return 256 + (size_t)((d.bw + 63) / 64 * 64) * 33 * sizeof(float) +
+         (size_t)kUnaryWaves * (((d.K + 15) & ~15) + kExpSlack);
+}
 
 template <int T>
 __global__ __launch_bounds__(64 * kUnaryWaves) void gemv_draft_unary_kernel(UnaryArgs a, const uint16_t* __restrict__ x,
@@ -352,18 +502,80 @@ static UnaryArgs make_uargs(const cas_udesc& u, const void* spec_raw, void* uspe
   return a;
 }
 
+template <int T>
+static int launch_expand_t(cas_ctx* ctx, const UnaryArgs& a, int row0, int nrows, int R, int cap, size_t lds, uint32_t* out) {
+  static LdsLimit lim;
+  const int rc = allow_lds(ctx, (const void*)unary_expand_kernel<T>, lds, lim);
+  if (rc != CAS_OK) return rc;
+  hipLaunchKernelGGL(unary_expand_kernel<T>, dim3((unsigned)((nrows + R - 1) / R)), dim3(64), lds, ctx->stream, a, row0,
+                     nrows, R, cap, out);
+  CAS_HIP(ctx, hipGetLastError());
+  return CAS_OK;
+}
+
 int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int64_t row0, int nrows, uint32_t* out) {
   const cas_wdesc& d = u.base;
   if (nrows <= 0 || d.sw == 0) return CAS_OK;
-  const size_t lds = 256 + (size_t)((d.K + 3) & ~3) + kExpSlack + ((size_t)u.smw + 1) * 4;  // codebook, exponents, sm fields
-  if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  // widest row: codebook, exponents and sign / mantissa fields of one row in the LDS of a workgroup
+  if (256 + (size_t)((d.K + 3) & ~3) + kExpSlack + ((size_t)u.smw + 1) * 4 > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  // code words a row may have on the fast way: 3 bits per value (1.7 to 2.9 are usual); counts are 16 bits wide
+  const int cap = d.K < 65536 ? (3 * d.K / 32 + 64 + 1) & ~1 : 0;
+  // rows per wave: whichever of 1 to 4 leaves the fewest lanes without a group in the last turn, as long as
+  // every SIMD gets kExpandWaves waves
+  const int G = (d.K + 31) / 32;
+  int R = 1;
+  auto turns = [&](int r) { return (double)((r * G + 63) / 64) / r; };
+  for (int r = 2; r <= kExpandRows; ++r)
+    if (turns(r) < 0.95 * turns(R) && (size_t)r * cap * 6 <= 16 * 1024 && nrows >= r * ctx->num_cu * 4 * kExpandWaves) R = r;
+  const size_t lds = std::max<size_t>((size_t)R * cap * 6, (size_t)((d.K + 3) & ~3) + kExpSlack);
   UnaryArgs a = make_uargs(u, nullptr, const_cast<void*>(uspec), nullptr);
-  static LdsLimit lim;
-  const int rc = allow_lds(ctx, (const void*)unary_expand_kernel, lds, lim);
-  if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL(unary_expand_kernel, dim3((unsigned)nrows), dim3(64), lds, ctx->stream, a, (int)row0, out);
-  CAS_HIP(ctx, hipGetLastError());
+#define CAS_T(TV) case TV: return launch_expand_t<TV>(ctx, a, (int)row0, nrows, R, cap, lds, out);
+  switch (d.t) {
+    CAS_T(0) CAS_T(1) CAS_T(2) CAS_T(3) CAS_T(4) CAS_T(5) CAS_T(6) CAS_T(7)
+  }
+#undef CAS_T
+  return CAS_EINVAL;
+}
+
+// Draft product through the raw form: blocks of rows are re-coded into the workspace and the GEMV of the
+// raw form, with its fused neighbours, runs on each of them (batch columns at once; every output has the
+// bits that the raw form gives).  CAS_ENOMEM where the caller is to take the kernel that decodes the codes
+// itself, column by column: for one column of a matrix whose rows leave that kernel two workgroups per CU or
+// more, and where the workspace holds no block worth a launch.  One column, through the workspace / decoded
+// in the kernel: 4096 x 14336 (one workgroup per CU) 48 / 70 us, 28672 x 4096 108 / 82 us, 4096 x 4096
+// 21.5 / 18.4 us; a second column costs the former a few us, the latter the same again.
+static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch, float* y,
+                            const uint16_t* gain, float eps, int epi, uint16_t* out16) {
+  const cas_wdesc& d = u.base;
+  if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
+  if (d.sw == 0 || (batch == 1 && 2 * unary_gemv_lds(u) <= (size_t)ctx->lds_max)) return CAS_ENOMEM;
+  const size_t row_bytes = (size_t)d.sw * 4;
+  int64_t blk = ctx->d_ws && ctx->ws_bytes > 256 ? (int64_t)((ctx->ws_bytes - 256) / row_bytes) : 0;
+  blk = std::min<int64_t>(blk, d.rows);
+  if (blk < d.rows) {
+    // equal blocks of an even number of rows
+    const int64_t nblk = blk < 2 ? d.rows : (d.rows + blk - 1) / blk;
+    blk = (d.rows + nblk - 1) / nblk;
+    blk += blk & 1;
+    if (blk < kUnaryMinBlock || blk * (int64_t)row_bytes + 256 > (int64_t)ctx->ws_bytes) return CAS_ENOMEM;
+  }
+  for (int64_t r0 = 0; r0 < d.rows; r0 += blk) {
+    const int nr = (int)std::min<int64_t>(blk, d.rows - r0);
+    int rc = launch_unary_expand(ctx, u, uspec, r0, nr, (uint32_t*)ctx->d_ws);
+    if (rc != CAS_OK) return rc;
+    rc = launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)uspec + u.off_bitmap) + (size_t)r0 * d.bw,
+                                 (const uint32_t*)ctx->d_ws, nr, x, batch, y ? y + r0 : nullptr, gain, eps, epi,
+                                 out16 ? out16 + (epi == 2 ? r0 / 2 : r0) : nullptr);
+    if (rc != CAS_OK) return rc;
+  }
   return CAS_OK;
+}
+
+int launch_gemv_draft_unary_fused(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch,
+                                  float* y, const uint16_t* gain, float eps, int epi, uint16_t* out16) {
+  if (u.base.rows <= 0) return CAS_OK;
+  if (unary_gemv_lds(u) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  return unary_draft_rows(ctx, u, uspec, x, batch, y, gain, eps, epi, out16);
 }
 
 static int64_t up256(int64_t v) { return (v + 255) / 256 * 256; }
@@ -539,9 +751,12 @@ extern "C" int cas_gemv_draft_unary(cas_ctx* ctx, const cas_udesc* udesc, const 
   if (d.rows == 0) return CAS_OK;
   if (!d_uspec || !d_x || !d_y || !aligned256(d_uspec)) return CAS_EINVAL;
   const int kpad = (d.K + 15) & ~15;
-  const size_t nseg = (size_t)((d.bw + 63) / 64 * 64);
-  const size_t lds = 256 + nseg * 33 * sizeof(float) + (size_t)kUnaryWaves * (kpad + kExpSlack);
+  const size_t lds = unary_gemv_lds(*udesc);
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  if (d.rows >= kUnaryMinBlock) {
+    const int rc = unary_draft_rows(ctx, *udesc, d_uspec, d_x, 1, d_y, nullptr, 0.f, 0, nullptr);
+    if (rc != CAS_ENOMEM) return rc;
+  }
   UnaryArgs a = make_uargs(*udesc, nullptr, const_cast<void*>(d_uspec), nullptr);
   // as many workgroups as stay resident: every one of them stages x once
   const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, (size_t)ctx->lds_max / lds));

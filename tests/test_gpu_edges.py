@@ -141,3 +141,32 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
         got.append((kv.spec_pool.clone(), kv.verif_pool.clone(), logits))
     for narrow, wide in zip(*got):
         assert torch.equal(narrow, wide)
+
+
+@pytest.mark.parametrize("rows,cols,keep", [(5, 1, 1000), (7, 31, 1000), (70, 33, 1000), (9, 64, 500), (1030, 4096, 600),
+                                            (66, 5001, 333), (1030, 14336, 700)])
+@pytest.mark.parametrize("t", [0, 4, 7])
+def test_unary_rows_recoded_in_the_workspace(env, rows, cols, keep, t):
+    """Rows of few exponents, rows with more than 16 of them (codes longer than a window takes), a row whose
+    codes are long throughout; kept counts around a group of 32.  Both products have the bits that the raw
+    form gives; without a workspace the draft product agrees up to the order of its sums."""
+    torch, B, _ = env
+    rng = np.random.Generator(np.random.Philox(rows + cols))
+    W = synth.weight_matrix(rows, cols, seed=8)
+    wide = rng.integers(100, 140, size=(rows, cols)).astype(np.uint16) << 7
+    W[1::5] = (W[1::5] & 0x807F) | wide[1::5]                      # 40 exponents in every fifth row
+    W[2] = (W[2] & 0x807F) | (98 << 7)                             # the rarest exponent throughout
+    x, X = _dev(torch, synth.activations(cols, 1, seed=9)), _dev(torch, synth.activations(cols, 3, seed=10))
+    with_ws = B.Context(workspace=torch.empty(8 << 20, dtype=torch.uint8, device="cuda"))
+    ew = B.cas_encode_weight(with_ws, _dev(torch, W), keep, t)
+    ue = B.cas_unary_encode(with_ws, ew)
+    want = B.cas_gemm_verify(with_ws, ew, X)
+    assert torch.equal(B.cas_gemm_verify_unary(with_ws, ue, X), want)
+    want = B.cas_gemv_draft(with_ws, ew, x)[0]
+    y = B.cas_gemv_draft_unary(with_ws, ue, x)
+    if cols > 8192 and rows >= 1024:
+        assert torch.equal(y, want)
+    none = B.cas_gemv_draft_unary(B.Context(), ue, x)
+    scale = np.linalg.norm(O.bf16_to_f64(W), axis=1) * np.linalg.norm(O.bf16_to_f64(x.cpu().numpy().view(np.uint16)))
+    for other in (y, none):
+        assert (np.abs((other - want).cpu().numpy().astype(np.float64)).reshape(-1) <= cols * 2.0 ** -23 * scale).all()
