@@ -273,8 +273,11 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   // ---- 3. K tile: this thread's 32 channels of its token
   {
     if (!own_new) {
+      // the exact form writes all 32 channels of a committed token: nothing to clear first
+      if (!FULL || !live) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(krow + 4 * q) = 0ull;
+        for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(krow + 4 * q) = 0ull;
+      }
       if (fresh) {
         const uint16_t* src = a.Knew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 32 * j;
 #pragma unroll
@@ -316,6 +319,11 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
     }
   }
   __syncthreads();  // every wave is done with Q and K: their regions may be overwritten
+  // the draft form clears the whole V tile with 16-byte writes (5 per thread; 32 of 2 bytes when every thread
+  // clears the channels of its own token)
+  if constexpr (!FULL) {
+    for (int i = tid; i < kVR * kVP / 8; i += 256) reinterpret_cast<uint4*>(Vt)[i] = make_uint4(0, 0, 0, 0);
+  }
   // ---- 5. softmax numerators of the page, head + remainder in bf16; row sums per wave
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -331,11 +339,16 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
       if (mi == 0) wl[wv * (MT * 16) + rr] = ps;
     }
   }
+  if constexpr (!FULL) __syncthreads();
   // ---- 6. V tile, transposed: Vt[channel][token]
   {
     if (!own_new) {
+      if constexpr (FULL) {
+        if (!live) {
 #pragma unroll
-      for (int c = 0; c < 32; ++c) vcol[c * kVP] = 0;
+          for (int c = 0; c < 32; ++c) vcol[c * kVP] = 0;
+        }
+      }
       if (fresh) {
         const uint16_t* src = a.Vnew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 32 * j;
 #pragma unroll
