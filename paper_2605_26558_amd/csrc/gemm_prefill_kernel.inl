@@ -63,9 +63,11 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   }
 
   // first bitmap word of block b in the order of the sums
+  // (wpl is a power of two; x / nslab by multiplication: x < 16 nslab, nslab <= 32)
+  const int wsh = __builtin_ctz(wpl), inv_nslab = (65536 + nslab - 1) / nslab;
   auto block_word = [&](int b) -> int {
-    const int part = b / per_part, rem = b - part * per_part, slab = rem / wpl;
-    return slab * 64 + part * (64 / Q) + 4 * (rem - slab * wpl);
+    const int x = b >> wsh, part = x * inv_nslab >> 16, slab = x - part * nslab;
+    return slab * 64 + part * (64 / Q) + 4 * (b & (wpl - 1));
   };
 
   // ---- decode role: row r of the tile, block qb of the step (the same for a whole wave), word j of the block
@@ -79,18 +81,16 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   WordWindows<T, true, MX> ww;
   uint32_t m_next = 0, m_cur = 0;
   int e_next = 0, e_cur = 0, nvalid = 0;
+  // Loads are issued on every path, past the last step for that step again: where a load may or may not
+  // have been issued, the compiler's wait for an older one waits for it as well.
   auto load_mask = [&](int st) {
-    m_next = 0;
-    if (st >= nsteps) return;
-    const int w = block_word(st * KB + qb) + j;
-    if (w < a.bw) {
-      m_next = bm_row[w];
-      if constexpr (MX) e_next = (int)a.sexp[(size_t)row * a.ew + w];
-    }
+    const int w = block_word(min(st, nsteps - 1) * KB + qb) + j, wc = min(w, a.bw - 1);
+    const uint32_t m = bm_row[wc];
+    m_next = w < a.bw ? m : 0u;
+    if constexpr (MX) e_next = (int)a.sexp[(size_t)row * a.ew + wc];
   };
   auto issue = [&](int st) {  // windows of the step whose mask came last
-    if (st >= nsteps) return;
-    const int w0 = block_word(st * KB + qb);
+    const int w0 = block_word(min(st, nsteps - 1) * KB + qb);
     m_cur = m_next;
     e_cur = e_next;
     const int cnt = __popc(m_cur);
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   const bool act0 = cb0 + 16 * wv < a.ncols, act1 = cb0 + 128 + 16 * wv < a.ncols;
   // X comes packed (pack_x_kernel): the fragments of 16 columns and 32 values of k are one run of 1 KB
   const size_t xrow = (size_t)nblk * 4 * 512;  // values of a block of 16 columns
-  const uint16_t* const xp0 = a.X + (size_t)((cb0 >> 4) + wv) * xrow + lane * 8;
+  const uint16_t* const xp0 = a.X + (size_t)((cb0 >> 4) + (act0 ? wv : 0)) * xrow + lane * 8;
   const uint16_t* const xp1 = act1 ? xp0 + 8 * xrow : xp0;
   f32x4 C[RT][2], S[RT][2];  // running sum of the part, sum of the parts before it
 #pragma unroll
@@ -127,8 +127,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
     for (int nb = 0; nb < 2; ++nb) C[i][nb] = S[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   uint4 xa[4][2], xb[4][2];
   auto load_x = [&](int b, uint4 (&x)[4][2]) {
-    const int blk = block_word(b) >> 2;
-    if (!act0 || b >= nsteps * KB || blk >= nblk) return;
+    const int blk = min(block_word(min(b, nsteps * KB - 1)) >> 2, nblk - 1);  // not used past the end
 #pragma unroll
     for (int kq = 0; kq < 4; ++kq) {
       x[kq][0] = *reinterpret_cast<const uint4*>(xp0 + (size_t)(blk * 4 + kq) * 512);
@@ -166,22 +165,29 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
       }
       if (block_word(b) >= a.bw) return;  // past the end of the rows
       const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 4 * mq;
+      auto block = [&](auto NB) {
+        bf16x4 av[2][RT];  // fragments of the rows, one product ahead
+        auto load_a = [&](int kk, bf16x4 (&f)[RT]) {
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        const int o = (kk >> 1) * kGroupPitch + (kk & 1) * 16;
-        const uint4 &f0 = x[kk >> 1][0], &f1 = x[kk >> 1][1];
-        const bf16x4 b0 = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f0.z, f0.w} : u32x2{f0.x, f0.y});
-        const bf16x4 b1 = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f1.z, f1.w} : u32x2{f1.x, f1.y});
-        bf16x4 av[RT];
+          for (int i = 0; i < RT; ++i)
+            f[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + (kk >> 1) * kGroupPitch + (kk & 1) * 16);
+        };
+        load_a(0, av[0]);
 #pragma unroll
-        for (int i = 0; i < RT; ++i) av[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + o);
+        for (int kk = 0; kk < 8; ++kk) {
+          if (kk < 7) load_a(kk + 1, av[(kk + 1) & 1]);
 #pragma unroll
-        for (int i = 0; i < RT; ++i) C[i][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[i], b0, C[i][0], 0, 0, 0);
-        if (act1) {
+          for (int nb = 0; nb < decltype(NB)::value; ++nb) {
+            const uint4& f = x[kk >> 1][nb];
+            const bf16x4 bv = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f.z, f.w} : u32x2{f.x, f.y});
 #pragma unroll
-          for (int i = 0; i < RT; ++i) C[i][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[i], b1, C[i][1], 0, 0, 0);
+            for (int i = 0; i < RT; ++i)
+              C[i][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[kk & 1][i], bv, C[i][nb], 0, 0, 0);
+          }
         }
-      }
+      };
+      if (act1) block(std::integral_constant<int, 2>{});
+      else block(std::integral_constant<int, 1>{});
     });
   };
 

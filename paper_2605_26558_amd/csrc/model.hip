@@ -419,7 +419,7 @@ static ActLayout act_layout(const cas_model_cfg& c) {
 // chunk's keys and values are appended to the cache, and attention runs over runs of `sub` columns, each of
 // which reads the positions before it from the cache and its own uncompressed, exactly as a pass of `sub`
 // columns does.  A chunk therefore leaves the bits in the cache that such passes leave.
-// 8B-shaped, 4 layers, 508 tokens: 5.3 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
+// 8B-shaped, 4 layers, 508 tokens: 4.9 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
 // and 31 unread rows of logits it saves).
 constexpr int kPrefillChunk = 512;
 constexpr int kPrefillMin = 48;  // fewer columns: passes through the narrow kernels are as fast
