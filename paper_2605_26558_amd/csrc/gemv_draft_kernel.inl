@@ -83,7 +83,7 @@ struct XStage<true> {
 // products of a word are summed unscaled and multiplied once by 2^(E + T - 134).  The signed
 // magnitude of a field comes from a table of 2^(9-T) floats in LDS, indexed with the field itself: two
 // operations and a gather, where taking it apart and converting it took five in a kernel that is
-// bound by them (8B shape, mean of the launches of a pass: 22.8 us, now 19.5 with the exponents read through a
+// bound by them (8B shape, mean of the launches of a pass: 22.8 us, now 19.9 with the exponents read through a
 // descriptor as well).
 template <int T, int NB, bool MX>
 __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
