@@ -441,7 +441,8 @@ int cas_model_destroy(cas_model* model);
 /* Switches one linear layer of the model to the unary form of its speculation data (Sec. 4.2
  * lossless configuration): from then on draft passes read d_uspec through the kernel of
  * cas_gemv_draft_unary (norm, residual add and SwiGLU run as separate launches with the same
- * roundings) and verification passes through cas_gemm_verify_unary, whose results equal those
+ * roundings) or, for several columns and for rows that leave that kernel one workgroup per CU, through
+ * rows re-coded in the context's workspace if that holds 1024 of them, and verification passes through cas_gemm_verify_unary, whose results equal those
  * of the raw form bit for bit; the tensor's raw d_spec is no longer read and may be freed.
  * layer: 0 .. n_layers-1, or -1 for the output head (which is then ignored); which: 0 wqkv,
  * 1 wo, 2 wgu, 3 wd.  udesc / d_uspec: from cas_unary_plan / cas_unary_encode on that tensor
@@ -509,8 +510,11 @@ int cas_spec_round(cas_ctx* ctx, cas_model* model, cas_kv* kv, int seq, int32_t 
 int cas_spec_round_multi(cas_ctx* ctx, cas_model* model, cas_kv* kv, int n_seqs, const int32_t* h_seqs,
                          const int32_t* h_pending, int k, int32_t* h_out, int32_t* h_n_accepted);
 
-/* Prefill (functional): runs n prompt tokens through the target path in chunks of as many
- * columns as one sequence may bring to a pass (see max_cols) and commits all of them.  d_tokens: int32 [n] on the device. */
+/* Prefill: runs n prompt tokens through the target path and commits all of them.  Chunks of up to 512
+ * tokens whose activations fit the context's workspace (some 90 KB per token for an 8B-shaped model, and
+ * the attention partials) go through every layer together; what is left, or all of it with a smaller
+ * workspace, goes in passes of as many columns as one sequence may bring to a pass (see max_cols).  Both ways
+ * leave the same bits in the cache.  d_tokens: int32 [n] on the device. */
 int cas_prefill(cas_ctx* ctx, cas_model* model, cas_kv* kv, int seq, const int32_t* d_tokens, int n);
 
 /* Plain bf16 decode step of the same model from UNCOMPRESSED weights and an uncompressed cache:

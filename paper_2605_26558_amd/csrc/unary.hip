@@ -537,7 +537,7 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
   return CAS_EINVAL;
 }
 
-// Draft product through the raw form: blocks of rows are re-coded into the workspace and the GEMV of the
+// Draft product of a model's pass through the raw form: blocks of rows are re-coded into the workspace and the GEMV of the
 // raw form, with its fused neighbours, runs on each of them (batch columns at once; every output has the
 // bits that the raw form gives).  CAS_ENOMEM where the caller is to take the kernel that decodes the codes
 // itself, column by column: for one column of a matrix whose rows leave that kernel two workgroups per CU or
@@ -753,10 +753,7 @@ extern "C" int cas_gemv_draft_unary(cas_ctx* ctx, const cas_udesc* udesc, const 
   const int kpad = (d.K + 15) & ~15;
   const size_t lds = unary_gemv_lds(*udesc);
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
-  if (d.rows >= kUnaryMinBlock) {
-    const int rc = unary_draft_rows(ctx, *udesc, d_uspec, d_x, 1, d_y, nullptr, 0.f, 0, nullptr);
-    if (rc != CAS_ENOMEM) return rc;
-  }
+  // never through the workspace (see unary_draft_rows): this call does not use it, whoever shares it
   UnaryArgs a = make_uargs(*udesc, nullptr, const_cast<void*>(d_uspec), nullptr);
   // as many workgroups as stay resident: every one of them stages x once
   const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, (size_t)ctx->lds_max / lds));
