@@ -49,7 +49,6 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
   static_assert(XST >= 1 && WPL % XST == 0 && NB >= 1 && NB <= 2, "staging divides the steps of a slab");
   constexpr int XQ = XST * 128;      // X columns one wave stages at a time
   constexpr int XQP = XQ + 8;        // row pitch of its private copy (bf16)
-  constexpr int XB = 2;              // pieces of X a lane has in flight while staging
   extern __shared__ uint16_t lds[];
   uint16_t* tiles = lds;                                 // [NW][16][kTilePitch]
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -150,8 +149,9 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
     kw.load(p4[0], sp_row, lo_row);
     // ---- this wave's X columns of the next XST steps (bf16, zero beyond the last column), in pieces
     // of 8 columns.  Where the number of columns is not a multiple of 8, a row of X starts at any multiple of
-    // 2 bytes and the 16-byte loads assume no more than that; XB pieces per lane are requested together.
-    // 11003 x 5001 with 20 columns: 59 us, with 2-byte loads 198 us.  The plain loop stays for the others: it
+    // 2 bytes and the 16-byte loads assume no more than that (loops left rolled: unrolled they cost the other
+    // matrices registers, in some forms a wave per SIMD).
+    // 11003 x 5001 with 20 columns: 60 us, with 2-byte loads 197 us.  The plain loop stays for the others: it
     // is 1 % faster in the passes of four sequences.
     auto stage_x = [&](int s) {
       const int col0 = slab * kSlabCols + part * (WPP * 32) + s * XQ;
@@ -163,29 +163,18 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
           *reinterpret_cast<uint4*>(Xq + c * XQP + o) = v;
         }
       } else {
-        const int n = a.ncols * (XQ / 8);
-        for (int i0 = lane; i0 < n; i0 += 64 * XB) {
-          uint4 v[XB];
-#pragma unroll
-          for (int q = 0; q < XB; ++q) {
-            const int i = i0 + 64 * q, c = i / (XQ / 8), col = col0 + (i - c * (XQ / 8)) * 8;
-            v[q] = make_uint4(0, 0, 0, 0);
-            if (i < n) {
-              const uint16_t* src = a.X + (size_t)c * a.cols + col;
-              if (col + 8 <= a.cols) {
-                __builtin_memcpy(&v[q], src, 16);
-              } else if (col < a.cols) {  // the ragged end of a row of X
-                uint16_t e[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) e[k] = col + k < a.cols ? src[k] : (uint16_t)0;
-                __builtin_memcpy(&v[q], e, 16);
-              }
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < XB; ++q) {
-            const int i = i0 + 64 * q, c = i / (XQ / 8), o = (i - c * (XQ / 8)) * 8;
-            if (i < n) *reinterpret_cast<uint4*>(Xq + c * XQP + o) = v[q];
+#pragma unroll 1
+        for (int i = lane; i < a.ncols * (XQ / 8); i += 64) {
+          const int c = i / (XQ / 8), o = (i - c * (XQ / 8)) * 8, col = col0 + o;
+          const uint16_t* src = a.X + (size_t)c * a.cols + col;
+          uint16_t* dst = Xq + c * XQP + o;
+          if (col + 8 <= a.cols) {
+            uint4 v;
+            __builtin_memcpy(&v, src, 16);
+            *reinterpret_cast<uint4*>(dst) = v;
+          } else {  // the ragged end of a row of X
+#pragma unroll 1
+            for (int k = 0; k < 8; ++k) dst[k] = col + k < a.cols ? src[k] : (uint16_t)0;
           }
         }
       }
