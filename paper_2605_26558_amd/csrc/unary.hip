@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64) void unary_decode_kernel(UnaryArgs a, uint16_t*
 // That holds for rows whose ranks stay below 16 (64 bits then hold four codes) and whose code stream is not
 // unusually long; step 1 looks for both, and the other rows go through unary_row_exponents one by one.
 // Bound by the arithmetic of step 2 (about 13 operations per kept value, 20 with the searches).  Mean of the
-// launches of a verification pass of the 8B shape: 40 us; 68 us when a lane walked the codes that end in one
+// launches of a round on 4 layers of the 8B shape: 34 us; 68 us when a lane walked the codes that end in one
 // code word and the words of the stream were put together field by field.
 constexpr int kExpandWaves = 3;
 constexpr int kExpandRows = 4;  // most rows of a workgroup
