@@ -439,11 +439,14 @@ int cas_model_create(const cas_model_cfg* cfg, const cas_model_weights* weights,
 int cas_model_destroy(cas_model* model);
 
 /* Switches one linear layer of the model to the unary form of its speculation data (Sec. 4.2
- * lossless configuration): from then on draft passes read d_uspec through the kernel of
- * cas_gemv_draft_unary (norm, residual add and SwiGLU run as separate launches with the same
- * roundings) or, for several columns and for rows that leave that kernel one workgroup per CU, through
- * rows re-coded in the context's workspace if that holds 1024 of them, and verification passes through cas_gemm_verify_unary, whose results equal those
- * of the raw form bit for bit; the tensor's raw d_spec is no longer read and may be freed.
+ * lossless configuration): from then on draft passes read d_uspec, either through the kernel of
+ * cas_gemv_draft_unary, column by column, or through rows re-coded in the context's workspace
+ * (several columns, or rows that leave that kernel one workgroup per CU, where the workspace holds
+ * the whole matrix or 1024 rows of it).  A column's values are the same either way, whatever
+ * columns come with it.  RMSNorm runs as a launch of its own: its sum has the order of the
+ * verification pass's norm.  Verification passes go through cas_gemm_verify_unary, whose results
+ * equal those of the raw form bit for bit; the tensor's raw d_spec is no longer read and may be
+ * freed.
  * layer: 0 .. n_layers-1, or -1 for the output head (which is then ignored); which: 0 wqkv,
  * 1 wo, 2 wgu, 3 wd.  udesc / d_uspec: from cas_unary_plan / cas_unary_encode on that tensor
  * (the descriptor is copied, the buffer stays caller-owned); udesc = NULL switches back.

@@ -83,10 +83,10 @@ int launch_gemv_draft_fused(cas_ctx*, const cas_wdesc&, const void* spec, const 
 int launch_gemv_draft_block(cas_ctx*, const cas_wdesc&, const uint32_t* bitmap, const uint32_t* spec, int nr,
                             const uint16_t* x, int batch, float* y, const uint16_t* gain, float eps, int epi,
                             uint16_t* out16);
-// unary.hip: the draft product with the fused neighbours through the raw form re-coded in the workspace;
+// unary.hip: the draft product and what follows it (epi) through the raw form re-coded in the workspace;
 // CAS_ENOMEM if that is too small
 int launch_gemv_draft_unary_fused(cas_ctx*, const cas_udesc&, const void* uspec, const uint16_t* x, int batch, float* y,
-                                  const uint16_t* gain, float eps, int epi, uint16_t* out16);
+                                  int epi, uint16_t* out16);
 int launch_gemm_verify(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X, int ncols, float* Y);
 // wide: the form for the columns of a prompt (any number of them, X from launch_pack_x), same bits
 int launch_gemm_verify_fused(cas_ctx*, const cas_wdesc&, const void* spec, const void* verif, const uint16_t* X,

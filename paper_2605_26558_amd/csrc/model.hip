@@ -268,9 +268,9 @@ static int forward(cas_ctx* ctx, cas_model* m, cas_kv* kv, const ColGroup* grp, 
   hipStream_t st = ctx->stream;
   float* logits = d_logits ? d_logits : m->logits;
   // A linear layer of the draft pass.  Raw form: one fused launch (norm of x, product, residual
-  // add or SwiGLU).  Unary form: the same on rows re-coded in the workspace; without one, the same
-  // operations with the same roundings as separate launches around the GEMV that reads the unary
-  // buffer, column by column.
+  // add or SwiGLU).  Unary form: the norm, then the product with what follows it fused on rows re-coded
+  // in the workspace; or the same operations with the same roundings as separate launches around the
+  // GEMV that reads the unary buffer, column by column.
   auto lin_draft = [&](const cas_tensor& T, const cas_model::UnaryRef& U, const uint16_t* x, float* y,
                        const uint16_t* gain, int epi, uint16_t* out16) -> int {
     const int rows = (int)T.desc.rows, cols = (int)T.desc.cols;
@@ -284,20 +284,22 @@ static int forward(cas_ctx* ctx, cas_model* m, cas_kv* kv, const ColGroup* grp, 
       return CAS_OK;
     }
     if (!U.on) return launch_gemv_draft_fused(ctx, T.desc, T.d_spec, x, ncols, y, gain, c.rms_eps, epi, out16);
+    // the norm is a launch of its own on every route, and both GEMVs add a row in the same order: a column's
+    // bits depend neither on the columns beside it nor on the workspace
+    if (gain) {
+      hipLaunchKernelGGL(rmsnorm_kernel, dim3(ncols), dim3(kNormThreads), 0, st, x, gain, m->xn, cols, c.rms_eps);
+      x = m->xn;
+    }
     {
       // through the raw form in the workspace: the columns at once, one by one where x of all of them does not fit the LDS
-      int rc = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x, ncols, y, gain, c.rms_eps, epi, out16);
+      int rc = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x, ncols, y, epi, out16);
       for (int col = 0; rc == CAS_ENOTSUP && ncols > 1 && col < ncols; ++col) {
         const int one = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x + (size_t)col * cols, 1,
-                                                      y ? y + (size_t)col * rows : nullptr, gain, c.rms_eps, epi,
+                                                      y ? y + (size_t)col * rows : nullptr, epi,
                                                       out16 ? out16 + (size_t)col * (epi == 2 ? rows / 2 : rows) : nullptr);
         if (one != CAS_OK || col == ncols - 1) rc = one;
       }
       if (rc != CAS_ENOMEM) return rc;
-    }
-    if (gain) {
-      hipLaunchKernelGGL(rmsnorm_kernel, dim3(ncols), dim3(kNormThreads), 0, st, x, gain, m->xn, cols, c.rms_eps);
-      x = m->xn;
     }
     float* yy = epi == 0 ? y : m->y;
     for (int col = 0; col < ncols; ++col) {

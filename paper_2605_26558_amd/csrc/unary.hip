@@ -538,14 +538,14 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
 }
 
 // Draft product of a model's pass through the raw form: blocks of rows are re-coded into the workspace and the GEMV of the
-// raw form, with its fused neighbours, runs on each of them (batch columns at once; every output has the
-// bits that the raw form gives).  CAS_ENOMEM where the caller is to take the kernel that decodes the codes
+// raw form, with the residual add or SwiGLU fused, runs on each of them (batch columns at once; every output has
+// the bits that the kernel below and the raw form give: all three walk a row in the same order).  CAS_ENOMEM where the caller is to take the kernel that decodes the codes
 // itself, column by column: for one column of a matrix whose rows leave that kernel two workgroups per CU or
 // more, and where the workspace holds no block worth a launch.  One column, through the workspace / decoded
 // in the kernel: 4096 x 14336 (one workgroup per CU) 48 / 70 us, 28672 x 4096 108 / 82 us, 4096 x 4096
 // 21.5 / 18.4 us; a second column costs the former a few us, the latter the same again.
 static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch, float* y,
-                            const uint16_t* gain, float eps, int epi, uint16_t* out16) {
+                            int epi, uint16_t* out16) {
   const cas_wdesc& d = u.base;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
   if (d.sw == 0 || (batch == 1 && 2 * unary_gemv_lds(u) <= (size_t)ctx->lds_max)) return CAS_ENOMEM;
@@ -564,7 +564,7 @@ static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec,
     int rc = launch_unary_expand(ctx, u, uspec, r0, nr, (uint32_t*)ctx->d_ws);
     if (rc != CAS_OK) return rc;
     rc = launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)uspec + u.off_bitmap) + (size_t)r0 * d.bw,
-                                 (const uint32_t*)ctx->d_ws, nr, x, batch, y ? y + r0 : nullptr, gain, eps, epi,
+                                 (const uint32_t*)ctx->d_ws, nr, x, batch, y ? y + r0 : nullptr, nullptr, 0.f, epi,
                                  out16 ? out16 + (epi == 2 ? r0 / 2 : r0) : nullptr);
     if (rc != CAS_OK) return rc;
   }
@@ -572,10 +572,10 @@ static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec,
 }
 
 int launch_gemv_draft_unary_fused(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch,
-                                  float* y, const uint16_t* gain, float eps, int epi, uint16_t* out16) {
+                                  float* y, int epi, uint16_t* out16) {
   if (u.base.rows <= 0) return CAS_OK;
   if (unary_gemv_lds(u) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
-  return unary_draft_rows(ctx, u, uspec, x, batch, y, gain, eps, epi, out16);
+  return unary_draft_rows(ctx, u, uspec, x, batch, y, epi, out16);
 }
 
 static int64_t up256(int64_t v) { return (v + 255) / 256 * 256; }

@@ -184,3 +184,71 @@ def test_unary_draft_pass_through_the_workspace_and_without(env, wide_models):
         B.cas_draft_step(ctx, model, kv, 0, tokens[-1:], 0, torch.empty(1, dtype=torch.int32, device="cuda"), logits)
         got.append(logits.double())
     assert float((got[0] - got[1]).norm() / got[0].norm()) < 0.01
+
+
+def _unary_draft_model(env, hidden, n_q, n_kv, ffn, ws, unary):
+    """Two layers and a head on unary-coded (or raw) weights, a context with a workspace of ws bytes."""
+    from types import SimpleNamespace
+    torch, B, _ = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    bits = lambda x: x.to(torch.bfloat16).view(torch.int16)  # noqa: E731
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    sh = SimpleNamespace(hidden=hidden, n_layers=2, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, ffn=ffn, vocab=301,
+                         rms_eps=1e-5)
+    dims = (("wqkv", (n_q + 2 * n_kv) * 128, hidden), ("wo", hidden, n_q * 128), ("wgu", 2 * ffn, hidden),
+            ("wd", hidden, ffn))
+    big = B.Context(workspace=torch.empty(8 << 20, dtype=torch.uint8, device="cuda"))
+    layers = []
+    for _ in range(2):
+        L = {n: B.cas_encode_weight(big, bits(rnd(r, c) * c ** -0.5), 600, 4) for n, r, c in dims}
+        layers.append(dict(L, g_attn=bits(1 + 0.1 * rnd(hidden)), g_ffn=bits(1 + 0.1 * rnd(hidden))))
+    head = B.cas_encode_weight(big, bits(rnd(301, hidden) * hidden ** -0.5), 600, 4)
+    embed, gain = bits(rnd(301, hidden)), bits(1 + 0.1 * rnd(hidden))
+    rope = torch.from_numpy(synth.rope_table(64, 128, 500000.0)).cuda()
+    ctx = B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda"))
+    model = B.Model(ctx, sh, layers, head, embed, gain, rope, max_cols=16, max_seqs=4)
+    if unary:
+        for i in range(2):
+            for which, (n, _, _) in enumerate(dims):
+                model.use_unary(i, which, B.cas_unary_encode(big, layers[i][n]))
+        model.use_unary(-1, 0, B.cas_unary_encode(big, head))
+    kv = B.KVCache(ctx, 2, n_kv, n_pages=4, max_seqs=4, max_pages_per_seq=1, keep_permille=600, trunc_bits=4)
+    return ctx, model, kv
+
+
+def _draft_kv(env, ctx, model, kv, n_seqs):
+    """The last layer's keys and values of 48 draft passes, sequence by sequence."""
+    torch, B, _ = env
+    tokens = torch.from_numpy(synth.token_ids(48, 301, seed=3)).cuda()
+    out = torch.empty(4, dtype=torch.int32, device="cuda")
+    for seq in range(n_seqs):
+        B.cas_kv_set_len(kv, seq, 0)
+    for i in range(48):
+        if n_seqs == 1:
+            B.cas_draft_step(ctx, model, kv, 0, tokens[i:i + 1], i % 16, out)
+        else:
+            B.cas_draft_step_multi(ctx, model, kv, list(range(n_seqs)), [i % 16] * n_seqs, tokens[i].repeat(n_seqs), out)
+        if i % 16 == 15:
+            for seq in range(n_seqs):
+                B.cas_commit(ctx, model, kv, seq, 15)
+    return [torch.stack(B.cas_kv_read(ctx, kv, 1, seq, 0, 48, True)) for seq in range(n_seqs)]
+
+
+@pytest.mark.parametrize("hidden,n_q,n_kv,ffn,blocks,raw", [(264, 4, 2, 520, 400 << 10, True),
+                                                            (2056, 14, 2, 1100, 2500 << 10, True),
+                                                            (8192, 8, 2, 1024, 8 << 20, False),
+                                                            (8199, 16, 4, 1031, 12 << 20, False)])
+def test_unary_draft_values_depend_on_neither_company_nor_workspace(env, hidden, n_q, n_kv, ffn, blocks, raw):
+    """One, two and four columns through a workspace that holds whole matrices, through one that cuts them into
+    blocks with a smaller last one (outputs of all three kinds: projection, residual add, SwiGLU) and through
+    one that holds none: the same bits.  For a hidden size in eights up to 4096 the raw form's fused norm adds in the same
+    order too, so the raw form gives these bits as well."""
+    torch = env[0]
+    want = None
+    for ws, unary in [(32 << 20, True), (blocks, True), (256 << 10, True)] + ([(32 << 20, False)] if raw else []):
+        ctx, model, kv = _unary_draft_model(env, hidden, n_q, n_kv, ffn, ws, unary)
+        for n_seqs in (1, 2, 4):
+            for got in _draft_kv(env, ctx, model, kv, n_seqs):
+                want = got if want is None else want
+                assert torch.equal(got, want), (ws, unary, n_seqs)
