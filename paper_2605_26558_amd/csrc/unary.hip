@@ -502,6 +502,33 @@ static UnaryArgs make_uargs(const cas_udesc& u, const void* spec_raw, void* uspe
   return a;
 }
 
+static int64_t up256(int64_t v) { return (v + 255) / 256 * 256; }
+constexpr int64_t kUnarySlack = 256;
+
+static void fill_layout(cas_udesc* u) {
+  const cas_wdesc& d = u->base;
+  u->smw = (int32_t)(((int64_t)d.K * (8 - d.t) + 31) / 32);
+  u->reserved = 0;
+  u->off_bitmap = 0;
+  u->off_sm = up256(d.rows * d.bw * 4);
+  u->off_table = up256(u->off_sm + d.rows * (int64_t)u->smw * 4 + kUnarySlack);
+  u->off_rowoff = u->off_table + 512;
+  u->off_ue = up256(u->off_rowoff + (d.rows + 1) * 4);
+  u->spec_bytes = up256(u->off_ue + u->ue_words * 4 + kUnarySlack);
+}
+
+static int check_udesc(const cas_udesc* u) {
+  if (!u) return CAS_EINVAL;
+  const cas_wdesc& d = u->base;
+  if (d.rows < 0 || d.cols < 1 || d.t < 0 || d.t > 7 || d.K < 0 || d.K > d.cols || u->ue_words < 0) return CAS_EINVAL;
+  cas_udesc chk = *u;
+  fill_layout(&chk);
+  if (chk.smw != u->smw || chk.off_sm != u->off_sm || chk.off_table != u->off_table ||
+      chk.off_rowoff != u->off_rowoff || chk.off_ue != u->off_ue || chk.spec_bytes != u->spec_bytes)
+    return CAS_EINVAL;
+  return CAS_OK;
+}
+
 template <int T>
 static int launch_expand_t(cas_ctx* ctx, const UnaryArgs& a, int row0, int nrows, int R, int cap, size_t lds, uint32_t* out) {
   static LdsLimit lim;
@@ -573,24 +600,12 @@ static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec,
 
 int launch_gemv_draft_unary_fused(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch,
                                   float* y, int epi, uint16_t* out16) {
+  // cas_model_use_unary compares shapes only: the layout is checked before anything reads by it, as by the
+  // kernel's own entry point
+  if (check_udesc(&u) != CAS_OK) return CAS_EINVAL;
   if (u.base.rows <= 0) return CAS_OK;
   if (unary_gemv_lds(u) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   return unary_draft_rows(ctx, u, uspec, x, batch, y, epi, out16);
-}
-
-static int64_t up256(int64_t v) { return (v + 255) / 256 * 256; }
-constexpr int64_t kUnarySlack = 256;
-
-static void fill_layout(cas_udesc* u) {
-  const cas_wdesc& d = u->base;
-  u->smw = (int32_t)(((int64_t)d.K * (8 - d.t) + 31) / 32);
-  u->reserved = 0;
-  u->off_bitmap = 0;
-  u->off_sm = up256(d.rows * d.bw * 4);
-  u->off_table = up256(u->off_sm + d.rows * (int64_t)u->smw * 4 + kUnarySlack);
-  u->off_rowoff = u->off_table + 512;
-  u->off_ue = up256(u->off_rowoff + (d.rows + 1) * 4);
-  u->spec_bytes = up256(u->off_ue + u->ue_words * 4 + kUnarySlack);
 }
 
 // codebook from the histogram: most frequent first, ties to the smaller exponent
@@ -663,18 +678,6 @@ extern "C" int cas_unary_plan(cas_ctx* ctx, const cas_wdesc* desc, const void* d
   }
   out->ue_words = off.back();
   fill_layout(out);
-  return CAS_OK;
-}
-
-static int check_udesc(const cas_udesc* u) {
-  if (!u) return CAS_EINVAL;
-  const cas_wdesc& d = u->base;
-  if (d.rows < 0 || d.cols < 1 || d.t < 0 || d.t > 7 || d.K < 0 || d.K > d.cols || u->ue_words < 0) return CAS_EINVAL;
-  cas_udesc chk = *u;
-  fill_layout(&chk);
-  if (chk.smw != u->smw || chk.off_sm != u->off_sm || chk.off_table != u->off_table ||
-      chk.off_rowoff != u->off_rowoff || chk.off_ue != u->off_ue || chk.spec_bytes != u->spec_bytes)
-    return CAS_EINVAL;
   return CAS_OK;
 }
 

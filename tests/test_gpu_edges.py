@@ -252,3 +252,24 @@ def test_unary_draft_values_depend_on_neither_company_nor_workspace(env, hidden,
             for got in _draft_kv(env, ctx, model, kv, n_seqs):
                 want = got if want is None else want
                 assert torch.equal(got, want), (ws, unary, n_seqs)
+
+
+@pytest.mark.parametrize("hidden,n_seqs", [(264, 1), (264, 2), (8199, 1), (8199, 4)])
+@pytest.mark.parametrize("field,by", [("smw", 1), ("off_sm", 256), ("off_table", -256), ("off_rowoff", 4), ("off_ue", 256),
+                                      ("ue_words", 64), ("spec_bytes", 256)])
+def test_unary_draft_pass_refuses_a_layout_that_is_not_the_matrix_s(env, hidden, n_seqs, field, by):
+    """Every route of a unary draft product (264 / 8199: with one column the kernel that reads the codes / re-coded
+    rows) refuses a descriptor whose layout does not follow from the shape, before a kernel reads by it."""
+    torch, B, _ = env
+    ctx, model, kv = _unary_draft_model(env, hidden, 4, 2, 520, 32 << 20, True)
+    bad = model._unary[(0, 0)]
+    setattr(bad.desc, field, getattr(bad.desc, field) + by)
+    model.use_unary(0, 0, bad)
+    out = torch.empty(4, dtype=torch.int32, device="cuda")
+    token = torch.zeros(n_seqs, dtype=torch.int32, device="cuda")
+    with pytest.raises(B.CasError) as err:
+        if n_seqs == 1:
+            B.cas_draft_step(ctx, model, kv, 0, token, 0, out)
+        else:
+            B.cas_draft_step_multi(ctx, model, kv, list(range(n_seqs)), [0] * n_seqs, token, out)
+    assert err.value.code == B.CAS_EINVAL
