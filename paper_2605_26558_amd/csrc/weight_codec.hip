@@ -285,14 +285,26 @@ static CodecArgs make_args(const cas_wdesc& d, const void* spec, const void* ver
   return a;
 }
 
+// One launch takes the rows whose threads number less than 2^32, the limit of a grid; a matrix of more rows (2^26
+// of up to 4096 columns) takes several.
 template <int T, int P>
-static int launch_encode_instance(cas_ctx* ctx, const uint16_t* W, const float* act, const CodecArgs& a, int waves) {
+static int launch_encode_instance(cas_ctx* ctx, const uint16_t* W, const float* act, CodecArgs a, int waves) {
   const size_t lds = sizeof(uint16_t) * ((size_t)((a.K + 31) & ~31) + (size_t)(a.cols - a.K) + 2);
   static LdsLimit lim;
   const int rc = allow_lds(ctx, (const void*)encode_rows_kernel<T, P>, lds, lim);
   if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL((encode_rows_kernel<T, P>), dim3((unsigned)a.rows), dim3(64 * waves), lds, ctx->stream, W, act, a);
-  CAS_HIP(ctx, hipGetLastError());
+  const int64_t most = 0xFFFFFFFFll / (64 * waves);
+  while (a.rows > 0) {
+    const int64_t n = std::min(a.rows, most);
+    hipLaunchKernelGGL((encode_rows_kernel<T, P>), dim3((unsigned)n), dim3(64 * waves), lds, ctx->stream, W, act, a);
+    CAS_HIP(ctx, hipGetLastError());
+    a.rows -= n;  // the slack behind the streams stays where it is
+    W += n * a.ld;
+    a.bitmap += n * a.bw;
+    a.spec += n * a.sw;
+    a.lo += n * a.lw;
+    a.pruned += n * a.pw;
+  }
   return CAS_OK;
 }
 

@@ -68,6 +68,24 @@ def test_encoder_around_the_sizes_of_its_pieces_and_waves(env, cols, keep, t, ac
         np.testing.assert_array_equal(got, want)
 
 
+def test_encoder_of_more_rows_than_a_grid_holds(env):
+    """2^26 workgroups of 64 threads are one more than a launch may have."""
+    torch, B, ctx = env
+    rows = (1 << 26) + 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    W = torch.randint(-32768, 32768, (rows, 2), device="cuda", generator=gen, dtype=torch.int16)
+    W[-1] = 0x3F80                                          # equal magnitudes: the lower column
+    ew = B.cas_encode_weight(ctx, W, 500, 4)
+    d = ew.desc
+    assert (d.K, d.bw, d.sw, d.lw, d.pw) == (1, 1, 1, 1, 1)
+    right = (W[:, 1] & 0x7FFF) > (W[:, 0] & 0x7FFF)
+    kept, other = torch.where(right, W[:, 1], W[:, 0]).int(), torch.where(right, W[:, 0], W[:, 1]).int()
+    for buf, off, want in ((ew.spec, d.off_bitmap, 1 + right.int()), (ew.spec, d.off_spec, (kept >> 4) & 0xFFF),
+                           (ew.verif, d.off_lo, kept & 15), (ew.verif, d.off_pruned, other & 0xFFFF)):
+        assert torch.equal(buf[off: off + 4 * rows].view(torch.int32), want)
+
+
 WIDE_SHAPES = {  # hidden, query heads, kv heads, feed-forward: 8 parts per row of every matrix; 4 parts (gate/up) and 16 (down)
     "a": (264, 4, 2, 520, 400 << 10),
     "b": (200, 14, 2, 8200, 1200 << 10),
