@@ -290,17 +290,8 @@ static int forward(cas_ctx* ctx, cas_model* m, cas_kv* kv, const ColGroup* grp, 
       hipLaunchKernelGGL(rmsnorm_kernel, dim3(ncols), dim3(kNormThreads), 0, st, x, gain, m->xn, cols, c.rms_eps);
       x = m->xn;
     }
-    {
-      // through the raw form in the workspace: the columns at once, one by one where x of all of them does not fit the LDS
-      int rc = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x, ncols, y, epi, out16);
-      for (int col = 0; rc == CAS_ENOTSUP && ncols > 1 && col < ncols; ++col) {
-        const int one = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x + (size_t)col * cols, 1,
-                                                      y ? y + (size_t)col * rows : nullptr, epi,
-                                                      out16 ? out16 + (size_t)col * (epi == 2 ? rows / 2 : rows) : nullptr);
-        if (one != CAS_OK || col == ncols - 1) rc = one;
-      }
-      if (rc != CAS_ENOMEM) return rc;
-    }
+    const int recoded = launch_gemv_draft_unary_fused(ctx, U.u, U.d_uspec, x, ncols, y, epi, out16);
+    if (recoded != CAS_ENOMEM) return recoded;
     float* yy = epi == 0 ? y : m->y;
     for (int col = 0; col < ncols; ++col) {
       const int rc = cas_gemv_draft_unary(ctx, &U.u, U.d_uspec, x + (size_t)col * cols, yy + (size_t)col * rows);

@@ -564,13 +564,14 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
   return CAS_EINVAL;
 }
 
-// Draft product of a model's pass through the raw form: blocks of rows are re-coded into the workspace and the GEMV of the
-// raw form, with the residual add or SwiGLU fused, runs on each of them (batch columns at once; every output has
-// the bits that the kernel below and the raw form give: all three walk a row in the same order).  CAS_ENOMEM where the caller is to take the kernel that decodes the codes
-// itself, column by column: for one column of a matrix whose rows leave that kernel two workgroups per CU or
-// more, and where the workspace holds no block worth a launch.  One column, through the workspace / decoded
-// in the kernel: 4096 x 14336 (one workgroup per CU) 48 / 70 us, 28672 x 4096 108 / 82 us, 4096 x 4096
-// 21.5 / 18.4 us; a second column costs the former a few us, the latter the same again.
+// Draft product of a model's pass through the raw form: blocks of rows are re-coded into the workspace and the GEMV
+// of the raw form, with the residual add or SwiGLU fused, runs on each of them, for all columns at once or, where
+// x of all of them does not fit the LDS, column by column.  Every output has the bits that the kernel above
+// and the raw form give: all of them walk a row in the same order.  CAS_ENOMEM where the caller is to take
+// the kernel that decodes the codes itself, column by column: for one column of a matrix whose rows leave that
+// kernel two workgroups per CU or more, and where the workspace holds no block worth a launch.  One column,
+// through the workspace / decoded in the kernel: 4096 x 14336 (one workgroup per CU) 48 / 70 us, 28672 x 4096
+// 108 / 82 us, 4096 x 4096 21.5 / 18.4 us; a second column costs the former a few us, the latter the same again.
 static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch, float* y,
                             int epi, uint16_t* out16) {
   const cas_wdesc& d = u.base;
@@ -590,9 +591,17 @@ static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec,
     const int nr = (int)std::min<int64_t>(blk, d.rows - r0);
     int rc = launch_unary_expand(ctx, u, uspec, r0, nr, (uint32_t*)ctx->d_ws);
     if (rc != CAS_OK) return rc;
-    rc = launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)uspec + u.off_bitmap) + (size_t)r0 * d.bw,
-                                 (const uint32_t*)ctx->d_ws, nr, x, batch, y ? y + r0 : nullptr, nullptr, 0.f, epi,
-                                 out16 ? out16 + (epi == 2 ? r0 / 2 : r0) : nullptr);
+    auto gemv = [&](int col, int n) {
+      return launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)uspec + u.off_bitmap) + (size_t)r0 * d.bw,
+                                     (const uint32_t*)ctx->d_ws, nr, x + (size_t)col * d.cols, n,
+                                     y ? y + (size_t)col * d.rows + r0 : nullptr, nullptr, 0.f, epi,
+                                     out16 ? out16 + ((size_t)col * d.rows + r0) / (epi == 2 ? 2 : 1) : nullptr);
+    };
+    rc = gemv(0, batch);
+    if (rc == CAS_ENOTSUP && batch > 1) {
+      rc = CAS_OK;
+      for (int col = 0; rc == CAS_OK && col < batch; ++col) rc = gemv(col, 1);
+    }
     if (rc != CAS_OK) return rc;
   }
   return CAS_OK;
