@@ -208,12 +208,14 @@ __global__ __launch_bounds__(64) void unary_decode_kernel(UnaryArgs a, uint16_t*
 // at fixed positions everywhere but in the code stream, and every lane has the same number of values.
 //   1. The code words of the R rows go to LDS with the running count of their ones.
 //   2. A lane finds the first code of its group by a search in the counts and a search inside the word,
-//      then takes four codes at a time from a window of 64 bits.
-// That holds for rows whose ranks stay below 16 (64 bits then hold four codes) and whose code stream is not
-// unusually long; step 1 looks for both, and the other rows go through unary_row_exponents one by one.
+//      then takes four codes at a time from a window of 64 bits, which holds four ranks below 16.  In rows
+//      with longer codes (step 1 looks for them) the lanes that meet one search their four codes word by word.
+// Rows with an unusually long code stream go through unary_row_exponents one by one.
 // Bound by the arithmetic of step 2 (about 13 operations per kept value, 20 with the searches).  Mean of the
 // launches of a round on 4 layers of the 8B shape: 34 us; 68 us when a lane walked the codes that end in one
-// code word and the words of the stream were put together field by field.
+// code word and the words of the stream were put together field by field.  With every value kept (most rows then
+// hold a code of 17 bits or more) 28672 x 4096 takes 105 us; 261 us when such rows went the way of the
+// overlong ones.
 constexpr int kExpandWaves = 3;
 constexpr int kExpandRows = 4;  // most rows of a workgroup
 constexpr int kUnaryPad = 6;    // words of ones behind a row's codes: what the windows of exhausted lanes see
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
   const int lane = threadIdx.x, first = blockIdx.x * R, n = min(R, nrows - first), G = (a.K + 31) >> 5;
   for (int i = lane; i < 256; i += 64) tab[i] = a.table[i];
   if (lane < 16) etab[lane] = (uint32_t)a.table[lane] << mb;
-  uint32_t slow = 0;  // rows of the workgroup that take the general way
+  uint32_t slow = 0, longs = 0;  // rows of the workgroup that take the general way, that hold codes of 17 bits and more
   // offsets and first code words of all rows are requested together
   const uint32_t off = a.rowoff[row0 + first + min(lane, n)];
   uint32_t o0[kExpandRows], c0[kExpandRows][2], c1[kExpandRows][2];
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
     }
     // the pad of a row that ends close to the last chunk's end
     for (int w = (nw + 63) / 64 * 64 + lane; w < nw + kUnaryPad; w += 64) codes[r * cap + w] = 0xFFFFFFFFu;
-    if (__builtin_amdgcn_ballot_w64(long_run)) slow |= 1u << r;
+    if (__builtin_amdgcn_ballot_w64(long_run)) longs |= 1u << r;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -322,24 +324,56 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
     uint32_t sp[FW];
 #pragma unroll
     for (int i = 0; i < FW; ++i) sp[i] = 0;
-    static_for<0, 8>([&](auto Q) {
-      constexpr int i0 = 4 * decltype(Q)::value;
-      const int wi = min((int)(q >> 5), nw + 2);
-      const uint32_t c0 = cw[wi], c1 = cw[wi + 1], c2 = cw[wi + 2];
-      uint32_t lo = __builtin_amdgcn_alignbit(c1, c0, q & 31u), hi = __builtin_amdgcn_alignbit(c2, c1, q & 31u);
-      static_for<0, 4>([&](auto I) {
-        constexpr int i = i0 + decltype(I)::value;
-        const uint32_t z = (uint32_t)lowest_bit(lo), used = z + 1u;  // 16 zeros are not in the window
-        lo = __builtin_amdgcn_alignbit(hi, lo, used);
-        hi >>= used;
-        q += used;
-        const uint32_t f4 = field_at<SW, i>(sm);  // sign, mantissa bits
-        const uint32_t f = (((f4 << 8) | f4) & ((1u << (FW - 1)) | ((1u << mb) - 1u))) | etab[z];
-        constexpr int bit = i * FW, w = bit >> 5, sh = bit & 31;
-        sp[w] |= f << sh;
-        if constexpr (sh + FW > 32) sp[w + 1] |= f >> (32 - sh);
+    auto fields = [&](auto LONG) {
+      static_for<0, 8>([&](auto Q) {
+        constexpr int i0 = 4 * decltype(Q)::value;
+        const int wi = min((int)(q >> 5), nw + 2);
+        const uint32_t c0 = cw[wi], c1 = cw[wi + 1], c2 = cw[wi + 2];
+        uint32_t lo = __builtin_amdgcn_alignbit(c1, c0, q & 31u), hi = __builtin_amdgcn_alignbit(c2, c1, q & 31u);
+        auto next = [&]() -> uint32_t {  // rank of the next code of the window; beyond 15 where that is not whole
+          const uint32_t z = (uint32_t)lowest_bit(lo), used = z + 1u;
+          lo = __builtin_amdgcn_alignbit(hi, lo, used);
+          hi >>= used & 31u;
+          q += used;
+          return z;
+        };
+        auto put = [&](auto I, uint32_t e) {
+          constexpr int i = i0 + decltype(I)::value;
+          const uint32_t f4 = field_at<SW, i>(sm);  // sign, mantissa bits
+          const uint32_t f = (((f4 << 8) | f4) & ((1u << (FW - 1)) | ((1u << mb) - 1u))) | e;
+          constexpr int bit = i * FW, w = bit >> 5, sh = bit & 31;
+          sp[w] |= f << sh;
+          if constexpr (sh + FW > 32) sp[w + 1] |= f >> (32 - sh);
+        };
+        if constexpr (!decltype(LONG)::value) {
+          static_for<0, 4>([&](auto I) { put(I, etab[next()]); });
+        } else {
+          uint32_t e[4], longest = 0, p = 32u * (uint32_t)wi + (q & 31u);
+          static_for<0, 4>([&](auto I) {
+            const uint32_t z = next();
+            longest = max(longest, z);
+            e[decltype(I)::value] = etab[z & 15u];
+          });
+          if (longest > 15u) {
+            static_for<0, 4>([&](auto I) {
+              int w = (int)(p >> 5);
+              uint32_t u = cw[w] >> (p & 31u), z = 0;
+              if (u == 0u) {  // the pad behind the codes ends the search
+                z = 32u - (p & 31u);
+                while ((u = cw[++w]) == 0u) z += 32u;
+              }
+              z += (uint32_t)lowest_bit(u);
+              p += z + 1u;
+              e[decltype(I)::value] = (uint32_t)tab[z & 255u] << mb;
+            });
+            q = p;
+          }
+          static_for<0, 4>([&](auto I) { put(I, e[decltype(I)::value]); });
+        }
       });
-    });
+    };
+    if (__builtin_amdgcn_ballot_w64((longs >> r) & 1u)) fields(std::true_type{});
+    else fields(std::false_type{});
     const int left = a.K - 32 * g;
     if (left < 32) {  // nothing behind the last value
 #pragma unroll
@@ -545,8 +579,11 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
   if (nrows <= 0 || d.sw == 0) return CAS_OK;
   // widest row: codebook, exponents and sign / mantissa fields of one row in the LDS of a workgroup
   if (256 + (size_t)((d.K + 3) & ~3) + kExpSlack + ((size_t)u.smw + 1) * 4 > (size_t)ctx->lds_max) return CAS_ENOTSUP;
-  // code words a row may have on the fast way: 3 bits per value (1.7 to 2.9 are usual); counts are 16 bits wide
-  const int cap = d.K < 65536 ? (3 * d.K / 32 + 64 + 1) & ~1 : 0;
+  // code words a row may have on the fast way: 3 bits per value (1.7 to 2.9 are usual) or a quarter more than the
+  // rows of this matrix have on average, within 60 KB of LDS; counts are 16 bits wide
+  const int64_t mean = d.rows > 0 ? u.ue_words / d.rows : 0;
+  const int64_t words = std::min<int64_t>(std::max<int64_t>(3 * (int64_t)d.K / 32, mean + mean / 4), 10000);
+  const int cap = d.K < 65536 ? (int)((words + 64 + 1) & ~(int64_t)1) : 0;
   // rows per wave: whichever of 1 to 4 leaves the fewest lanes without a group in the last turn, as long as
   // every SIMD gets kExpandWaves waves
   const int G = (d.K + 31) / 32;

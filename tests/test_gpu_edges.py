@@ -188,6 +188,24 @@ def test_unary_rows_recoded_in_the_workspace(env, rows, cols, keep, t):
         assert (np.abs((other - want).cpu().numpy().astype(np.float64)).reshape(-1) <= cols * 2.0 ** -23 * scale).all()
 
 
+@pytest.mark.parametrize("rows,cols", [(3, 33), (70, 300), (4101, 300), (9, 4096), (6, 14336)])
+@pytest.mark.parametrize("keep,t", [(1000, 0), (600, 4), (1000, 7)])
+def test_unary_rows_with_a_few_long_codes(env, rows, cols, keep, t):
+    """Most values share a few exponents, one in a hundred has any of 254: codes of up to 255 bits between short
+    ones, over word boundaries and at the end of a row.  The verification product has the raw form's bits."""
+    torch, B, _ = env
+    rng = np.random.Generator(np.random.Philox(rows + cols + t))
+    W = synth.weight_matrix(rows, cols, seed=12)
+    rare = rng.random((rows, cols)) < 0.01
+    rare[0] = False                                           # a row without any
+    rare[-1, -1] = True                                       # the last value of a row
+    W = np.where(rare, (W & 0x807F) | (rng.integers(1, 255, size=(rows, cols)).astype(np.uint16) << 7), W)
+    ctx = B.Context(workspace=torch.empty(8 << 20, dtype=torch.uint8, device="cuda"))
+    X = _dev(torch, synth.activations(cols, 3, seed=10))
+    ew = B.cas_encode_weight(ctx, _dev(torch, W.astype(np.uint16)), keep, t)
+    assert torch.equal(B.cas_gemm_verify_unary(ctx, B.cas_unary_encode(ctx, ew), X), B.cas_gemm_verify(ctx, ew, X))
+
+
 def test_unary_draft_pass_through_the_workspace_and_without(env, wide_models):
     """The down projection of shape b (8200 columns) leaves the unary draft kernel one workgroup per CU and goes
     through re-coded rows where the workspace holds them; the small workspace does not.  Bound: bf16 between the
