@@ -290,8 +290,10 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
-  for (int it = lane; it < n * G; it += 64) {
-    const int r = it / G, g = it - r * G, row = row0 + first + r;
+  // lanes without a group do the last one again (the same words to the same places): a wave of few active lanes
+  // took longer, 1024 rows of 38 to 250 kept values 8.5 us instead of 5.5
+  for (int it0 = lane; it0 < max(n * G, 64); it0 += 64) {
+    const int it = min(it0, n * G - 1), r = it / G, g = it - r * G, row = row0 + first + r;
     if ((slow >> r) & 1u) continue;
     const int nw = (int)(a.rowoff[row + 1] - a.rowoff[row]);
     uint32_t sm[SW];
@@ -584,13 +586,20 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
   const int64_t mean = d.rows > 0 ? u.ue_words / d.rows : 0;
   const int64_t words = std::min<int64_t>(std::max<int64_t>(3 * (int64_t)d.K / 32, mean + mean / 4), 10000);
   const int cap = d.K < 65536 ? (int)((words + 64 + 1) & ~(int64_t)1) : 0;
-  // rows per wave: whichever of 1 to 4 leaves the fewest lanes without a group in the last turn, as long as
-  // every SIMD gets kExpandWaves waves
+  // Rows per wave.  As many (up to 4) as fill a wave's lanes once, if every SIMD still gets a wave: short rows
+  // leave lanes idle otherwise (60 % kept, 4096 x 256: 6.4 us, 9.8 with one row per wave; 2048 x 256 5.9 / 7.0).
+  // Of longer rows whichever number leaves the fewest lanes without a group in the last turn, if every SIMD
+  // gets kExpandWaves waves (8192 x 4096: 24.7 us, 27.0 with two of them, 27.2 with one; 4096 x 14336
+  // 35.4, 42.0, 42.6; 6144 x 4096 20.9, 22.7, 25.8) and a gain of 5 % is in it (28672 x 4096 with four rows a
+  // wave 70.7 us, with one 76.9; 28672 x 2048 33.8, 43.4).
   const int G = (d.K + 31) / 32;
   int R = 1;
   auto turns = [&](int r) { return (double)((r * G + 63) / 64) / r; };
-  for (int r = 2; r <= kExpandRows; ++r)
-    if (turns(r) < 0.95 * turns(R) && (size_t)r * cap * 6 <= 16 * 1024 && nrows >= r * ctx->num_cu * 4 * kExpandWaves) R = r;
+  for (int r = 2; r <= kExpandRows; ++r) {
+    const bool once = r * G <= 64 && nrows >= r * ctx->num_cu * 4;
+    if (once || (turns(r) < 0.95 * turns(R) && (size_t)r * cap * 6 <= 16 * 1024 && nrows >= r * ctx->num_cu * 4 * kExpandWaves))
+      R = r;
+  }
   const size_t lds = std::max<size_t>((size_t)R * cap * 6, (size_t)((d.K + 3) & ~3) + kExpSlack);
   UnaryArgs a = make_uargs(u, nullptr, const_cast<void*>(uspec), nullptr);
 #define CAS_T(TV) case TV: return launch_expand_t<TV>(ctx, a, (int)row0, nrows, R, cap, lds, out);

@@ -188,7 +188,7 @@ def test_unary_rows_recoded_in_the_workspace(env, rows, cols, keep, t):
         assert (np.abs((other - want).cpu().numpy().astype(np.float64)).reshape(-1) <= cols * 2.0 ** -23 * scale).all()
 
 
-@pytest.mark.parametrize("rows,cols", [(3, 33), (70, 300), (4101, 300), (9, 4096), (6, 14336)])
+@pytest.mark.parametrize("rows,cols", [(3, 33), (70, 300), (4101, 300), (2050, 700), (9, 4096), (6, 14336)])
 @pytest.mark.parametrize("keep,t", [(1000, 0), (600, 4), (1000, 7)])
 def test_unary_rows_with_a_few_long_codes(env, rows, cols, keep, t):
     """Most values share a few exponents, one in a hundred has any of 254: codes of up to 255 bits between short
