@@ -11,10 +11,10 @@ namespace cas {
 
 // One wave formats one 128-value vector, four tokens per workgroup.  Keys (magnitude << 7 | 127 - column)
 // are unique, so the K-th largest key is found bit by bit with wave ballots and "key >= threshold" keeps
-// exactly K values with ties going to the lower column; the search ends as soon as K keys are left above
-// the candidate (after some 14 of the 22 bits on normal values).  Bound by the issue of the search's scalar
-// instructions and of the rest's vector instructions: the vectors of 1021 tokens, 8 heads take 12.9 us, with
-// one wave per workgroup, all 22 bits and the page entry looked up at the end 14.2 us.
+// exactly K values with ties going to the lower column.  All 22 bits are searched: ending when K keys are left
+// (after some 14 bits on normal values) costs a branch per bit, 0.4 us of the 4 us that up to some 100 vectors
+// take and as much of the 13.0 us for the vectors of 1021 tokens, 8 heads (14.5 us with one wave per
+// workgroup and the page entry looked up at the end).
 constexpr int kAppendWaves = 4;
 __global__ __launch_bounds__(64 * kAppendWaves) void kv_append_kernel(KvGeom g, uint32_t* spec_pool, uint32_t* verif_pool,
                                                                       const int32_t* __restrict__ page_row, int layer0,
@@ -36,14 +36,10 @@ __global__ __launch_bounds__(64 * kAppendWaves) void kv_append_kernel(KvGeom g, 
   const uint32_t key1 = ((v1 & 0x7FFFu) << 7) | (uint32_t)(63 - lane);
   for (int i = lane; i < g.sw + g.lw + g.pw; i += 64) stage[i] = 0;
   uint32_t T = g.K > 0 ? 0u : 0xFFFFFFFFu;
-  int cnt = g.K > 0 ? 128 : 0;  // keys >= T
-  for (int bit = 21; bit >= 0 && cnt != g.K; --bit) {
+  for (int bit = 21; bit >= 0; --bit) {
     const uint32_t cand = T | (1u << bit);
     const int c = __popcll(__builtin_amdgcn_ballot_w64(key0 >= cand)) + __popcll(__builtin_amdgcn_ballot_w64(key1 >= cand));
-    if (c >= g.K) {
-      T = cand;
-      cnt = c;
-    }
+    if (c >= g.K) T = cand;
   }
   const bool k0 = key0 >= T, k1 = key1 >= T;
   const uint64_t m01 = __builtin_amdgcn_ballot_w64(k0), m23 = __builtin_amdgcn_ballot_w64(k1);
