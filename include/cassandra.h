@@ -442,7 +442,7 @@ int cas_model_destroy(cas_model* model);
  * lossless configuration): from then on draft passes read d_uspec, either through the kernel of
  * cas_gemv_draft_unary, column by column, or through rows re-coded in the context's workspace
  * (several columns, or rows that leave that kernel one workgroup per CU, where the workspace holds
- * the whole matrix or 1024 rows of it).  A column's values are the same either way, whatever
+ * the whole matrix or enough rows of it to be the faster way).  A column's values are the same either way, whatever
  * columns come with it.  RMSNorm runs as a launch of its own: its sum has the order of the
  * verification pass's norm.  Verification passes go through cas_gemm_verify_unary, whose results
  * equal those of the raw form bit for bit; the tensor's raw d_spec is no longer read and may be

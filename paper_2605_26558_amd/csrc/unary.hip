@@ -429,7 +429,6 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
 // per chunk whose row 0 is 0.0, so a lane that has run out of set bits multiplies by zero, and
 // a lane reads only its own 4-byte column of the block (no bank conflicts between lanes).
 constexpr int kUnaryWaves = 8;
-constexpr int kUnaryMinBlock = 1024;  // rows of a block that is worth two launches
 
 // LDS of that kernel: codebook, x as fp32, the exponents of a row per wave
 static size_t unary_gemv_lds(const cas_udesc& u) {
@@ -615,14 +614,23 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
 // x of all of them does not fit the LDS, column by column.  Every output has the bits that the kernel above
 // and the raw form give: all of them walk a row in the same order.  CAS_ENOMEM where the caller is to take
 // the kernel that decodes the codes itself, column by column: for one column of a matrix whose rows leave that
-// kernel two workgroups per CU or more, and where the workspace holds no block worth a launch.  One column,
-// through the workspace / decoded in the kernel: 4096 x 14336 (one workgroup per CU) 48 / 70 us, 28672 x 4096
-// 108 / 82 us, 4096 x 4096 21.5 / 18.4 us; a second column costs the former a few us, the latter the same again.
+// kernel two workgroups per CU or more (28672 x 4096: 82 us, through the workspace 108; 4096 x 4096
+// 18.4 / 21.5; with one workgroup per CU, 4096 x 14336, 70 / 48), and where the workspace holds too few rows.
+// A block costs two launches, some 10 us, and a small one leaves CUs idle; what there is to win grows with
+// the rows, their length (the kernel takes some 0.38 ns per row and 1000 + 0.5 columns, twice that with one
+// workgroup per CU) and the columns after the first, or all of them with one workgroup per CU.  Total of a
+// small pass, in the kernel / through blocks of so many rows, us:
+//   28672 x 4096, two columns  174 / 165 (9558), 179 (7168);  four  309 / 282 (2390), 324 (1792)
+//   28672 x 1024, two columns  101 /  91 (14336), 102 (9558); four  170 / 156 (3584), 195 (2390)
+//   128000 x 2048, two columns 359 / 325 (16000), 379 (10667)
+//   16384 x 8192, one column   147 / 146 (8192), 163 (5462);  two   252 / 248 (2048), 324 (1366)
+//   8192 x 14336, one column   193 / 185 (2731), 206 (2048);  four  579 / 491 (683), 616 (512)
 static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch, float* y,
                             int epi, uint16_t* out16) {
   const cas_wdesc& d = u.base;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
-  if (d.sw == 0 || (batch == 1 && 2 * unary_gemv_lds(u) <= (size_t)ctx->lds_max)) return CAS_ENOMEM;
+  const bool one_wg = 2 * unary_gemv_lds(u) > (size_t)ctx->lds_max;
+  if (d.sw == 0 || (batch == 1 && !one_wg)) return CAS_ENOMEM;
   const size_t row_bytes = (size_t)d.sw * 4;
   int64_t blk = ctx->d_ws && ctx->ws_bytes > 256 ? (int64_t)((ctx->ws_bytes - 256) / row_bytes) : 0;
   blk = std::min<int64_t>(blk, d.rows);
@@ -631,7 +639,9 @@ static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec,
     const int64_t nblk = blk < 2 ? d.rows : (d.rows + blk - 1) / blk;
     blk = (d.rows + nblk - 1) / nblk;
     blk += blk & 1;
-    if (blk < kUnaryMinBlock || blk * (int64_t)row_bytes + 256 > (int64_t)ctx->ws_bytes) return CAS_ENOMEM;
+    const int64_t gain = (blk * (d.cols + 2048) * (one_wg ? batch : batch - 1)) >> 20;
+    if (gain < (!one_wg ? 44 : batch == 1 ? 80 : 40) || blk * (int64_t)row_bytes + 256 > (int64_t)ctx->ws_bytes)
+      return CAS_ENOMEM;
   }
   for (int64_t r0 = 0; r0 < d.rows; r0 += blk) {
     const int nr = (int)std::min<int64_t>(blk, d.rows - r0);

@@ -275,15 +275,16 @@ def _draft_kv(env, ctx, model, kv, n_seqs):
                                                                  (2056, 14, 2, 1100, 600, 2500 << 10, True),
                                                                  (8192, 8, 2, 1024, 600, 8 << 20, False),
                                                                  (8199, 16, 4, 1031, 600, 12 << 20, False),
-                                                                 (264, 4, 2, 19000, 250, 1 << 20, False)])
+                                                                 (264, 4, 2, 19000, 250, 1 << 20, False),
+                                                                 (2600, 64, 8, 14339, 600, 17 << 20, True)])
 def test_unary_draft_values_depend_on_neither_company_nor_workspace(env, hidden, n_q, n_kv, ffn, keep, blocks, raw):
-    """One, two and four columns through a workspace that holds whole matrices, through one that cuts them into
-    blocks with a smaller last one (outputs of all three kinds: projection, residual add, SwiGLU) and through
-    one that holds none: the same bits (19000: x of four columns does not fit the LDS).  For a hidden size in eights
+    """One, two and four columns through a workspace that holds whole matrices, through one that holds some of them
+    (2600: cuts the projection, the gate/up and the down matrix into blocks with smaller last ones, outputs of all
+    three kinds) and through one that holds none: the same bits (19000: x of four columns does not fit the LDS).  For a hidden size in eights
     up to 4096 the raw form's fused norm adds in the same order too, so the raw form gives these bits as well."""
     torch = env[0]
     want = None
-    for ws, unary in [(32 << 20, True), (blocks, True), (256 << 10, True)] + ([(32 << 20, False)] if raw else []):
+    for ws, unary in [(80 << 20, True), (blocks, True), (256 << 10, True)] + ([(80 << 20, False)] if raw else []):
         ctx, model, kv = _unary_draft_model(env, hidden, n_q, n_kv, ffn, ws, unary, keep)
         for n_seqs in (1, 2, 4):
             for got in _draft_kv(env, ctx, model, kv, n_seqs):
