@@ -74,7 +74,6 @@ __global__ __launch_bounds__(64 * G * Q) void gemm_verify_kernel(VerifyArgs a) {
   const uint16_t* b_base[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) b_base[nb] = Xq + (16 * nb + mi < a.ncols ? 16 * nb + mi : 0) * XQP + 4 * mq;
-
   const bool xvec = (a.cols & 7) == 0;  // 16-byte pieces of X rows are aligned and never straddle the end
 
   f32x4 C[NB];

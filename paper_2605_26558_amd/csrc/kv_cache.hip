@@ -14,7 +14,9 @@ namespace cas {
 // exactly K values with ties going to the lower column.  All 22 bits are searched: ending when K keys are left
 // (after some 14 bits on normal values) costs a branch per bit, 0.4 us of the 4 us that up to some 100 vectors
 // take and as much of the 13.0 us for the vectors of 1021 tokens, 8 heads (14.5 us with one wave per
-// workgroup and the page entry looked up at the end).
+// workgroup and the page entry looked up at the end).  Bound by the scalar instructions of the search: counters of
+// that call have 21.0 K of them per CU, whose SIMDs share one a cycle, in the 26.3 K cycles that it is busy
+// (vector instructions 43 % of those cycles, waves waiting to issue 55 %), half of the launch.
 constexpr int kAppendWaves = 4;
 __global__ __launch_bounds__(64 * kAppendWaves) void kv_append_kernel(KvGeom g, uint32_t* spec_pool, uint32_t* verif_pool,
                                                                       const int32_t* __restrict__ page_row, int layer0,

@@ -415,7 +415,10 @@ static ActLayout act_layout(const cas_model_cfg& c) {
 // 8B-shaped, 4 layers, 508 tokens: 4.9 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
 // and 31 unread rows of logits it saves).
 constexpr int kPrefillChunk = 512;
-constexpr int kPrefillMin = 48;  // fewer columns: passes through the narrow kernels are as fast
+// Fewer columns go through the passes.  A chunk and passes of 16 columns for the same prompt, one layer, us: 8B shape 49
+// tokens 642 / 929, 33 tokens 632 / 685, 21 tokens 630 / 633; 70B shape 33 tokens 1744 / 3181; hidden 256 (two
+// layers) 33 tokens 271 / 332.  So a chunk is the faster way at every length it takes (and would be from some 20 on).
+constexpr int kPrefillMin = 48;
 
 struct ChunkLayout {
   size_t h, xn, y, q, ao, k, v, px, total;  // y: the fp32 projection, then the SwiGLU output; px: a layer's packed input

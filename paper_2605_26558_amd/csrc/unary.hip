@@ -578,7 +578,8 @@ static int launch_expand_t(cas_ctx* ctx, const UnaryArgs& a, int row0, int nrows
 int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int64_t row0, int nrows, uint32_t* out) {
   const cas_wdesc& d = u.base;
   if (nrows <= 0 || d.sw == 0) return CAS_OK;
-  // widest row: codebook, exponents and sign / mantissa fields of one row in the LDS of a workgroup
+  // The widest row that is taken: codebook, exponents and sign / mantissa fields in the LDS of a workgroup.  The
+  // kernel reads those fields from memory and needs less (below).
   if (256 + (size_t)((d.K + 3) & ~3) + kExpSlack + ((size_t)u.smw + 1) * 4 > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   // code words a row may have on the fast way: 3 bits per value (1.7 to 2.9 are usual) or a quarter more than the
   // rows of this matrix have on average, within 60 KB of LDS; counts are 16 bits wide

@@ -27,7 +27,8 @@ __device__ __forceinline__ uint32_t score_of(uint32_t w, bool weighted, float ac
 
 // One workgroup of NW = blockDim / 64 waves formats one row; a lane owns P pieces of 8
 // consecutive columns, piece (q, wave, lane) being columns 8 ((q NW + wave) 64 + lane) ..+7, so the row and
-// the norms come in with 16-byte loads and are read from memory once: values and keys stay in registers.
+// the norms come in with 16-byte loads and are read from memory once: values and keys stay in registers (with 10
+// pieces, rows of more than 65536 columns, 98 of the 128 registers that sixteen waves leave a lane spill).
 //
 //   1. The K-th largest key is found bit by bit: a wave counts the keys >= a candidate with ballots (one
 //      compare per key, the counting runs on the scalar unit), the waves of a row add their counts in LDS.
@@ -38,9 +39,10 @@ __device__ __forceinline__ uint32_t score_of(uint32_t w, bool weighted, float ac
 //   3. A thread packs 32 consecutive kept values into the FW words of the spec stream and the T words of the
 //      lo stream that they fill exactly; the pruned list already is the pruned stream.
 //
-// Bound by the compares of step 1 (about 22 of them per value) and by memory traffic, in about equal parts.
-// 28672 x 4096 with norms: 269 us, 1.8 TB/s of input and output; radix selection through histograms in
-// LDS, whose atomics met in the few exponents that a row holds, took 2602 us.
+// Bound by the issue of vector instructions, the compares of step 1 (about 22 of them per value) above all:
+// counters of 28672 x 4096 with norms have them in 71 % of the cycles that the CUs are busy (92 % of the launch);
+// scalar instructions, one a cycle for the four SIMDs, in 61 %.  269 us, 1.8 TB/s of input and output; radix
+// selection through histograms in LDS, whose atomics met in the few exponents that a row holds, took 2602 us.
 template <int T, int P>
 __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ act, CodecArgs a) {
@@ -310,21 +312,20 @@ static int launch_encode_instance(cas_ctx* ctx, const uint16_t* W, const float* 
 
 // 512 columns per wave and piece.  One wave of 2, 4 or 8 pieces takes rows of up to 4096 columns (no
 // barriers in the search); longer rows go to as many waves of 8 pieces as they need, and those beyond 16 of
-// them (65536 columns) to 16 waves of 10 pieces.
+// them (65536 columns) to 16 waves of 10 pieces, which hold 81920: more than launch_encode_weight lets through.
 template <int T>
 static int launch_encode_t(cas_ctx* ctx, const uint16_t* W, const float* act, const CodecArgs& a) {
   if (a.cols <= 1024) return launch_encode_instance<T, 2>(ctx, W, act, a, 1);
   if (a.cols <= 2048) return launch_encode_instance<T, 4>(ctx, W, act, a, 1);
   if (a.cols <= 65536) return launch_encode_instance<T, 8>(ctx, W, act, a, (int)((a.cols + 4095) / 4096));
-  if (a.cols <= 81920) return launch_encode_instance<T, 10>(ctx, W, act, a, 16);
-  return CAS_ENOTSUP;
+  return launch_encode_instance<T, 10>(ctx, W, act, a, 16);
 }
 
 int launch_encode_weight(cas_ctx* ctx, const uint16_t* W, int64_t ld, const float* act, const cas_wdesc& d,
                          void* spec, void* verif) {
   CodecArgs a = make_args(d, spec, verif, ld);
-  // longest row: its streams, two counters per bitmap word and 1 KB within the LDS of a workgroup
-  // (some 72000 columns); the kernel needs less than that
+  // The longest row that is taken: its streams, two counters per bitmap word and 1 KB within the LDS of a
+  // workgroup, 72366 columns at most.  The kernel itself needs two bytes per column and a little.
   if (sizeof(uint32_t) * ((size_t)d.sw + d.lw + d.pw + 256 + 2 * (size_t)d.bw) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   if (d.rows < 1) return CAS_OK;
   switch (d.t) {

@@ -167,7 +167,8 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
 def test_unary_rows_recoded_in_the_workspace(env, rows, cols, keep, t):
     """Rows of few exponents, rows with more than 16 of them (codes longer than a window takes), a row whose
     codes are long throughout; kept counts around a group of 32.  The verification product has the bits that
-    the raw form gives; the draft product agrees up to the order of its sums."""
+    the raw form gives, and so has the draft product, which reads the codes itself (the draft product through
+    re-coded rows is a pass of a model: test_unary_draft_values_depend_on_neither_company_nor_workspace)."""
     torch, B, _ = env
     rng = np.random.Generator(np.random.Philox(rows + cols))
     W = synth.weight_matrix(rows, cols, seed=8)
@@ -180,12 +181,7 @@ def test_unary_rows_recoded_in_the_workspace(env, rows, cols, keep, t):
     ue = B.cas_unary_encode(with_ws, ew)
     want = B.cas_gemm_verify(with_ws, ew, X)
     assert torch.equal(B.cas_gemm_verify_unary(with_ws, ue, X), want)
-    want = B.cas_gemv_draft(with_ws, ew, x)[0]
-    y = B.cas_gemv_draft_unary(with_ws, ue, x)
-    none = B.cas_gemv_draft_unary(B.Context(), ue, x)
-    scale = np.linalg.norm(O.bf16_to_f64(W), axis=1) * np.linalg.norm(O.bf16_to_f64(x.cpu().numpy().view(np.uint16)))
-    for other in (y, none):
-        assert (np.abs((other - want).cpu().numpy().astype(np.float64)).reshape(-1) <= cols * 2.0 ** -23 * scale).all()
+    assert torch.equal(B.cas_gemv_draft_unary(with_ws, ue, x).reshape(-1), B.cas_gemv_draft(with_ws, ew, x)[0])
 
 
 @pytest.mark.parametrize("rows,cols", [(3, 33), (70, 300), (4101, 300), (2050, 700), (9, 4096), (6, 14336)])
@@ -208,8 +204,7 @@ def test_unary_rows_with_a_few_long_codes(env, rows, cols, keep, t):
 
 def test_unary_draft_pass_through_the_workspace_and_without(env, wide_models):
     """The down projection of shape b (8200 columns) leaves the unary draft kernel one workgroup per CU and goes
-    through re-coded rows where the workspace holds them; the small workspace does not.  Bound: bf16 between the
-    operations of two layers, as for any other order of the sums."""
+    through re-coded rows where the workspace holds them; the small workspace does not.  The logits are the same."""
     torch, B, _ = env
     tokens = torch.from_numpy(synth.token_ids(40, 301, seed=3)).cuda()
     got = []
@@ -218,8 +213,8 @@ def test_unary_draft_pass_through_the_workspace_and_without(env, wide_models):
         B.cas_prefill(ctx, model, kv, 0, tokens[:-1])
         logits = torch.empty((1, 301), device="cuda")
         B.cas_draft_step(ctx, model, kv, 0, tokens[-1:], 0, torch.empty(1, dtype=torch.int32, device="cuda"), logits)
-        got.append(logits.double())
-    assert float((got[0] - got[1]).norm() / got[0].norm()) < 0.01
+        got.append(logits)
+    assert torch.equal(*got)
 
 
 def _unary_draft_model(env, hidden, n_q, n_kv, ffn, ws, unary, keep=600):
