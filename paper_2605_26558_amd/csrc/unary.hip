@@ -208,8 +208,9 @@ __global__ __launch_bounds__(64) void unary_decode_kernel(UnaryArgs a, uint16_t*
 // at fixed positions everywhere but in the code stream, and every lane has the same number of values.
 //   1. The code words of the R rows go to LDS with the running count of their ones.
 //   2. A lane finds the first code of its group by a search in the counts and a search inside the word,
-//      then takes four codes at a time from a window of 64 bits, which holds four ranks below 16.  In rows
-//      with longer codes (step 1 looks for them) the lanes that meet one search their four codes word by word.
+//      then takes four codes at a time from a window of 64 bits, which holds four ranks below 16.  In waves
+//      whose rows have longer codes (step 1 looks for them) the lanes that meet one search their four codes
+//      word by word.
 // Rows with an unusually long code stream go through unary_row_exponents one by one.
 // Bound by the arithmetic of step 2 (about 13 operations per kept value, 20 with the searches).  Mean of the
 // launches of a round on 4 layers of the 8B shape: 34 us; 68 us when a lane walked the codes that end in one
@@ -290,11 +291,9 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
-  // lanes without a group do the last one again (the same words to the same places): a wave of few active lanes
-  // took longer, 1024 rows of 38 to 250 kept values 8.5 us instead of 5.5
-  for (int it0 = lane; it0 < max(n * G, 64); it0 += 64) {
-    const int it = min(it0, n * G - 1), r = it / G, g = it - r * G, row = row0 + first + r;
-    if ((slow >> r) & 1u) continue;
+  auto group = [&](int it, auto LONG) {
+    const int r = it / G, g = it - r * G, row = row0 + first + r;
+    if ((slow >> r) & 1u) return;
     const int nw = (int)(a.rowoff[row + 1] - a.rowoff[row]);
     uint32_t sm[SW];
     __builtin_memcpy(sm, a.u_sm + (size_t)row * a.smw + g * SW, 4 * SW);
@@ -326,56 +325,52 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
     uint32_t sp[FW];
 #pragma unroll
     for (int i = 0; i < FW; ++i) sp[i] = 0;
-    auto fields = [&](auto LONG) {
-      static_for<0, 8>([&](auto Q) {
-        constexpr int i0 = 4 * decltype(Q)::value;
-        const int wi = min((int)(q >> 5), nw + 2);
-        const uint32_t c0 = cw[wi], c1 = cw[wi + 1], c2 = cw[wi + 2];
-        uint32_t lo = __builtin_amdgcn_alignbit(c1, c0, q & 31u), hi = __builtin_amdgcn_alignbit(c2, c1, q & 31u);
-        auto next = [&]() -> uint32_t {  // rank of the next code of the window; beyond 15 where that is not whole
-          const uint32_t z = (uint32_t)lowest_bit(lo), used = z + 1u;
-          lo = __builtin_amdgcn_alignbit(hi, lo, used);
-          hi >>= used & 31u;
-          q += used;
-          return z;
-        };
-        auto put = [&](auto I, uint32_t e) {
-          constexpr int i = i0 + decltype(I)::value;
-          const uint32_t f4 = field_at<SW, i>(sm);  // sign, mantissa bits
-          const uint32_t f = (((f4 << 8) | f4) & ((1u << (FW - 1)) | ((1u << mb) - 1u))) | e;
-          constexpr int bit = i * FW, w = bit >> 5, sh = bit & 31;
-          sp[w] |= f << sh;
-          if constexpr (sh + FW > 32) sp[w + 1] |= f >> (32 - sh);
-        };
-        if constexpr (!decltype(LONG)::value) {
-          static_for<0, 4>([&](auto I) { put(I, etab[next()]); });
-        } else {
-          uint32_t e[4], longest = 0, p = 32u * (uint32_t)wi + (q & 31u);
+    static_for<0, 8>([&](auto Q) {
+      constexpr int i0 = 4 * decltype(Q)::value;
+      const int wi = min((int)(q >> 5), nw + 2);
+      const uint32_t c0 = cw[wi], c1 = cw[wi + 1], c2 = cw[wi + 2];
+      uint32_t lo = __builtin_amdgcn_alignbit(c1, c0, q & 31u), hi = __builtin_amdgcn_alignbit(c2, c1, q & 31u);
+      auto next = [&]() -> uint32_t {  // rank of the next code of the window; beyond 15 where that is not whole
+        const uint32_t z = (uint32_t)lowest_bit(lo), used = z + 1u;
+        lo = __builtin_amdgcn_alignbit(hi, lo, used);
+        hi >>= used & 31u;
+        q += used;
+        return z;
+      };
+      auto put = [&](auto I, uint32_t e) {
+        constexpr int i = i0 + decltype(I)::value;
+        const uint32_t f4 = field_at<SW, i>(sm);  // sign, mantissa bits
+        const uint32_t f = (((f4 << 8) | f4) & ((1u << (FW - 1)) | ((1u << mb) - 1u))) | e;
+        constexpr int bit = i * FW, w = bit >> 5, sh = bit & 31;
+        sp[w] |= f << sh;
+        if constexpr (sh + FW > 32) sp[w + 1] |= f >> (32 - sh);
+      };
+      if constexpr (!decltype(LONG)::value) {
+        static_for<0, 4>([&](auto I) { put(I, etab[next()]); });
+      } else {
+        uint32_t e[4], longest = 0, p = 32u * (uint32_t)wi + (q & 31u);
+        static_for<0, 4>([&](auto I) {
+          const uint32_t z = next();
+          longest = max(longest, z);
+          e[decltype(I)::value] = etab[z & 15u];
+        });
+        if (longest > 15u) {
           static_for<0, 4>([&](auto I) {
-            const uint32_t z = next();
-            longest = max(longest, z);
-            e[decltype(I)::value] = etab[z & 15u];
+            int w = (int)(p >> 5);
+            uint32_t u = cw[w] >> (p & 31u), z = 0;
+            if (u == 0u) {  // the pad behind the codes ends the search
+              z = 32u - (p & 31u);
+              while ((u = cw[++w]) == 0u) z += 32u;
+            }
+            z += (uint32_t)lowest_bit(u);
+            p += z + 1u;
+            e[decltype(I)::value] = (uint32_t)tab[z & 255u] << mb;
           });
-          if (longest > 15u) {
-            static_for<0, 4>([&](auto I) {
-              int w = (int)(p >> 5);
-              uint32_t u = cw[w] >> (p & 31u), z = 0;
-              if (u == 0u) {  // the pad behind the codes ends the search
-                z = 32u - (p & 31u);
-                while ((u = cw[++w]) == 0u) z += 32u;
-              }
-              z += (uint32_t)lowest_bit(u);
-              p += z + 1u;
-              e[decltype(I)::value] = (uint32_t)tab[z & 255u] << mb;
-            });
-            q = p;
-          }
-          static_for<0, 4>([&](auto I) { put(I, e[decltype(I)::value]); });
+          q = p;
         }
-      });
-    };
-    if (__builtin_amdgcn_ballot_w64((longs >> r) & 1u)) fields(std::true_type{});
-    else fields(std::false_type{});
+        static_for<0, 4>([&](auto I) { put(I, e[decltype(I)::value]); });
+      }
+    });
     const int left = a.K - 32 * g;
     if (left < 32) {  // nothing behind the last value
 #pragma unroll
@@ -392,6 +387,14 @@ __global__ __launch_bounds__(64) void unary_expand_kernel(UnaryArgs a, int row0,
       for (int i = 0; i < FW; ++i)
         if (g * FW + i < a.sw) dst[i] = sp[i];
     }
+  };
+  // lanes without a group do the last one again (the same words to the same places): a wave of few active lanes
+  // took longer, 1024 rows of 38 to 250 kept values 8.5 us instead of 5.5
+  const int turns = max(n * G, 64);
+  if (longs) {
+    for (int it = lane; it < turns; it += 64) group(min(it, n * G - 1), std::true_type{});
+  } else {
+    for (int it = lane; it < turns; it += 64) group(min(it, n * G - 1), std::false_type{});
   }
   if (!slow) return;
   uint8_t* const exps = reinterpret_cast<uint8_t*>(lds32);  // [K + kExpSlack], over the code words
