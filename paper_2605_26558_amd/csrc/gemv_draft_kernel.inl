@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     auto step = [&](auto I) {
       constexpr int i = decltype(I)::value;
       int pos = lowest_bit(m);
-      m &= m - 1u;
+      m = drop_lowest(m);
       const XT* xp = xb + pos * (64 * NB);
       if constexpr (MX) {
         // the field is the index of its signed magnitude; a lane past its last field reads neighbouring

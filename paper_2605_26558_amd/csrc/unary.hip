@@ -144,7 +144,7 @@ __device__ __forceinline__ void unary_row_exponents(const uint32_t* __restrict__
     while (__builtin_amdgcn_ballot_w64(u != 0u)) {
       if (u) {
         const int pos = lowest_bit(u);
-        u &= u - 1u;
+        u = drop_lowest(u);
         *p++ = tab[(pos - q) & 255];  // rank = zeros since the previous one-bit
         q = pos + 1;
       }
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * kUnaryWaves) void gemv_draft_unary_kernel(Unar
       auto step = [&](auto I) {
         constexpr int i = decltype(I)::value;
         const int pos = lowest_bit(m);
-        m &= m - 1u;
+        m = drop_lowest(m);
         const uint32_t top = field_top<SW, i>(win);  // sign at bit 31, mantissa bits below
         // fp32 pattern of the zero-padded bf16: sign | exponent | leading mantissa bits
         const uint32_t mant = __builtin_amdgcn_ubfe(top, 8, 23);
