@@ -64,12 +64,9 @@ __device__ __forceinline__ float wave_max(float v) {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 
-// float -> bf16, round to nearest even (NaN stays a quiet NaN).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t b = __float_as_uint(f);
-  if ((b & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((b >> 16) | 0x40u);
-  return (uint16_t)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
-}
+// float -> bf16, round to nearest even (NaN stays a quiet NaN): one v_cvt_pk_bf16_f32, the bits of the arithmetic
+// form ((b + 0x7FFF + (b >> 16 & 1)) >> 16, a NaN's upper half with the quiet bit) for all 2^32 patterns.
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float round_bf16(float f) { return bf16_to_f32(f32_to_bf16(f)); }
 
 // position of the lowest set bit, -1 if none: exactly what v_ffbl_b32 returns, so no select
