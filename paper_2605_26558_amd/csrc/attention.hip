@@ -116,6 +116,11 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnBatch batch) {
   }
 }
 
+static void set_group(AttnArgs& a, int grp) {
+  a.grp = grp;
+  a.grp_inv = grp > 0 ? (65536u + (uint32_t)grp - 1u) / (uint32_t)grp : 0u;
+}
+
 // Up to kAttnBatch sequences of one pass in one pair of launches (same layer, same form, same
 // number of query heads); every sequence gets exactly what a launch of its own would give it.
 // ws / ws_bytes: device memory for the per-split partial results; prof: bracket the launch with
@@ -131,7 +136,8 @@ static int launch_attention_group(cas_ctx* ctx, cas_kv* kv, const AttnCall* call
   a.spec_pool = (const uint32_t*)kv->d_spec;
   a.verif_pool = (const uint32_t*)kv->d_verif;
   a.layer = c0.layer;
-  a.n_q_heads = c0.n_q_heads; a.grp = c0.n_q_heads / g.n_kv_heads;
+  a.n_q_heads = c0.n_q_heads;
+  set_group(a, c0.n_q_heads / g.n_kv_heads);
   a.ystride = c0.ystride; a.rope = c0.rope;
   a.scale = 0.08838834764831845f;  // 1 / sqrt(128)
   a.pages_per_split = kPagesPerSplit;  // fixed: a query's value must not depend on the length
@@ -228,7 +234,8 @@ int launch_attention_dense(cas_ctx* ctx, int n_kv_heads, int n_q_heads, uint16_t
   a.g = KvGeom{};
   a.g.n_kv_heads = n_kv_heads; a.g.page_tokens = kPT; a.g.n_pages = 1;
   a.layer = 0;
-  a.n_q_heads = n_q_heads; a.grp = n_q_heads / n_kv_heads;
+  a.n_q_heads = n_q_heads;
+  set_group(a, n_q_heads / n_kv_heads);
   a.ystride = ystride; a.rope = rope;
   a.scale = 0.08838834764831845f;
   a.pages_per_split = kPagesPerSplit;

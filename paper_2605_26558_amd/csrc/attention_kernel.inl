@@ -17,6 +17,7 @@ struct AttnArgs {
   int layer, len, nsplit, pages_per_split;
   const uint16_t* Q;
   int ncols, n_q_heads, grp;  // grp = query heads per kv head
+  uint32_t grp_inv;           // ceil(2^16 / grp): row / grp = row * grp_inv >> 16 for rows below 256
   const uint16_t* Knew;
   const uint16_t* Vnew;
   int n_new;
@@ -111,6 +112,8 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   float* wl = wm + 4 * MT * 16;                        // [4 waves][MT*16] row sum of exponentials
 
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the column of a query row without a division (some 20 instructions; there were 8 of them per lane)
+  auto col_of = [&](int rr) { return (int)((uint32_t)rr * a.grp_inv >> 16); };
   const int pg = blockIdx.x, head = blockIdx.y;  // one page (64 positions) per workgroup
   const int R = a.ncols * a.grp;
   const KvGeom& g = a.g;
@@ -121,7 +124,6 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
 
   const int total = a.len + a.n_new;             // committed + in-flight positions
   const int tok0 = pg * kPT;
-  const int ntok = min(kPT, total - tok0);
   const int pos = tok0 + r;                      // position of this thread's token
   const bool live = pos < a.len;                 // committed: decode from the cache
   const bool fresh = !live && pos < total;       // in flight: uncompressed vector
@@ -150,11 +152,11 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   }
   if (a.qkv) {
 #pragma unroll
-    for (int it = 0; it < NQ; ++it) {
-      const int i = tid + it * 256, rr = i >> 6, d = i & 63;
+    for (int it = 0; it < NQ; ++it) {  // a wave takes a row at a time
+      const int rr = wv + 4 * it, d = lane;
       x0[it] = x1[it] = cc[it] = sn[it] = 0.f;
       if (rr < R) {
-        const int c = rr / a.grp, gi = rr - c * a.grp;
+        const int c = col_of(rr), gi = rr - c * a.grp;
         const float* src = a.qkv + (size_t)c * a.ystride + (size_t)(head * a.grp + gi) * 128;
         const float2 cs = *reinterpret_cast<const float2*>(a.rope + ((size_t)(first + c) * 64 + d) * 2);
         x0[it] = src[d]; x1[it] = src[d + 64]; cc[it] = cs.x; sn[it] = cs.y;
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
       const int i = tid + it * 256, rr = i >> 4, d = (i & 15) * 8;
       qraw[it] = make_uint4(0, 0, 0, 0);
       if (rr < R) {
-        const int c = rr / a.grp, gi = rr - c * a.grp;
+        const int c = col_of(rr), gi = rr - c * a.grp;
         qraw[it] = *reinterpret_cast<const uint4*>(a.Q + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + d);
       }
     }
@@ -205,11 +207,13 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
       ev = (int)((vs[kPT * 4 + r] >> (8 * j)) & 0xFFu);
     }
   }
-  // ---- 2. queries to LDS: row rr = column * grp + member; rows past R are 0
+  // ---- 2. queries to LDS: row rr = column * grp + member.  Rows past R stay as they are: a row of the
+  //         products depends on its own query alone, and nothing reads those
   if (a.qkv) {
 #pragma unroll
     for (int it = 0; it < NQ; ++it) {
-      const int i = tid + it * 256, rr = i >> 6, d = i & 63;
+      const int rr = wv + 4 * it, d = lane;
+      if (rr >= R) break;
       const float a0 = round_bf16(x0[it]), a1 = round_bf16(x1[it]);
       Qs[rr * kQP + d] = f32_to_bf16(a0 * cc[it] - a1 * sn[it]);
       Qs[rr * kQP + d + 64] = f32_to_bf16(a1 * cc[it] + a0 * sn[it]);
@@ -293,6 +297,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   // ---- 4. scores of this wave's 16 tokens against all query rows, kept in registers:
   //         lane (mi, mq) holds token 16 wv + mi of rows mt*16 + 4 mq + e
   float sc[MT][4];
+  const int visible = total - a.ncols - tok0;  // last token of the page that column 0 sees
   {
     const uint16_t* b_base = Kt + (16 * wv + mi) * kKP + 4 + 4 * mq;
     const int t = 16 * wv + mi;
@@ -306,16 +311,15 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
         bf16x4 bv = *reinterpret_cast<const bf16x4*>(b_base + (kk >> 1) * kKG + (kk & 1) * 16);
         C = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, C, 0, 0, 0);
       }
+      float mx[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int rr = mt * 16 + 4 * mq + e;
         // column c sees positions 0 .. len + n_new - ncols + c
-        const int c = rr / a.grp;
-        const bool ok = t < ntok && (tok0 + t <= total - a.ncols + c);
-        sc[mt][e] = ok ? C[e] * a.scale : -INFINITY;
-        const float mx = row16_max(sc[mt][e]);
-        if (mi == 0) wm[wv * (MT * 16) + rr] = mx;
+        sc[mt][e] = t <= visible + col_of(rr) ? C[e] * a.scale : -INFINITY;
+        mx[e] = row16_max(sc[mt][e]);
       }
+      if (mi == 0) *reinterpret_cast<float4*>(wm + wv * (MT * 16) + mt * 16 + 4 * mq) = make_float4(mx[0], mx[1], mx[2], mx[3]);
     }
   }
   __syncthreads();  // every wave is done with Q and K: their regions may be overwritten
@@ -327,6 +331,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   // ---- 5. softmax numerators of the page, head + remainder in bf16; row sums per wave
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
+    float ps[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int rr = mt * 16 + 4 * mq + e, t = 16 * wv + mi;
@@ -335,9 +340,10 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
       const uint16_t ph = f32_to_bf16(p);
       Ph[rr * kPP + t] = ph;
       Pl[rr * kPP + t] = f32_to_bf16(p - bf16_to_f32(ph));
-      const float ps = row16_sum(p);
-      if (mi == 0) wl[wv * (MT * 16) + rr] = ps;
+      ps[e] = row16_sum(p);
     }
+    // lane 0's sums: the lanes of a row add the same values in orders of their own
+    if (mi == 0) *reinterpret_cast<float4*>(wl + wv * (MT * 16) + mt * 16 + 4 * mq) = make_float4(ps[0], ps[1], ps[2], ps[3]);
   }
   if constexpr (!FULL) __syncthreads();
   // ---- 6. V tile, transposed: Vt[channel][token]
