@@ -79,16 +79,20 @@ constexpr size_t attn_lds_bytes() {
   return sizeof(uint16_t) * (MT * 16 * kQPRows + kKVTile) + sizeof(float) * (8 * MT * 16);
 }
 
-// all-reduce over the 16 lanes of a DPP row by rotations; every lane ends with the result
+// All-reduce over the 16 lanes of a DPP row by rotations; every lane ends with the result (of a sum, with the
+// result of an order of its own).  The rotation is part of the operation: an addition folds the move of a builtin with no
+// old value into itself, a maximum does not (the compiler first makes its operands quiet numbers, two more
+// operations), so that one is written out, behind the wait states that a rotation of a fresh result needs.
 template <int CTRL>
 __device__ __forceinline__ float row_rot(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, row_rot<0x121>(v));
-  v = fmaxf(v, row_rot<0x122>(v));
-  v = fmaxf(v, row_rot<0x124>(v));
-  return fmaxf(v, row_rot<0x128>(v));
+  asm volatile("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:1 row_mask:0xf bank_mask:0xf\n\t"
+               "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+               "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+               "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf" : "+v"(v));
+  return v;
 }
 __device__ __forceinline__ float row16_sum(float v) {
   v += row_rot<0x121>(v);
@@ -326,17 +330,24 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   // the draft form clears the whole V tile with 16-byte writes (5 per thread; 32 of 2 bytes when every thread
   // clears the channels of its own token)
   if constexpr (!FULL) {
-    for (int i = tid; i < kVR * kVP / 8; i += 256) reinterpret_cast<uint4*>(Vt)[i] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < (kVR * kVP / 8 + 255) / 256; ++k)
+      if (tid + 256 * k < kVR * kVP / 8) reinterpret_cast<uint4*>(Vt)[tid + 256 * k] = make_uint4(0, 0, 0, 0);
   }
   // ---- 5. softmax numerators of the page, head + remainder in bf16; row sums per wave
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     float ps[4];
+    const f32x4 m0 = *reinterpret_cast<const f32x4*>(wm + mt * 16 + 4 * mq),
+                m1 = *reinterpret_cast<const f32x4*>(wm + (MT + mt) * 16 + 4 * mq),
+                m2 = *reinterpret_cast<const f32x4*>(wm + (2 * MT + mt) * 16 + 4 * mq),
+                m3 = *reinterpret_cast<const f32x4*>(wm + (3 * MT + mt) * 16 + 4 * mq);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int rr = mt * 16 + 4 * mq + e, t = 16 * wv + mi;
-      const float mx = fmaxf(fmaxf(wm[rr], wm[MT * 16 + rr]), fmaxf(wm[2 * MT * 16 + rr], wm[3 * MT * 16 + rr]));
-      const float p = (sc[mt][e] == -INFINITY) ? 0.f : __expf(sc[mt][e] - mx);
+      // at least the lowest finite number: where a row sees nothing of the page, its maximum is -inf as its scores are
+      const float mx = fmaxf(fmaxf(fmaxf(m0[e], m1[e]), fmaxf(m2[e], m3[e])), -3.402823466e38f);
+      const float p = __expf(sc[mt][e] - mx);
       const uint16_t ph = f32_to_bf16(p);
       Ph[rr * kPP + t] = ph;
       Pl[rr * kPP + t] = f32_to_bf16(p - bf16_to_f32(ph));
