@@ -17,13 +17,23 @@
 
 namespace cas {
 
+// A batch takes x as fp32 where that fits (2 columns to 18432 values each, 3 to 12288, 4 to 8192): it is the faster
+// form at every size measured (XStage); wider rows keep to bf16.
+template <int T, int NB>
+static int launch_nb(cas_ctx* ctx, const GemvArgs& a, int grid) {
+  const size_t lds = gemv_lds_bytes(a.bw, NB, false);
+  if (lds <= (size_t)ctx->lds_max) return launch_gemv_instance<T, NB, false, false>(ctx, a, grid, lds);
+  if constexpr (NB > 1) return launch_gemv_instance<T, NB, false, true>(ctx, a, grid, gemv_lds_bytes(a.bw, NB, true));
+  return CAS_ENOTSUP;
+}
+
 template <int T>
-static int launch_t(cas_ctx* ctx, const GemvArgs& a, int batch, int grid, size_t lds) {
+static int launch_t(cas_ctx* ctx, const GemvArgs& a, int batch, int grid) {
   switch (batch) {
-    case 1: return launch_gemv_instance<T, 1, false>(ctx, a, grid, lds);
-    case 2: return launch_gemv_instance<T, 2, false>(ctx, a, grid, lds);
-    case 3: return launch_gemv_instance<T, 3, false>(ctx, a, grid, lds);
-    case 4: return launch_gemv_instance<T, 4, false>(ctx, a, grid, lds);
+    case 1: return launch_nb<T, 1>(ctx, a, grid);
+    case 2: return launch_nb<T, 2>(ctx, a, grid);
+    case 3: return launch_nb<T, 3>(ctx, a, grid);
+    case 4: return launch_nb<T, 4>(ctx, a, grid);
     default: return CAS_EINVAL;
   }
 }
@@ -41,12 +51,10 @@ int launch_gemv_draft_block(cas_ctx* ctx, const cas_wdesc& d, const uint32_t* bi
   a.bitmap = bitmap;
   a.spec = spec;
   a.x = x; a.y = y; a.yld = (int)d.rows;
-  // x: fp32 for one column, bf16 for a batch (see XStage)
-  const size_t lds = gemv_lds_bytes(d.bw, batch);
-  if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  if (gemv_lds_bytes(d.bw, batch, batch > 1) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   const int grid = gemv_grid(ctx, epi == 2 ? nr / 2 : nr);  // a gate/up row pair stays in one wave
   a.nwaves = grid * kGemvWaves;
-#define CAS_T(TV) case TV: return launch_t<TV>(ctx, a, batch, grid, lds);
+#define CAS_T(TV) case TV: return launch_t<TV>(ctx, a, batch, grid);
   switch (d.t) {
     CAS_T(0) CAS_T(1) CAS_T(2) CAS_T(3) CAS_T(4) CAS_T(5) CAS_T(6) CAS_T(7)
   }
@@ -58,7 +66,7 @@ int launch_gemv_draft_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec, 
                             float* y, const uint16_t* gain, float eps, int epi, uint16_t* out16) {
   if (d.rows <= 0) return CAS_OK;
   if (epi == 2 && (d.rows & 1)) return CAS_EINVAL;
-  if (gemv_lds_bytes(d.bw, batch) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
+  if (gemv_lds_bytes(d.bw, batch, batch > 1) > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   ProfScope prof(ctx, PROF_GEMV_DRAFT, 4.0 * (double)d.rows * (d.bw + d.sw));
   return launch_gemv_draft_block(ctx, d, (const uint32_t*)((const char*)spec + d.off_bitmap),
                                  (const uint32_t*)((const char*)spec + d.off_spec), (int)d.rows, x, batch, y, gain, eps,

@@ -49,9 +49,10 @@ constexpr int kRawBufferFlags = 0x00020000;  // word 3 of a raw (unstructured, 3
 constexpr int kGemvThreads = 1024;  // 16 waves share one staged copy of x
 constexpr int kGemvWaves = kGemvThreads / 64;
 
-// x in LDS: fp32 for one column; bf16 bit patterns (XH) for a batch, whose gathers of NB
-// values per kept weight would otherwise saturate the LDS (measured 2.4x slower at NB = 4).
-// The staged values are bf16-representable either way; XH costs one shift per use.
+// x in LDS: fp32 where that fits; bf16 bit patterns (XH) for a batch that does not, which costs an operation per
+// use and column.  The staged values are bf16-representable either way, so both give the same bits.  The kernel is
+// bound by its instructions, and two or four columns come with one (aligned) read: 28672 x 4096 with 2 / 3 / 4
+// columns 37.0 / 43.6 / 40.1 us as bf16, 30.3 / 34.2 / 33.4 as fp32; 4096 x 4096 7.7 / 9.1 / 8.8 and 7.6 / 7.6 / 7.7.
 // Layout: per chunk of 64 bitmap words a block [1 + 32][64 lanes][NB]; row 0 holds zeros, row
 // 1 + k the values of column k of every lane's word.  A lane only ever reads entries of its own
 // 4-byte column of the block, so the gathers of a wave never meet in a bank whatever positions
@@ -87,13 +88,12 @@ struct XStage<true> {
 // descriptor as well).  The table of a small T is long enough for gathers of a wave to meet in a bank, which eats
 // some of the gain but not all: 28672 x 4096 33.1 -> 30.4 us at T = 0 (2.3 conflict cycles per LDS instruction),
 // 33.6 -> 28.7 at T = 2 (1.6), 33.6 -> 28.0 at T = 4 (none); 4096 x 4096 7.1 -> 7.1, 6.6, 6.5.
-template <int T, int NB, bool MX>
+template <int T, int NB, bool MX, bool XH>
 __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   constexpr int FW = MX ? 9 - T : 16 - T;
-  constexpr bool XH = NB > 1;
   using XS = XStage<XH>;
   using XT = typename XS::type;
-  extern __shared__ uint8_t xs_raw[];
+  extern __shared__ __attribute__((aligned(16))) uint8_t xs_raw[];
   // shared-exponent form: the table of signed magnitudes in front of x
   const uint8_t* const mag_tab = xs_raw;
   XT* xs = reinterpret_cast<XT*>(xs_raw + (MX ? kMagTabBytes<FW> : 0));
@@ -169,16 +169,26 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
       int pos = lowest_bit(m);
       m = drop_lowest(m);
       const XT* xp = xb + pos * (64 * NB);
+      float xv[NB];  // two or four columns with one read
+      if constexpr (!XH && (NB == 2 || NB == 4)) {
+        typedef float xvec __attribute__((ext_vector_type(NB)));
+        const xvec v = *reinterpret_cast<const xvec*>(xp);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) xv[b] = v[b];
+      } else {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) xv[b] = XS::get(xp[b]);
+      }
       if constexpr (MX) {
         // the field is the index of its signed magnitude; a lane past its last field reads neighbouring
         // bits, always the index of a finite number, and multiplies it by the zero entry of the segment
         const float f = *reinterpret_cast<const float*>(mag_tab + field_scaled<FW, i, 2>(win));
 #pragma unroll
-        for (int b = 0; b < NB; ++b) accw[b] = fmaf(f, XS::get(xp[b]), accw[b]);
+        for (int b = 0; b < NB; ++b) accw[b] = fmaf(f, xv[b], accw[b]);
       } else {
         const float f = __uint_as_float(field_top<FW, i>(win));
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = fmaf(f, XS::get(xp[b]), acc[b]);
+        for (int b = 0; b < NB; ++b) acc[b] = fmaf(f, xv[b], acc[b]);
       }
     };
     // the first 16 set bits unconditionally, then pairs until every lane has run out
@@ -366,19 +376,19 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 }
 
 // LDS allowance of the instantiation, then the launch
-template <int T, int NB, bool MX>
+template <int T, int NB, bool MX, bool XH>
 static int launch_gemv_instance(cas_ctx* ctx, const GemvArgs& a, int grid, size_t lds) {
   static LdsLimit lim;
-  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX>, lds, lim);
+  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH>, lds, lim);
   if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
+  hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX, XH>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
   CAS_HIP(ctx, hipGetLastError());
   return CAS_OK;
 }
 
 // LDS bytes of the staged x
-static inline size_t gemv_lds_bytes(int bw, int batch) {
-  return (batch > 1 ? sizeof(uint16_t) : sizeof(float)) * (size_t)((bw + 63) / 64 * 64) * 33 * batch;
+static inline size_t gemv_lds_bytes(int bw, int batch, bool half) {
+  return (half ? sizeof(uint16_t) : sizeof(float)) * (size_t)((bw + 63) / 64 * 64) * kXRows * batch;
 }
 
 // one or two workgroups per CU (two fill its 32 wave slots), whichever leaves the most loaded

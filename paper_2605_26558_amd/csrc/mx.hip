@@ -183,11 +183,11 @@ int launch_gemv_draft_mx_fused(cas_ctx* ctx, const cas_mxdesc& mx, const void* d
   a.sexp = (const uint8_t*)d_mxspec + mx.off_sexp;
   a.ew = mx.ew;
   a.x = d_x; a.y = d_y; a.yld = (int)d.rows;
-  const size_t lds = gemv_lds_bytes(d.bw, 1) + (sizeof(float) << (9 - d.t));  // x, the table of signed magnitudes
+  const size_t lds = gemv_lds_bytes(d.bw, 1, false) + (sizeof(float) << (9 - d.t));  // x, the table of signed magnitudes
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   const int grid = gemv_grid(ctx, epi == 2 ? d.rows / 2 : d.rows);  // a gate/up row pair stays in one wave
   a.nwaves = grid * kGemvWaves;
-#define CAS_T(TV) case TV: return launch_gemv_instance<TV, 1, true>(ctx, a, grid, lds);
+#define CAS_T(TV) case TV: return launch_gemv_instance<TV, 1, true, false>(ctx, a, grid, lds);
   switch (d.t) {
     CAS_T(0) CAS_T(1) CAS_T(2) CAS_T(3) CAS_T(4) CAS_T(5) CAS_T(6) CAS_T(7)
   }

@@ -229,6 +229,18 @@ def test_fused_draft_gemv_batch_equals_single_columns(env, rows, cols, batch):
         assert torch.equal(yb[b:b + 1], y1) and torch.equal(hb[b:b + 1], h1) and torch.equal(ab[b:b + 1], a1)
 
 
+@pytest.mark.parametrize("batch,cols", [(2, 18432), (2, 18433), (3, 12288), (3, 12289), (4, 8192), (4, 8193), (4, 31)])
+def test_draft_gemv_batch_keeps_its_bits_on_both_sides_of_the_lds(env, batch, cols):
+    """x of a batch is staged as fp32 up to the first of each pair of sizes and as bf16 above it: every column has
+    the bits of the one-column call."""
+    torch, B, ctx = env
+    ew = B.cas_encode_weight(ctx, _dev(torch, synth.weight_matrix(19, cols, seed=9)), 600, 3)
+    X = _dev(torch, synth.normal_bf16((batch, cols), 2.0, seed=10))
+    got = B.cas_gemv_draft(ctx, ew, X)
+    for b in range(batch):
+        assert torch.equal(got[b:b + 1], B.cas_gemv_draft(ctx, ew, X[b:b + 1].contiguous()))
+
+
 def _special_patterns(rows, cols, seed):
     """bf16 words that exercise the selection order and the bit split: +-0, subnormals, the
     largest finite values, +-Inf and NaNs with several payloads, among ordinary values."""
