@@ -40,80 +40,136 @@ extern template int launch_mt<1, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<2, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<3, false, true>(cas_ctx*, const AttnBatch&, dim3);
 
-// Combine the splits: o = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, rounded to bf16.
-// One workgroup per (query row, kv head, half of the channels): the split weights are computed
-// once into LDS, then thread (channel d, part p) sums the splits s = p, p + 8, ... with
-// independent loads and the eight parts are added in part order (a fixed order: the result
-// does not depend on timing, nor on how many rows ride along).
+// Combine the splits: o = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, rounded to bf16.  Splits p, p + 8, ... are
+// added one after the other in each of eight parts p, then the parts in order; the denominator adds blocks of 64
+// splits, each in the order of wave_sum.  These orders are fixed: the result depends neither on timing, nor on how
+// many rows ride along, nor on which of the two kernels below combines a row.
 constexpr int kMergeParts = 8;
-constexpr int kMergePre = 20;  // splits per thread whose outputs are requested before the weights exist
-__global__ __launch_bounds__(512) void attn_merge_kernel(AttnBatch batch) {
+
+__device__ __forceinline__ float split_weight(float m, float M) { return m == -INFINITY ? 0.f : __expf(m - M); }
+
+// One workgroup per (query row, kv head, half of the channels), a wave per part.  Bound by latency: everything a wave
+// needs first is requested at once, kMergePre outputs of its part, the maxima of these splits (lane q: the q-th) and
+// the pairs of its block of the denominator.  The outputs come through buffer descriptors, of no length past the end
+// of the part: what lies there reads as 0 and adds nothing, without a branch per load (with branches the compiler's
+// code took 5.2 us where this takes 4.8, and 15.8 for 9.8).
+constexpr int kMergePre = 32;
+__global__ __launch_bounds__(512, 4) void attn_merge_kernel(AttnBatch batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z >> 1);  // blockIdx.z = 2 * sequence + channel half
-  extern __shared__ float sw[];  // [nsplit] weights, then [kMergeParts][64] partial sums
-  __shared__ float red[16];
-  const int rr = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
-  const int d = (blockIdx.z & 1) * 64 + (tid & 63), part = tid >> 6;
-  const int R = a.ncols * a.grp;
+  __shared__ float red[2][kMergeParts];
+  __shared__ float ps[kMergeParts][64];
+  const int rr = blockIdx.x, head = blockIdx.y, lane = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = (blockIdx.z & 1) * 64 + lane;
+  const int R = a.ncols * a.grp, n = a.nsplit;
   if (rr >= R) return;  // a sequence with fewer rows than the widest of the launch
-  const size_t sstride = (size_t)a.g.n_kv_heads * R * kPartStride;
-  const float* base = a.part + ((size_t)head * R + rr) * kPartStride;
-  // everything this thread needs from the first 512 splits goes out in one batch: its split's
-  // (max, sum) and the outputs of splits part, part + 8, ... of its channel
-  float m0 = -INFINITY, l0 = 0.f;
-  if (tid < a.nsplit) {
-    m0 = base[tid * sstride + 128];
-    l0 = base[tid * sstride + 129];
-  }
+  const size_t step = (size_t)a.g.n_kv_heads * R * 128 * kMergeParts * 4;  // bytes from a split of the part to the next
+  const char* base = reinterpret_cast<const char*>(a.part + (((size_t)part * a.g.n_kv_heads + head) * R + rr) * 128);
+  const float2* ml = attn_ml(a, R) + ((size_t)head * R + rr) * n;
+  const int cnt = (n - part + kMergeParts - 1) / kMergeParts;  // splits of this part
+  const int s0 = 64 * part + lane;
+  float2 blk = make_float2(-INFINITY, 0.f);
+  if (s0 < n) blk = ml[s0];
+  float m_own = -INFINITY;
+  if (lane < cnt) m_own = ml[part + kMergeParts * lane].x;
   float o[kMergePre];
+  auto request = [&](int from) {  // outputs from .. from + kMergePre - 1 of the part
+    const int q0 = __builtin_amdgcn_readfirstlane(from);  // uniform, and known to be
+    const char* row = base + (size_t)q0 * step;
 #pragma unroll
-  for (int q = 0; q < kMergePre; ++q) {
-    const int s = part + q * kMergeParts;
-    o[q] = s < a.nsplit ? base[s * sstride + d] : 0.f;
-  }
-  float mx = m0;
-  for (int s = tid + 512; s < a.nsplit; s += 512) mx = fmaxf(mx, base[s * sstride + 128]);
-  mx = wave_max(mx);
-  if ((tid & 63) == 0) red[tid >> 6] = mx;
+    for (int q = 0; q < kMergePre; ++q) {
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), 0, q0 + q < cnt ? 512 : 0, kRawBufferFlags);
+      o[q] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, 4 * d, 0, 0));
+      row += step;
+    }
+  };
+  request(0);
+  float M = blk.x;
+  for (int s = s0 + 512; s < n; s += 512) M = fmaxf(M, ml[s].x);
+  M = wave_max(M);
+  if (lane == 0) red[0][part] = M;
   __syncthreads();
-  float M = red[0];
 #pragma unroll
-  for (int w = 1; w < 8; ++w) M = fmaxf(M, red[w]);
-  float den = 0.f;
-  if (tid < a.nsplit) {
-    const float w = (m0 == -INFINITY) ? 0.f : __expf(m0 - M);
-    sw[tid] = w;
-    den = w * l0;
-  }
-  for (int s = tid + 512; s < a.nsplit; s += 512) {
-    float m = base[s * sstride + 128];
-    float w = (m == -INFINITY) ? 0.f : __expf(m - M);
-    sw[s] = w;
-    den += w * base[s * sstride + 129];
-  }
+  for (int q = 0; q < kMergeParts; ++q) M = fmaxf(M, red[0][q]);
+  float den = split_weight(blk.x, M) * blk.y;
+  for (int s = s0 + 512; s < n; s += 512) den += split_weight(ml[s].x, M) * ml[s].y;
   den = wave_sum(den);
-  if ((tid & 63) == 0) red[8 + (tid >> 6)] = den;
-  __syncthreads();
-  den = 0.f;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) den += red[8 + w];
+  if (lane == 0) red[1][part] = den;
   float num = 0.f;
+  for (int q0 = 0; q0 < cnt;) {
+    const int w = __float_as_int(split_weight(m_own, M));
 #pragma unroll
-  for (int q = 0; q < kMergePre; ++q) {
-    const int s = part + q * kMergeParts;
-    if (s < a.nsplit) num += sw[s] * o[q];
+    for (int i = 0; i < kMergePre; ++i) num += __int_as_float(__builtin_amdgcn_readlane(w, i)) * o[i];
+    q0 += kMergePre;
+    if (q0 >= cnt) break;
+    m_own = q0 + lane < cnt ? ml[part + kMergeParts * (q0 + lane)].x : -INFINITY;
+    request(q0);
   }
-#pragma unroll 8
-  for (int s = part + kMergePre * kMergeParts; s < a.nsplit; s += kMergeParts) num += sw[s] * base[s * sstride + d];
-  float* ps = sw + a.nsplit;
-  ps[part * 64 + (tid & 63)] = num;
+  ps[part][lane] = num;
   __syncthreads();
   if (part == 0) {
-    num = ps[tid];
+    den = 0.f;
 #pragma unroll
-    for (int q = 1; q < kMergeParts; ++q) num += ps[q * 64 + tid];
+    for (int q = 0; q < kMergeParts; ++q) den += red[1][q];
+#pragma unroll
+    for (int q = 1; q < kMergeParts; ++q) num += ps[q][lane];
     const int c = rr / a.grp, gi = rr - c * a.grp;
     a.O[((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + d] = f32_to_bf16(num / den);
   }
+}
+
+// Few splits: a wave per (query row, kv head) with all channels and all parts, no LDS and no barrier: with 4 splits
+// 2.8 us for 3.5 of the other, with up to 8 splits of 64 rows of four sequences 4.6 us for 10.7.  One wave's loads
+// reach to 32 splits; from there on the other form, whose eight waves share them: 129 splits 4.8 us (4.9 with the
+// pairs behind each output, LDS weights and a barrier more), 65 to 513 splits of four sequences 9.8 (13.1).
+constexpr int kMergeFew = 32;
+__global__ __launch_bounds__(256) void attn_merge_few_kernel(AttnBatch batch) {
+  const AttnArgs a = attn_args_of(batch, blockIdx.z);
+  const int rr = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), head = blockIdx.y, lane = threadIdx.x & 63;
+  const int R = a.ncols * a.grp, n = a.nsplit;
+  if (rr >= R) return;
+  const size_t sstride = (size_t)a.g.n_kv_heads * R * 64;
+  const float2* base = reinterpret_cast<const float2*>(a.part) + ((size_t)head * R + rr) * 64 + lane;
+  float2 ml = make_float2(-INFINITY, 0.f);
+  if (lane < n) ml = attn_ml(a, R)[((size_t)head * R + rr) * n + lane];
+  float2 o[kMergeFew];
+#pragma unroll
+  for (int s = 0; s < kMergeFew; ++s) {
+    o[s] = make_float2(0.f, 0.f);
+    if (s < n) o[s] = base[(size_t)s * sstride];
+  }
+  const float w = split_weight(ml.x, wave_max(ml.x)), den = wave_sum(w * ml.y);
+  float2 num[kMergeParts];
+#pragma unroll
+  for (int p = 0; p < kMergeParts; ++p) num[p] = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int s = 0; s < kMergeFew; ++s) {
+    if (s < n) {
+      const float ws = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s));
+      num[s % kMergeParts].x += ws * o[s].x;
+      num[s % kMergeParts].y += ws * o[s].y;
+    }
+  }
+#pragma unroll
+  for (int p = 1; p < kMergeParts; ++p) {
+    num[0].x += num[p].x;
+    num[0].y += num[p].y;
+  }
+  const int c = rr / a.grp, gi = rr - c * a.grp;
+  uint16_t* out = a.O + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + 2 * lane;
+  out[0] = f32_to_bf16(num[0].x / den);
+  out[1] = f32_to_bf16(num[0].y / den);
+}
+
+static int launch_merge(cas_ctx* ctx, const AttnBatch& b, int max_r, int max_split, int n) {
+  const int heads = b.common.g.n_kv_heads;
+  if (max_split <= kMergeFew)
+    hipLaunchKernelGGL(attn_merge_few_kernel, dim3((max_r + 3) / 4, heads, n), dim3(256), 0, ctx->stream, b);
+  else
+    hipLaunchKernelGGL(attn_merge_kernel, dim3(max_r, heads, 2 * n), dim3(512), 0, ctx->stream, b);
+  CAS_HIP(ctx, hipGetLastError());
+  return CAS_OK;
 }
 
 static void set_group(AttnArgs& a, int grp) {
@@ -200,10 +256,7 @@ static int launch_attention_group(cas_ctx* ctx, cas_kv* kv, const AttnCall* call
     }
   }
   if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL(attn_merge_kernel, dim3(max_r, g.n_kv_heads, 2 * n), dim3(512),
-                     sizeof(float) * (max_split + kMergeParts * 64), ctx->stream, b);
-  CAS_HIP(ctx, hipGetLastError());
-  return CAS_OK;
+  return launch_merge(ctx, b, max_r, max_split, n);
 }
 
 int launch_attention_batch(cas_ctx* ctx, cas_kv* kv, const AttnCall* calls, int n) {
@@ -251,10 +304,7 @@ int launch_attention_dense(cas_ctx* ctx, int n_kv_heads, int n_q_heads, uint16_t
   q.part = (float*)ctx->d_ws;
   const int rc = launch_mt<1, false>(ctx, b, dim3(q.nsplit, n_kv_heads, 1));
   if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL(attn_merge_kernel, dim3(a.grp, n_kv_heads, 2), dim3(512),
-                     sizeof(float) * (q.nsplit + kMergeParts * 64), ctx->stream, b);
-  CAS_HIP(ctx, hipGetLastError());
-  return CAS_OK;
+  return launch_merge(ctx, b, a.grp, q.nsplit, 1);
 }
 
 // ---- the variant for callers that cannot allocate: the partial results live in a fixed array of

@@ -30,7 +30,7 @@ struct AttnArgs {
   uint16_t* Kslot;    // writable views of Knew / Vnew
   uint16_t* Vslot;
   float scale;
-  float* part;  // [nsplit][n_kv_heads][R][132]
+  float* part;  // [nsplit][n_kv_heads][R][128] outputs, then [n_kv_heads][R][nsplit] pairs (maximum, sum)
   uint16_t* O;
 };
 
@@ -67,9 +67,14 @@ constexpr int kKG = 36, kKP = 148;  // K tile: group pitch (4 dump + 32), row pi
 constexpr int kVP = 72;          // transposed V tile: token pitch per channel row
 constexpr int kVR = 132;         // channel rows: 4 groups x (1 dump + 32)
 constexpr int kPP = 72;          // probability row pitch (bf16)
-constexpr int kPartStride = 132;
+constexpr int kPartStride = 132; // floats of workspace per (split, row): 128 outputs, maximum and sum, 2 to spare
 constexpr int kPagesPerSplit = 1;
 constexpr int kMaxCols = 16;     // columns of one pass whose k, v may be split from the projection here
+
+// the (maximum, sum) pairs of a sequence: those of a row lie side by side, as the merge reads them
+__device__ __forceinline__ float2* attn_ml(const AttnArgs& a, int R) {
+  return reinterpret_cast<float2*>(a.part + (size_t)a.nsplit * a.g.n_kv_heads * R * 128);
+}
 
 constexpr int kKVTile = kPT * kKP > kVR * kVP ? kPT * kKP : kVR * kVP;  // K and V^T tiles share one region
 constexpr int kQPRows = kQP > 2 * kPP ? kQP : 2 * kPP;                  // Q and (P head, P remainder) share one region
@@ -384,7 +389,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   }
   __syncthreads();
   // ---- 7. O = P V ; wave w owns channels 32w .. 32w+31; partial result of this page
-  float* part = a.part + ((size_t)pg * g.n_kv_heads + head) * R * kPartStride;
+  float* part = a.part + ((size_t)pg * g.n_kv_heads + head) * R * 128;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -402,15 +407,16 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int rr = mt * 16 + 4 * mq + e;
-        if (rr < R) part[rr * kPartStride + 32 * wv + nt * 16 + mi] = C[e];
+        if (rr < R) part[rr * 128 + 32 * wv + nt * 16 + mi] = C[e];
       }
     }
   }
   if (tid < R) {
     const float* m4 = wm + tid;
     const float* l4 = wl + tid;
-    part[tid * kPartStride + 128] = fmaxf(fmaxf(m4[0], m4[MT * 16]), fmaxf(m4[2 * MT * 16], m4[3 * MT * 16]));
-    part[tid * kPartStride + 129] = ((l4[0] + l4[MT * 16]) + l4[2 * MT * 16]) + l4[3 * MT * 16];
+    attn_ml(a, R)[((size_t)head * R + tid) * a.nsplit + pg] =
+        make_float2(fmaxf(fmaxf(m4[0], m4[MT * 16]), fmaxf(m4[2 * MT * 16], m4[3 * MT * 16])),
+                    ((l4[0] + l4[MT * 16]) + l4[2 * MT * 16]) + l4[3 * MT * 16]);
   }
 }
 

@@ -62,6 +62,8 @@ __device__ __forceinline__ float wave_max(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+constexpr int kRawBufferFlags = 0x00020000;  // word 3 of a raw (unstructured, 32-bit data) buffer descriptor
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 
 // float -> bf16, round to nearest even (NaN stays a quiet NaN): one v_cvt_pk_bf16_f32, the bits of the arithmetic

@@ -44,7 +44,6 @@ struct Cursor {  // walks the (row, chunk) items of one wave in order
 };
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kRawBufferFlags = 0x00020000;  // word 3 of a raw (unstructured, 32-bit data) buffer descriptor
 
 constexpr int kGemvThreads = 1024;  // 16 waves share one staged copy of x
 constexpr int kGemvWaves = kGemvThreads / 64;

@@ -140,6 +140,31 @@ def test_attention_matches_oracle(env, len_cache, ncols, n_new, full):
             np.testing.assert_array_equal(o1[0], out[c])
 
 
+@pytest.mark.parametrize("length", [2047, 2048, 16383, 16384, 32767, 32768])
+def test_attention_merge_of_few_and_of_many_pages(env, length):
+    """Partial results of 32 / 33, 256 / 257 and 512 / 513 pages, the ends of what a merge takes in one go, against
+    the oracle; next to another sequence, whose launch merges both in one form, gives the same
+    bits."""
+    torch, B, ctx = env
+    nq, nkv = 4, 2
+    kv = B.KVCache(ctx, 1, nkv, n_pages=1100, max_seqs=2, max_pages_per_seq=550)
+    Kh, Vh = synth.kv_tensor(length, nkv, 128, seed=3), synth.kv_tensor(length, nkv, 128, seed=4, outlier_channels=0)
+    for seq in (0, 1):
+        B.cas_kv_append(ctx, kv, 0, seq, _dev(torch, Kh), _dev(torch, Vh))
+    B.cas_kv_set_len(kv, 0, length)
+    B.cas_kv_set_len(kv, 1, 1 if length > 4000 else length)
+    Q, Kn, Vn = (synth.normal_bf16((1, n, 128), 1.0, seed=5 + n) for n in (nq, nkv, nkv))
+    args = [_dev(torch, x) for x in (Q, Kn, Vn)]
+    out = _host(B.cas_attention(ctx, kv, 0, 0, True, *args))
+    ref = _ref_attention(Q, Kh, Vh, Kn, Vn, 1, nq, nkv)
+    reff = O.bf16_to_f64(ref)
+    assert (np.abs(O.bf16_to_f64(out) - reff) <= _attn_tol(Q, Kh, Vh, Kn, Vn, 1, nq, nkv, reff)).all()
+    alone = [_host(B.cas_attention(ctx, kv, 0, seq, True, *args)) for seq in (0, 1)]
+    both = B.cas_attention_multi(ctx, kv, 0, [0, 1], True, [args[0]] * 2, [args[1]] * 2, [args[2]] * 2)
+    for one, two in zip(alone, both):
+        np.testing.assert_array_equal(one, _host(two))
+
+
 def test_attention_llama70b_head_grouping(env):
     """64 query heads on 8 kv heads (group of 8), 9 verification columns = 72 query rows per
     kv head, and the matching one-column draft call."""
