@@ -40,6 +40,11 @@ extern template int launch_mt<1, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<2, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<3, false, true>(cas_ctx*, const AttnBatch&, dim3);
 
+// runs of columns (exact form): attention_runs.hip
+extern template int launch_mt<4, true, false>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<4, true, true>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<5, true, true>(cas_ctx*, const AttnRuns&, dim3);
+
 // Combine the splits: o = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, rounded to bf16.  Splits p, p + 8, ... are
 // added one after the other in each of eight parts p, then the parts in order; the denominator adds blocks of 64
 // splits, each in the order of wave_sum.  These orders are fixed: the result depends neither on timing, nor on how
@@ -54,7 +59,8 @@ __device__ __forceinline__ float split_weight(float m, float M) { return m == -I
 // of the part: what lies there reads as 0 and adds nothing, without a branch per load (with branches the compiler's
 // code took 5.2 us where this takes 4.8, and 15.8 for 9.8).
 constexpr int kMergePre = 32;
-__global__ __launch_bounds__(512, 4) void attn_merge_kernel(AttnBatch batch) {
+template <class BATCH>
+__global__ __launch_bounds__(512, 4) void attn_merge_kernel(BATCH batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z >> 1);  // blockIdx.z = 2 * sequence + channel half
   __shared__ float red[2][kMergeParts];
   __shared__ float ps[kMergeParts][64];
@@ -124,7 +130,8 @@ __global__ __launch_bounds__(512, 4) void attn_merge_kernel(AttnBatch batch) {
 // reach to 32 splits; from there on the other form, whose eight waves share them: 129 splits 4.8 us (4.9 with the
 // pairs behind each output, LDS weights and a barrier more), 65 to 513 splits of four sequences 9.8 (13.1).
 constexpr int kMergeFew = 32;
-__global__ __launch_bounds__(256) void attn_merge_few_kernel(AttnBatch batch) {
+template <class BATCH>
+__global__ __launch_bounds__(256) void attn_merge_few_kernel(BATCH batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z);
   const int rr = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), head = blockIdx.y, lane = threadIdx.x & 63;
   const int R = a.ncols * a.grp, n = a.nsplit;
@@ -162,12 +169,13 @@ __global__ __launch_bounds__(256) void attn_merge_few_kernel(AttnBatch batch) {
   out[1] = f32_to_bf16(num[0].y / den);
 }
 
-static int launch_merge(cas_ctx* ctx, const AttnBatch& b, int max_r, int max_split, int n) {
-  const int heads = b.common.g.n_kv_heads;
+template <class BATCH>
+static int launch_merge(cas_ctx* ctx, const BATCH& b, int max_r, int max_split, int n) {
+  const int heads = attn_common(b).g.n_kv_heads;
   if (max_split <= kMergeFew)
-    hipLaunchKernelGGL(attn_merge_few_kernel, dim3((max_r + 3) / 4, heads, n), dim3(256), 0, ctx->stream, b);
+    hipLaunchKernelGGL(attn_merge_few_kernel<BATCH>, dim3((max_r + 3) / 4, heads, n), dim3(256), 0, ctx->stream, b);
   else
-    hipLaunchKernelGGL(attn_merge_kernel, dim3(max_r, heads, 2 * n), dim3(512), 0, ctx->stream, b);
+    hipLaunchKernelGGL(attn_merge_kernel<BATCH>, dim3(max_r, heads, 2 * n), dim3(512), 0, ctx->stream, b);
   CAS_HIP(ctx, hipGetLastError());
   return CAS_OK;
 }
@@ -175,6 +183,46 @@ static int launch_merge(cas_ctx* ctx, const AttnBatch& b, int max_r, int max_spl
 static void set_group(AttnArgs& a, int grp) {
   a.grp = grp;
   a.grp_inv = grp > 0 ? (65536u + (uint32_t)grp - 1u) / (uint32_t)grp : 0u;
+}
+
+static int launch_partial(cas_ctx* ctx, const AttnBatch& b, int MT, int full, dim3 grid) {
+  if (b.common.g.mx) {
+    if (full)
+      return MT == 1   ? launch_mt<1, true, true>(ctx, b, grid)
+             : MT == 2 ? launch_mt<2, true, true>(ctx, b, grid)
+             : MT == 3 ? launch_mt<3, true, true>(ctx, b, grid)
+             : MT == 4 ? launch_mt<4, true, true>(ctx, b, grid)
+                       : launch_mt<5, true, true>(ctx, b, grid);
+    return MT == 1   ? launch_mt<1, false, true>(ctx, b, grid)
+           : MT == 2 ? launch_mt<2, false, true>(ctx, b, grid)
+                     : launch_mt<3, false, true>(ctx, b, grid);
+  }
+  if (full)
+    return MT == 1   ? launch_mt<1, true>(ctx, b, grid)
+           : MT == 2 ? launch_mt<2, true>(ctx, b, grid)
+           : MT == 3 ? launch_mt<3, true>(ctx, b, grid)
+           : MT == 4 ? launch_mt<4, true>(ctx, b, grid)
+                     : launch_mt<5, true>(ctx, b, grid);
+  return MT == 1   ? launch_mt<1, false>(ctx, b, grid)
+         : MT == 2 ? launch_mt<2, false>(ctx, b, grid)
+                   : launch_mt<3, false>(ctx, b, grid);
+}
+
+static void set_common(AttnArgs& a, const cas_kv* kv, const AttnCall& c) {
+  a.g = kv->geom;
+  a.spec_pool = (const uint32_t*)kv->d_spec;
+  a.verif_pool = (const uint32_t*)kv->d_verif;
+  a.layer = c.layer;
+  a.n_q_heads = c.n_q_heads;
+  set_group(a, c.n_q_heads / kv->geom.n_kv_heads);
+  a.ystride = c.ystride; a.rope = c.rope;
+  a.scale = 0.08838834764831845f;  // 1 / sqrt(128)
+  a.pages_per_split = kPagesPerSplit;  // fixed: a query's value must not depend on the length
+}
+
+// bytes of committed positions (bitmap + spec (+ lo + pruned) of K and V) and of plain bf16 in-flight ones
+static double attn_bytes(const KvGeom& g, int full, double len, double n_new) {
+  return 2.0 * g.n_kv_heads * (4.0 * (4 + g.mx + g.sw + (full ? g.lw + g.pw : 0)) * len + 256.0 * n_new);
 }
 
 // Up to kAttnBatch sequences of one pass in one pair of launches (same layer, same form, same
@@ -188,15 +236,7 @@ static int launch_attention_group(cas_ctx* ctx, cas_kv* kv, const AttnCall* call
   const AttnCall& c0 = calls[0];
   AttnBatch b{};
   AttnArgs& a = b.common;
-  a.g = g;
-  a.spec_pool = (const uint32_t*)kv->d_spec;
-  a.verif_pool = (const uint32_t*)kv->d_verif;
-  a.layer = c0.layer;
-  a.n_q_heads = c0.n_q_heads;
-  set_group(a, c0.n_q_heads / g.n_kv_heads);
-  a.ystride = c0.ystride; a.rope = c0.rope;
-  a.scale = 0.08838834764831845f;  // 1 / sqrt(128)
-  a.pages_per_split = kPagesPerSplit;  // fixed: a query's value must not depend on the length
+  set_common(a, kv, c0);
   int max_r = 0, max_split = 0;
   double bytes = 0.0;
   for (int i = 0; i < n; ++i) {
@@ -224,36 +264,13 @@ static int launch_attention_group(cas_ctx* ctx, cas_kv* kv, const AttnCall* call
     *ws_used += (need + 255) / 256 * 256;
     max_r = std::max(max_r, R);
     max_split = std::max(max_split, q.nsplit);
-    // committed positions: bitmap + spec (+ lo + pruned) of K and V; in-flight ones: plain bf16
-    const double per_tok = 4.0 * (4 + g.mx + g.sw + (c.full ? g.lw + g.pw : 0));
-    bytes += 2.0 * g.n_kv_heads * (per_tok * q.len + 256.0 * q.n_new);
+    bytes += attn_bytes(g, c.full, q.len, q.n_new);
   }
   const int MT = (max_r + 15) / 16;
-  dim3 grid(max_split, g.n_kv_heads, n);
   int rc;
   {
     ProfScope scope(prof ? ctx : nullptr, c0.full ? PROF_ATTN_VERIFY : PROF_ATTN_DRAFT, bytes);
-    if (g.mx) {
-      if (c0.full) {
-        rc = MT == 1   ? launch_mt<1, true, true>(ctx, b, grid)
-             : MT == 2 ? launch_mt<2, true, true>(ctx, b, grid)
-             : MT == 3 ? launch_mt<3, true, true>(ctx, b, grid)
-             : MT == 4 ? launch_mt<4, true, true>(ctx, b, grid)
-                       : launch_mt<5, true, true>(ctx, b, grid);
-      } else {
-        rc = MT == 1 ? launch_mt<1, false, true>(ctx, b, grid) : MT == 2 ? launch_mt<2, false, true>(ctx, b, grid)
-                                                                          : launch_mt<3, false, true>(ctx, b, grid);
-      }
-    } else if (c0.full) {
-      rc = MT == 1   ? launch_mt<1, true>(ctx, b, grid)
-           : MT == 2 ? launch_mt<2, true>(ctx, b, grid)
-           : MT == 3 ? launch_mt<3, true>(ctx, b, grid)
-           : MT == 4 ? launch_mt<4, true>(ctx, b, grid)
-                     : launch_mt<5, true>(ctx, b, grid);
-    } else {
-      rc = MT == 1 ? launch_mt<1, false>(ctx, b, grid) : MT == 2 ? launch_mt<2, false>(ctx, b, grid)
-                                                                  : launch_mt<3, false>(ctx, b, grid);
-    }
+    rc = launch_partial(ctx, b, MT, c0.full, dim3(max_split, g.n_kv_heads, n));
   }
   if (rc != CAS_OK) return rc;
   return launch_merge(ctx, b, max_r, max_split, n);
@@ -268,6 +285,56 @@ int launch_attention_batch(cas_ctx* ctx, cas_kv* kv, const AttnCall* calls, int 
     const int rc = launch_attention_group(ctx, kv, calls + i, std::min(kAttnBatch, n - i), ctx->d_ws, ctx->ws_bytes,
                                           &ws_used, true);
     if (rc != CAS_OK) return rc;
+  }
+  return CAS_OK;
+}
+
+// A call of c.ncols columns in runs of `run` columns, each as a call of its own whose c.len grows by the columns
+// before it.  One run of 16 columns leaves most of the chip idle (up to 8 pages x 8 heads for a prompt's first 512
+// positions), so as many run together as the workspace holds the partial results of: for 508 columns of the 8B shape
+// 37 + 8 us per layer in one launch of 32 runs, 8 x (13 + 4.6) in launches of four.
+int launch_attention_runs(cas_ctx* ctx, cas_kv* kv, const AttnCall& c, int run, void* ws, size_t ws_bytes) {
+  const KvGeom& g = kv->geom;
+  AttnRuns b{};
+  AttnArgs& a = b.first;
+  set_common(a, kv, c);
+  a.page_row = kv->d_page_table + (size_t)c.seq * g.max_pages_per_seq;
+  run = std::min(run, c.ncols);
+  const int max_r = run * a.grp;
+  if (run < 1 || run > kPT || !c.full || c.qkv || max_r > (g.mx ? 80 : 64) || c.len < 0) return CAS_EINVAL;
+  if ((c.len + c.ncols + kPT - 1) / kPT > g.max_pages_per_seq) return CAS_ENOMEM;
+  const size_t page_bytes = sizeof(float) * (size_t)c.n_q_heads * run * kPartStride;
+  b.run_cols = run;
+  a.part = (float*)ws;
+  for (int c0 = 0; c0 < c.ncols;) {
+    size_t pages = 0;
+    int n = 0, end = c0, split = 0;
+    double bytes = 0.0;
+    for (; n < kAttnRuns && end < c.ncols; ++n) {
+      const int cols = std::min(run, c.ncols - end), p = (c.len + end + cols + kPT - 1) / kPT;
+      if ((pages + p) * page_bytes > ws_bytes) break;
+      bytes += attn_bytes(g, 1, c.len + end, cols);
+      b.run_page[n] = (uint32_t)pages;
+      pages += p;
+      end += cols;
+      split = p;
+    }
+    if (n == 0) return CAS_ENOMEM;
+    b.cols = end - c0;
+    a.len = c.len + c0;
+    a.Q = c.Q + (size_t)c0 * c.n_q_heads * 128; a.O = c.O + (size_t)c0 * c.n_q_heads * 128;
+    a.Knew = c.Knew + (size_t)c0 * g.n_kv_heads * 128; a.Vnew = c.Vnew + (size_t)c0 * g.n_kv_heads * 128;
+    const dim3 grid(split, g.n_kv_heads, n);
+    int rc;
+    {
+      ProfScope scope(ctx, PROF_ATTN_VERIFY, bytes);
+      rc = !g.mx         ? launch_mt<4, true, false>(ctx, b, grid)
+           : max_r <= 64 ? launch_mt<4, true, true>(ctx, b, grid)
+                         : launch_mt<5, true, true>(ctx, b, grid);
+    }
+    if (rc == CAS_OK) rc = launch_merge(ctx, b, max_r, split, n);
+    if (rc != CAS_OK) return rc;
+    c0 = end;
   }
   return CAS_OK;
 }

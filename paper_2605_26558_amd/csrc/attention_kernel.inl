@@ -61,13 +61,37 @@ __device__ __forceinline__ AttnArgs attn_args_of(const AttnBatch& b, int z) {
   return a;
 }
 
+constexpr int kPartStride = 132;  // floats of workspace per (split, row): 128 outputs, maximum and sum, 2 to spare
+
+// The columns of one call in runs: blockIdx.z picks a run of run_cols of them (the last may be shorter), which reads
+// the positions before it from the cache; every pointer steps on by its columns.  A form of its own, since the steps
+// cost the decode pass up to 1.7 % (four sequences of the 8B shape, 9.10 -> 9.25 ms).
+constexpr int kAttnRuns = 32;
+struct AttnRuns {
+  AttnArgs first;  // the members of the first run
+  int run_cols, cols;
+  uint32_t run_page[kAttnRuns];  // pages of the runs before: where the run's partial results begin
+};
+__device__ __forceinline__ AttnArgs attn_args_of(const AttnRuns& b, int z) {
+  AttnArgs a = b.first;
+  const int c0 = z * b.run_cols;
+  const size_t qo = (size_t)c0 * a.n_q_heads * 128, ko = (size_t)c0 * a.g.n_kv_heads * 128;
+  a.len += c0;
+  a.ncols = a.n_new = min(b.run_cols, b.cols - c0);
+  a.nsplit = (a.len + a.ncols + 63) >> 6;
+  a.Q += qo; a.O += qo; a.Knew += ko; a.Vnew += ko;
+  a.part += (size_t)b.run_page[z] * a.n_q_heads * b.run_cols * kPartStride;
+  return a;
+}
+__host__ __device__ inline const AttnArgs& attn_common(const AttnBatch& b) { return b.common; }
+__host__ __device__ inline const AttnArgs& attn_common(const AttnRuns& b) { return b.first; }
+
 constexpr int kPT = 64;          // tokens per page
 constexpr int kQP = 136;         // Q row pitch (bf16)
 constexpr int kKG = 36, kKP = 148;  // K tile: group pitch (4 dump + 32), row pitch
 constexpr int kVP = 72;          // transposed V tile: token pitch per channel row
 constexpr int kVR = 132;         // channel rows: 4 groups x (1 dump + 32)
 constexpr int kPP = 72;          // probability row pitch (bf16)
-constexpr int kPartStride = 132; // floats of workspace per (split, row): 128 outputs, maximum and sum, 2 to spare
 constexpr int kPagesPerSplit = 1;
 constexpr int kMaxCols = 16;     // columns of one pass whose k, v may be split from the projection here
 
@@ -107,8 +131,8 @@ __device__ __forceinline__ float row16_sum(float v) {
 }
 
 // MX: the cache is in the shared-exponent form (one exponent per 32-channel block of a vector)
-template <int MT, bool FULL, int T, bool MX = false>
-__global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
+template <int MT, bool FULL, int T, bool MX, class BATCH>
+__global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z);
   if ((int)blockIdx.x >= a.nsplit) return;  // a shorter sequence of the launch: uniform for the workgroup
   extern __shared__ uint16_t lds16[];
@@ -420,17 +444,17 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnBatch batch) {
   }
 }
 
-template <int MT, bool FULL, bool MX = false>
-int launch_mt(cas_ctx* ctx, const AttnBatch& a, dim3 grid) {
+template <int MT, bool FULL, bool MX = false, class BATCH = AttnBatch>
+int launch_mt(cas_ctx* ctx, const BATCH& a, dim3 grid) {
   constexpr size_t lds = attn_lds_bytes<MT>();
 #define CAS_LAUNCH(TV)                                                                                     \
   case TV: {                                                                                               \
     static LdsLimit lim;                                                                                   \
-    const int rc = allow_lds(ctx, (const void*)attn_partial_kernel<MT, FULL, TV, MX>, lds, lim);               \
+    const int rc = allow_lds(ctx, (const void*)attn_partial_kernel<MT, FULL, TV, MX, BATCH>, lds, lim);               \
     if (rc != CAS_OK) return rc;                                                                           \
-    hipLaunchKernelGGL((attn_partial_kernel<MT, FULL, TV, MX>), grid, dim3(256), lds, ctx->stream, a);         \
+    hipLaunchKernelGGL((attn_partial_kernel<MT, FULL, TV, MX, BATCH>), grid, dim3(256), lds, ctx->stream, a);         \
   } break;
-  switch (a.common.g.t) {
+  switch (attn_common(a).g.t) {
     CAS_LAUNCH(0) CAS_LAUNCH(1) CAS_LAUNCH(2) CAS_LAUNCH(3) CAS_LAUNCH(4) CAS_LAUNCH(5) CAS_LAUNCH(6) CAS_LAUNCH(7)
     default: return CAS_EINVAL;
   }

@@ -134,6 +134,10 @@ int launch_attention_static(cas_ctx*, cas_kv*, const AttnCall&);
 size_t attention_static_capacity();
 // the same for the sequences of one pass (same layer and form), four of them per pair of launches
 int launch_attention_batch(cas_ctx*, cas_kv*, const AttnCall* calls, int n);
+// exact attention of any number of columns in runs of `run` columns that follow one another (c.len >= 0, n_new =
+// ncols, no split of the projection; at most 64 query rows of a run per kv head, 80 over shared exponents), with the
+// partial results in ws
+int launch_attention_runs(cas_ctx*, cas_kv*, const AttnCall& c, int run, void* ws, size_t ws_bytes);
 // plain bf16 attention of one decode step over an uncompressed cache (baseline for context figures)
 int launch_attention_dense(cas_ctx*, int n_kv_heads, int n_q_heads, uint16_t* Kc, uint16_t* Vc, int len,
                            const float* qkv, int ystride, const float* rope, uint16_t* O);

@@ -409,10 +409,10 @@ static ActLayout act_layout(const cas_model_cfg& c) {
 // The activations of a chunk do not fit the model's own block (max_cols <= 32 columns): they take the front
 // of the context's workspace, the rest of which holds the attention partials and the re-coded rows of a
 // unary matrix.  Layer by layer the linear layers see all columns at once (wide verification GEMM), the
-// chunk's keys and values are appended to the cache, and attention runs over runs of `sub` columns, each of
-// which reads the positions before it from the cache and its own uncompressed, exactly as a pass of `sub`
-// columns does.  A chunk therefore leaves the bits in the cache that such passes leave.
-// 8B-shaped, 4 layers, 508 tokens: 4.9 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
+// chunk's keys and values are appended to the cache, and attention runs over runs of some columns, each of
+// which reads the positions before it from the cache and its own uncompressed, exactly as a pass of
+// these columns does.  A chunk therefore leaves the bits in the cache that such passes leave.
+// 8B-shaped, 4 layers, 508 tokens: 4.2 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
 // and 31 unread rows of logits it saves).
 constexpr int kPrefillChunk = 512;
 // Fewer columns go through the passes.  A chunk and passes of 16 columns for the same prompt, one layer, us: 8B shape 49
@@ -421,7 +421,9 @@ constexpr int kPrefillChunk = 512;
 constexpr int kPrefillMin = 48;
 
 struct ChunkLayout {
-  size_t h, xn, y, q, ao, k, v, px, total;  // y: the fp32 projection, then the SwiGLU output; px: a layer's packed input
+  // y: the fp32 projection, then the SwiGLU output; px: a layer's packed input.  xn, y and px hold nothing that
+  // outlives the attention of a layer: they lie next to the rest of the workspace and take its partial results with it
+  size_t h, q, ao, k, v, xn, y, px, total;
 };
 
 static ChunkLayout chunk_layout(const cas_model_cfg& c, size_t n) {
@@ -429,20 +431,20 @@ static ChunkLayout chunk_layout(const cas_model_cfg& c, size_t n) {
   ChunkLayout L;
   size_t off = 0;
   L.h = carve(off, n * c.hidden * 2);
-  L.xn = carve(off, n * c.hidden * 2);
-  L.y = carve(off, n * std::max<size_t>((qd + 2 * kvd) * 4, (size_t)c.ffn * 2));
   L.q = carve(off, n * qd * 2);
   L.ao = carve(off, n * qd * 2);
   L.k = carve(off, n * kvd * 2);
   L.v = carve(off, n * kvd * 2);
+  L.xn = carve(off, n * c.hidden * 2);
+  L.y = carve(off, n * std::max<size_t>((qd + 2 * kvd) * 4, (size_t)c.ffn * 2));
   L.px = carve(off, gemm_wide_x_bytes(std::max<int64_t>({c.hidden, (int64_t)qd, c.ffn}), (int)n));
   L.total = off;
   return L;
 }
 
-// columns of one attention call inside a chunk: any number gives the same bits where the cache is lossless
+// columns of the shortest attention run inside a chunk that is not its last: any number gives the same bits where the cache is lossless
 static int chunk_sub(const cas_model* m, const cas_kv* kv) {
-  return kv->geom.mx ? seq_cols_max(m->cfg) : std::min(16, 80 / (m->cfg.n_q_heads / m->cfg.n_kv_heads));
+  return kv->geom.mx ? seq_cols_max(m->cfg) : std::min(16, 64 / (m->cfg.n_q_heads / m->cfg.n_kv_heads));
 }
 
 static size_t chunk_partials(const cas_model_cfg& c, int sub, int end) {  // of one attention call that ends at `end`
@@ -499,8 +501,12 @@ static int prefill_chunk(cas_ctx* ctx, cas_model* m, cas_kv* kv, int seq, const 
     if (!U.on) return launch_gemm_verify_fused(ctx, T.desc, T.d_spec, T.d_verif, px, n, Y, epi, out16, true);
     return launch_gemm_verify_unary_fused(ctx, U.u, U.d_uspec, T.d_verif, px, n, Y, epi, out16, true);
   };
-  const int sub = chunk_sub(m, kv), heads = c.n_q_heads + 2 * c.n_kv_heads;
-  const int together = (int)std::clamp<size_t>(ctx->ws_bytes / std::max<size_t>(1, chunk_partials(c, std::min(sub, n), len + n)), 1, 4);
+  const int heads = c.n_q_heads + 2 * c.n_kv_heads;
+  // a lossless cache leaves the length of a run free: 64 query rows per kv head (the shortest run of chunk_columns fits)
+  int run = std::min(chunk_sub(m, kv), n);
+  const size_t part_bytes = tail.bytes - (size_t)((char*)xn - (char*)tail.ws);
+  const int most = 64 / (c.n_q_heads / c.n_kv_heads);
+  if (!kv->geom.mx && chunk_partials(c, most, len + n) <= part_bytes) run = most;
   hipLaunchKernelGGL(embed_kernel, dim3(n), dim3(256), 0, st, d_tokens, m->d_embed, h, c.hidden, c.vocab);
   for (int l = 0; l < c.n_layers; ++l) {
     const cas_layer_weights& W = m->layers[l];
@@ -510,21 +516,13 @@ static int prefill_chunk(cas_ctx* ctx, cas_model* m, cas_kv* kv, int seq, const 
     hipLaunchKernelGGL(qkv_split_kernel, dim3(n, (heads + 3) / 4), dim3(256), 0, st, y, qd + 2 * kvd, m->d_rope, len,
                        c.n_q_heads, c.n_kv_heads, q, k, v);
     CAS_TRY(launch_kv_append(ctx, kv, l, seq, k, v, n, len));
-    for (int c0 = 0; c0 < n;) {
-      AttnCall calls[4];
-      int ng = 0;
-      for (; ng < together && c0 < n; ++ng) {
-        AttnCall& ac = calls[ng];
-        ac.layer = l; ac.seq = seq; ac.full = 1;
-        ac.len = len + c0;
-        ac.ncols = ac.n_new = std::min(sub, n - c0);
-        ac.n_q_heads = c.n_q_heads;
-        ac.Q = q + (size_t)c0 * qd; ac.Knew = k + (size_t)c0 * kvd; ac.Vnew = v + (size_t)c0 * kvd;
-        ac.O = ao + (size_t)c0 * qd;
-        c0 += ac.ncols;
-      }
-      CAS_TRY(launch_attention_batch(ctx, kv, calls, ng));
-    }
+    AttnCall ac;
+    ac.layer = l; ac.seq = seq; ac.full = 1;
+    ac.len = len;
+    ac.ncols = ac.n_new = n;
+    ac.n_q_heads = c.n_q_heads;
+    ac.Q = q; ac.Knew = k; ac.Vnew = v; ac.O = ao;
+    CAS_TRY(launch_attention_runs(ctx, kv, ac, run, xn, part_bytes));
     CAS_TRY(linear(W.wo, UL[1], ao, nullptr, 1, h));
     hipLaunchKernelGGL(rmsnorm_kernel, dim3(n), dim3(kNormThreads), 0, st, h, W.d_g_ffn, xn, c.hidden, c.rms_eps);
     CAS_TRY(linear(W.wgu, UL[2], xn, nullptr, 2, act));

@@ -161,6 +161,29 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
         assert torch.equal(narrow, wide)
 
 
+@pytest.mark.parametrize("ws", [4 << 20, 5 << 20, 6 << 20, 8 << 20])
+@pytest.mark.parametrize("shape,kv_form", [("a", "raw"), ("b", "shared")])
+def test_runs_of_a_prompt_in_one_launch_and_in_several(env, wide_models, shape, kv_form, ws):
+    """The workspace decides how many runs of columns attention takes together and how long the chunks and the runs
+    are: logits and cache are those of the workspace that holds everything at once."""
+    torch, B, _ = env
+    tokens = torch.from_numpy(synth.token_ids(521, 301, seed=4)).cuda()
+    big, model, kv = wide_models(shape, "raw" if kv_form == "raw" else "shared", kv_form, *((600, 4) if kv_form == "raw" else (400, 3)))[1]
+    small = B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda"))
+    got = []
+    for ctx in (big, small):
+        kv.spec_pool.zero_()
+        kv.verif_pool.zero_()
+        B.cas_kv_set_len(kv, 0, 0)
+        B.cas_prefill(ctx, model, kv, 0, tokens[:-1])
+        logits = torch.empty((1, 301), device="cuda")
+        B.cas_verify_step(ctx, model, kv, 0, tokens[-1:], 0, torch.empty(1, dtype=torch.int32, device="cuda"), logits)
+        torch.cuda.synchronize()
+        got.append((kv.spec_pool.clone(), kv.verif_pool.clone(), logits))
+    for one, several in zip(*got):
+        assert torch.equal(one, several)
+
+
 @pytest.mark.parametrize("rows,cols,keep", [(5, 1, 1000), (7, 31, 1000), (70, 33, 1000), (9, 64, 500), (1030, 4096, 600),
                                             (66, 5001, 333), (1030, 14336, 700)])
 @pytest.mark.parametrize("t", [0, 4, 7])
