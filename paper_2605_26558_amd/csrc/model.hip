@@ -442,7 +442,8 @@ static ChunkLayout chunk_layout(const cas_model_cfg& c, size_t n) {
   return L;
 }
 
-// columns of the shortest attention run inside a chunk that is not its last: any number gives the same bits where the cache is lossless
+// columns of the shortest attention run that a chunk is planned with: any number gives the same bits where the cache
+// is lossless
 static int chunk_sub(const cas_model* m, const cas_kv* kv) {
   return kv->geom.mx ? seq_cols_max(m->cfg) : std::min(16, 64 / (m->cfg.n_q_heads / m->cfg.n_kv_heads));
 }
