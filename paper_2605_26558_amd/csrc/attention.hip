@@ -40,8 +40,14 @@ extern template int launch_mt<1, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<2, false, true>(cas_ctx*, const AttnBatch&, dim3);
 extern template int launch_mt<3, false, true>(cas_ctx*, const AttnBatch&, dim3);
 
-// runs of columns (exact form): attention_runs.hip
+// runs of columns (exact form): attention_runs.hip, attention_mx_runs.hip
+extern template int launch_mt<1, true, false>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<2, true, false>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<3, true, false>(cas_ctx*, const AttnRuns&, dim3);
 extern template int launch_mt<4, true, false>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<1, true, true>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<2, true, true>(cas_ctx*, const AttnRuns&, dim3);
+extern template int launch_mt<3, true, true>(cas_ctx*, const AttnRuns&, dim3);
 extern template int launch_mt<4, true, true>(cas_ctx*, const AttnRuns&, dim3);
 extern template int launch_mt<5, true, true>(cas_ctx*, const AttnRuns&, dim3);
 
@@ -289,6 +295,22 @@ int launch_attention_batch(cas_ctx* ctx, cas_kv* kv, const AttnCall* calls, int 
   return CAS_OK;
 }
 
+// By the query rows of a run, as for a call of its own: a small group with shared exponents, or a workspace too small for
+// longer runs, has 16 rows in runs of 16 columns, and over 8000 positions of 32 kv heads products for 64 rows make the
+// attention of a prompt take 1.3 times as long (shared exponents) and 1.37 times (raw) as the calls do.
+static int launch_runs(cas_ctx* ctx, const AttnRuns& b, int MT, dim3 grid) {
+  if (b.first.g.mx)
+    return MT == 1   ? launch_mt<1, true, true>(ctx, b, grid)
+           : MT == 2 ? launch_mt<2, true, true>(ctx, b, grid)
+           : MT == 3 ? launch_mt<3, true, true>(ctx, b, grid)
+           : MT == 4 ? launch_mt<4, true, true>(ctx, b, grid)
+                     : launch_mt<5, true, true>(ctx, b, grid);
+  return MT == 1   ? launch_mt<1, true, false>(ctx, b, grid)
+         : MT == 2 ? launch_mt<2, true, false>(ctx, b, grid)
+         : MT == 3 ? launch_mt<3, true, false>(ctx, b, grid)
+                   : launch_mt<4, true, false>(ctx, b, grid);
+}
+
 // A call of c.ncols columns in runs of `run` columns, each as a call of its own whose c.len grows by the columns
 // before it.  One run of 16 columns leaves most of the chip idle (up to 8 pages x 8 heads for a prompt's first 512
 // positions), so as many run together as the workspace holds the partial results of: for 508 columns of the 8B shape
@@ -328,9 +350,7 @@ int launch_attention_runs(cas_ctx* ctx, cas_kv* kv, const AttnCall& c, int run, 
     int rc;
     {
       ProfScope scope(ctx, PROF_ATTN_VERIFY, bytes);
-      rc = !g.mx         ? launch_mt<4, true, false>(ctx, b, grid)
-           : max_r <= 64 ? launch_mt<4, true, true>(ctx, b, grid)
-                         : launch_mt<5, true, true>(ctx, b, grid);
+      rc = launch_runs(ctx, b, (max_r + 15) / 16, grid);
     }
     if (rc == CAS_OK) rc = launch_merge(ctx, b, max_r, split, n);
     if (rc != CAS_OK) return rc;

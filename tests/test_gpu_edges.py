@@ -184,6 +184,122 @@ def test_runs_of_a_prompt_in_one_launch_and_in_several(env, wide_models, shape, 
         assert torch.equal(one, several)
 
 
+def _prompt_model(env, n_q, n_kv, kv_form, ctx, positions, layers=1, ffn=520):
+    """A small model whose cache holds `positions` vectors that nothing computed, and room for 520 more."""
+    from types import SimpleNamespace
+    torch, B, _ = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(23)
+    bits = lambda x: x.to(torch.bfloat16).view(torch.int16)  # noqa: E731
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    hidden = 264
+    sh = SimpleNamespace(hidden=hidden, n_layers=layers, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, ffn=ffn, vocab=301,
+                         rms_eps=1e-5)
+    dims = (("wqkv", (n_q + 2 * n_kv) * 128, hidden), ("wo", hidden, n_q * 128), ("wgu", 2 * ffn, hidden), ("wd", hidden, ffn))
+    enc = lambda r, c: B.cas_encode_weight(ctx, bits(rnd(r, c) * c ** -0.5), 600, 4)  # noqa: E731
+    gain = lambda: bits(1 + 0.1 * rnd(hidden))  # noqa: E731
+    weights = [{**{n: enc(r, c) for n, r, c in dims}, "g_attn": gain(), "g_ffn": gain()} for _ in range(layers)]
+    rope = torch.from_numpy(synth.rope_table(positions + 640, 128, 500000.0)).cuda()
+    model = B.Model(ctx, sh, weights, enc(301, hidden), bits(rnd(301, hidden)), gain(), rope, max_cols=16)
+    pages = (positions + 520 + 63) // 64
+    kv = B.KVCache(ctx, layers, n_kv, n_pages=pages, max_seqs=1, max_pages_per_seq=pages,
+                   exp_mode=B.CAS_EXP_SHARED if kv_form == "shared" else B.CAS_EXP_RAW)
+    kv.spec_pool.zero_()
+    kv.verif_pool.zero_()
+    for layer in range(layers):
+        if positions:
+            B.cas_kv_append(ctx, kv, layer, 0, bits(rnd(positions, n_kv, 128)), bits(rnd(positions, n_kv, 128)))
+    return model, kv
+
+
+def _attention_of(env, ctx, call):
+    """(launches, milliseconds) of the exact attention of one call"""
+    _, B, _ = env
+    B.cas_prof_reset(ctx)
+    B.cas_prof_enable(ctx, True)
+    call()
+    launches, ms, _ = B.cas_prof_read(ctx, B.PROF_ATTN_VERIFY)
+    B.cas_prof_enable(ctx, False)
+    return launches, ms
+
+
+@pytest.mark.parametrize("kv_form,heads,ws", [("shared", 32, 256 << 20), ("raw", 32, 100 << 20)])
+def test_runs_of_few_query_rows_take_no_longer_than_calls_of_their_own(env, kv_form, heads, ws):
+    """One query head per kv head, and runs of 16 columns (shared exponents, or a workspace too small for runs of 64):
+    16 query rows.  The best of five timings of a prompt's attention against the same columns in cas_attention, 16 at a
+    time: 0.87 and 0.92 of it; 1.30 and 1.37 with products for 64 query rows.  The bound lies between."""
+    torch, B, _ = env
+    before, n = 8000, 256
+    ctx = B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda"))
+    model, kv = _prompt_model(env, heads, heads, kv_form, ctx, before)
+    tokens = torch.from_numpy(synth.token_ids(n, 301, seed=3)).cuda()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q, k, v = (torch.randn((16, heads, 128), device="cuda", generator=gen).to(torch.bfloat16).view(torch.int16) for _ in range(3))
+    out = torch.empty_like(q)
+
+    def prompt():
+        B.cas_kv_set_len(kv, 0, before)
+        B.cas_prefill(ctx, model, kv, 0, tokens)
+
+    def calls():
+        for c in range(0, n, 16):
+            B.cas_kv_set_len(kv, 0, before + c)
+            B.cas_attention(ctx, kv, 0, 0, True, q, k, v, out)
+
+    prompt()
+    calls()
+    runs = [_attention_of(env, ctx, prompt) for _ in range(5)]
+    own = min(_attention_of(env, ctx, calls)[1] for _ in range(5))
+    assert runs[0][0] < n // 16, "the prompt went through narrow passes"
+    ratio = min(ms for _, ms in runs) / own
+    print(f"runs / calls: {ratio:.3f} in {runs[0][0]} launches", flush=True)
+    assert ratio < 1.1
+
+
+@pytest.mark.parametrize("kv_form,n_q,n_kv", [("raw", 2, 2), ("raw", 4, 2), ("raw", 6, 2), ("raw", 8, 2), ("shared", 2, 2),
+                                              ("shared", 4, 2), ("shared", 6, 2), ("shared", 8, 2), ("shared", 10, 2)])
+@pytest.mark.parametrize("before,n", [(0, 203), (1930, 250)])
+def test_runs_of_every_group_size_leave_the_bits_of_narrow_passes(env, kv_form, n_q, n_kv, before, n):
+    """16 to 80 query rows in a run, with a workspace for runs of 64 rows and with one for runs of 16 columns, on few
+    pages and with the 32nd and 33rd page (where the merge changes its form) in one launch: logits and cache are those of
+    the same columns a pass at a time."""
+    torch, B, _ = env
+    tokens = torch.from_numpy(synth.token_ids(n + 1, 301, seed=4)).cuda()
+    big = B.Context(workspace=torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+    model, kv = _prompt_model(env, n_q, n_kv, kv_form, big, before, layers=2)
+    piece = min(16, 80 // (n_q // n_kv))  # a pass of its own: too short for a chunk
+
+    def once(ctx, step):
+        B.cas_kv_set_len(kv, 0, before)
+        for c in range(0, n, step):
+            B.cas_prefill(ctx, model, kv, 0, tokens[c:min(c + step, n)])
+
+    def result(ctx, step):
+        launches, _ = _attention_of(env, ctx, lambda: once(ctx, step))
+        logits = torch.empty((1, 301), device="cuda")
+        B.cas_verify_step(ctx, model, kv, 0, tokens[-1:], 0, torch.empty(1, dtype=torch.int32, device="cuda"), logits)
+        torch.cuda.synchronize()
+        return launches, (kv.spec_pool.clone(), kv.verif_pool.clone(), logits)
+
+    passes, want = result(big, piece)
+    assert passes == 2 * -(-n // piece) and bool(torch.isfinite(want[2]).all())
+    wide, got = result(big, n)
+    assert wide == 2
+    for x, y in zip(got, want):
+        assert torch.equal(x, y)
+    # the smallest workspace that takes a chunk has room for the partial results of the shortest runs only
+    for ws in range(1 << 19, 16 << 20, 1 << 17):
+        if ws < -(-(before + n) // 64) * n_q * piece * 132 * 4:
+            continue
+        short, got = result(B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda")), n)
+        for x, y in zip(got, want):
+            assert torch.equal(x, y)
+        if short < passes:
+            break
+    assert wide < short < passes
+
+
 @pytest.mark.parametrize("rows,cols,keep", [(5, 1, 1000), (7, 31, 1000), (70, 33, 1000), (9, 64, 500), (1030, 4096, 600),
                                             (66, 5001, 333), (1030, 14336, 700)])
 @pytest.mark.parametrize("t", [0, 4, 7])
