@@ -300,6 +300,42 @@ def test_runs_of_every_group_size_leave_the_bits_of_narrow_passes(env, kv_form, 
     assert wide < short < passes
 
 
+@pytest.mark.parametrize("piece", [16, 500])
+def test_rounding_to_bf16_of_every_exponent(env, piece):
+    """Ties, subnormals, numbers that round up to the next power or to infinity, NaNs with a payload in the low half
+    alone, of both signs: one column of the projection is 1, so the rotated key is the cosine of the rotary table, any
+    fp32 pattern, rounded.  In passes of 16 columns (split by the attention kernel) and in a chunk (by a kernel of
+    its own), against the oracle's rounding."""
+    from types import SimpleNamespace
+    torch, B, _ = env
+    low = [0, 1, 0x7FFF, 0x8000, 0x8001, 0xFFFF, 0x10000, 0x17FFF, 0x18000, 0x18001, 0x400000, 0x7F7FFF, 0x7F8000, 0x7FFFFF]
+    pat = np.array([s << 31 | e << 23 | m for e in range(256) for s in (0, 1) for m in low], dtype=np.uint32)
+    n = len(pat) // 64
+    cos = pat.view(np.float32).reshape(n, 64)
+    want = O.f64_to_bf16(cos)
+    hidden = 264
+    ctx = B.Context(workspace=torch.empty(16 << 20, dtype=torch.uint8, device="cuda"))
+    sh = SimpleNamespace(hidden=hidden, n_layers=1, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn=520, vocab=301, rms_eps=1e-5)
+    one = 0x3F80
+    zeros = lambda *s: torch.zeros(s, dtype=torch.int16, device="cuda")  # noqa: E731
+    ones = lambda *s: torch.full(s, one, dtype=torch.int16, device="cuda")  # noqa: E731
+    qkv = zeros(768, hidden)
+    qkv[256:512].view(2, 128, hidden)[:, :64, 0] = one  # keys: 1 in the lower half of the channels, 0 in the upper
+    enc = lambda w: B.cas_encode_weight(ctx, w, 600, 4)  # noqa: E731
+    layer = {"wqkv": enc(qkv), "wo": enc(zeros(hidden, 256)), "wgu": enc(zeros(1040, hidden)), "wd": enc(zeros(hidden, 520)),
+             "g_attn": ones(hidden), "g_ffn": ones(hidden)}
+    rope = torch.zeros((n, 64, 2), device="cuda")
+    rope[:, :, 0] = torch.from_numpy(pat.view(np.int32).reshape(n, 64)).cuda().view(torch.float32)
+    model = B.Model(ctx, sh, [layer], enc(zeros(301, hidden)), ones(301, hidden), ones(hidden), rope, max_cols=16)
+    kv = B.KVCache(ctx, 1, 2, n_pages=2, max_seqs=1, max_pages_per_seq=2)
+    tokens = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for c in range(0, n, piece):
+        B.cas_prefill(ctx, model, kv, 0, tokens[c:c + piece])
+    got = B.cas_kv_read(ctx, kv, 0, 0, 0, n, full=True)[0].cpu().numpy().view(np.uint16)
+    for head in (0, 1):
+        np.testing.assert_array_equal(got[:, head, :64], want)
+
+
 @pytest.mark.parametrize("rows,cols,keep", [(5, 1, 1000), (7, 31, 1000), (70, 33, 1000), (9, 64, 500), (1030, 4096, 600),
                                             (66, 5001, 333), (1030, 14336, 700)])
 @pytest.mark.parametrize("t", [0, 4, 7])

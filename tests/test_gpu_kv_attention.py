@@ -143,8 +143,8 @@ def test_attention_matches_oracle(env, len_cache, ncols, n_new, full):
 @pytest.mark.parametrize("length", [2047, 2048, 16383, 16384, 32767, 32768])
 def test_attention_merge_of_few_and_of_many_pages(env, length):
     """Partial results of 32 / 33, 256 / 257 and 512 / 513 pages, the ends of what a merge takes in one go, against
-    the oracle; next to another sequence, whose launch merges both in one form, gives the same
-    bits."""
+    the oracle; next to another sequence of the same launch the bits are the same (the two forms of the merge are
+    compared in the next test)."""
     torch, B, ctx = env
     nq, nkv = 4, 2
     kv = B.KVCache(ctx, 1, nkv, n_pages=1100, max_seqs=2, max_pages_per_seq=550)
@@ -161,6 +161,35 @@ def test_attention_merge_of_few_and_of_many_pages(env, length):
     assert (np.abs(O.bf16_to_f64(out) - reff) <= _attn_tol(Q, Kh, Vh, Kn, Vn, 1, nq, nkv, reff)).all()
     alone = [_host(B.cas_attention(ctx, kv, 0, seq, True, *args)) for seq in (0, 1)]
     both = B.cas_attention_multi(ctx, kv, 0, [0, 1], True, [args[0]] * 2, [args[1]] * 2, [args[2]] * 2)
+    for one, two in zip(alone, both):
+        np.testing.assert_array_equal(one, _host(two))
+
+
+@pytest.mark.parametrize("full,ncols", [(False, 1), (False, 9), (True, 1), (True, 9)])
+@pytest.mark.parametrize("pages", [2, 8, 9, 31, 32])
+def test_a_row_has_the_same_bits_from_the_merge_of_few_and_of_many_pages(env, pages, full, ncols):
+    """Up to 32 pages a call alone takes the merge for few pages; next to a sequence of 40 pages the other form combines
+    the same partial results.  The pages of a pair cancel (equal keys, opposite values) and what is left is 2^-12 of
+    them, so that the order of the additions shows in the outputs: from 9 pages on, adding the splits one after the
+    other, in parts of neighbours or in four parts instead of eight changes 3 to 6 % of them (in numpy)."""
+    torch, B, ctx = env
+    nq, nkv, length = 8, 2, 64 * pages - ncols
+    kv = B.KVCache(ctx, 1, nkv, n_pages=96, max_seqs=2, max_pages_per_seq=48)
+    K, V = synth.normal_bf16((length, nkv, 128), 1.0, seed=3), synth.normal_bf16((length, nkv, 128), 2.0 ** -12, seed=4)
+    for first in range(0, (pages - 1) // 2 * 128, 128):
+        K[first + 64:first + 128] = K[first:first + 64]
+        V[first:first + 64] = synth.normal_bf16((64, nkv, 128), 1.0, seed=5 + first)
+        V[first + 64:first + 128] = V[first:first + 64] ^ 0x8000
+    B.cas_kv_append(ctx, kv, 0, 0, _dev(torch, K), _dev(torch, V))
+    B.cas_kv_set_len(kv, 0, length)
+    other = synth.normal_bf16((40 * 64 - ncols, nkv, 128), 1.0, seed=6)
+    B.cas_kv_append(ctx, kv, 0, 1, _dev(torch, other), _dev(torch, other))
+    B.cas_kv_set_len(kv, 1, len(other))
+    args = [_dev(torch, x) for x in (synth.normal_bf16((ncols, nq, 128), 0.3, seed=7),
+                                     synth.normal_bf16((ncols, nkv, 128), 1.0, seed=8),
+                                     synth.normal_bf16((ncols, nkv, 128), 2.0 ** -12, seed=9))]
+    alone = [_host(B.cas_attention(ctx, kv, 0, seq, full, *args)) for seq in (0, 1)]
+    both = B.cas_attention_multi(ctx, kv, 0, [0, 1], full, [args[0]] * 2, [args[1]] * 2, [args[2]] * 2)
     for one, two in zip(alone, both):
         np.testing.assert_array_equal(one, _host(two))
 
