@@ -503,11 +503,22 @@ static int prefill_chunk(cas_ctx* ctx, cas_model* m, cas_kv* kv, int seq, const 
     return launch_gemm_verify_unary_fused(ctx, U.u, U.d_uspec, T.d_verif, px, n, Y, epi, out16, true);
   };
   const int heads = c.n_q_heads + 2 * c.n_kv_heads;
-  // a lossless cache leaves the length of a run free: 64 query rows per kv head (the shortest run of chunk_columns fits)
-  int run = std::min(chunk_sub(m, kv), n);
+  // A lossless cache leaves the length of a run free (the shortest run of chunk_columns fits).  Runs of up to 64 query rows
+  // decode a page for more columns (four times as many for a group of one, 21 for 16 columns for a group of three), but
+  // a workgroup takes longer: they are taken where they save more workgroups than three a CU, since a chip that is not
+  // full has nothing to save.  One layer, short / long, us, and the workgroups saved: 32 heads over 8000 positions 508
+  // tokens 1724 / 1236 (102 K), 8 heads over 4000 48 tokens 116 / 113 (1024), from an empty cache 300 tokens 146 / 149
+  // (560), 64 tokens of 2 heads 85.5 / 88 (6); groups of two, 16 kv heads, 508 tokens 402 / 395 (2048), 300 tokens 340 / 342
+  // (720); groups of three, 8 kv heads over 4000, 300 tokens 393 / 386 (2176), 128 tokens 225 / 229 (520).
   const size_t part_bytes = tail.bytes - (size_t)((char*)xn - (char*)tail.ws);
-  const int most = 64 / (c.n_q_heads / c.n_kv_heads);
-  if (!kv->geom.mx && chunk_partials(c, most, len + n) <= part_bytes) run = most;
+  int run = std::min(chunk_sub(m, kv), n);
+  if (!kv->geom.mx) {
+    const int most = 64 / (c.n_q_heads / c.n_kv_heads);
+    auto runs_of = [&](int cols) { return (n + cols - 1) / cols; };
+    const int64_t saved = (int64_t)(runs_of(run) - runs_of(most)) * ((len + n + 63) / 64) * c.n_kv_heads;
+    if (saved > 3 * ctx->num_cu && chunk_partials(c, most, len + n) <= part_bytes) run = most;
+    run = (n + runs_of(run) - 1) / runs_of(run);  // all of one length: a shorter last one would take as much of the workspace
+  }
   hipLaunchKernelGGL(embed_kernel, dim3(n), dim3(256), 0, st, d_tokens, m->d_embed, h, c.hidden, c.vocab);
   for (int l = 0; l < c.n_layers; ++l) {
     const cas_layer_weights& W = m->layers[l];

@@ -257,16 +257,32 @@ def test_runs_of_few_query_rows_take_no_longer_than_calls_of_their_own(env, kv_f
     assert ratio < 1.1
 
 
+@pytest.mark.parametrize("n_q,n,columns", [(6, 64, 72), (4, 48, 56), (2, 130, 140), (8, 64, 72)])
+def test_runs_waste_no_workspace(env, n_q, n, columns):
+    """A workspace for the partial results of a few columns more than the prompt has takes them in one launch: runs of
+    one length, and no longer ones that only a part of them would fit (groups of 3, 2, 1 and 4 query heads)."""
+    torch, B, _ = env
+    before, n_kv, hidden = 1930, 2, 264
+    pages = -(-(before + n) // 64)
+    front = n * 2 * (hidden + 2 * n_q * 128 + 2 * n_kv * 128) + 8 * 256  # what outlives attention, with its alignment
+    ctx = B.Context(workspace=torch.empty(front + pages * n_q * columns * 132 * 4, dtype=torch.uint8, device="cuda"))
+    model, kv = _prompt_model(env, n_q, n_kv, "raw", ctx, before)
+    B.cas_kv_set_len(kv, 0, before)
+    tokens = torch.from_numpy(synth.token_ids(n, 301, seed=3)).cuda()
+    launches, _ = _attention_of(env, ctx, lambda: B.cas_prefill(ctx, model, kv, 0, tokens))
+    assert launches == 1
+
+
 @pytest.mark.parametrize("kv_form,n_q,n_kv", [("raw", 2, 2), ("raw", 4, 2), ("raw", 6, 2), ("raw", 8, 2), ("shared", 2, 2),
                                               ("shared", 4, 2), ("shared", 6, 2), ("shared", 8, 2), ("shared", 10, 2)])
-@pytest.mark.parametrize("before,n", [(0, 203), (1930, 250)])
+@pytest.mark.parametrize("before,n", [(0, 203), (1930, 490)])
 def test_runs_of_every_group_size_leave_the_bits_of_narrow_passes(env, kv_form, n_q, n_kv, before, n):
-    """16 to 80 query rows in a run, with a workspace for runs of 64 rows and with one for runs of 16 columns, on few
-    pages and with the 32nd and 33rd page (where the merge changes its form) in one launch: logits and cache are those of
-    the same columns a pass at a time."""
+    """16 to 80 query rows in a run (the longer prompt has 64 for the groups of one and two), with a workspace for all of
+    them at once and with a small one, on few pages and with the 32nd and 33rd page (where the merge changes its form) in
+    one launch: logits and cache are those of the same columns a pass at a time."""
     torch, B, _ = env
     tokens = torch.from_numpy(synth.token_ids(n + 1, 301, seed=4)).cuda()
-    big = B.Context(workspace=torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+    big = B.Context(workspace=torch.empty(160 << 20, dtype=torch.uint8, device="cuda"))
     model, kv = _prompt_model(env, n_q, n_kv, kv_form, big, before, layers=2)
     piece = min(16, 80 // (n_q // n_kv))  # a pass of its own: too short for a chunk
 
