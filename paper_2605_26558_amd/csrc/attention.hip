@@ -52,9 +52,10 @@ extern template int launch_mt<4, true, true>(cas_ctx*, const AttnRuns&, dim3);
 extern template int launch_mt<5, true, true>(cas_ctx*, const AttnRuns&, dim3);
 
 // Combine the splits: o = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, rounded to bf16.  Splits p, p + 8, ... are
-// added one after the other in each of eight parts p, then the parts in order; the denominator adds blocks of 64
-// splits, each in the order of wave_sum.  These orders are fixed: the result depends neither on timing, nor on how
-// many rows ride along, nor on which of the two kernels below combines a row.
+// added one after the other in each of eight parts p, then the parts in order.  The denominator: lane i of part p adds
+// splits 64 p + i, 64 p + i + 512, ..., the lanes of a part are added in the order of wave_sum, then the parts in order.
+// These orders are fixed: the result depends neither on timing, nor on how many rows ride along, nor on which of the
+// two kernels below combines a row.
 constexpr int kMergeParts = 8;
 
 __device__ __forceinline__ float split_weight(float m, float M) { return m == -INFINITY ? 0.f : __expf(m - M); }
@@ -135,6 +136,9 @@ __global__ __launch_bounds__(512, 4) void attn_merge_kernel(BATCH batch) {
 // 2.8 us for 3.5 of the other, with up to 8 splits of 64 rows of four sequences 4.6 us for 10.7.  One wave's loads
 // reach to 32 splits; from there on the other form, whose eight waves share them: 129 splits 4.8 us (4.9 with the
 // pairs behind each output, LDS weights and a barrier more), 65 to 513 splits of four sequences 9.8 (13.1).
+// A whole attention call of the 8B heads with this form / the other, us: 1 column over 8 pages 8.5 / 9.3, 16 pages 8.8 /
+// 9.3, 24 pages 9.0 / 9.4, 32 pages 9.4 / 9.4; 5 columns 11.0 / 12.7, 11.3 / 12.9, 11.8 / 13.2, 12.3 / 13.4; 9 columns
+// 12.1 / 14.8, 12.6 / 15.4, 13.7 / 15.8, 14.6 / 16.3.  4 query and 2 kv heads over 32 pages: 9.2 / 9.1 and 10.6 / 10.5.
 constexpr int kMergeFew = 32;
 template <class BATCH>
 __global__ __launch_bounds__(256) void attn_merge_few_kernel(BATCH batch) {
@@ -314,7 +318,7 @@ static int launch_runs(cas_ctx* ctx, const AttnRuns& b, int MT, dim3 grid) {
 // A call of c.ncols columns in runs of `run` columns, each as a call of its own whose c.len grows by the columns
 // before it.  One run of 16 columns leaves most of the chip idle (up to 8 pages x 8 heads for a prompt's first 512
 // positions), so as many run together as the workspace holds the partial results of: for 508 columns of the 8B shape
-// 37 + 8 us per layer in one launch of 32 runs, 8 x (13 + 4.6) in launches of four.
+// 38 + 11 us per layer (both kernels) in one launch of 32 runs, 8 x (16 + 11) in launches of four.
 int launch_attention_runs(cas_ctx* ctx, cas_kv* kv, const AttnCall& c, int run, void* ws, size_t ws_bytes) {
   const KvGeom& g = kv->geom;
   AttnRuns b{};
