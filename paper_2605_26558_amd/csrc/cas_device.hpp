@@ -174,6 +174,23 @@ __device__ __forceinline__ uint32_t mx_word(uint32_t sign, int E, uint32_t mag) 
   return (mag >= special ? 0x7F00u + mag : f) | (sign << 15);
 }
 
+// N consecutive words at byte offset `off` of a buffer, in the widest loads
+template <int N>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, int off, uint32_t* d) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int q = 0; q + 4 <= N; q += 4) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * q, 0, 0);
+    d[q] = v.x; d[q + 1] = v.y; d[q + 2] = v.z; d[q + 3] = v.w;
+  }
+  if constexpr ((N & 2) != 0) {
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 4 * (N & ~3), 0, 0);
+    d[N & ~3] = v.x; d[(N & ~3) + 1] = v.y;
+  }
+  if constexpr ((N & 1) != 0) d[N - 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * (N - 1), 0, 0);
+}
+
 // Raw windows of the packed streams at one 32-column bitmap word, before alignment: the words
 // that hold the word's kept fields (spec) and their dropped bits (lo) in KeptWindows, those of
 // its pruned values in PrunedWindows.  Loading and decoding are separate so the loads of the
@@ -210,6 +227,21 @@ struct KeptWindows {
       const uint32_t* src = lo_row + (bit >> 5);
 #pragma unroll
       for (int q = 0; q <= T; ++q) dl[q] = src[q];
+    }
+  }
+
+  // the same through buffer descriptors of the streams; row_s, row_l: bytes before the row
+  __device__ __forceinline__ void load(uint32_t p, __amdgpu_buffer_rsrc_t rs, int row_s, __amdgpu_buffer_rsrc_t rl,
+                                       int row_l) {
+    {
+      const uint32_t bit = p * FW;
+      shs = bit & 31u;
+      load_words<FW + 1>(rs, row_s + (int)(bit >> 5) * 4, ds);
+    }
+    if constexpr (FULL && T > 0) {
+      const uint32_t bit = p * T;
+      shl = bit & 31u;
+      load_words<T + 1>(rl, row_l + (int)(bit >> 5) * 4, dl);
     }
   }
 
@@ -268,6 +300,11 @@ struct PrunedWindows {
     const uint32_t* src = pr_row + (u >> 1);
 #pragma unroll
     for (int q = 0; q <= 16; ++q) dp[q] = src[q];
+  }
+
+  __device__ __forceinline__ void load(uint32_t u, __amdgpu_buffer_rsrc_t rp, int row_p) {
+    shp = (u & 1u) << 4;
+    load_words<17>(rp, row_p + (int)(u >> 1) * 4, dp);
   }
 
   // pm: mask of the word's unselected columns

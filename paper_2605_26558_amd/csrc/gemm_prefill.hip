@@ -4,32 +4,28 @@
 namespace cas {
 
 // X [ncols][cols] into the order in which the product reads it: per 16 columns and 32 values of k a run of
-// 64 lanes, lane (mi, mq) holding k = 4 mq ..+3 and 16 + 4 mq ..+3 of column mi.  Columns past ncols and k past
+// 64 lanes, lane (mi, mq) holding k = 8 mq ..+7 of column mi.  Columns past ncols and k past
 // cols are 0.  Read in place, the 16 rows of X that a fragment touches lay a power of two apart (8 KB at
 // cols = 4096) and met in the same sets of the caches: the whole prompt
 // of 508 tokens through 4 layers of the 8B shape took 7.7 ms instead of 5.3.
 __global__ __launch_bounds__(256) void pack_x_kernel(const uint16_t* __restrict__ X, int ncols, int cols, int nk,
                                                      uint4* __restrict__ out) {
   const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int n16 = wave / nk, k0 = (wave - n16 * nk) * 32 + 4 * (lane >> 4), n = n16 * 16 + (lane & 15);
+  const int n16 = wave / nk, k = (wave - n16 * nk) * 32 + 8 * (lane >> 4), n = n16 * 16 + (lane & 15);
   if (n16 * 16 >= ncols) return;
-  uint2 v[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int k = k0 + 16 * h;
-    v[h] = make_uint2(0, 0);
-    if (n >= ncols) continue;
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (n < ncols) {
     const uint16_t* src = X + (size_t)n * cols + k;
-    if (k + 4 <= cols) {
-      __builtin_memcpy(&v[h], src, 8);
+    if (k + 8 <= cols) {
+      __builtin_memcpy(&v, src, 16);
     } else {
-      uint16_t e[4];
+      uint16_t e[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = k + i < cols ? src[i] : (uint16_t)0;
-      __builtin_memcpy(&v[h], e, 8);
+      for (int i = 0; i < 8; ++i) e[i] = k + i < cols ? src[i] : (uint16_t)0;
+      __builtin_memcpy(&v, e, 16);
     }
   }
-  out[(size_t)wave * 64 + lane] = make_uint4(v[0].x, v[0].y, v[1].x, v[1].y);
+  out[(size_t)wave * 64 + lane] = v;
 }
 
 int launch_gemm_prefill(cas_ctx* ctx, const VerifyArgs& a, int t) { return launch_wide<false>(ctx, a, t); }

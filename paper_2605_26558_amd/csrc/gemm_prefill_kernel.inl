@@ -9,8 +9,6 @@
 
 namespace cas {
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kWideThreads = 512;
 constexpr int kWideCols = 256;  // columns of X per workgroup
 
@@ -19,8 +17,8 @@ constexpr int kWideCols = 256;  // columns of X per workgroup
 // with its own columns n and n + 128 of X, which it reads from memory (no other wave of the workgroup needs
 // them).  Two tiles: while one is multiplied the next one is filled, with one barrier per step; the waves
 // w and w + 4, which share a SIMD, take the two halves of a step in opposite order, so that the decode of
-// the one runs under the matrix operations of the other.  Blocks come in the order (part, slab, block of
-// the part), which makes a part one running sum; the counts of kept values in front of every block of
+// the one runs under the matrix operations of the other.  Blocks come part by part (part p of
+// Q has the blocks p, p + Q, ...), which makes a part one running sum; the counts of kept values in front of every block of
 // every row are made at the start (pre).
 // Bound by waiting, not by one unit.  Counters of 28672 x 4096 with 508 columns (370 us): of the 703 K cycles
 // that a CU is busy, the matrix operations (8 K flops in 16 cycles) take 229 K on each SIMD and the other
@@ -39,9 +37,9 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ncb = (a.ncols + kWideCols - 1) / kWideCols;
   const int cb0 = (int)(blockIdx.x % ncb) * kWideCols, row0 = (int)(blockIdx.x / ncb) * ROWS;
-  const int nblk = (a.bw + 3) >> 2, nslab = (a.bw + 63) >> 6;
-  const int wpl = 16 / Q, per_part = nslab * wpl;  // blocks per part and slab, blocks per part
-  const int nsteps = nslab * 16 / KB;
+  const int nblk = (a.bw + 3) >> 2;
+  const int per_part = (nblk + Q - 1) / Q;  // blocks of a part: part p has the blocks p, p + Q, ...
+  const int nsteps = (Q * per_part + KB - 1) / KB;
 
   // ---- kept values in front of every block
   {
@@ -67,12 +65,12 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
     __syncthreads();
   }
 
-  // first bitmap word of block b in the order of the sums
-  // (wpl is a power of two; x / nslab by multiplication: x < 16 nslab, nslab <= 32)
-  const int wsh = __builtin_ctz(wpl), inv_nslab = (65536 + nslab - 1) / nslab;
+  // first bitmap word of block b in the order of the sums (b / per_part by multiplication: b per_part <= 2^16
+  // for every b before the last step's end); blocks past the end of the rows lie past their words
+  const int inv_per = (65536 + per_part - 1) / per_part;
   auto block_word = [&](int b) -> int {
-    const int x = b >> wsh, part = x * inv_nslab >> 16, slab = x - part * nslab;
-    return slab * 64 + part * (64 / Q) + 4 * (b & (wpl - 1));
+    const int part = b * inv_per >> 16;
+    return 4 * ((b - part * per_part) * Q + part);
   };
 
   // ---- decode role: row r of the tile, block qb of the step (the same for a whole wave), word j of the block
@@ -169,13 +167,13 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
         }
       }
       if (block_word(b) >= a.bw) return;  // past the end of the rows
-      const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 4 * mq;
+      const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 8 * mq;
       auto block = [&](auto NB) {
         bf16x4 av[2][RT];  // fragments of the rows, one product ahead
         auto load_a = [&](int kk, bf16x4 (&f)[RT]) {
 #pragma unroll
           for (int i = 0; i < RT; ++i)
-            f[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + (kk >> 1) * kGroupPitch + (kk & 1) * 16);
+            f[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + (kk >> 1) * kGroupPitch + (kk & 1) * 4);
         };
         load_a(0, av[0]);
 #pragma unroll
@@ -285,8 +283,7 @@ static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
 // 2461, 513 tokens 4547 / 5013 / 4799.
 template <bool MX>
 static int launch_wide(cas_ctx* ctx, const VerifyArgs& a, int t) {
-  const int groups = (a.yld + 15) / 16;
-  const int q = groups >= kFewGroups ? 4 : a.cols >= 4 * kSlabCols ? 16 : 8;
+  const int q = verify_parts(a.yld, a.cols);
   const int64_t wgs = (int64_t)((a.rows + 63) / 64) * ((a.ncols + kWideCols - 1) / kWideCols);
   if (wgs * 3 < (int64_t)ctx->num_cu * 2) return launch_wide_rt<2, MX>(ctx, a, t, q);
   return launch_wide_rt<4, MX>(ctx, a, t, q);

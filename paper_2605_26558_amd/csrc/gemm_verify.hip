@@ -2,17 +2,15 @@
 // inside the kernel (Sec. 4.1 target inference, Sec. 5.1 mantissa concatenation and bitmap
 // de-sparsification) and X holding the k+1 columns of one verification pass (Sec. 2.2).
 //
-// Mapping.  A workgroup of four waves owns 16 output rows and walks the columns in slabs of
-// 2048; wave w takes the w-th 512-column quarter of every slab.  Inside a quarter lane (r, j)
-// owns bitmap words 4j..4j+3 of row r (128 consecutive columns), so its kept fields, dropped
-// mantissa bits and pruned words are contiguous runs of the three streams.  For each of its
-// four words the lane walks the set bits (kept: leading bits from spec, low bits from lo) and
-// then the clear bits (pruned: verbatim word) and scatters the bf16 values into a 16 x 128
-// tile in LDS.  The tile is then multiplied with the matching 128 rows of X by eight
-// 16x16x16 bf16 MFMA operations, accumulating in fp32.  Every wave stages the X columns of
-// its own part of the slab into its own LDS region, so waves never wait for each other inside
-// the column loop.  Each output column uses the same
-// sequence of operations whatever the number of columns is.  The four partial tiles of a
+// Mapping.  A workgroup of four waves (more for matrices of few rows) owns 16 output rows and walks
+// the columns in steps of 128 per wave.  In a step a wave decodes four rows of the step's 512 columns:
+// lane (r, j) owns bitmap word j of row r, so its kept fields, dropped mantissa bits and pruned words
+// are contiguous runs of the three streams.  The lane walks the set bits of its word (kept: leading
+// bits from spec, low bits from lo) and then the clear bits (pruned: verbatim word) and scatters the
+// bf16 values into a tile in LDS that the waves share.  After a barrier each wave multiplies the 16
+// rows of its own 128 columns with the matching part of X by eight 16x16x16 bf16 MFMA operations,
+// accumulating in fp32, while the next step's values go to a second tile.  Each output column uses
+// the same sequence of operations whatever the number of columns is.  The four partial tiles of a
 // workgroup are added in wave order through LDS.
 #include "gemm_verify_kernel.inl"
 
@@ -25,8 +23,8 @@ int launch_gemm_verify(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const
 
 static int launch_verify_args(cas_ctx* ctx, const VerifyArgs& a, int t, bool wide) {
   if (wide) return launch_gemm_prefill(ctx, a, t);
-  if (a.ncols > 8) return launch_gemm_verify_wide(ctx, a, t);
-  return verify_narrow<false>(ctx, a, t);
+  if (a.ncols > 16) return launch_gemm_verify_wide(ctx, a, t);
+  return launch_verify<1, false>(ctx, a, t);
 }
 
 int launch_gemm_verify_fused(cas_ctx* ctx, const cas_wdesc& d, const void* spec, const void* verif,

@@ -27,8 +27,8 @@ int launch_gemm_verify_mx_fused(cas_ctx* ctx, const cas_mxdesc& x, const void* m
   a.X = X; a.Y = Y; a.yld = (int)d.rows;
   ProfScope prof(ctx, PROF_GEMM_VERIFY, 4.0 * (double)d.rows * (d.bw + x.fw + d.lw + d.pw) + (double)d.rows * x.ew);
   if (wide) return launch_gemm_prefill_mx(ctx, a, d.t);
-  if (ncols > 8) return verify_wide<true>(ctx, a, d.t);
-  return verify_narrow<true>(ctx, a, d.t);
+  if (ncols > 16) return launch_verify<2, true>(ctx, a, d.t);
+  return launch_verify<1, true>(ctx, a, d.t);
 }
 
 }  // namespace cas

@@ -4,6 +4,6 @@
 
 namespace cas {
 
-int launch_gemm_verify_wide(cas_ctx* ctx, const VerifyArgs& a, int t) { return verify_wide<false>(ctx, a, t); }
+int launch_gemm_verify_wide(cas_ctx* ctx, const VerifyArgs& a, int t) { return launch_verify<2, false>(ctx, a, t); }
 
 }  // namespace cas

@@ -334,3 +334,30 @@ def test_draft_gemv_rows_do_not_see_their_neighbours(env, cols, keep, t):
     wn = np.linalg.norm(O.bf16_to_f64(W[good]), axis=1) * np.linalg.norm(O.bf16_to_f64(X[0]))
     assert (np.abs(y[good] - ref[good]) <= 2e-5 * wn).all()
     assert not np.isfinite(y[1::3]).any() and np.isnan(y[2::3]).all()
+
+
+@pytest.mark.parametrize("rows,cols", [(4803, 131), (4800, 640), (40, 7), (40, 129), (40, 1026), (33, 8199), (16, 8192 + 136)])
+@pytest.mark.parametrize("ncols", [1, 5, 17, 32])
+def test_verification_gemm_at_the_ends_of_x(rows, cols, ncols):
+    """Rows cut into 4, 8 and 16 parts, row lengths around words, pieces of 8 and blocks of 128, X from an aligned
+    address and from the middle of a word: the reference's products, the same bits from both addresses, and nothing of
+    a column's neighbours (its last pieces are read across its end; the neighbour is set to NaN)."""
+    import torch
+    from paper_2605_26558_amd import binding as B
+    ctx = B.Context()
+    W = synth.weight_matrix(rows, cols, seed=rows + cols)
+    X = synth.activations(cols, ncols, seed=cols + ncols)
+    ew = B.cas_encode_weight(ctx, torch.from_numpy(W.view(np.int16)).cuda(), 600, 4)
+    xd = torch.from_numpy(X.view(np.int16)).cuda()
+    y = B.cas_gemm_verify(ctx, ew, xd).cpu().numpy()
+    w64, x64 = O.bf16_to_f64(W), O.bf16_to_f64(X)
+    bar = 2e-5 * np.linalg.norm(w64, axis=1)[None, :] * np.linalg.norm(x64, axis=1)[:, None] + 1e-30
+    assert (np.abs(y - x64 @ w64.T) <= bar).all()
+    buf = torch.full((ncols * cols + 1,), 0x7FC0, dtype=torch.int16, device="cuda")
+    buf[1:] = xd.reshape(-1)
+    np.testing.assert_array_equal(B.cas_gemm_verify(ctx, ew, buf[1:].view(ncols, cols)).cpu().numpy(), y)
+    if ncols > 1:
+        for c in (0, ncols - 1):
+            xn = xd.clone()
+            xn[[k for k in range(ncols) if k != c]] = 0x7FC0
+            np.testing.assert_array_equal(B.cas_gemm_verify(ctx, ew, xn).cpu().numpy()[c], y[c])
