@@ -31,7 +31,7 @@ template <int T, int RT, bool MX>
 __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a, int Q) {
   constexpr int ROWS = 16 * RT, KB = 128 / ROWS;
   static_assert(KB == 2 || KB == 4, "the fragments of X alternate between two sets");
-  constexpr int TILE = KB * ROWS * kTilePitch;  // values of one tile: [block][row][kTilePitch]
+  constexpr int TILE = KB * RT * kBlockVals;  // values of one tile: blocks of 16 rows x 128 columns
   extern __shared__ uint16_t lds[];
   uint16_t* pre = lds + 2 * TILE;  // [ROWS][nblk] kept values of the row before each block of 128 columns
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
   const uint32_t* sp_row = a.spec + (size_t)row * a.sw;
   const uint32_t* lo_row = a.lo + (size_t)row * a.lw;
   const uint32_t* pr_row = a.pruned + (size_t)row * a.pw;
-  uint16_t* const trow = lds + (qb * ROWS + r) * kTilePitch + j * kGroupPitch + 4;
+  uint16_t* const trow = lds + (qb * RT + (r >> 4)) * kBlockVals + kPosPitch + (r & 15) * 4 + j;
   WordWindows<T, true, MX> ww;
   uint32_t m_next = 0, m_cur = 0;
   int e_next = 0, e_cur = 0, nvalid = 0;
@@ -109,9 +109,9 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
     const uint32_t valid = nvalid >= 32 ? 0xFFFFFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
     if (nvalid < 32) {  // columns past the end are not placed below
 #pragma unroll
-      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(dst + 4 * q) = 0ull;
+      for (int q = 0; q < 32; ++q) dst[q * kPosPitch] = 0;
     }
-    ww.decode(m_cur, ~m_cur & valid, [&](int pos, uint16_t v) { dst[pos] = v; }, MX ? e_cur : 0);
+    ww.decode(m_cur, ~m_cur & valid, [&](int pos, uint16_t v) { dst[pos * kPosPitch] = v; }, MX ? e_cur : 0);
     issue(st + 1);
     load_mask(st + 2);
   };
@@ -167,13 +167,14 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
         }
       }
       if (block_word(b) >= a.bw) return;  // past the end of the rows
-      const uint16_t* at = lds + (st & 1) * TILE + (jb * ROWS + mi) * kTilePitch + 4 + 8 * mq;
+      const uint16_t* const a_even = lds + (st & 1) * TILE + jb * RT * kBlockVals + (1 + 8 * mq + (mq & 1)) * kPosPitch + mi * 4;
+      const uint16_t* const a_odd = a_even - 2 * (mq & 1) * kPosPitch;
       auto block = [&](auto NB) {
         bf16x4 av[2][RT];  // fragments of the rows, one product ahead
         auto load_a = [&](int kk, bf16x4 (&f)[RT]) {
 #pragma unroll
           for (int i = 0; i < RT; ++i)
-            f[i] = *reinterpret_cast<const bf16x4*>(at + i * 16 * kTilePitch + (kk >> 1) * kGroupPitch + (kk & 1) * 4);
+            f[i] = *reinterpret_cast<const bf16x4*>((kk & 1 ? a_odd : a_even) + i * kBlockVals + kk * kPosPitch);
         };
         load_a(0, av[0]);
 #pragma unroll
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
 
 template <int RT>
 static size_t wide_lds_bytes(int bw) {
-  return sizeof(uint16_t) * (2 * (size_t)128 * kTilePitch + (size_t)16 * RT * ((bw + 3) / 4));
+  return sizeof(uint16_t) * (2 * (size_t)8 * kBlockVals + (size_t)16 * RT * ((bw + 3) / 4));
 }
 
 // Whether the wide form takes a matrix of this shape: counts of kept values in 16 bits, the LDS.

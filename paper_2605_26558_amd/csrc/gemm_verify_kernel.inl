@@ -30,8 +30,15 @@ struct VerifyArgs {
 constexpr int kFewGroups = 300;          // row groups below which a matrix gets more waves per row group
 constexpr int kLongRow = 8192;           // columns from which it then gets sixteen
 constexpr int kNowhere = 0x7FFFF000;     // a byte offset past the records of every stream: reads as 0, fetches nothing
-constexpr int kGroupPitch = 36;          // 4 dump slots + 32 columns
-constexpr int kTilePitch = 148;          // 4 groups + 4 pad, keeps 8-byte alignment, spreads banks
+// A block of 16 rows x 128 columns in LDS: [1 + 32 positions][16 rows][4 words] values, position p of the four bitmap
+// words of a row side by side (row 0 takes what lanes without a value left write).  Whatever positions the lanes of a
+// wave are at, at most the two lanes that share a word of their position's row meet in a bank: with a row's values in
+// column order the writes of the walks met in banks for 73 % of the cycles in which the LDS was active, and it was
+// active for 79 % of the kernel's (28672 x 4096, 7 columns).  The four values that lie together are one lane's operand
+// of a product; product kk takes position 8 mq + (kk ^ (mq & 1)) in lane group mq, so that the reads of two groups
+// go to either half of the banks.
+constexpr int kPosPitch = 64;
+constexpr int kBlockVals = 33 * kPosPitch;
 
 // A workgroup of Q waves owns 16 output rows and takes 128 Q columns per step.  Decode: wave w places the values of
 // 16 / Q rows in a tile in LDS, a lane 32 columns of one row, so that a wave reads runs of 128 Q columns of each stream
@@ -39,23 +46,25 @@ constexpr int kTilePitch = 148;          // 4 groups + 4 pad, keeps 8-byte align
 // multiplies all 16 rows of its own block of 128 columns (part w of a row = blocks w, w + Q, ...) and goes on to the next
 // step in the other tile.  Where every wave decoded the 16 x 128 block that it multiplied, the runs were a quarter as
 // long and a line was fetched 1.4 times on average.  X goes from memory to the operand registers, eight consecutive
-// columns per lane for two products (which columns meet in a product is free as long as both operands agree): staged in
+// columns per lane, word and load (which columns meet in a product is free as long as both operands agree): staged in
 // LDS it cost a wave a round trip per staging with nothing else to do.  NB: blocks of 16 output columns (MFMA N = 16);
 // every column is computed by the same operations whichever block and whatever company it has.
 // Loads run half a step ahead: the pruned values of a step are fetched while its kept values are placed, the kept
 // fields of the next step while the pruned values are placed; X of a step before its decode.  All are issued on every
 // path: where a load may or may not have been issued, the wait for an older one waits for it as well.
-// Measured, matrices read from HBM, 1 / 7 / 20 columns, us (before: private tiles, X through LDS): 28672 x 4096
-// 64 / 69 / 86 (71 / 85 / 116), 4096 x 14336 38 / 39 / 45 (48 / 48 / 52), 6144 x 4096 21.1 / 21.5 / 26.2 (22.5 / 25.4 /
-// 34.0), 4096 x 4096 14.2 / 14.4 / 17.6 (15.9 / 17.4 / 20.4), 128256 x 4096 275 / 281 / 338 (308 / 332 / 422), 11003 x
-// 5001 39 / 42 / 53 (43 / 50 / 62).  28672 x 4096 with 7 columns is 3.6 TB/s; vector issue, LDS and memory are each in
-// use for half of that time or more.  One tile and a second barrier instead of two tiles (five workgroups per CU
-// instead of four): the same within 2 %.
+// Measured, matrices read from HBM, 1 / 7 / 20 columns, us (before: private tiles in column order, X through LDS): 28672
+// x 4096 59 / 67 / 84 (71 / 85 / 116), 4096 x 14336 35 / 36 / 45 (48 / 48 / 52), 6144 x 4096 20.7 / 21.1 / 26.0 (22.5 /
+// 25.4 / 34.0), 4096 x 4096 13.2 / 13.6 / 17.0 (15.9 / 17.4 / 20.4), 128256 x 4096 254 / 263 / 341 (308 / 332 / 422),
+// 11003 x 5001 39 / 42 / 53 (43 / 50 / 62).  28672 x 4096 with 7 columns is 3.7 TB/s; vector issue takes half of that
+// time, and the loads of X (sixteen columns, 64 bytes of each) the 8 us between 1 and 7 columns.  Tried: lanes side by
+// side reading a column together and handing the pieces on through ds_bpermute, the same (67.5 / 82); one tile and a
+// second barrier instead of two tiles (five workgroups per CU instead of four), the same within 2 %.
 template <int T, int Q, int NB, bool MX = false>
 __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
   constexpr int WPR = 4 * Q;         // bitmap words per row and step = lanes per row
   constexpr int RPW = 64 / WPR;      // rows a wave decodes
-  constexpr int TILE = Q * 16 * kTilePitch;  // values of one tile: [block][row][kTilePitch]
+  constexpr int BLOCK = kBlockVals + 64 / Q;  // values from block to block
+  constexpr int TILE = Q * BLOCK;
   static_assert(RPW * Q == 16 && NB >= 1 && NB <= 2, "sixteen rows, at most two blocks of output columns");
   extern __shared__ uint16_t lds[];          // two tiles
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -74,11 +83,13 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
   const int row_b = rr * a.bw * 4;
   const __amdgpu_buffer_rsrc_t rs_e = __builtin_amdgcn_make_buffer_rsrc(  // of the exponent bytes
       MX ? (void*)(a.sexp + (size_t)row0 * a.ew) : nullptr, 0, MX ? 16 * a.ew : 0, kRawBufferFlags);
-  uint16_t* const trow = lds + ((j >> 2) * 16 + r) * kTilePitch + (j & 3) * kGroupPitch + 4;
+  uint16_t* const trow = lds + (j >> 2) * BLOCK + kPosPitch + r * 4 + (j & 3);
 
-  // ---- product role: A[i = lane%16][k = 4*(lane/16)..+3], B[k][n = lane%16]
+  // ---- product role: A[i = lane%16][four k of lane/16], B[k][n = lane%16]
   const int mi = lane & 15, mq = lane >> 4;
-  const uint16_t* const a_base = lds + (wv * 16 + mi) * kTilePitch + 4 + 8 * mq;
+  const uint16_t* const a_even = lds + wv * BLOCK + (1 + 8 * mq + (mq & 1)) * kPosPitch + mi * 4;
+  const uint16_t* const a_odd = a_even - 2 * (mq & 1) * kPosPitch;
+  const uint32_t sel_even = mq & 1 ? 0x07060302u : 0x05040100u, sel_odd = mq & 1 ? 0x05040100u : 0x07060302u;
   // X is read through a descriptor that ends with its last word: words past it read as 0.  Columns of X (rows of the
   // array) that start in the middle of a word are read from the word's start on and shifted into place (align_x): a
   // 16-byte load that is not aligned to words takes its 64 lanes one by one.
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
     kw.load(in ? p : 0u, rs_s, in ? row_s : kNowhere, rs_l, in ? row_l : kNowhere);
   };
 
-  // X of the step, eight values k = 32 g + 8 mq ..+7 of the wave's block per piece
+  // X of the step: positions 8 mq ..+7 of word g of the wave's block
   u32x4 xf[NB][4];
   uint32_t xe[NB];  // the word behind the block
   auto load_x = [&](int s) {
@@ -174,27 +185,28 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
     const uint32_t valid = nvalid >= 32 ? 0xFFFFFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
     if (nvalid < 32) {  // columns past the end are not placed below
 #pragma unroll
-      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(dst + 4 * q) = 0ull;
+      for (int q = 0; q < 32; ++q) dst[q * kPosPitch] = 0;
     }
     load_x(s);
     pw.load(nvalid > 0 ? (uint32_t)(s * WPR + j) * 32u - p : 0u, rs_p, nvalid > 0 ? row_p : kNowhere);
     const uint32_t pm = ~m & valid;
-    kw.decode(m, [&](int pos, uint16_t v) { dst[pos] = v; }, MX ? e : 0);
+    kw.decode(m, [&](int pos, uint16_t v) { dst[pos * kPosPitch] = v; }, MX ? e : 0);
     load_kept(s + 1);
     load_mask(s + 2);
-    pw.decode(pm, [&](int pos, uint16_t v) { dst[pos] = v; });
+    pw.decode(pm, [&](int pos, uint16_t v) { dst[pos * kPosPitch] = v; });
     __syncthreads();
     if (x_odd) align_x();
     if ((s * Q + wv) * 128 + 128 > a.cols) trim_x(s);
-    const uint16_t* const at = a_base + (s & 1) * TILE;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      const bf16x4 av = *reinterpret_cast<const bf16x4*>(at + (kk >> 1) * kGroupPitch + (kk & 1) * 4);
+      const bf16x4 av = *reinterpret_cast<const bf16x4*>((kk & 1 ? a_odd : a_even) + (s & 1) * TILE + kk * kPosPitch);
+      const uint32_t sel = kk & 1 ? sel_odd : sel_even;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        const u32x4& f = xf[nb][kk >> 1];
-        const bf16x4 bv = __builtin_bit_cast(bf16x4, (kk & 1) ? u32x2{f.z, f.w} : u32x2{f.x, f.y});
-        C[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, C[nb], 0, 0, 0);
+        const u32x4* f = xf[nb];
+        const u32x2 bv = {__builtin_amdgcn_perm(f[1][kk >> 1], f[0][kk >> 1], sel),
+                          __builtin_amdgcn_perm(f[3][kk >> 1], f[2][kk >> 1], sel)};
+        C[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, __builtin_bit_cast(bf16x4, bv), C[nb], 0, 0, 0);
       }
     }
   }
@@ -242,7 +254,7 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
 
 template <int Q, int NB, bool MX = false>
 static int launch_q(cas_ctx* ctx, const VerifyArgs& a, int t) {
-  constexpr size_t lds = sizeof(uint16_t) * 2 * Q * 16 * kTilePitch;
+  constexpr size_t lds = sizeof(uint16_t) * 2 * Q * (kBlockVals + 64 / Q);
   static_assert(lds >= sizeof(float) * NB * Q * 64 * 4, "the partial sums reuse the tiles");
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   const int grid = (a.rows + 15) / 16;
