@@ -8,7 +8,8 @@
 // committed, nor on the number of columns or the total length.
 //
 // One workgroup handles one kv head and one page (64 positions) of the sequence:
-//   1. thread (token r, word j) decodes its 32 channels of K into a 64 x 128 bf16 tile in LDS;
+//   1. thread (token r, word j) decodes its 32 channels of K into a bf16 tile in LDS, ordered by the position in the
+//      word so that the scattered writes of a wave do not meet in banks;
 //   2. each wave multiplies its 16 tokens with the query rows (grouped-query: the query heads
 //      of the group x columns share the kv head) by 16x16x16 bf16 MFMA; the scaled, masked
 //      scores stay in the MFMA result registers;
@@ -16,8 +17,8 @@
 //      rotations inside a wave and a few LDS words across the four waves (kept for the
 //      merge); probabilities are split into a bf16 head and a bf16 remainder, so the second
 //      product keeps 16 mantissa bits, and stored over the query tile, which is dead by then;
-//   4. the V tile is decoded transposed over the dead K tile and P V is formed in fp32 MFMA
-//      registers.
+//   4. the V tile is decoded over the dead K tile, the tokens of a word and position side by side, and P V is formed
+//      in fp32 MFMA registers.
 // Partial (max, sum, output) of every page go to the workspace; a merge kernel combines them
 // in a fixed order.
 #include <algorithm>
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(512, 4) void attn_merge_kernel(BATCH batch) {
 #pragma unroll
     for (int q = 1; q < kMergeParts; ++q) num += ps[q][lane];
     const int c = rr / a.grp, gi = rr - c * a.grp;
-    a.O[((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + d] = f32_to_bf16(num / den);
+    a.O[((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + part_channel(d)] = f32_to_bf16(num / den);
   }
 }
 
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(256) void attn_merge_few_kernel(BATCH batch) {
     num[0].y += num[p].y;
   }
   const int c = rr / a.grp, gi = rr - c * a.grp;
-  uint16_t* out = a.O + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + 2 * lane;
+  uint16_t* out = a.O + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + part_channel(2 * lane);
   out[0] = f32_to_bf16(num[0].x / den);
   out[1] = f32_to_bf16(num[0].y / den);
 }

@@ -88,9 +88,14 @@ __host__ __device__ inline const AttnArgs& attn_common(const AttnRuns& b) { retu
 
 constexpr int kPT = 64;          // tokens per page
 constexpr int kQP = 136;         // Q row pitch (bf16)
-constexpr int kKG = 36, kKP = 148;  // K tile: group pitch (4 dump + 32), row pitch
-constexpr int kVP = 72;          // transposed V tile: token pitch per channel row
-constexpr int kVR = 132;         // channel rows: 4 groups x (1 dump + 32)
+// K and V of a wave's 16 tokens in LDS: [1 + 32 positions][64] values, the four words of a token at one position side by
+// side for K, the tokens of a word for V (row 0 takes what lanes without a value left write).  At most two lanes of a wave
+// meet in a bank, whatever positions they are at; with rows of a token (K) or a channel (V) in order the writes of the
+// walks met in banks for half of the cycles in which the LDS was active, and it was active for 78 % of the kernel's
+// (draft form, four sequences of up to 32768 positions: 80 us, 76 with this order; 62 % and 4.4 cycles a write, which is
+// what one takes without any conflict).
+constexpr int kPos = 64;          // values of a position
+constexpr int kWaveKV = 33 * kPos;
 constexpr int kPP = 72;          // probability row pitch (bf16)
 constexpr int kPagesPerSplit = 1;
 constexpr int kMaxCols = 16;     // columns of one pass whose k, v may be split from the projection here
@@ -100,13 +105,21 @@ __device__ __forceinline__ float2* attn_ml(const AttnArgs& a, int R) {
   return reinterpret_cast<float2*>(a.part + (size_t)a.nsplit * a.g.n_kv_heads * R * 128);
 }
 
-constexpr int kKVTile = kPT * kKP > kVR * kVP ? kPT * kKP : kVR * kVP;  // K and V^T tiles share one region
+constexpr int kKVTile = 4 * kWaveKV;  // K and V share one region
 constexpr int kQPRows = kQP > 2 * kPP ? kQP : 2 * kPP;                  // Q and (P head, P remainder) share one region
 
 template <int MT>
 constexpr size_t attn_lds_bytes() {
   return sizeof(uint16_t) * (MT * 16 * kQPRows + kKVTile) + sizeof(float) * (8 * MT * 16);
 }
+
+__device__ __forceinline__ uint32_t low_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
+__device__ __forceinline__ uint32_t high_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
+
+// where a channel of a query lies in its row in LDS: the four words of a position side by side, as K has them
+__device__ __forceinline__ int q_index(int ch) { return (ch & 31) * 4 + (ch >> 5); }
+// the channel of value i of a partial result: a wave's 16 columns are four positions of each word
+__device__ __forceinline__ int part_channel(int i) { return ((i >> 2) & 3) * 32 + (i >> 5) * 8 + ((i >> 4) & 1) * 4 + (i & 3); }
 
 // All-reduce over the 16 lanes of a DPP row by rotations; every lane ends with the result (of a sum, with the
 // result of an order of its own).  The rotation is part of the operation: an addition folds the move of a builtin with no
@@ -130,8 +143,23 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v + row_rot<0x128>(v);
 }
 
+// the first E of four values of a lane group's rows
+template <int E>
+__device__ __forceinline__ void put_rows(float* dst, const float (&v)[4]) {
+  if constexpr (E == 4) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+  else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) dst[e] = v[e];
+  }
+}
+
 // MX: the cache is in the shared-exponent form (one exponent per 32-channel block of a vector)
-template <int MT, bool FULL, int T, bool MX, class BATCH>
+// E: query rows per lane group of a product.  A product has 16 rows, four per group of 16 lanes, and what follows it up to
+// the partial results (masks, maxima, exponentials, rounding, sums) is done row by row of a group: few query rows are
+// dealt to the groups, query row rr to row 4 (rr / E) + rr % E, so that R <= 4 MT E rows cost E of the four.
+// One column of the 8B heads (4 rows) over four sequences of up to 32768 positions 76 -> 70 us, over 8192 positions 12.5
+// -> 11.8 (19 % fewer vector instructions); 5 columns (20 rows of 32) 6 % fewer instructions, 2 % fewer cycles.
+template <int MT, int E, bool FULL, int T, bool MX, class BATCH>
 __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z);
   if ((int)blockIdx.x >= a.nsplit) return;  // a shorter sequence of the launch: uniform for the workgroup
@@ -139,8 +167,8 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   uint16_t* Qs = lds16;                       // [MT*16][kQP]; dead once the scores are in registers
   uint16_t* Ph = lds16;                       // [MT*16][kPP] over the Q region
   uint16_t* Pl = Ph + MT * 16 * kPP;          // [MT*16][kPP]
-  uint16_t* Kt = lds16 + MT * 16 * kQPRows;   // [64][kKP]
-  uint16_t* Vt = Kt;                          // [kVR][kVP]: the K tile is dead once the scores are out
+  uint16_t* Kt = lds16 + MT * 16 * kQPRows;   // [4 waves][kWaveKV]
+  uint16_t* Vt = Kt;                          // the K tile is dead once the scores are out
   float* wm = reinterpret_cast<float*>(Kt + kKVTile);  // [4 waves][MT*16] row maximum over the wave's 16 tokens
   float* wl = wm + 4 * MT * 16;                        // [4 waves][MT*16] row sum of exponentials
 
@@ -149,11 +177,12 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   auto col_of = [&](int rr) { return (int)((uint32_t)rr * a.grp_inv >> 16); };
   const int pg = blockIdx.x, head = blockIdx.y;  // one page (64 positions) per workgroup
   const int R = a.ncols * a.grp;
+  auto row_of = [](int rr) { return E == 4 ? rr : 4 * (rr / E) + rr % E; };  // row of the products, of query row rr
   const KvGeom& g = a.g;
   const int r = tid >> 2, j = tid & 3;           // decode role: token r of the page, word j
   const int mi = lane & 15, mq = lane >> 4;      // MFMA role
-  uint16_t* krow = Kt + r * kKP + j * kKG + 4;
-  uint16_t* vcol = Vt + (33 * j + 1) * kVP + r;
+  uint16_t* const kcol = Kt + wv * kWaveKV + kPos + (r & 15) * 4 + j;   // position 0 of the thread's token and word
+  uint16_t* const vcol = Vt + wv * kWaveKV + kPos + j * 16 + (r & 15);
 
   const int total = a.len + a.n_new;             // committed + in-flight positions
   const int tok0 = pg * kPT;
@@ -167,11 +196,17 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   // positions alone needs no pool page yet (and the plain-bf16 form has no pool at all)
   const int page = tok0 < a.len ? min(max(a.page_row[pg], 0), g.n_pages - 1) : 0;
 
+  // the exact form writes all channels of a page of committed tokens; otherwise what is not written has to read as 0
+  const bool clear = !FULL || tok0 + kPT > a.len;
+  auto clear_tile = [&](uint16_t* t) {  // the wave's own part
+#pragma unroll
+    for (int k = 0; k < 4; ++k) reinterpret_cast<uint4*>(t + wv * kWaveKV + kPos)[lane + 64 * k] = make_uint4(0, 0, 0, 0);
+  };
   // ---- 0. loads that do not depend on the page table entry go out first: the queries and,
   //         in the fused form, the k, v of this pass's columns that fall into this page
-  constexpr int NQ = MT * 4;
+  constexpr int NQ = MT * E;
   float x0[NQ], x1[NQ], cc[NQ], sn[NQ];
-  uint4 qraw[MT];
+  uint32_t qraw[MT][4];
   // fused k, v split: thread (column cf of a batch of 8, channel quarter dq) handles channels
   // dq, dq+32 and their rotation partners dq+64, dq+96
   const int cf = tid >> 5, dq = tid & 31;
@@ -213,12 +248,15 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
     }
   } else {
 #pragma unroll
-    for (int it = 0; it < MT; ++it) {  // 16-byte pieces
-      const int i = tid + it * 256, rr = i >> 4, d = (i & 15) * 8;
-      qraw[it] = make_uint4(0, 0, 0, 0);
+    for (int it = 0; it < MT; ++it) {  // two positions of the four words
+      const int i = tid + it * 256, rr = i >> 4, d = (i & 15) * 2;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) qraw[it][w] = 0;
       if (rr < R) {
         const int c = col_of(rr), gi = rr - c * a.grp;
-        qraw[it] = *reinterpret_cast<const uint4*>(a.Q + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + d);
+        const uint16_t* src = a.Q + ((size_t)c * a.n_q_heads + head * a.grp + gi) * 128 + d;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) qraw[it][w] = *reinterpret_cast<const uint32_t*>(src + 32 * w);
       }
     }
   }
@@ -248,14 +286,17 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
       const int rr = wv + 4 * it, d = lane;
       if (rr >= R) break;
       const float a0 = round_bf16(x0[it]), a1 = round_bf16(x1[it]);
-      Qs[rr * kQP + d] = f32_to_bf16(a0 * cc[it] - a1 * sn[it]);
-      Qs[rr * kQP + d + 64] = f32_to_bf16(a1 * cc[it] + a0 * sn[it]);
+      Qs[row_of(rr) * kQP + q_index(d)] = f32_to_bf16(a0 * cc[it] - a1 * sn[it]);
+      Qs[row_of(rr) * kQP + q_index(d + 64)] = f32_to_bf16(a1 * cc[it] + a0 * sn[it]);
     }
   } else {
 #pragma unroll
     for (int it = 0; it < MT; ++it) {
-      const int i = tid + it * 256, rr = i >> 4, d = (i & 15) * 8;
-      *reinterpret_cast<uint4*>(Qs + rr * kQP + d) = qraw[it];
+      const int i = tid + it * 256, rr = i >> 4, d = (i & 15) * 2;
+      const uint32_t* q = qraw[it];
+      if (E == 4 || rr < 4 * MT * E)
+        *reinterpret_cast<uint4*>(Qs + row_of(rr) * kQP + d * 4) =
+            make_uint4(low_halves(q[0], q[1]), low_halves(q[2], q[3]), high_halves(q[0], q[1]), high_halves(q[2], q[3]));
     }
   }
   WordWindows<T, FULL, MX> wk, wvw;
@@ -279,6 +320,9 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   // the draft form has registers to spare for both windows; the exact form asks for V later
   if constexpr (!FULL) load_v();
 
+  if (clear) clear_tile(Kt);
+  // the tokens of this pass may lie in any wave's part of the tile: cleared before they are written (uniform)
+  if (a.qkv != nullptr && first < tok0 + kPT && first + a.ncols > tok0) __syncthreads();
   // k, v of this pass's columns: round, rotate k; k goes straight into its tile row, v waits
   // in registers until the tile region is free; both go to their in-flight slots
   uint16_t fv[2][4];
@@ -286,15 +330,16 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   for (int cb = 0; cb < 2; ++cb) {
     if (fnew[cb]) {
       const int c = cb * 8 + cf, fpos = first + c;
-      uint16_t* kdst = Kt + (fpos - tok0) * kKP + 4;
+      const int tr = fpos - tok0;
+      uint16_t* kdst = Kt + (tr >> 4) * kWaveKV + (1 + dq) * kPos + (tr & 15) * 4;
       const size_t so = ((size_t)(fpos - a.len) * g.n_kv_heads + head) * 128;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {  // channel pair (dq + 32h, dq + 32h + 64)
         const float a0 = round_bf16(kx[cb][h]), a1 = round_bf16(kx[cb][h + 2]);
         const uint16_t k0 = f32_to_bf16(a0 * kcs[cb][h].x - a1 * kcs[cb][h].y);
         const uint16_t k1 = f32_to_bf16(a1 * kcs[cb][h].x + a0 * kcs[cb][h].y);
-        kdst[h * kKG + dq] = k0;
-        kdst[(h + 2) * kKG + dq] = k1;
+        kdst[h] = k0;
+        kdst[h + 2] = k1;
         a.Kslot[so + dq + 32 * h] = k0;
         a.Kslot[so + dq + 32 * h + 64] = k1;
       }
@@ -309,20 +354,24 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
 
   // ---- 3. K tile: this thread's 32 channels of its token
   {
-    if (!own_new) {
-      // the exact form writes all 32 channels of a committed token: nothing to clear first
-      if (!FULL || !live) {
+    if (fresh && !own_new) {  // positions 8 j ..+7 of the token's four words
+      const uint16_t* src = a.Knew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 8 * j;
+      uint16_t* dst = kcol - j + 8 * j * kPos;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) *reinterpret_cast<uint64_t*>(krow + 4 * q) = 0ull;
-      }
-      if (fresh) {
-        const uint16_t* src = a.Knew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 32 * j;
+      for (int q = 0; q < 2; ++q) {
+        uint2 x[4];
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          *reinterpret_cast<uint64_t*>(krow + 4 * q) = *reinterpret_cast<const uint64_t*>(src + 4 * q);
+        for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const uint2*>(src + 32 * w + 4 * q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t x0 = i < 2 ? x[0].x : x[0].y, x1 = i < 2 ? x[1].x : x[1].y, x2 = i < 2 ? x[2].x : x[2].y,
+                         x3 = i < 2 ? x[3].x : x[3].y;
+          *reinterpret_cast<uint2*>(dst + (4 * q + i) * kPos) =
+              i & 1 ? make_uint2(high_halves(x0, x1), high_halves(x2, x3)) : make_uint2(low_halves(x0, x1), low_halves(x2, x3));
+        }
       }
     }
-    wk.decode(mk, (FULL && live) ? ~mk : 0u, [&](int bp, uint16_t v) { krow[bp] = v; }, ek);
+    wk.decode(mk, (FULL && live) ? ~mk : 0u, [&](int bp, uint16_t v) { kcol[bp * kPos] = v; }, ek);
   }
   if constexpr (FULL) load_v();
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -332,7 +381,8 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   float sc[MT][4];
   const int visible = total - a.ncols - tok0;  // last token of the page that column 0 sees
   {
-    const uint16_t* b_base = Kt + (16 * wv + mi) * kKP + 4 + 4 * mq;
+    // product kk: position 4 kk + mq in lane group mq
+    const uint16_t* b_base = Kt + wv * kWaveKV + (1 + mq) * kPos + 4 * mi;
     const int t = 16 * wv + mi;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -341,28 +391,22 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         bf16x4 av = *reinterpret_cast<const bf16x4*>(a_base + kk * 16);
-        bf16x4 bv = *reinterpret_cast<const bf16x4*>(b_base + (kk >> 1) * kKG + (kk & 1) * 16);
+        bf16x4 bv = *reinterpret_cast<const bf16x4*>(b_base + 4 * kk * kPos);
         C = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, C, 0, 0, 0);
       }
       float mx[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int rr = mt * 16 + 4 * mq + e;
+      for (int e = 0; e < E; ++e) {
+        const int rr = (mt * 4 + mq) * E + e;
         // column c sees positions 0 .. len + n_new - ncols + c
         sc[mt][e] = t <= visible + col_of(rr) ? C[e] * a.scale : -INFINITY;
         mx[e] = row16_max(sc[mt][e]);
       }
-      if (mi == 0) *reinterpret_cast<float4*>(wm + wv * (MT * 16) + mt * 16 + 4 * mq) = make_float4(mx[0], mx[1], mx[2], mx[3]);
+      if (mi == 0) put_rows<E>(wm + wv * (MT * 16) + mt * 16 + 4 * mq, mx);
     }
   }
   __syncthreads();  // every wave is done with Q and K: their regions may be overwritten
-  // the draft form clears the whole V tile with 16-byte writes (5 per thread; 32 of 2 bytes when every thread
-  // clears the channels of its own token)
-  if constexpr (!FULL) {
-#pragma unroll
-    for (int k = 0; k < (kVR * kVP / 8 + 255) / 256; ++k)
-      if (tid + 256 * k < kVR * kVP / 8) reinterpret_cast<uint4*>(Vt)[tid + 256 * k] = make_uint4(0, 0, 0, 0);
-  }
+  if (clear) clear_tile(Vt);
   // ---- 5. softmax numerators of the page, head + remainder in bf16; row sums per wave
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -372,8 +416,8 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
                 m2 = *reinterpret_cast<const f32x4*>(wm + (2 * MT + mt) * 16 + 4 * mq),
                 m3 = *reinterpret_cast<const f32x4*>(wm + (3 * MT + mt) * 16 + 4 * mq);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int rr = mt * 16 + 4 * mq + e, t = 16 * wv + mi;
+    for (int e = 0; e < E; ++e) {
+      const int rr = mt * 16 + 4 * mq + e, t = 16 * wv + mi;  // row of the product
       // at least the lowest finite number: where a row sees nothing of the page, its maximum is -inf as its scores are
       const float mx = fmaxf(fmaxf(fmaxf(m0[e], m1[e]), fmaxf(m2[e], m3[e])), -3.402823466e38f);
       const float p = __expf(sc[mt][e] - mx);
@@ -383,76 +427,69 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
       ps[e] = row16_sum(p);
     }
     // lane 0's sums: the lanes of a row add the same values in orders of their own
-    if (mi == 0) *reinterpret_cast<float4*>(wl + wv * (MT * 16) + mt * 16 + 4 * mq) = make_float4(ps[0], ps[1], ps[2], ps[3]);
+    if (mi == 0) put_rows<E>(wl + wv * (MT * 16) + mt * 16 + 4 * mq, ps);
   }
-  if constexpr (!FULL) __syncthreads();
-  // ---- 6. V tile, transposed: Vt[channel][token]
+  if (clear) __syncthreads();
+  // ---- 6. V tile
   {
-    if (!own_new) {
-      if constexpr (FULL) {
-        if (!live) {
+    if (fresh && !own_new) {
+      const uint16_t* src = a.Vnew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 32 * j;
 #pragma unroll
-          for (int c = 0; c < 32; ++c) vcol[c * kVP] = 0;
-        }
-      }
-      if (fresh) {
-        const uint16_t* src = a.Vnew + ((size_t)(pos - a.len) * g.n_kv_heads + head) * 128 + 32 * j;
-#pragma unroll
-        for (int c = 0; c < 32; ++c) vcol[c * kVP] = src[c];
-      }
+      for (int c = 0; c < 32; ++c) vcol[c * kPos] = src[c];
     }
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
       if (fnew[cb]) {
         const int tr = first + cb * 8 + cf - tok0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) Vt[(33 * q + 1 + dq) * kVP + tr] = fv[cb][q];
+        for (int q = 0; q < 4; ++q) Vt[(tr >> 4) * kWaveKV + (1 + dq) * kPos + q * 16 + (tr & 15)] = fv[cb][q];
       }
     }
-    wvw.decode(mv, (FULL && live) ? ~mv : 0u, [&](int bp, uint16_t v) { vcol[bp * kVP] = v; }, ev);
+    wvw.decode(mv, (FULL && live) ? ~mv : 0u, [&](int bp, uint16_t v) { vcol[bp * kPos] = v; }, ev);
   }
   __syncthreads();
-  // ---- 7. O = P V ; wave w owns channels 32w .. 32w+31; partial result of this page
+  // ---- 7. O = P V; wave w owns positions 8w .. 8w+7 of the four words, column n of a product position n % 4 of word
+  //         n / 4 (part_channel); partial result of this page
   float* part = a.part + ((size_t)pg * g.n_kv_heads + head) * R * 128;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
       f32x4 C = {0.f, 0.f, 0.f, 0.f};
-      const uint16_t* b_base = Vt + (33 * wv + 1 + nt * 16 + mi) * kVP + 4 * mq;
+      const uint16_t* b_base = Vt + (1 + 8 * wv + 4 * nt + (mi & 3)) * kPos + (mi >> 2) * 16 + 4 * mq;
       const uint16_t* ah = Ph + (mt * 16 + mi) * kPP + 4 * mq;
       const uint16_t* al = Pl + (mt * 16 + mi) * kPP + 4 * mq;
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
-        bf16x4 bv = *reinterpret_cast<const bf16x4*>(b_base + kb * 16);
+        bf16x4 bv = *reinterpret_cast<const bf16x4*>(b_base + kb * kWaveKV);
         C = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4*>(ah + kb * 16), bv, C, 0, 0, 0);
         C = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4*>(al + kb * 16), bv, C, 0, 0, 0);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int rr = mt * 16 + 4 * mq + e;
+      for (int e = 0; e < E; ++e) {
+        const int rr = (mt * 4 + mq) * E + e;
         if (rr < R) part[rr * 128 + 32 * wv + nt * 16 + mi] = C[e];
       }
     }
   }
   if (tid < R) {
-    const float* m4 = wm + tid;
-    const float* l4 = wl + tid;
+    const float* m4 = wm + row_of(tid);
+    const float* l4 = wl + row_of(tid);
     attn_ml(a, R)[((size_t)head * R + tid) * a.nsplit + pg] =
         make_float2(fmaxf(fmaxf(m4[0], m4[MT * 16]), fmaxf(m4[2 * MT * 16], m4[3 * MT * 16])),
                     ((l4[0] + l4[MT * 16]) + l4[2 * MT * 16]) + l4[3 * MT * 16]);
   }
 }
 
-template <int MT, bool FULL, bool MX = false, class BATCH = AttnBatch>
-int launch_mt(cas_ctx* ctx, const BATCH& a, dim3 grid) {
+template <int MT, int E, bool FULL, bool MX, class BATCH>
+int launch_rows(cas_ctx* ctx, const BATCH& a, dim3 grid) {
   constexpr size_t lds = attn_lds_bytes<MT>();
 #define CAS_LAUNCH(TV)                                                                                     \
   case TV: {                                                                                               \
     static LdsLimit lim;                                                                                   \
-    const int rc = allow_lds(ctx, (const void*)attn_partial_kernel<MT, FULL, TV, MX, BATCH>, lds, lim);               \
+    const int rc = allow_lds(ctx, (const void*)attn_partial_kernel<MT, E, FULL, TV, MX, BATCH>, lds, lim);            \
     if (rc != CAS_OK) return rc;                                                                           \
-    hipLaunchKernelGGL((attn_partial_kernel<MT, FULL, TV, MX, BATCH>), grid, dim3(256), lds, ctx->stream, a);         \
+    hipLaunchKernelGGL((attn_partial_kernel<MT, E, FULL, TV, MX, BATCH>), grid, dim3(256), lds, ctx->stream, a);      \
   } break;
   switch (attn_common(a).g.t) {
     CAS_LAUNCH(0) CAS_LAUNCH(1) CAS_LAUNCH(2) CAS_LAUNCH(3) CAS_LAUNCH(4) CAS_LAUNCH(5) CAS_LAUNCH(6) CAS_LAUNCH(7)
@@ -461,6 +498,27 @@ int launch_mt(cas_ctx* ctx, const BATCH& a, dim3 grid) {
 #undef CAS_LAUNCH
   CAS_HIP(ctx, hipGetLastError());
   return CAS_OK;
+}
+
+// query rows of a kv head in the widest call of a launch
+inline int attn_rows(const AttnRuns& b) { return b.run_cols * b.first.grp; }
+inline int attn_rows(const AttnBatch& b) {
+  int cols = 0;
+  for (const AttnSeq& q : b.s) cols = q.ncols > cols ? q.ncols : cols;
+  return cols * b.common.grp;
+}
+
+template <int MT, bool FULL, bool MX = false, class BATCH = AttnBatch>
+int launch_mt(cas_ctx* ctx, const BATCH& a, dim3 grid) {
+  if constexpr (MT == 1) {
+    const int rows = attn_rows(a);
+    if (rows <= 4) return launch_rows<1, 1, FULL, MX>(ctx, a, grid);
+    if (rows <= 8) return launch_rows<1, 2, FULL, MX>(ctx, a, grid);
+  }
+  if constexpr (MT == 2) {
+    if (attn_rows(a) <= 24) return launch_rows<2, 3, FULL, MX>(ctx, a, grid);
+  }
+  return launch_rows<MT, 4, FULL, MX>(ctx, a, grid);
 }
 
 }  // namespace cas

@@ -367,3 +367,24 @@ def test_attention_over_a_shared_exponent_cache_matches_oracle(env, len_cache, n
             o1 = _host(B.cas_attention(ctx, kv, layer, seq, True, _dev(torch, Q[c:c + 1]),
                                        _dev(torch, Kn[:vis]), _dev(torch, Vn[:vis])))
             np.testing.assert_array_equal(o1[0], out[c])
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("full", [False, True])
+def test_a_query_row_has_the_same_bits_whatever_rows_ride_along(env, full, shared):
+    """Row counts on both sides of every line between the forms of the products (4, 8, 16, 24, 32, 48, 64 rows of a kv
+    head): the rows of the widest call, which has one form, are those of every narrower one.  A page of committed
+    positions alone and one with positions in flight."""
+    torch, B, ctx = env
+    length, most = 119, 80 if full else 48
+    kv = B.KVCache(ctx, 1, 1, n_pages=2, max_seqs=1, max_pages_per_seq=2,
+                   exp_mode=B.CAS_EXP_SHARED if shared else B.CAS_EXP_RAW)
+    g = torch.Generator().manual_seed(11)
+    bits = lambda *s: torch.randn(s, generator=g).to(torch.bfloat16).view(torch.int16).cuda()
+    B.cas_kv_append(ctx, kv, 0, 0, bits(length, 1, 128), bits(length, 1, 128))
+    B.cas_kv_set_len(kv, 0, length)
+    q, k, v = bits(1, most, 128), bits(3, 1, 128), bits(3, 1, 128)
+    wide = B.cas_attention(ctx, kv, 0, 0, full, q, k, v)
+    for rows in (1, 3, 4, 5, 8, 9, 16, 17, 24, 25, 32, 33, 48, 49, 64, 65):
+        if rows <= most:
+            assert torch.equal(B.cas_attention(ctx, kv, 0, 0, full, q[:, :rows].contiguous(), k, v), wide[:, :rows]), rows
