@@ -9,14 +9,12 @@
 
 namespace cas {
 
-// One wave formats one 128-value vector, four tokens per workgroup.  Keys (magnitude << 7 | 127 - column)
-// are unique, so the K-th largest key is found bit by bit with wave ballots and "key >= threshold" keeps
-// exactly K values with ties going to the lower column.  All 22 bits are searched: ending when K keys are left
-// (after some 14 bits on normal values) costs a branch per bit, 0.4 us of the 4 us that up to some 100 vectors
-// take and as much of the 13.0 us for the vectors of 1021 tokens, 8 heads (14.5 us with one wave per
-// workgroup and the page entry looked up at the end).  Bound by the scalar instructions of the search: counters of
-// that call have 21.0 K of them per CU, whose SIMDs share one a cycle, in the 26.3 K cycles that it is busy
-// (vector instructions 43 % of those cycles, waves waiting to issue 55 %), half of the launch.
+// One wave formats one 128-value vector, four tokens per workgroup.  The K-th largest magnitude is found bit by
+// bit with wave ballots; its equals are kept in the order of the columns.  All 15 bits are searched: ending when K
+// values are left costs a branch per bit, as much as it saves.  Bound by the scalar instructions of the search, of
+// which the SIMDs of a CU share one a cycle: 1021 tokens of 8 heads take 11.6 us, and 12.6 with keys of 22 bits that
+// held the column as well (no ties then, but a third more steps), 14.5 with one wave per workgroup and the page
+// entry looked up at the end.
 constexpr int kAppendWaves = 4;
 __global__ __launch_bounds__(64 * kAppendWaves) void kv_append_kernel(KvGeom g, uint32_t* spec_pool, uint32_t* verif_pool,
                                                                       const int32_t* __restrict__ page_row, int layer0,
@@ -34,20 +32,27 @@ __global__ __launch_bounds__(64 * kAppendWaves) void kv_append_kernel(KvGeom g, 
   const uint16_t* src = (kv ? Vn : Kn) + (size_t)(blockIdx.z >> 1) * layer_stride +
                         ((size_t)tok * g.n_kv_heads + head) * 128;
   const uint32_t v0 = src[lane], v1 = src[lane + 64];
-  const uint32_t key0 = ((v0 & 0x7FFFu) << 7) | (uint32_t)(127 - lane);
-  const uint32_t key1 = ((v1 & 0x7FFFu) << 7) | (uint32_t)(63 - lane);
+  const uint32_t key0 = v0 & 0x7FFFu, key1 = v1 & 0x7FFFu;
   for (int i = lane; i < g.sw + g.lw + g.pw; i += 64) stage[i] = 0;
-  uint32_t T = g.K > 0 ? 0u : 0xFFFFFFFFu;
-  for (int bit = 21; bit >= 0; --bit) {
+  uint32_t T = g.K > 0 ? 0u : 0xFFFFFFFFu;  // the K-th largest magnitude
+  auto count = [](uint64_t m0, uint64_t m1) { return __popcll(m0) + __popcll(m1); };
+#pragma unroll
+  for (int bit = 14; bit >= 0; --bit) {
     const uint32_t cand = T | (1u << bit);
-    const int c = __popcll(__builtin_amdgcn_ballot_w64(key0 >= cand)) + __popcll(__builtin_amdgcn_ballot_w64(key1 >= cand));
-    if (c >= g.K) T = cand;
+    if (count(__builtin_amdgcn_ballot_w64(key0 >= cand), __builtin_amdgcn_ballot_w64(key1 >= cand)) >= g.K) T = cand;
   }
-  const bool k0 = key0 >= T, k1 = key1 >= T;
-  const uint64_t m01 = __builtin_amdgcn_ballot_w64(k0), m23 = __builtin_amdgcn_ballot_w64(k1);
-  const uint32_t below = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m01 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m01, 0u));
-  const uint32_t below2 = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m23 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m23, 0u));
-  const uint32_t r0 = below, r1 = (uint32_t)__popcll(m01) + below2;
+  // the larger ones, and as many of its equals as are needed, in the order of the columns
+  uint64_t m01 = __builtin_amdgcn_ballot_w64(key0 > T), m23 = __builtin_amdgcn_ballot_w64(key1 > T);
+  const uint64_t eq0 = __builtin_amdgcn_ballot_w64(key0 == T), eq1 = __builtin_amdgcn_ballot_w64(key1 == T);
+  const int need = g.K - count(m01, m23), need1 = need - __popcll(eq0);
+  auto rank_in = [](uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  };
+  const int e0 = rank_in(eq0), e1 = rank_in(eq1);
+  const bool k0 = (key0 > T) | ((key0 == T) & (e0 < need)), k1 = (key1 > T) | ((key1 == T) & (e1 < need1));
+  m01 = __builtin_amdgcn_ballot_w64(k0);
+  m23 = __builtin_amdgcn_ballot_w64(k1);
+  const uint32_t r0 = (uint32_t)rank_in(m01), r1 = (uint32_t)(__popcll(m01) + rank_in(m23));
 
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
