@@ -17,39 +17,39 @@ struct CodecArgs {
   uint32_t* pruned;
 };
 
-// The comparison key of one value: its score as an unsigned pattern (a NaN score ranks above every finite one).
-__device__ __forceinline__ uint32_t score_of(uint32_t w, bool weighted, float act) {
-  const uint32_t mag = w & 0x7FFFu;
-  if (!weighted) return mag;
-  const float s = __fmul_rn(__uint_as_float(mag << 16), act);
-  return (s != s) ? 0x7FFFFFFFu : __float_as_uint(s);
-}
-
 // One workgroup of NW = blockDim / 64 waves formats one row; a lane owns P pieces of 8
 // consecutive columns, piece (q, wave, lane) being columns 8 ((q NW + wave) 64 + lane) ..+7, so the row and
 // the norms come in with 16-byte loads and are read from memory once: values and keys stay in registers (with 10
 // pieces, rows of more than 65536 columns, 98 of the 128 registers that sixteen waves leave a lane spill).
 //
-//   1. The K-th largest key is found bit by bit: a wave counts the keys >= a candidate with ballots (one
-//      compare per key, the counting runs on the scalar unit), the waves of a row add their counts in LDS.
-//      The search ends early when exactly K keys are left above the candidate.
-//   2. Prefix sums over (piece, wave, lane), which is column order, rank the kept values; equal keys at the
-//      threshold are granted in column order.  A value is written once, as 16 bits, to its place in the
+//   1. The threshold, a value that exactly K keys reach or the K-th largest key itself, lies between two others
+//      whose counts are known.  A sample of 64 keys gives the first of them; from there on the next candidate is
+//      where a straight line between the two counts meets K.  Seven counts find it among 4096 keys, where a search
+//      bit by bit took 22 (with norms; five instead of 15 without).  A lane counts its own keys, two instructions
+//      a key; the sum goes over the lanes, and in LDS over the waves of the row.
+//   2. Where keys equal the threshold, the first in column order of them are raised above it.  Prefix sums over
+//      (piece, wave, lane), which is column order, rank the kept values.  A value is written once, as 16 bits, to its place in the
 //      row's kept or pruned list in LDS.
 //   3. A thread packs 32 consecutive kept values into the FW words of the spec stream and the T words of the
 //      lo stream that they fill exactly; the pruned list already is the pruned stream.
 //
-// Bound by the issue of vector instructions, the compares of step 1 (about 22 of them per value) above all:
-// counters of 28672 x 4096 with norms have them in 71 % of the cycles that the CUs are busy (92 % of the launch);
-// scalar instructions, one a cycle for the four SIMDs, in 61 %.  269 us, 1.8 TB/s of input and output; radix
-// selection through histograms in LDS, whose atomics met in the few exponents that a row holds, took 2602 us.
+// Bound by the issue of instructions, some 45 per value, and by the start of a row, when its wave waits for its
+// loads: all of them are in flight together (a branch around each had them wait one by one, 46 us of the launch).
+// 28672 x 4096 with norms from HBM 162 us, 3.1 TB/s of input and output (268 with the search bit by bit and branched
+// loads), without 149 (226); 8192 x 12288, three waves a row, 152 (301); 28672 x 1000 58 (74).  Radix selection
+// through histograms in LDS, whose atomics met in the few exponents that a row holds, took 2602 us; counting
+// with ballots, which are three instructions a key, 231 instead of 170.
+constexpr int kSampleStep = 4;       // places of the sample on either side of the expected one: one standard deviation
+constexpr int kInterpolations = 12;  // counts after which the rest of the interval is halved
 template <int T, int P>
 __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ act, CodecArgs a) {
   constexpr int FW = 16 - T;
   extern __shared__ uint16_t vals[];  // [kpad] kept values of the row, then the pruned ones
   __shared__ int wave_cnt[2][16];
-  __shared__ uint32_t tot_gt[P * 16], tot_eq[P * 16];
+  __shared__ __attribute__((aligned(16))) uint16_t end_raw[8];
+  __shared__ __attribute__((aligned(16))) float end_act[8];
+  __shared__ uint32_t tot[P * 16], sample[64];
 
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthr = blockDim.x, NW = nthr >> 6;
@@ -62,45 +62,74 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
   }
   const int64_t row = blockIdx.x;
   const uint16_t* wr = W + row * a.ld;
+  if (cols & 7) {  // the piece that the row ends in, filled up with zeros
+    const int col = (cols & ~7) + tid;
+    if (tid < 8) {
+      end_raw[tid] = col < cols ? wr[col] : (uint16_t)0;
+      end_act[tid] = weighted && col < cols ? act[col] : 0.f;
+    }
+    __syncthreads();
+  }
+  // All loads are issued without a branch between them (a wait for each of the 3 P otherwise): lanes past the last
+  // whole piece of the row read its first one and are corrected below.
   uint32_t raw[P][4], key[P][8];
+  const int whole = cols & ~7;
+  if (whole) {
+    auto at = [&](int q) -> uint32_t {
+      const int col = ((q * NW + wv) * 64 + lane) * 8;
+      return col < whole ? (uint32_t)col : 0u;
+    };
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int col = ((q * NW + wv) * 64 + lane) * 8;
+    for (int q = 0; q < P; ++q)  // a row may start at any multiple of 2 bytes
+      __builtin_memcpy(raw[q], reinterpret_cast<const char*>(wr) + at(q) * 2u, 16);
+    if (weighted) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) key[q][e] = 0u;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) raw[q][e] = 0u;
-    if (col + 8 <= cols) {  // a row may start at any multiple of 2 bytes
-      __builtin_memcpy(raw[q], wr + col, 16);
-      if (weighted) __builtin_memcpy(key[q], act + col, 32);
-    } else if (col < cols) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (col + e < cols) {
-          raw[q][e >> 1] |= (uint32_t)wr[col + e] << (16 * (e & 1));
-          if (weighted) key[q][e] = __float_as_uint(act[col + e]);
-        }
-      }
+      for (int q = 0; q < P; ++q) __builtin_memcpy(key[q], reinterpret_cast<const char*>(act) + at(q) * 4u, 32);
     }
   }
 #pragma unroll
   for (int q = 0; q < P; ++q) {
-    // columns past the end have value 0 and norm 0, hence the smallest key: no candidate counts them
+    if (((q * NW + wv) * 64 + 64) * 8 <= whole) continue;
+    const int col = ((q * NW + wv) * 64 + lane) * 8;
+    const bool in = col < whole, end = col == whole && whole < cols;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      key[q][e] = score_of(raw[q][e >> 1] >> (16 * (e & 1)), weighted, __uint_as_float(key[q][e]));
-    __builtin_amdgcn_sched_barrier(0);
+    for (int e = 0; e < 4; ++e) {
+      uint32_t last;
+      __builtin_memcpy(&last, end_raw + 2 * e, 4);
+      raw[q][e] = in ? raw[q][e] : end ? last : 0u;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) key[q][e] = in ? key[q][e] : end ? __float_as_uint(end_act[e]) : 0u;
   }
-  // ---- 1. thr: the largest value that at least K keys reach
+  // The comparison keys: magnitudes, or scores as unsigned patterns (a NaN score ranks above every finite one).
+  // Columns past the end have value 0 and norm 0, hence the smallest key: no candidate counts them.
+  if (weighted) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t mag = e & 1 ? raw[q][e >> 1] & 0x7FFF0000u : raw[q][e >> 1] << 17 >> 1;
+        const float s = __fmul_rn(__uint_as_float(mag), __uint_as_float(key[q][e]));
+        const uint32_t nan = 0u - (uint32_t)(s != s);  // a select here becomes a branch per value
+        key[q][e] = (nan & 0x7FFFFFFFu) | (~nan & __float_as_uint(s));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) key[q][e] = (raw[q][e >> 1] >> (16 * (e & 1))) & 0x7FFFu;
+  }
+  // ---- 1. thr: a value with `need` of the keys equal to it and all the larger ones kept
   int buf = 0;
   auto count_ge = [&](uint32_t cand) -> int {
     int c = 0;
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
+    for (int q = 0; q < P; ++q)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) c += __popcll(__builtin_amdgcn_ballot_w64(key[q][e] >= cand));
-      __builtin_amdgcn_sched_barrier(0);  // eight masks at a time: all of them together do not fit the scalar registers
-    }
+      for (int e = 0; e < 8; ++e) c += key[q][e] >= cand ? 1 : 0;  // two instructions; ballots took three
+    c = __builtin_amdgcn_readlane(wave_incl_scan(c), 63);
     if (NW > 1) {  // two sets of slots: one barrier per count keeps a fast wave out of the set being read
       if (lane == 0) wave_cnt[buf][wv] = c;
       __syncthreads();
@@ -112,76 +141,137 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
     return c;
   };
   uint32_t thr = 0;
-  bool exact = K == cols;  // exactly K keys are >= thr
-  int need = 0;            // how many of the keys equal to thr are kept, when not exact
+  bool exact = false;  // exactly K keys are >= thr
+  int need = 0;        // how many of the keys equal to thr are kept, when not exact
   if (K == 0) {
     thr = 0xFFFFFFFFu;     // no key is that large: the largest are those of -Inf norms, 0xFF800000
     exact = true;
-  } else if (!exact) {
-    for (int bit = weighted ? 31 : 14; bit >= 0 && !exact; --bit) {
-      const uint32_t cand = thr | (1u << bit);
+  } else if (K == cols) {
+    need = K - count_ge(1u);
+  } else {
+    // the sample: a key of every lane (of some lanes, where several waves share the row), from all its pieces
+    const int per = 64 / NW;
+    uint32_t mine = key[0][0];
+    const int sq = NW == 1 ? lane * P >> 6 : min(lane, per - 1) * P / per;
+#pragma unroll
+    for (int q = 1; q < P; ++q) mine = sq == q ? key[q][0] : mine;
+    if (((sq * NW + wv) * 64 + lane) * 8 >= cols || lane >= per) mine = 0xFFFFFFFFu;  // not a column of the row
+    if (NW > 1) {
+      if (tid < 64) sample[tid] = 0xFFFFFFFFu;
+      __syncthreads();
+      if (lane < per) sample[wv * per + lane] = mine;
+      __syncthreads();
+      mine = sample[lane];
+    }
+    const bool real = mine != 0xFFFFFFFFu;
+    mine = real ? mine : 0u;
+    const int n = __popcll(__builtin_amdgcn_ballot_w64(real));
+    // ranks, largest first, of keys made different by their lane
+    const uint32_t own = (weighted ? mine & ~63u : mine << 6) | (uint32_t)lane;
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < 64; ++j) rank += (uint32_t)__builtin_amdgcn_readlane((int)own, j) > own;
+    auto ranked = [&](int i) -> uint32_t {
+      const uint64_t at = __builtin_amdgcn_ballot_w64(rank == max(min(i, n - 1), 0));
+      return (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(at));
+    };
+    // lo: reached by clo >= K keys; hi: by chi < K
+    const uint32_t top = weighted ? 0xFFFFFFFFu : 0x8000u;
+    uint32_t lo = 0, hi = top;
+    int clo = cols, chi = 0;
+    const int mid = (int)((float)K / (float)cols * (float)n);
+    int below = kSampleStep, above = kSampleStep;
+    for (int it = 0; hi - lo > 1u; ++it) {
+      uint32_t cand;
+      if (lo == 0u && mid + below < n + kSampleStep) {
+        cand = ranked(mid + below);
+        below *= 3;
+      } else if (hi == top && mid - above > -kSampleStep) {
+        cand = ranked(mid - above) + 1u;
+        above *= 3;
+      } else if (lo == 0u || hi == top || it >= kInterpolations) {
+        cand = lo + ((hi - lo) >> 1);
+      } else {
+        cand = lo + (uint32_t)((float)(hi - lo) * ((float)(clo - K) / (float)(clo - chi)));
+      }
+      cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(max(cand, lo + 1u), hi - 1u));
       const int c = count_ge(cand);
       if (c >= K) {
-        thr = cand;
+        lo = cand;
+        clo = c;
         exact = c == K;
+        if (exact) break;
+      } else {
+        hi = cand;
+        chi = c;
       }
     }
-    if (!exact) need = K - count_ge(thr + 1u);
+    thr = lo;
+    need = K - chi;  // not exact: hi = lo + 1, which chi keys reach
   }
   // ---- 2. ranks
-  const uint32_t sure = exact ? thr : thr + 1u, tied = thr;
-  uint32_t gt[P], excl[P];  // bit e: kept for certain, bit 8 + e: equal to thr; counts before the lane's piece
+  // counts of the pieces before a wave's piece q: entries of tot that it has not added yet
+  uint32_t base = 0;
+  int next = 0;
+  auto before = [&](int q) -> uint32_t {
+    for (; next < q * NW + wv; ++next) base += tot[next];
+    return base;
+  };
+  uint32_t rank[P];  // bits of the lane's piece, and from bit 8 on the count in front of it within the wave's
+  if (!exact) {      // the first `need` of the keys equal to thr become the largest key
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int col = ((q * NW + wv) * 64 + lane) * 8;
-    uint32_t g = 0, eq = 0;
+    for (int q = 0; q < P; ++q) {
+      const int left = cols - ((q * NW + wv) * 64 + lane) * 8;
+      uint32_t m = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      g |= (uint32_t)(key[q][e] >= sure) << e;
-      eq |= (uint32_t)(key[q][e] == tied) << e;
+      for (int e = 0; e < 8; ++e) m |= key[q][e] == thr ? 1u << e : 0u;
+      m &= left >= 8 ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
+      const int c = __popc(m), incl = wave_incl_scan(c);
+      rank[q] = (uint32_t)(incl - c) << 8 | m;
+      if (lane == 63) tot[q * NW + wv] = (uint32_t)incl;
     }
-    const uint32_t in = cols - col >= 8 ? 0xFFu : (cols > col ? (1u << (cols - col)) - 1u : 0u);
-    g &= in;
-    eq &= exact ? 0u : in;
-    gt[q] = g | (eq << 8);
-    __builtin_amdgcn_sched_barrier(0);
-    const int c = __popc(g) | (__popc(eq) << 16);
-    const int incl = wave_incl_scan(c);
-    excl[q] = (uint32_t)(incl - c);
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
-    if (lane == 0) {
-      tot_gt[q * NW + wv] = total & 0xFFFFu;
-      tot_eq[q * NW + wv] = total >> 16;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const int grant = need - (int)(before(q) + (rank[q] >> 8));  // to the first of the piece
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool eq = (rank[q] >> e) & 1u;
+        if (eq & ((int)__popc(rank[q] & ((1u << e) - 1u)) < grant)) key[q][e] = 0xFFFFFFFFu;
+      }
     }
+    __syncthreads();
+    base = 0;
+    next = 0;
   }
-  __syncthreads();
-  uint32_t base_gt = 0, base_eq = 0;
-  int next = 0;  // entries of the totals already added to the bases
+  const uint32_t sure = exact ? thr : thr + 1u;  // above 0, the key of columns past the end
 #pragma unroll
   for (int q = 0; q < P; ++q) {
-    for (; next < q * NW + wv; ++next) {
-      base_gt += tot_gt[next];
-      base_eq += tot_eq[next];
-    }
-    const int piece = (q * NW + wv) * 64 + lane, col = piece * 8;
-    uint32_t eq_run = base_eq + (excl[q] >> 16);
-    uint32_t p = base_gt + (excl[q] & 0xFFFFu) + min(eq_run, (uint32_t)need);  // kept values before the piece
     uint32_t m = 0;
 #pragma unroll
+    for (int e = 0; e < 8; ++e) m |= key[q][e] >= sure ? 1u << e : 0u;
+    const int c = __popc(m), incl = wave_incl_scan(c);
+    rank[q] = (uint32_t)(incl - c) << 8 | m;
+    if (lane == 63) tot[q * NW + wv] = (uint32_t)incl;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+  uint32_t bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)sure);
+  asm("" : "+s"(bound));  // the comparisons are made again: 64 masks do not fit the scalar registers
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int piece = (q * NW + wv) * 64 + lane, col = piece * 8;
+    uint32_t p = before(q) + (rank[q] >> 8);  // kept values before the piece
+#pragma unroll
     for (int e = 0; e < 8; ++e) {
-      bool kept = (gt[q] >> e) & 1u;
-      if ((gt[q] >> (8 + e)) & 1u) {
-        kept = eq_run < (uint32_t)need;
-        ++eq_run;
-      }
+      const bool kept = key[q][e] >= bound;
       // columns past the end go to a slot that nothing reads
       const uint32_t at = kept ? p : min((uint32_t)(kpad + col + e) - p, (uint32_t)(kpad + npruned + 1));
       vals[at] = (uint16_t)(raw[q][e >> 1] >> (16 * (e & 1)));
-      m |= (uint32_t)kept << e;
       p += kept ? 1u : 0u;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (piece < 4 * a.bw) reinterpret_cast<uint8_t*>(a.bitmap + row * a.bw)[piece] = (uint8_t)m;
+    if (piece < 4 * a.bw) reinterpret_cast<uint8_t*>(a.bitmap + row * a.bw)[piece] = (uint8_t)rank[q];
   }
   if (tid < kpad - K) vals[K + tid] = 0;
   if (tid == 0 && (npruned & 1)) vals[kpad + npruned] = 0;

@@ -44,6 +44,26 @@ def _streams(ew):
     return reg(sp, d.off_bitmap, d.bw), reg(sp, d.off_spec, d.sw), reg(vf, d.off_lo, d.lw), reg(vf, d.off_pruned, d.pw)
 
 
+@pytest.mark.parametrize("cols,keep", [(9, 500), (600, 3), (1030, 997), (4096, 600), (4096, 1000), (4099, 2), (9000, 900)])
+@pytest.mark.parametrize("act", [False, True])
+def test_encoder_finds_the_threshold_in_any_distribution(env, cols, keep, act):
+    """Rows on which a search between two counts has little to go by: two values, one in a thousand, ramps and
+    powers of two, subnormal and infinite values, few distinct values.  Streams are compared bit for bit."""
+    torch, B, ctx = env
+    rng = np.random.default_rng(cols + keep)
+    i = np.arange(cols)
+    W = np.stack([
+        np.where(i % 2, 0x3F80, 0x0001), np.where(i % 1000 == 7, 0x4000, 0x3C23), i % 0x7F80, (cols - i) % 0x7F80,
+        (i % 255) << 7, rng.integers(0, 128, cols), np.where(rng.random(cols) < 0.3, 0x7F80, 0xFF80),
+        rng.choice([0x3F80, 0xBF81, 0x3F82], cols), np.sort(rng.integers(0, 0x10000, cols)), np.zeros(cols, np.int64),
+    ]).astype(np.uint16)
+    a = np.where(i % 3 == 1, 1.0, np.exp2(rng.integers(-60, 60, cols))).astype(np.float32) if act else None
+    ew = B.cas_encode_weight(ctx, _dev(torch, W), keep, 4, None if a is None else torch.from_numpy(a).cuda())
+    p = O.encode_weight(W, keep, 4, a)
+    for got, want in zip(_streams(ew), (p.bitmap, p.spec, p.lo, p.pruned)):
+        np.testing.assert_array_equal(got, want)
+
+
 @pytest.mark.parametrize("cols", [1, 7, 9, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 28672, 65536, 65543])
 @pytest.mark.parametrize("keep,t,act", [(600, 4, True), (333, 0, False), (999, 7, True)])
 def test_encoder_around_the_sizes_of_its_pieces_and_waves(env, cols, keep, t, act):
