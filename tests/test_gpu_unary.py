@@ -146,6 +146,28 @@ def test_gemm_verify_unary_in_row_blocks_and_without_room(env):
     assert e.value.code == B.CAS_ENOMEM
 
 
+@pytest.mark.parametrize("cols,keep", [(33, 0), (33, 30), (33, 61), (33, 91), (40, 100), (64, 78), (64, 94), (65, 110), (2081, 500)])
+@pytest.mark.parametrize("spread", [1, 40])
+def test_codes_of_a_word_in_groups_of_four_and_what_is_left(env, cols, keep, spread):
+    """Zero to seven codes in a row and full words of them (one exponent: 32 one-bit codes to a word), and exponents
+    spread over 40 values, whose codes cross words.  Exact: each value reconstructs to itself, and the draft product
+    with a vector of one 1 is the kept, truncated value of that column."""
+    torch, B, ctx = env
+    rows = 12
+    rng = np.random.default_rng(cols + keep)
+    W = (((100 + rng.integers(0, spread, (rows, cols))) << 7) | rng.integers(0, 128, (rows, cols))).astype(np.uint16)
+    W |= rng.integers(0, 2, (rows, cols)).astype(np.uint16) << 15
+    ew = B.cas_encode_weight(ctx, _dev(torch, W), keep, 4)
+    uw = B.cas_unary_encode(ctx, ew)
+    np.testing.assert_array_equal(B.cas_unary_decode(ctx, uw, full=True).cpu().numpy().view(np.uint16), W)
+    draft = O.bf16_to_f64(O.decode_draft(O.encode_weight(W, keep, 4)))
+    for col in (0, 31, cols // 2, cols - 1):
+        x = np.zeros((1, cols), np.uint16)
+        x[0, col] = 0x3F80
+        y = B.cas_gemv_draft_unary(ctx, uw, _dev(torch, x)).cpu().numpy()
+        np.testing.assert_array_equal(y.reshape(-1).astype(np.float64), draft[:, col])
+
+
 def test_unary_empty_matrix(env):
     torch, B, ctx = env
     ew = B.cas_encode_weight(ctx, torch.empty((0, 256), dtype=torch.int16, device="cuda"), 600, 4)
