@@ -20,13 +20,14 @@ struct CodecArgs {
 // One workgroup of NW = blockDim / 64 waves formats one row; a lane owns P pieces of 8
 // consecutive columns, piece (q, wave, lane) being columns 8 ((q NW + wave) 64 + lane) ..+7, so the row and
 // the norms come in with 16-byte loads and are read from memory once: values and keys stay in registers (with 10
-// pieces, rows of more than 65536 columns, 98 of the 128 registers that sixteen waves leave a lane spill).
+// pieces, rows of more than 65536 columns, 79 of the 128 registers that sixteen waves leave a lane spill).
 //
-//   1. The threshold, a value that exactly K keys reach or the K-th largest key itself, lies between two others
-//      whose counts are known.  A sample of 64 keys gives the first of them; from there on the next candidate is
-//      where a straight line between the two counts meets K.  Seven counts find it among 4096 keys, where a search
-//      bit by bit took 22 (with norms; five instead of 15 without).  A lane counts its own keys, two instructions
-//      a key; the sum goes over the lanes, and in LDS over the waves of the row.
+//   1. The threshold is a value that exactly K keys reach, or the K-th largest key itself.  A lane counts its own keys,
+//      two instructions a key; the sum goes over the lanes, and in LDS over the waves of the row.  Long rows, and
+//      matrices of many rows with norms: it lies between two values whose counts are known; a sample of 64 keys gives
+//      the first of them, and from there on the next candidate is where a straight line between the two counts meets
+//      K.  Seven counts find it among 4096 keys, where a search bit by bit takes 19 (with norms; five instead of 16
+//      without).  The others bit by bit (search_bits).
 //   2. Where keys equal the threshold, the first in column order of them are raised above it.  Prefix sums over
 //      (piece, wave, lane), which is column order, rank the kept values.  A value is written once, as 16 bits, to its place in the
 //      row's kept or pruned list in LDS.
@@ -35,12 +36,27 @@ struct CodecArgs {
 //
 // Bound by the issue of instructions, some 45 per value, and by the start of a row, when its wave waits for its
 // loads: all of them are in flight together (a branch around each had them wait one by one, 46 us of the launch).
-// 28672 x 4096 with norms from HBM 162 us, 3.1 TB/s of input and output (268 with the search bit by bit and branched
-// loads), without 149 (226); 8192 x 12288, three waves a row, 152 (301); 28672 x 1000 58 (74).  Radix selection
+// 28672 x 4096 with norms, which is more than the caches hold, 160 us, 3.0 TB/s of input and output (283 with the search
+// bit by bit and branched loads), without 158 (234); 8192 x 14336, four waves a row, 199 (381).  Radix selection
 // through histograms in LDS, whose atomics met in the few exponents that a row holds, took 2602 us; counting
-// with ballots, which are three instructions a key, 231 instead of 170.
+// with ballots, which are three instructions a key, 231 where this took 170.
 constexpr int kSampleStep = 4;       // places of the sample on either side of the expected one: one standard deviation
 constexpr int kInterpolations = 12;  // counts after which the rest of the interval is halved
+constexpr unsigned kFewRows = 4096;  // four waves of one row each for every SIMD
+
+// Whether a row's threshold is found bit by bit.  Such a count has next to nothing to work out before it, and there are
+// at most 17 of them (34 with norms) whatever the values are; the line needs fewer on average, but some rows need as many
+// and each takes longer.  Bit by bit / by the line, us.  Rows of up to 1024 columns without norms: 512 x 256 7.8 / 8.7,
+// 28672 x 1000 61.2 / 56.4; values that are whole numbers up to 10, so that most keys are equal: 7.9 / 11.6 and
+// 64.1 / 70.2.  With norms, where such rows lack a full sample or a wave has its SIMD to itself or nearly so: 512 x 256
+// 9.1 / 10.9, 8192 x 256 21.8 / 21.8, 2048 x 1000 11.1 / 11.5 (25 % kept: 11.7 / 13.3), 4096 x 512 15.5 / 15.5 (14.8 / 16.1),
+// 8192 x 768 23.8 / 22.9, 28672 x 1000 66.3 / 58.7.  Longer rows: 256 x 2000 without norms 12.9 / 10.4, where it is only
+// such whole numbers 12.9 / 14.9; 4096 x 4096 43.2 / 32.7 and 43.2 / 42.4.
+template <int P>
+__device__ __forceinline__ bool search_bits(bool weighted, int cols) {
+  return P == 2 && (!weighted || cols < 512 || gridDim.x <= kFewRows);
+}
+
 template <int T, int P>
 __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ act, CodecArgs a) {
@@ -54,7 +70,7 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthr = blockDim.x, NW = nthr >> 6;
   const int cols = (int)a.cols, K = a.K, kpad = (K + 31) & ~31, npruned = cols - K;
-  const bool weighted = act != nullptr;
+  const bool weighted = act != nullptr && K < cols;  // norms choose among the columns
   if (blockIdx.x == 0 && tid < 64) {  // the slack kernels may over-read must hold finite values
     a.spec[a.rows * a.sw + tid] = 0;
     a.lo[a.rows * a.lw + tid] = 0;
@@ -128,7 +144,10 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
 #pragma unroll
     for (int q = 0; q < P; ++q)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) c += key[q][e] >= cand ? 1 : 0;  // two instructions; ballots took three
+      for (int e = 0; e < 8; ++e) {
+        c += key[q][e] >= cand ? 1 : 0;  // two instructions; ballots took three
+        asm("" : "+v"(c));               // one after the other: 64 masks at a time do not fit the scalar registers
+      }
     c = __builtin_amdgcn_readlane(wave_incl_scan(c), 63);
     if (NW > 1) {  // two sets of slots: one barrier per count keeps a fast wave out of the set being read
       if (lane == 0) wave_cnt[buf][wv] = c;
@@ -147,7 +166,20 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
     thr = 0xFFFFFFFFu;     // no key is that large: the largest are those of -Inf norms, 0xFF800000
     exact = true;
   } else if (K == cols) {
-    need = K - count_ge(1u);
+    need = K;
+  } else if (search_bits<P>(weighted, cols)) {
+    int c = weighted ? count_ge(1u) : K + 1;  // with norms 32 counts would find that fewer than K keys are above 0
+    if (c > K) {
+      for (int bit = weighted ? 31 : 14; bit >= 0 && !exact; --bit) {
+        const uint32_t cand = thr | (1u << bit);
+        c = count_ge(cand);
+        if (c >= K) {
+          thr = cand;
+          exact = c == K;
+        }
+      }
+    }
+    if (!exact) need = K - count_ge(thr + 1u);
   } else {
     // the sample: a key of every lane (of some lanes, where several waves share the row), from all its pieces
     const int per = 64 / NW;
@@ -180,7 +212,11 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
     uint32_t lo = 0, hi = top;
     int clo = cols, chi = 0;
     const int mid = (int)((float)K / (float)cols * (float)n);
-    int below = kSampleStep, above = kSampleStep;
+    int below = kSampleStep, above = kSampleStep, last = 0;
+    // Without norms few keys may hold all the values, and one end of the line would stay where it is for many counts:
+    // its weight is halved with every count that the other end moves again.
+    const float stay = weighted ? 1.f : 0.5f;
+    float wlo = 1.f, whi = 1.f;
     for (int it = 0; hi - lo > 1u; ++it) {
       uint32_t cand;
       if (lo == 0u && mid + below < n + kSampleStep) {
@@ -192,7 +228,8 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
       } else if (lo == 0u || hi == top || it >= kInterpolations) {
         cand = lo + ((hi - lo) >> 1);
       } else {
-        cand = lo + (uint32_t)((float)(hi - lo) * ((float)(clo - K) / (float)(clo - chi)));
+        const float dlo = (float)(clo - K) * wlo, dhi = (float)(K - chi) * whi;
+        cand = lo + (uint32_t)((float)(hi - lo) * (dlo * __builtin_amdgcn_rcpf(dlo + dhi)));
       }
       cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(max(cand, lo + 1u), hi - 1u));
       const int c = count_ge(cand);
@@ -201,9 +238,15 @@ __global__ __launch_bounds__(1024) void encode_rows_kernel(const uint16_t* __res
         clo = c;
         exact = c == K;
         if (exact) break;
+        wlo = 1.f;
+        if (last > 0) whi *= stay;
+        last = 1;
       } else {
         hi = cand;
         chi = c;
+        whi = 1.f;
+        if (last < 0) wlo *= stay;
+        last = -1;
       }
     }
     thr = lo;

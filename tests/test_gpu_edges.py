@@ -64,6 +64,31 @@ def test_encoder_finds_the_threshold_in_any_distribution(env, cols, keep, act):
         np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("cols", [64, 511, 512, 513, 1000, 1024])
+@pytest.mark.parametrize("keep", [1, 250, 600, 1000])
+def test_encoder_finds_the_same_threshold_by_either_search(env, cols, keep):
+    """4097 rows with norms are searched along a line between two counts from 512 columns on, 4096 rows and less bit by
+    bit: the streams of the whole matrix are those of its parts, and of the oracle where a distribution comes first."""
+    torch, B, ctx = env
+    rows = 4097
+    rng = np.random.default_rng(cols * 7 + keep)
+    W = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32).view(np.uint32) >> 16
+    kinds = [np.where(rng.random(cols) < 0.5, 0, 0x3F80), np.zeros(cols), rng.choice([0x3F80, 0xBF81, 0x3F82], cols),
+             np.round(rng.standard_normal(cols) * 3).astype(np.float32).view(np.uint32) >> 16, np.full(cols, 0x7F80),
+             rng.integers(0, 128, cols), np.arange(cols) % 0x7F80, np.where(np.arange(cols) % 100 == 7, 0x4000, 0)]
+    for k, row in enumerate(kinds):
+        W[k::97] = row
+    W = W.astype(np.uint16)
+    a = np.exp2(rng.integers(-3, 4, cols)).astype(np.float32)
+    ad, Wd = torch.from_numpy(a).cuda(), _dev(torch, W)
+    whole = _streams(B.cas_encode_weight(ctx, Wd, keep, 4, ad))
+    parts = [_streams(B.cas_encode_weight(ctx, Wd[i:j], keep, 4, ad)) for i, j in ((0, 4096), (4096, rows))]
+    p = O.encode_weight(W[:len(kinds)], keep, 4, a)
+    for got, one, two, want in zip(whole, *parts, (p.bitmap, p.spec, p.lo, p.pruned)):
+        np.testing.assert_array_equal(got, np.concatenate([one, two]))
+        np.testing.assert_array_equal(got[:len(kinds)], want)
+
+
 @pytest.mark.parametrize("cols", [1, 7, 9, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 28672, 65536, 65543])
 @pytest.mark.parametrize("keep,t,act", [(600, 4, True), (333, 0, False), (999, 7, True)])
 def test_encoder_around_the_sizes_of_its_pieces_and_waves(env, cols, keep, t, act):
