@@ -9,7 +9,7 @@
 //
 // One workgroup handles one kv head and one page (64 positions) of the sequence:
 //   1. thread (token r, word j) decodes its 32 channels of K into a bf16 tile in LDS, ordered by the position in the
-//      word so that the scattered writes of a wave do not meet in banks;
+//      word so that no more than two of the scattered writes of a wave meet in a bank;
 //   2. each wave multiplies its 16 tokens with the query rows (grouped-query: the query heads
 //      of the group x columns share the kv head) by 16x16x16 bf16 MFMA; the scaled, masked
 //      scores stay in the MFMA result registers;

@@ -92,8 +92,8 @@ constexpr int kQP = 136;         // Q row pitch (bf16)
 // side for K, the tokens of a word for V (row 0 takes what lanes without a value left write).  At most two lanes of a wave
 // meet in a bank, whatever positions they are at; with rows of a token (K) or a channel (V) in order the writes of the
 // walks met in banks for half of the cycles in which the LDS was active, and it was active for 78 % of the kernel's
-// (draft form, four sequences of up to 32768 positions: 80 us, 76 with this order; 62 % and 4.4 cycles a write, which is
-// what one takes without any conflict).
+// (draft form, four sequences of up to 32768 positions: 80 us, 76 with this order; the LDS is active for 63 % of the
+// kernel's cycles, 37 % of that for the second lane of a bank).
 constexpr int kPos = 64;          // values of a position
 constexpr int kWaveKV = 33 * kPos;
 constexpr int kPP = 72;          // probability row pitch (bf16)
@@ -158,7 +158,9 @@ __device__ __forceinline__ void put_rows(float* dst, const float (&v)[4]) {
 // the partial results (masks, maxima, exponentials, rounding, sums) is done row by row of a group: few query rows are
 // dealt to the groups, query row rr to row 4 (rr / E) + rr % E, so that R <= 4 MT E rows cost E of the four.
 // One column of the 8B heads (4 rows) over four sequences of up to 32768 positions 76 -> 70 us, over 8192 positions 12.5
-// -> 11.8 (19 % fewer vector instructions); 5 columns (20 rows of 32) 6 % fewer instructions, 2 % fewer cycles.
+// -> 11.8 (19 % fewer vector instructions).  5 columns (20 rows of 32; partial results and merge) 24.3 -> 23.5 us over
+// 8192 positions, 12.0 -> 11.1 over 1000, draft form 21.2 -> 20.7 and 10.9 -> 10.1; 17 to 24 rows of all head shapes,
+// either cache, 1 to 5 %.  9 to 12 rows of one tile and 33 to 36 of three have no form of their own (not tried).
 template <int MT, int E, bool FULL, int T, bool MX, class BATCH>
 __global__ __launch_bounds__(256) void attn_partial_kernel(BATCH batch) {
   const AttnArgs a = attn_args_of(batch, blockIdx.z);

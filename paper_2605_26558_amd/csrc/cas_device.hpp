@@ -352,16 +352,6 @@ struct WordWindows {
   }
 };
 
-// One-shot form: load the windows of a word and decode it.
-template <int T, bool FULL, class W>
-__device__ __forceinline__ void decode_word(uint32_t m, uint32_t pm, uint32_t p, uint32_t u,
-                                            const uint32_t* __restrict__ sp_row, const uint32_t* __restrict__ lo_row,
-                                            const uint32_t* __restrict__ pr_row, W&& write) {
-  WordWindows<T, FULL> w;
-  w.load(p, u, sp_row, lo_row, pr_row);
-  w.decode(m, pm, write);
-}
-
 template <int CTRL>
 __device__ __forceinline__ int quad_dpp(int v) {
   return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);

@@ -20,11 +20,11 @@ constexpr int kWideCols = 256;  // columns of X per workgroup
 // the one runs under the matrix operations of the other.  Blocks come part by part (part p of
 // Q has the blocks p, p + Q, ...), which makes a part one running sum; the counts of kept values in front of every block of
 // every row are made at the start (pre).
-// Bound by waiting, not by one unit.  Counters of 28672 x 4096 with 508 columns (370 us): of the 703 K cycles
+// Bound by waiting, not by one unit.  Counters of 28672 x 4096 with 508 columns (386 us): of the 702 K cycles
 // that a CU is busy, the matrix operations (8 K flops in 16 cycles) take 229 K on each SIMD and the other
-// vector instructions, the decode's 14 or so per value and 256 columns above all, 218 K, 64 % together; LDS is active
-// for 253 K; each of the two waves of a SIMD waits for 42 % of its cycles (one barrier per step, operands
-// from memory).  The CUs are busy for 84 % of the launch (896 workgroups, one per CU at a time).
+// vector instructions, the decode's 14 or so per value and 256 columns above all, 175 K, 58 % together; LDS is active
+// for 177 K (a quarter of it conflicts); each of the two waves of a SIMD waits for 41 % of its cycles (one barrier per
+// step, operands from memory).  The CUs are busy for 85 % of the launch (896 workgroups, one per CU at a time).
 // With nothing else on the chip the 16x16x16 operations reach 668 TFLOP/s from two waves per SIMD (30 cycles
 // an operation at 2.4 GHz) and 736 from eight (17 cycles, but the clock falls to 1.5 GHz under that load).
 template <int T, int RT, bool MX>
@@ -288,9 +288,9 @@ static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
 
 // The parts are those the verification GEMM cuts the rows of the WHOLE matrix (a.yld rows) into.  Rows per
 // workgroup: 64, or 32 where 64 would leave a third of the CUs or more without a workgroup.  A prompt through one
-// layer, us, by this rule / with 32 rows throughout / with 64: 8B shape 65 tokens 655 / 664 / 835, 257 tokens
-// 840 / 876 / 1013, 513 tokens 1170 / 1213 / 1302; 70B shape 65 tokens 1812 / 1760 / 2113, 257 tokens 2206 / 2240 /
-// 2461, 513 tokens 4547 / 5013 / 4799.
+// layer, us, by this rule / with 32 rows throughout / with 64: 8B shape 65 tokens 466 / 482 / 633, 257 tokens
+// 717 / 746 / 825, 513 tokens 940 / 975 / 1070; 70B shape 65 tokens 1335 / 1315 / 1574, 257 tokens 2249 / 2674 /
+// 2244, 513 tokens 3784 / 4268 / 4007.
 template <bool MX>
 static int launch_wide(cas_ctx* ctx, const VerifyArgs& a, int t) {
   const int q = verify_parts(a.yld, a.cols);

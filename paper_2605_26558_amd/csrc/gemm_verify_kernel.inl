@@ -32,7 +32,8 @@ constexpr int kLongRow = 8192;           // columns from which it then gets sixt
 constexpr int kNowhere = 0x7FFFF000;     // a byte offset past the records of every stream: reads as 0, fetches nothing
 // A block of 16 rows x 128 columns in LDS: [1 + 32 positions][16 rows][4 words] values, position p of the four bitmap
 // words of a row side by side (row 0 takes what lanes without a value left write).  Whatever positions the lanes of a
-// wave are at, at most the two lanes that share a word of their position's row meet in a bank: with a row's values in
+// wave are at, at most the two lanes that share a word of their position's row meet in a bank (such pairs are 5.0 of the
+// 12.5 M cycles in which the LDS is active, 28672 x 4096 with 20 columns): with a row's values in
 // column order the writes of the walks met in banks for 73 % of the cycles in which the LDS was active, and it was
 // active for 79 % of the kernel's (28672 x 4096, 7 columns).  The four values that lie together are one lane's operand
 // of a product; product kk takes position 8 mq + (kk ^ (mq & 1)) in lane group mq, so that the reads of two groups
@@ -280,7 +281,9 @@ static int launch_q(cas_ctx* ctx, const VerifyArgs& a, int t) {
 // is then shortest and the barrier waits for the fewest waves), more where there are hardly more groups than CUs, so
 // that each CU has waves to switch between.  7 columns, 4 / 8 / 16 waves, us: 28672 x 4096 68 / 80 / 88, 8192 x 4096
 // 24.0 / 24.0 / 26.4, 6144 x 4096 22.3 / 22.9 / 25.0, 5120 x 4096 21.6 / 22.2 / 23.8, 4096 x 4096 17.0 / 14.4 / 14.2,
-// 3072 x 4096 16.7 / 13.7 / 14.1, 4096 x 14336 50 / 42 / 40, 1024 x 8192 28.8 / 22.7 / 21.0, 512 x 256 3.9 / 5.1 / 7.9.
+// 3072 x 4096 16.7 / 13.7 / 14.1, 4096 x 14336 50 / 42 / 40, 1024 x 8192 28.8 / 22.7 / 21.0, 512 x 1024 5.3 / 4.7 / 6.7.
+// The line by row groups is not the best one for rows of up to 512 columns, which a step of four waves covers: 512 x 512
+// takes 3.8 / 4.9 / 6.7, 512 x 256 4.1 / 4.9 / 6.7 (6.3 with the kernel before).
 static inline int verify_parts(int64_t rows, int64_t cols) {
   const int64_t groups = (rows + 15) / 16;
   return groups >= kFewGroups ? 4 : cols >= kLongRow ? 16 : 8;

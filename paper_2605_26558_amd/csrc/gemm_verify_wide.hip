@@ -1,4 +1,5 @@
-// Verification GEMM for 9 to 32 columns on the raw form: instantiates the wide forms of the kernel
+// Verification GEMM for 17 to 32 columns on the raw form: instantiates the forms of the kernel with two
+// blocks of output columns
 // (see gemm_verify_kernel.inl) in a translation unit of their own.
 #include "gemm_verify_kernel.inl"
 

@@ -641,17 +641,21 @@ int launch_unary_expand(cas_ctx* ctx, const cas_udesc& u, const void* uspec, int
 // x of all of them does not fit the LDS, column by column.  Every output has the bits that the kernel above
 // and the raw form give: all of them walk a row in the same order.  CAS_ENOMEM where the caller is to take
 // the kernel that decodes the codes itself, column by column: for one column of a matrix whose rows leave that
-// kernel two workgroups per CU or more (28672 x 4096: 68 us, through the workspace 108; 4096 x 4096
-// 17.0 / 21.5; with one workgroup per CU, 4096 x 14336, 56 / 48), and where the workspace holds too few rows.
+// kernel two workgroups per CU or more (28672 x 4096 68 us, 18 more through the workspace, 4096 x 4096 17 and 6 more;
+// with one workgroup per CU, 4096 x 14336, 56 and 8 less), and where the workspace holds too few rows.
 // A block costs two launches, some 10 us, and a small one leaves CUs idle; what there is to win grows with
-// the rows, their length (the kernel took some 0.38 ns, now 0.35, per row and 1000 + 0.5 columns, twice that with one
+// the rows, their length (the kernel takes some 0.35 ns per row and 1000 + 0.5 columns, twice that with one
 // workgroup per CU) and the columns after the first, or all of them with one workgroup per CU.  Total of a
 // small pass, in the kernel / through blocks of so many rows, us:
-//   28672 x 4096, two columns  174 / 165 (9558), 179 (7168);  four  309 / 282 (2390), 324 (1792)
-//   28672 x 1024, two columns  101 /  91 (14336), 102 (9558); four  170 / 156 (3584), 195 (2390)
-//   128000 x 2048, two columns 359 / 325 (16000), 379 (10667)
-//   16384 x 8192, one column   147 / 146 (8192), 163 (5462);  two   252 / 248 (2048), 324 (1366)
-//   8192 x 14336, one column   193 / 185 (2731), 206 (2048);  four  579 / 491 (683), 616 (512)
+//   28672 x 4096, two columns  197 / 177 (9558), 191 (7168);  four  336 / 251 (3584), 288 (2390), 327 (1792)
+//   28672 x 1024, two columns  102 /  92 (14336), 103 (9558); four  173 / 163 (3584), 200 (2390)
+//   128000 x 2048, two columns 361 / 339 (16000), 366 (10667)
+//   16384 x 8192, one column   143 / 161 (16384), 156 (8192); two   239 / 198 (4096), 250 (2048)
+//   8192 x 14336, one column   183 / 196 (8192), 186 (4096), 184 (2731), 225 (2048); two 288 / 238 (2048), 288 (1366);
+//                 four columns 502 / 338 (1366), 499 (683), 624 (512)
+//   4096 x 14336, one column   131 / 124 (4096), 142 (2048);  11003 x 12288, one column 209 / 205 (5502)
+// The lines below keep to the safe side: with two workgroups per CU blocks win from a gain between 30 and 42 on; with
+// one, a single column of a matrix that the workspace holds whole is within 5 % either way where the rows are many.
 static int unary_draft_rows(cas_ctx* ctx, const cas_udesc& u, const void* uspec, const uint16_t* x, int batch, float* y,
                             int epi, uint16_t* out16) {
   const cas_wdesc& d = u.base;

@@ -123,7 +123,7 @@ def test_gemm_verify_matches_oracle_and_is_column_invariant(env, rows, cols, kee
 @pytest.mark.parametrize("rows,cols,keep,t", [(70, 4096, 600, 4), (33, 2500, 250, 0), (300, 300, 1000, 7), (20, 9000, 600, 3)])
 @pytest.mark.parametrize("ncols", [9, 16, 20, 32])
 def test_gemm_verify_many_columns(env, rows, cols, keep, t, ncols):
-    """9 to 32 columns (X staged per decode step; a second block of output columns above 16):
+    """9 to 32 columns (a second block of output columns above 16):
     against the oracle, and every column bit-identical to the one-column call."""
     torch, B, ctx = env
     print(f"case rows={rows} cols={cols} keep={keep} t={t} ncols={ncols}", flush=True)
