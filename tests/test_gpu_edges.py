@@ -542,3 +542,53 @@ def test_unary_draft_pass_refuses_a_layout_that_is_not_the_matrix_s(env, hidden,
         else:
             B.cas_draft_step_multi(ctx, model, kv, list(range(n_seqs)), [0] * n_seqs, token, out)
     assert err.value.code == B.CAS_EINVAL
+
+
+@pytest.mark.parametrize("keep,t,exp_mode", [(5, 0, 0), (117, 3, 0), (600, 5, 0), (631, 1, 0), (992, 7, 0), (996, 2, 0),
+                                             (5, 1, 2), (250, 6, 2), (605, 3, 2), (992, 0, 2)])
+@pytest.mark.parametrize("pos0,ntok", [(0, 1), (3, 2), (14, 5), (62, 67), (47, 17)])
+def test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok):
+    """One to 127 kept values, fields of any width, runs that begin and end inside the four rows of a wave and the
+    sixteen of a workgroup: the rows of the run bit for bit like the oracle's, every other byte of the pools as before;
+    and the same from vectors that lie at odd multiples of two bytes."""
+    torch, B, ctx = env
+    heads = 3
+    rng = np.random.default_rng(keep + 7 * pos0 + ntok)
+    K, V = (synth.kv_tensor(ntok, heads, 128, seed=s) for s in (31, 32))
+    K[0, 0, :] = 0x3F81                                              # equal magnitudes: the first columns are kept
+    K[0, 1, :] = rng.choice([0x3F80, 0xBF80, 0x3F81], 128)           # the line falls among equals, with either sign
+    K[0, 2, :] = rng.integers(0, 0x10000, 128)                       # any pattern: NaN, infinities, subnormal values
+    V[0, 0, :] = rng.choice([0x7F80, 0xFF80, 0x7FFF, 0xFFFF, 0x0000, 0x8000], 128)
+    kv = B.KVCache(ctx, 1, heads, n_pages=4, max_seqs=1, max_pages_per_seq=3, keep_permille=keep, trunc_bits=t,
+                   page_table=torch.tensor([[2, 0, 3]], dtype=torch.int32), exp_mode=exp_mode)
+    d, page_of = kv.desc, [2, 0, 3]
+    packed = [O.encode_kv(x.reshape(-1, 128), keep, t) for x in (K, V)]
+    coded = [O.to_mx(p) for p in packed] if exp_mode else None
+    for shift in (0, 1):
+        kv.spec_pool.fill_(0xA5)
+        kv.verif_pool.fill_(0xA5)
+        spec, verif = kv.spec_pool.cpu().numpy(), kv.verif_pool.cpu().numpy()
+        for tok in range(ntok):
+            page, row = page_of[(pos0 + tok) // 64], (pos0 + tok) % 64
+            for which in range(2):
+                for head in range(heads):
+                    tile, i = (page * 2 + which) * heads + head, tok * heads + head
+                    ts = spec[tile * d.tile_spec_bytes: (tile + 1) * d.tile_spec_bytes].view("<u4")
+                    tv = verif[tile * d.tile_verif_bytes: (tile + 1) * d.tile_verif_bytes].view("<u4")
+                    ts[row * 4: row * 4 + 4] = packed[which].bitmap[i]
+                    off = 256
+                    if exp_mode:
+                        ts[256 + row: 257 + row] = np.ascontiguousarray(coded[which].sexp[i]).view("<u4")
+                        off = 320
+                    fields, lo = (coded[which].field, coded[which].lo) if exp_mode else (packed[which].spec, packed[which].lo)
+                    ts[off + row * d.sw: off + (row + 1) * d.sw] = fields[i]
+                    tv[row * d.lw: (row + 1) * d.lw] = lo[i]
+                    tv[64 * d.lw + row * d.pw: 64 * d.lw + (row + 1) * d.pw] = packed[which].pruned[i]
+        def at(x):
+            buf = torch.empty(x.size + 1, dtype=torch.int16, device="cuda")
+            buf[shift: shift + x.size] = _dev(torch, x).flatten()
+            return buf[shift: shift + x.size].view(x.shape)
+        B.cas_kv_set_len(kv, 0, pos0)
+        B.cas_kv_append(ctx, kv, 0, 0, at(K), at(V))
+        np.testing.assert_array_equal(kv.spec_pool.cpu().numpy(), spec)
+        np.testing.assert_array_equal(kv.verif_pool.cpu().numpy(), verif)
