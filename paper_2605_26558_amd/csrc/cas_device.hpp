@@ -87,6 +87,14 @@ __device__ __forceinline__ uint32_t drop_lowest(uint32_t m) {
   return m;
 }
 
+// A copy made here and now.  Where a loop carries a value that is loaded one turn ahead, the compiler otherwise copies it
+// at the end of the turn, and the wait for that load, which is the last of its turn, is a wait for all of them.
+__device__ __forceinline__ uint32_t taken(uint32_t v) {
+  uint32_t r;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
+  return r;
+}
+
 // Read a `width`-bit field (1..32 bits) at bit offset `bit` of a little-endian word stream
 // (generic path).  The word after the field's first one is always read as well and the two are
 // funnel-shifted: no 64-bit arithmetic, no divergent second load.  Every stream region ends

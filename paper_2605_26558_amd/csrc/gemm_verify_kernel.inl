@@ -7,7 +7,7 @@
 
 namespace cas {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -28,7 +28,7 @@ struct VerifyArgs {
 };
 
 constexpr int kFewGroups = 300;          // row groups below which a matrix gets more waves per row group
-constexpr int kLongRow = 8192;           // columns from which it then gets sixteen
+constexpr int kOneEach = 256;            // row groups up to which every CU has one at most
 constexpr int kNowhere = 0x7FFFF000;     // a byte offset past the records of every stream: reads as 0, fetches nothing
 // A block of 16 rows x 128 columns in LDS: [1 + 32 positions][16 rows][4 words] values, position p of the four bitmap
 // words of a row side by side (row 0 takes what lanes without a value left write).  Whatever positions the lanes of a
@@ -49,7 +49,10 @@ constexpr int kBlockVals = 33 * kPosPitch;
 // long and a line was fetched 1.4 times on average.  X goes from memory to the operand registers, eight consecutive
 // columns per lane, word and load (which columns meet in a product is free as long as both operands agree): staged in
 // LDS it cost a wave a round trip per staging with nothing else to do.  NB: blocks of 16 output columns (MFMA N = 16);
-// every column is computed by the same operations whichever block and whatever company it has.
+// every column is computed by the same operations whichever block and whatever company it has.  Products of 32 columns
+// (16x16x32): twice the rate of 16x16x16, which the wide GEMM needs; here within 1 % either way.  The parts of a row are
+// added two by two and the pairs in order: relative error against 64 bits over 40 shapes of all sizes 1.07e-7 with the
+// present parts, 1.12e-7 with products of 16 columns and the parts one after the other.
 // Loads run half a step ahead: the pruned values of a step are fetched while its kept values are placed, the kept
 // fields of the next step while the pruned values are placed; X of a step before its decode.  All are issued on every
 // path: where a load may or may not have been issued, the wait for an older one waits for it as well.
@@ -199,20 +202,21 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
     if (x_odd) align_x();
     if ((s * Q + wv) * 128 + 128 > a.cols) trim_x(s);
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      const bf16x4 av = *reinterpret_cast<const bf16x4*>((kk & 1 ? a_odd : a_even) + (s & 1) * TILE + kk * kPosPitch);
-      const uint32_t sel = kk & 1 ? sel_odd : sel_even;
+    for (int w = 0; w < 4; ++w) {
+      const u32x2 a0 = *reinterpret_cast<const u32x2*>(a_even + (s & 1) * TILE + 2 * w * kPosPitch);
+      const u32x2 a1 = *reinterpret_cast<const u32x2*>(a_odd + (s & 1) * TILE + (2 * w + 1) * kPosPitch);
+      const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{a0.x, a0.y, a1.x, a1.y});
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const u32x4* f = xf[nb];
-        const u32x2 bv = {__builtin_amdgcn_perm(f[1][kk >> 1], f[0][kk >> 1], sel),
-                          __builtin_amdgcn_perm(f[3][kk >> 1], f[2][kk >> 1], sel)};
-        C[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, __builtin_bit_cast(bf16x4, bv), C[nb], 0, 0, 0);
+        const u32x4 bv = {__builtin_amdgcn_perm(f[1][w], f[0][w], sel_even), __builtin_amdgcn_perm(f[3][w], f[2][w], sel_even),
+                          __builtin_amdgcn_perm(f[1][w], f[0][w], sel_odd), __builtin_amdgcn_perm(f[3][w], f[2][w], sel_odd)};
+        C[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bv), C[nb], 0, 0, 0);
       }
     }
   }
 
-  // ---- add the Q partial tiles of each row group in part order; C[i][n]: i = 4*(lane/16) + e, n = lane%16
+  // ---- add the Q partial tiles of each row group, pairs of parts in order; C[i][n]: i = 4*(lane/16) + e, n = lane%16
   __syncthreads();
   float* red = reinterpret_cast<float*>(lds);  // [NB][Q][64][4], reuses the tiles
 #pragma unroll
@@ -222,9 +226,10 @@ __global__ __launch_bounds__(64 * Q, 4) void gemm_verify_kernel(VerifyArgs a) {
   for (int nb = 0; nb < NB; ++nb) {
     const int col = 16 * nb + mi;
     if (wv != 0 || col >= a.ncols) continue;
-    f32x4 s = *reinterpret_cast<f32x4*>(red + (nb * Q * 64 + lane) * 4);
+    auto part = [&](int w) { return *reinterpret_cast<f32x4*>(red + ((nb * Q + w) * 64 + lane) * 4); };
+    f32x4 s = part(0) + part(1);
 #pragma unroll
-    for (int w = 1; w < Q; ++w) s += *reinterpret_cast<f32x4*>(red + ((nb * Q + w) * 64 + lane) * 4);
+    for (int w = 2; w < Q; w += 2) s += part(w) + part(w + 1);
     if (a.epi == 0) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -278,15 +283,17 @@ static int launch_q(cas_ctx* ctx, const VerifyArgs& a, int t) {
 // Waves per row group = parts that a row's columns are cut into.  The choice depends on the shape of the WHOLE matrix
 // (not on the number of columns or on the block of rows a launch covers): it fixes the order in which a row's partial
 // sums are added, and a column must get the same bits in every call.  Four where the row groups fill the chip (a step
-// is then shortest and the barrier waits for the fewest waves), more where there are hardly more groups than CUs, so
-// that each CU has waves to switch between.  7 columns, 4 / 8 / 16 waves, us: 28672 x 4096 68 / 80 / 88, 8192 x 4096
-// 24.0 / 24.0 / 26.4, 6144 x 4096 22.3 / 22.9 / 25.0, 5120 x 4096 21.6 / 22.2 / 23.8, 4096 x 4096 17.0 / 14.4 / 14.2,
-// 3072 x 4096 16.7 / 13.7 / 14.1, 4096 x 14336 50 / 42 / 40, 1024 x 8192 28.8 / 22.7 / 21.0, 512 x 1024 5.3 / 4.7 / 6.7.
-// The line by row groups is not the best one for rows of up to 512 columns, which a step of four waves covers: 512 x 512
-// takes 3.8 / 4.9 / 6.7, 512 x 256 4.1 / 4.9 / 6.7 (6.3 with the kernel before).
+// is then shortest and the barrier waits for the fewest waves) and for rows that one step of theirs covers.  Else more, so
+// that each CU has waves to switch between: sixteen where a CU has one group and no half of a step is wasted, unless there
+// are four steps or more.  5 columns, matrices read in turn, 4 / 8 / 16 waves, us: 4096 rows of 512 columns 5.0 / 5.4 /
+// 7.0, 1024 6.0 / 5.4 / 7.2, 2048 9.0 / 7.7 / 7.0, 3072 12.8 / 10.4 / 12.2, 4096 15.8 / 12.6 / 12.3, 6144 22.3 / 17.0 /
+// 16.4; 1024 rows of 1024 5.5 / 5.0 / 6.9, 2048 8.6 / 7.0 / 6.6, 3072 11.8 / 9.2 / 10.4, 4096 14.8 / 11.3 / 10.0, 6144
+// 21.3 / 15.8 / 13.5; 4700 rows (294 groups) of 512 5.0 / 6.9 / 12.2, 4096 19.3 / 18.8 / 21.4, 6144 27.6 / 26.1 / 28.9;
+// 8192 rows of 512 5.3 / 7.0 / 12.5, 4096 20.3 / 20.0 / 23.1.
 static inline int verify_parts(int64_t rows, int64_t cols) {
-  const int64_t groups = (rows + 15) / 16;
-  return groups >= kFewGroups ? 4 : cols >= kLongRow ? 16 : 8;
+  const int64_t groups = (rows + 15) / 16, steps8 = (cols + 1023) / 1024, steps16 = (cols + 2047) / 2048;
+  if (groups >= kFewGroups || cols <= 512) return 4;
+  return groups <= kOneEach && 17 * steps16 < 10 * steps8 ? 16 : 8;
 }
 
 template <int NB, bool MX>

@@ -131,9 +131,11 @@ def test_encoder_of_more_rows_than_a_grid_holds(env):
         assert torch.equal(buf[off: off + 4 * rows].view(torch.int32), want)
 
 
-WIDE_SHAPES = {  # hidden, query heads, kv heads, feed-forward: 8 parts per row of every matrix; 4 parts (gate/up) and 16 (down)
+WIDE_SHAPES = {  # hidden, query heads, kv heads, feed-forward: 4 parts per row, 8 (down); 4 and 16 (out, down)
     "a": (264, 4, 2, 520, 400 << 10),
     "b": (200, 14, 2, 8200, 1200 << 10),
+    # 16 parts (qkv, out), 4 (gate/up, 64 rows a workgroup, 89 groups of them), 8 (down); the last run of a row is a part of one
+    "c": (3900, 16, 4, 2840, 1600 << 10),
 }
 
 
@@ -204,6 +206,13 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
         got.append((kv.spec_pool.clone(), kv.verif_pool.clone(), logits))
     for narrow, wide in zip(*got):
         assert torch.equal(narrow, wide)
+
+
+@pytest.mark.parametrize("form,kv_form,keep,t", [("raw", "raw", 600, 4), ("shared", "raw", 700, 1)])
+@pytest.mark.parametrize("before,n", [(0, 129), (70, 257), (3, 500)])
+def test_prompt_in_chunks_over_all_numbers_of_parts(env, wide_models, form, kv_form, keep, t, before, n):
+    """Rows cut into 4, 8 and 16 parts, two column blocks, workgroups of 32 and of 64 rows: the bits of narrow passes."""
+    test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, "c", form, kv_form, keep, t, before, n)
 
 
 @pytest.mark.parametrize("ws", [4 << 20, 5 << 20, 6 << 20, 8 << 20])
