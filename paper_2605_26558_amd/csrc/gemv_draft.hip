@@ -10,7 +10,8 @@
 // walks the set bits of its word: field i of the window belongs to the i-th set bit.  Placing
 // a field at the top of a 32-bit register yields the fp32 value of the zero-padded bf16.
 // x sits in LDS as fp32 in segments of 1+32 entries per bitmap word; entry 0 of a segment is
-// 0.0, so a lane that has run out of set bits (bit position -1) multiplies by zero.
+// 0.0, so a lane that has run out of set bits (bit position -1) multiplies by zero (one column of up to 4096 values:
+// 256 bytes from position to position, FAR in the kernel).
 // The (row, chunk) items of a wave run through a three-stage software pipeline: bitmap word of
 // item q+2, prefix + window loads of item q+1, arithmetic of item q.
 #include "gemv_draft_kernel.inl"
@@ -21,6 +22,9 @@ namespace cas {
 // form at every size measured (XStage); wider rows keep to bf16.
 template <int T, int NB>
 static int launch_nb(cas_ctx* ctx, const GemvArgs& a, int grid) {
+  if constexpr (NB == 1) {
+    if (const size_t far = gemv_far_bytes(ctx, a.bw)) return launch_gemv_instance<T, 1, false, false, true>(ctx, a, grid, far);
+  }
   const size_t lds = gemv_lds_bytes(a.bw, NB, false);
   if (lds <= (size_t)ctx->lds_max) return launch_gemv_instance<T, NB, false, false>(ctx, a, grid, lds);
   if constexpr (NB > 1) return launch_gemv_instance<T, NB, false, true>(ctx, a, grid, gemv_lds_bytes(a.bw, NB, true));

@@ -65,6 +65,19 @@ __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the 
   const int w = col >> 5;
   return (((w >> 6) * kXRows + 1 + (col & 31)) * 64 + (w & 63)) * NB;
 }
+// FAR: one column of up to 4096 values, a block of 64 KB per chunk that begins at a multiple of 64 KB.  A position lies
+// 256 bytes from the next, so it is the second byte of the address, and the bit search writes it there itself: one
+// operation where the search and the address took two, of four cycles each (same bits).  A lane that has run out writes 255, the row
+// of zeros at the end of the block.  The 55 KB between are free: the sums of the norm and the table of
+// magnitudes lie there.  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 19.98 -> 19.59
+// ms, over shared exponents (8 layers) 6.31 -> 6.14, 4096 x 4096 at 25 % 5.02 -> 4.94 us.
+constexpr int kFarChunk = 64 << 10, kFarRed = 8 << 10, kFarTab = 16 << 10;  // bytes
+__device__ __forceinline__ int far_row(int chunk, int row) { return chunk * (kFarChunk / 4) + row * 64; }
+__device__ __forceinline__ int far_index(int col) { return far_row(col >> 11, col & 31) + ((col >> 5) & 63); }
+// the position of the lowest set bit of m (255 if there is none) in the second byte of addr
+__device__ __forceinline__ void put_lowest_bit(uint32_t& addr, uint32_t m) {
+  asm("v_ffbl_b32_sdwa %0, %1 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD" : "+v"(addr) : "v"(m));
+}
 template <bool XH>
 struct XStage {
   using type = float;
@@ -87,15 +100,16 @@ struct XStage<true> {
 // descriptor as well).  The table of a small T is long enough for gathers of a wave to meet in a bank, which eats
 // some of the gain but not all: 28672 x 4096 33.1 -> 30.4 us at T = 0 (2.3 conflict cycles per LDS instruction),
 // 33.6 -> 28.7 at T = 2 (1.6), 33.6 -> 28.0 at T = 4 (none); 4096 x 4096 7.1 -> 7.1, 6.6, 6.5.
-template <int T, int NB, bool MX, bool XH>
+template <int T, int NB, bool MX, bool XH, bool FAR = false>
 __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   constexpr int FW = MX ? 9 - T : 16 - T;
   using XS = XStage<XH>;
   using XT = typename XS::type;
+  static_assert(!FAR || (NB == 1 && !XH), "one column as fp32");
   extern __shared__ __attribute__((aligned(16))) uint8_t xs_raw[];
   // shared-exponent form: the table of signed magnitudes in front of x
-  const uint8_t* const mag_tab = xs_raw;
-  XT* xs = reinterpret_cast<XT*>(xs_raw + (MX ? kMagTabBytes<FW> : 0));
+  uint8_t* const mag_tab = xs_raw + (FAR ? kFarTab : 0);
+  XT* xs = reinterpret_cast<XT*>(xs_raw + (MX && !FAR ? kMagTabBytes<FW> : 0));
   const int tid = threadIdx.x;
   const int nchunk = (a.bw + 63) >> 6;
   const int nseg = nchunk * 64;
@@ -160,16 +174,27 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     for (int j = 0; j < FW; ++j) win[j] = __builtin_amdgcn_alignbit(w.d[j + 1], w.d[j], w.sh);
     uint32_t m = w.m;
     const XT* xb = xs + ((c.chunk * kXRows + 1) * 64 + lane) * NB;
+    uint32_t far[4];
+    if constexpr (FAR) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);  // LDS begins with x
+    }
     float accw[NB];  // shared-exponent form: unscaled sum of the lane's word
 #pragma unroll
     for (int b = 0; b < NB; ++b) accw[b] = 0.f;
     auto step = [&](auto I) {
       constexpr int i = decltype(I)::value;
-      int pos = lowest_bit(m);
-      m = drop_lowest(m);
-      const XT* xp = xb + pos * (64 * NB);
       float xv[NB];  // two or four columns with one read
-      if constexpr (!XH && (NB == 2 || NB == 4)) {
+      const XT* xp = nullptr;
+      if constexpr (FAR) {
+        put_lowest_bit(far[i & 3], m);
+      } else {
+        xp = xb + lowest_bit(m) * (64 * NB);
+      }
+      m = drop_lowest(m);
+      if constexpr (FAR) {
+        xv[0] = *(const __attribute__((address_space(3))) float*)(uintptr_t)far[i & 3];
+      } else if constexpr (!XH && (NB == 2 || NB == 4)) {
         typedef float xvec __attribute__((ext_vector_type(NB)));
         const xvec v = *reinterpret_cast<const xvec*>(xp);
 #pragma unroll
@@ -256,29 +281,38 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     if constexpr (MX) {
       if (tid < (1 << FW)) {
         const float mag = (float)(tid & ((1 << (FW - 1)) - 1));
-        reinterpret_cast<float*>(xs_raw)[tid] = (tid >> (FW - 1)) ? -mag : mag;
+        reinterpret_cast<float*>(mag_tab)[tid] = (tid >> (FW - 1)) ? -mag : mag;
       }
     }
-    for (int sgi = tid; sgi < nseg; sgi += kGemvThreads) {
+    if constexpr (FAR) {
+      for (int sgi = tid; sgi < nseg; sgi += kGemvThreads) xs[far_row(sgi >> 6, 255) + (sgi & 63)] = 0.f;
+    }
+    for (int sgi = tid; sgi < (FAR ? 0 : nseg); sgi += kGemvThreads) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) xs[(((sgi >> 6) * kXRows) * 64 + (sgi & 63)) * NB + b] = XS::put(0.f);
     }
     float rn[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) rn[b] = 1.f;
-    __shared__ float red[NB][kGemvWaves];
+    float* red;  // [NB][kGemvWaves]
+    if constexpr (FAR) {
+      red = reinterpret_cast<float*>(xs_raw + kFarRed);
+    } else {
+      __shared__ float red_[NB * kGemvWaves];
+      red = red_;
+    }
     auto finish_norm = [&](const float (&ss)[NB]) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         float t = wave_sum(ss[b]);
-        if (lane == 0) red[b][tid >> 6] = t;
+        if (lane == 0) red[b * kGemvWaves + (tid >> 6)] = t;
       }
       __syncthreads();
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         float t = 0.f;
 #pragma unroll
-        for (int w = 0; w < kGemvWaves; ++w) t += red[b][w];
+        for (int w = 0; w < kGemvWaves; ++w) t += red[b * kGemvWaves + w];
         rn[b] = 1.0f / sqrtf(t / (float)a.cols + a.eps);
       }
     };
@@ -307,7 +341,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
         const int col = piece * 8;
         if (piece < npiece) {
           const uint32_t gw4[4] = {gv[k].x, gv[k].y, gv[k].z, gv[k].w};
-          XT* dst = xs + x_index<NB>(col);  // the 8 columns of a piece lie in one word: 64 * NB apart
+          XT* dst = xs + (FAR ? far_index(col) : x_index<NB>(col));  // the 8 columns of a piece lie in one word: 64 * NB apart
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             const uint32_t wd[4] = {raw[k][b].x, raw[k][b].y, raw[k][b].z, raw[k][b].w};
@@ -345,7 +379,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
             v = bf16_to_f32(a.x[(size_t)b * a.cols + col]);
             if (a.gain) v = round_bf16(v * rn[b] * bf16_to_f32(a.gain[col]));
           }
-          xs[x_index<NB>(col) + b] = XS::put(v);
+          xs[(FAR ? far_index(col) : x_index<NB>(col)) + b] = XS::put(v);
         }
       }
     }
@@ -375,14 +409,22 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 }
 
 // LDS allowance of the instantiation, then the launch
-template <int T, int NB, bool MX, bool XH>
+template <int T, int NB, bool MX, bool XH, bool FAR = false>
 static int launch_gemv_instance(cas_ctx* ctx, const GemvArgs& a, int grid, size_t lds) {
   static LdsLimit lim;
-  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH>, lds, lim);
+  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH, FAR>, lds, lim);
   if (rc != CAS_OK) return rc;
-  hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX, XH>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
+  hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX, XH, FAR>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
   CAS_HIP(ctx, hipGetLastError());
   return CAS_OK;
+}
+
+// LDS bytes of the form with a block of 64 KB per chunk, 0 where it does not take the rows: more than 4096 columns, or so
+// few that the walk is nothing against the launch (a round of the small model, rows of 256 and 512, 322-326 us and 328-329
+// with it)
+static inline size_t gemv_far_bytes(const cas_ctx* ctx, int bw) {
+  const size_t lds = (size_t)((bw + 63) / 64) * kFarChunk;
+  return bw > 32 && lds <= (size_t)ctx->lds_max ? lds : 0;
 }
 
 // LDS bytes of the staged x

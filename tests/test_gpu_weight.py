@@ -361,3 +361,24 @@ def test_verification_gemm_at_the_ends_of_x(rows, cols, ncols):
             xn = xd.clone()
             xn[[k for k in range(ncols) if k != c]] = 0x7FC0
             np.testing.assert_array_equal(B.cas_gemm_verify(ctx, ew, xn).cpu().numpy()[c], y[c])
+
+
+@pytest.mark.parametrize("cols", [1024, 1025, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("keep,t", [(600, 4), (1000, 0), (3, 7), (250, 3)])
+def test_draft_gemv_of_one_column_whatever_form_its_x_has(env, cols, keep, t):
+    """The form for one column of 1025 to 4096 values and the ones beside it, words with all, some and no kept values:
+    the bits of the same column in company."""
+    torch, B, ctx = env
+    rows = 37
+    W = synth.weight_matrix(rows, cols, seed=41)
+    W[3, :] = 0x3F80                         # equal scores: the first columns are kept, the words behind them are empty
+    x = synth.activations(cols, 2, seed=42)
+    ew = B.cas_encode_weight(ctx, _dev(torch, W), keep, t)
+    pair = B.cas_gemv_draft(ctx, ew, _dev(torch, x))
+    one = B.cas_gemv_draft(ctx, ew, _dev(torch, x[:1]))
+    assert torch.equal(one[0], pair[0])
+    assert torch.equal(B.cas_gemv_draft(ctx, ew, _dev(torch, x[1:]))[0], pair[1])
+    ref = O.gemv_draft(O.encode_weight(W, keep, t), x[0])
+    wn, xn = np.linalg.norm(O.bf16_to_f64(W), axis=1), np.linalg.norm(O.bf16_to_f64(x[0]))
+    # fp32 sums of exact products: cols * 2^-24 |W| |x| at worst
+    assert (np.abs(one.cpu().numpy()[0] - ref) <= cols * 2.0 ** -24 * wn * xn).all()
