@@ -601,3 +601,39 @@ def test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok)
         B.cas_kv_append(ctx, kv, 0, 0, at(K), at(V))
         np.testing.assert_array_equal(kv.spec_pool.cpu().numpy(), spec)
         np.testing.assert_array_equal(kv.verif_pool.cpu().numpy(), verif)
+
+
+@pytest.mark.parametrize("vocab", [1, 2, 63, 65, 1024, 1025, 4095, 4096, 4097, 9001])
+def test_token_is_the_first_of_the_largest_logits(env, vocab):
+    """One launch up to 4096 tokens, two above: with every row of the head present several times, the first of equal
+    maxima; rows of infinities (logits that are NaN are never chosen, token 0 where all are)."""
+    from types import SimpleNamespace
+    torch, B, _ = env
+    hidden, n_q, n_kv, ffn = 256, 4, 2, 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    bits = lambda x: x.to(torch.bfloat16).view(torch.int16)  # noqa: E731
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    ctx = B.Context(workspace=torch.empty(8 << 20, dtype=torch.uint8, device="cuda"))
+    sh = SimpleNamespace(hidden=hidden, n_layers=1, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, ffn=ffn, vocab=vocab, rms_eps=1e-5)
+    dims = (("wqkv", (n_q + 2 * n_kv) * 128, hidden), ("wo", hidden, n_q * 128), ("wgu", 2 * ffn, hidden), ("wd", hidden, ffn))
+    layer = {n: B.cas_encode_weight(ctx, bits(rnd(r, c) * c ** -0.5), 600, 4) for n, r, c in dims}
+    layer.update(g_attn=bits(1 + 0.1 * rnd(hidden)), g_ffn=bits(1 + 0.1 * rnd(hidden)))
+    rows = rnd(max(1, vocab // 3), hidden)
+    rope = torch.from_numpy(synth.rope_table(64, 128, 500000.0)).cuda()
+    embed, g = bits(rnd(vocab, hidden)), bits(1 + 0.1 * rnd(hidden))
+    for special in (False, True):
+        head = bits(rows[torch.arange(vocab, device="cuda") % rows.shape[0]] * hidden ** -0.5)
+        if special:
+            head[:] = 0x7F80  # infinities of one sign: products of either sign, sums that are NaN
+        head = B.cas_encode_weight(ctx, head.contiguous(), 1000, 0)
+        model = B.Model(ctx, sh, [layer], head, embed, g, rope, max_cols=8)
+        kv = B.KVCache(ctx, 1, n_kv, n_pages=1, max_seqs=1, max_pages_per_seq=1)
+        B.cas_kv_set_len(kv, 0, 0)
+        out, logits = torch.full((3,), -7, dtype=torch.int32, device="cuda"), torch.empty((3, vocab), device="cuda")
+        tokens = torch.tensor([0, vocab // 2, vocab - 1], dtype=torch.int32, device="cuda")
+        B.cas_verify_step(ctx, model, kv, 0, tokens, 2, out, logits)
+        for lg, got in zip(logits.cpu().numpy(), out.cpu().numpy()):
+            ok = ~np.isnan(lg)
+            want = int(np.flatnonzero(ok & (lg == lg[ok].max()))[0]) if ok.any() else 0
+            assert got == want, (special, got, want)
