@@ -31,7 +31,7 @@ __host__ __device__ constexpr size_t wide_pre_bytes(int bw) {
 // every row are made at the start (pre).
 // Bound by memory, by what leaves the L2s and by the order in which loads come back.  28672 x 4096 with 508 columns: 1.47
 // GB from behind the L2s and 368 us, where blocks came part by part (runs of 115 bytes of spec) and the workgroups of a row
-// group went to different XCDs; 0.80 GB with these on one XCD, and less again with runs of KB blocks.  A prompt of 509 tokens
+// group went to different XCDs; 0.80 GB with these on one XCD, 0.59 with runs of KB blocks as well.  A prompt of 509 tokens
 // through four layers, ms: 3.88 before; workgroups of a row group on one XCD 3.57 for 3.77; runs of KB blocks 3.47; loads
 // issued on every path and no copy of a value in flight, so that no wait is for more than its own load, 3.41; five fragments
 // ahead instead of three 3.40; 368 us are 317 then.  X of two blocks ahead instead of one is the same, products of 16 columns 3.57.
