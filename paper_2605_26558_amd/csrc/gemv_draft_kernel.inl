@@ -72,6 +72,12 @@ __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the 
 // magnitudes lie there.  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 19.98 -> 19.59
 // ms, over shared exponents (8 layers) 6.31 -> 6.14, 4096 x 4096 at 25 % 5.02 -> 4.94 us.
 constexpr int kFarChunk = 64 << 10, kFarRed = 8 << 10, kFarTab = 16 << 10;  // bytes
+// Reads of x ahead of their products.  Left to itself the compiler waits for each read before it issues the next one,
+// which the waves of a full chip hide and those of a matrix of few rows do not, us, general form / FAR so / FAR with four
+// ahead: 1024 x 4096 4.38 / 4.81 / 4.32, 2048 x 4096 5.1 / 5.3 / 4.9, 5120 x 2560 7.4 / 7.8 / 7.0, 6144 x 4096 8.3 / 8.6 /
+// 7.9, 14336 x 4096 15.7 / 14.0 / 14.1, 28672 x 4096 27.8 / 25.8 / 24.9; over shared exponents 1024 x 4096 4.8 / 5.0 / 4.7,
+// 5120 x 2560 7.6 / 8.2 / 7.5, 28672 x 4096 31.7 / 29.6 / 28.9.  Eight ahead, or groups of four or eight, are within 3 %.
+constexpr int kFarAhead = 4;
 __device__ __forceinline__ int far_row(int chunk, int row) { return chunk * (kFarChunk / 4) + row * 64; }
 __device__ __forceinline__ int far_index(int col) { return far_row(col >> 11, col & 31) + ((col >> 5) & 63); }
 // the position of the lowest set bit of m (255 if there is none) in the second byte of addr
@@ -174,55 +180,85 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     for (int j = 0; j < FW; ++j) win[j] = __builtin_amdgcn_alignbit(w.d[j + 1], w.d[j], w.sh);
     uint32_t m = w.m;
     const XT* xb = xs + ((c.chunk * kXRows + 1) * 64 + lane) * NB;
-    uint32_t far[4];
+    uint32_t far[kFarAhead];
     if constexpr (FAR) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);  // LDS begins with x
+      for (int k = 0; k < kFarAhead; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);  // LDS begins with x
     }
     float accw[NB];  // shared-exponent form: unscaled sum of the lane's word
 #pragma unroll
     for (int b = 0; b < NB; ++b) accw[b] = 0.f;
-    auto step = [&](auto I) {
+    // a step, value I of the lane's word: the reads from LDS (xv: x at its position, fv: the magnitude of the shared-exponent
+    // form), then the product
+    auto fetch = [&](auto I, float (&xv)[NB], float& fv) {
       constexpr int i = decltype(I)::value;
-      float xv[NB];  // two or four columns with one read
-      const XT* xp = nullptr;
       if constexpr (FAR) {
-        put_lowest_bit(far[i & 3], m);
+        put_lowest_bit(far[i % kFarAhead], m);
+        m = drop_lowest(m);
+        xv[0] = *(const __attribute__((address_space(3))) float*)(uintptr_t)far[i % kFarAhead];
       } else {
-        xp = xb + lowest_bit(m) * (64 * NB);
-      }
-      m = drop_lowest(m);
-      if constexpr (FAR) {
-        xv[0] = *(const __attribute__((address_space(3))) float*)(uintptr_t)far[i & 3];
-      } else if constexpr (!XH && (NB == 2 || NB == 4)) {
-        typedef float xvec __attribute__((ext_vector_type(NB)));
-        const xvec v = *reinterpret_cast<const xvec*>(xp);
+        const XT* xp = xb + lowest_bit(m) * (64 * NB);
+        m = drop_lowest(m);
+        if constexpr (!XH && (NB == 2 || NB == 4)) {  // two or four columns with one read
+          typedef float xvec __attribute__((ext_vector_type(NB)));
+          const xvec v = *reinterpret_cast<const xvec*>(xp);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) xv[b] = v[b];
-      } else {
+          for (int b = 0; b < NB; ++b) xv[b] = v[b];
+        } else {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) xv[b] = XS::get(xp[b]);
+          for (int b = 0; b < NB; ++b) xv[b] = XS::get(xp[b]);
+        }
       }
+      // the field is the index of its signed magnitude; a lane past its last field reads neighbouring
+      // bits, always the index of a finite number, and multiplies it by the zero entry of the segment
+      if constexpr (MX) fv = *reinterpret_cast<const float*>(mag_tab + field_scaled<FW, i, 2>(win));
+    };
+    auto use = [&](auto I, const float (&xv)[NB], float fv) {
+      constexpr int i = decltype(I)::value;
       if constexpr (MX) {
-        // the field is the index of its signed magnitude; a lane past its last field reads neighbouring
-        // bits, always the index of a finite number, and multiplies it by the zero entry of the segment
-        const float f = *reinterpret_cast<const float*>(mag_tab + field_scaled<FW, i, 2>(win));
 #pragma unroll
-        for (int b = 0; b < NB; ++b) accw[b] = fmaf(f, xv[b], accw[b]);
+        for (int b = 0; b < NB; ++b) accw[b] = fmaf(fv, xv[b], accw[b]);
       } else {
         const float f = __uint_as_float(field_top<FW, i>(win));
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[b] = fmaf(f, xv[b], acc[b]);
       }
     };
+    auto step = [&](auto I) {
+      float xv[NB], fv = 0.f;
+      fetch(I, xv, fv);
+      use(I, xv, fv);
+    };
     // the first 16 set bits unconditionally, then pairs until every lane has run out
-    static_for<0, 16>(step);
+    if constexpr (FAR) {
+      float xv[16][NB], fv[16] = {};
+      static_for<0, 16 + kFarAhead>([&](auto I) {
+        constexpr int i = decltype(I)::value, done = i - kFarAhead;
+        if constexpr (i < 16) fetch(I, xv[i], fv[i]);
+        if constexpr (done >= 0) {
+          __builtin_amdgcn_sched_barrier(0);
+          use(std::integral_constant<int, done>{}, xv[done], fv[done]);
+        }
+      });
+    } else {
+      static_for<0, 16>(step);
+    }
     auto tail = [&](auto self, auto I) -> void {
       constexpr int i = decltype(I)::value;
       if constexpr (i < 32) {
         if (__builtin_amdgcn_ballot_w64(m != 0u)) {
-          step(std::integral_constant<int, i>{});
-          step(std::integral_constant<int, i + 1>{});
+          std::integral_constant<int, i + 1> I1;
+          if constexpr (FAR) {
+            float xv[2][NB], fv[2] = {};
+            fetch(I, xv[0], fv[0]);
+            fetch(I1, xv[1], fv[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            use(I, xv[0], fv[0]);
+            use(I1, xv[1], fv[1]);
+          } else {
+            step(I);
+            step(I1);
+          }
           self(self, std::integral_constant<int, i + 2>{});
         }
       }
