@@ -62,10 +62,17 @@ namespace cas {
 struct LdsLimit {
   std::atomic<size_t> granted[16];
 };
-inline int allow_lds(cas_ctx* ctx, const void* kernel, size_t lds, LdsLimit& lim) {
-  if (lds <= 48 * 1024) return CAS_OK;
+// from_zero: the kernel counts on its dynamic LDS beginning at address 0, that is on having no static LDS; one that
+// has some is refused.
+inline int allow_lds(cas_ctx* ctx, const void* kernel, size_t lds, LdsLimit& lim, bool from_zero = false) {
+  if (lds <= 48 * 1024 && !from_zero) return CAS_OK;
   std::atomic<size_t>& g = lim.granted[ctx->device & 15];
   if (lds > g.load(std::memory_order_relaxed)) {
+    if (from_zero) {
+      hipFuncAttributes fa;
+      CAS_HIP(ctx, hipFuncGetAttributes(&fa, kernel));
+      if (fa.sharedSizeBytes != 0) return CAS_ENOTSUP;
+    }
     CAS_HIP(ctx, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     g.store(lds, std::memory_order_relaxed);
   }

@@ -69,7 +69,8 @@ __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the 
 // 256 bytes from the next, so it is the second byte of the address, and the bit search writes it there itself: one
 // operation where the search and the address took two, of four cycles each (same bits).  A lane that has run out writes 255, the row
 // of zeros at the end of the block.  The 55 KB between are free: the sums of the norm and the table of
-// magnitudes lie there.  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 19.98 -> 19.59
+// magnitudes lie there, and not in static LDS: blocks begin at multiples of 64 KB only if the dynamic LDS begins at address
+// 0, which the launch checks (allow_lds).  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 19.98 -> 19.59
 // ms, over shared exponents (8 layers) 6.31 -> 6.14, 4096 x 4096 at 25 % 5.02 -> 4.94 us.
 constexpr int kFarChunk = 64 << 10, kFarRed = 8 << 10, kFarTab = 16 << 10;  // bytes
 // Reads of x ahead of their products.  Left to itself the compiler waits for each read before it issues the next one,
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     uint32_t far[kFarAhead];
     if constexpr (FAR) {
 #pragma unroll
-      for (int k = 0; k < kFarAhead; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);  // LDS begins with x
+      for (int k = 0; k < kFarAhead; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);
     }
     float accw[NB];  // shared-exponent form: unscaled sum of the lane's word
 #pragma unroll
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 template <int T, int NB, bool MX, bool XH, bool FAR = false>
 static int launch_gemv_instance(cas_ctx* ctx, const GemvArgs& a, int grid, size_t lds) {
   static LdsLimit lim;
-  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH, FAR>, lds, lim);
+  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH, FAR>, lds, lim, FAR);
   if (rc != CAS_OK) return rc;
   hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX, XH, FAR>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
   CAS_HIP(ctx, hipGetLastError());

@@ -3,6 +3,7 @@ No compute calls (no GPU needed)."""
 import ctypes
 import os
 import re
+import struct
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -154,3 +155,41 @@ def test_kv_geometry_of_both_exponent_modes_in_closed_form():
             assert d.spec_pool_bytes >= tiles * d.tile_spec_bytes and d.verif_pool_bytes >= tiles * d.tile_verif_bytes
     d.fmt = B.cas_fmt(600, 4, 1)
     assert lib.cas_kv_desc_init(ctypes.byref(d)) == B.CAS_ENOTSUP
+
+
+def _kernels(path):
+    """Name and static LDS of every kernel in the library: the metadata notes of its gfx950 code objects."""
+    import msgpack
+    blob = open(path, "rb").read()
+    for at in (m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob)):
+        pos = at + 32
+        for _ in range(struct.unpack_from("<Q", blob, at + 24)[0]):
+            off, size, n = struct.unpack_from("<QQQ", blob, pos)
+            target, pos = blob[pos + 24: pos + 24 + n], pos + 24 + n
+            if b"gfx950" not in target:
+                continue
+            elf = blob[at + off: at + off + size]
+            shoff, = struct.unpack_from("<Q", elf, 40)
+            shentsize, shnum = struct.unpack_from("<HH", elf, 58)
+            for i in range(shnum):
+                kind, = struct.unpack_from("<I", elf, shoff + i * shentsize + 4)
+                note, = struct.unpack_from("<Q", elf, shoff + i * shentsize + 24)
+                if kind != 7:  # SHT_NOTE
+                    continue
+                namesz, descsz, ntype = struct.unpack_from("<III", elf, note)
+                start = note + 12 + (namesz + 3) // 4 * 4
+                if ntype == 32:  # NT_AMDGPU_METADATA
+                    for k in msgpack.unpackb(elf[start: start + descsz])["amdhsa.kernels"]:
+                        yield k[".name"], k[".group_segment_fixed_size"]
+
+
+def test_the_draft_product_that_counts_on_lds_address_0_has_no_static_lds():
+    """The form for one column of up to 4096 values writes bit positions into the second byte of an LDS address, which
+    is x's only where the dynamic LDS begins at address 0."""
+    from paper_2605_26558_amd import binding as B
+    if not os.path.exists(B.LIB_PATH):
+        import __graft_entry__ as g
+        g.build()
+    far = {n: lds for n, lds in _kernels(B.LIB_PATH) if re.search(r"gemv_draft_kernelILi\dELi1ELb[01]ELb0ELb1E", n)}
+    assert len(far) == 16  # t = 0..7, raw and shared exponents
+    assert all(lds == 0 for lds in far.values()), far
