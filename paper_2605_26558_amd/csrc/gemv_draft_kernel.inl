@@ -456,12 +456,10 @@ static int launch_gemv_instance(cas_ctx* ctx, const GemvArgs& a, int grid, size_
   return CAS_OK;
 }
 
-// LDS bytes of the form with a block of 64 KB per chunk, 0 where it does not take the rows: more than 4096 columns, or so
-// few that the walk is nothing against the launch (a round of the small model, rows of 256 and 512, 322-326 us and 328-329
-// with it)
+// LDS bytes of the form with a block of 64 KB per chunk, 0 where they do not fit: more than 4096 columns
 static inline size_t gemv_far_bytes(const cas_ctx* ctx, int bw) {
   const size_t lds = (size_t)((bw + 63) / 64) * kFarChunk;
-  return bw > 32 && lds <= (size_t)ctx->lds_max ? lds : 0;
+  return lds <= (size_t)ctx->lds_max ? lds : 0;
 }
 
 // LDS bytes of the staged x

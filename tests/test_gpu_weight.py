@@ -363,10 +363,10 @@ def test_verification_gemm_at_the_ends_of_x(rows, cols, ncols):
             np.testing.assert_array_equal(B.cas_gemm_verify(ctx, ew, xn).cpu().numpy()[c], y[c])
 
 
-@pytest.mark.parametrize("cols", [1024, 1025, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("cols", [1, 63, 257, 1000, 1024, 1025, 2048, 2049, 4095, 4096, 4097])
 @pytest.mark.parametrize("keep,t", [(600, 4), (1000, 0), (3, 7), (250, 3)])
 def test_draft_gemv_of_one_column_whatever_form_its_x_has(env, cols, keep, t):
-    """The form for one column of 1025 to 4096 values and the ones beside it, words with all, some and no kept values:
+    """The form for one column of up to 4096 values and the one beside it, words with all, some and no kept values:
     the bits of the same column in company."""
     torch, B, ctx = env
     rows = 37
