@@ -556,12 +556,11 @@ def test_unary_draft_pass_refuses_a_layout_that_is_not_the_matrix_s(env, hidden,
 @pytest.mark.parametrize("keep,t,exp_mode", [(5, 0, 0), (117, 3, 0), (600, 5, 0), (631, 1, 0), (992, 7, 0), (996, 2, 0),
                                              (5, 1, 2), (250, 6, 2), (605, 3, 2), (992, 0, 2)])
 @pytest.mark.parametrize("pos0,ntok", [(0, 1), (3, 2), (14, 5), (62, 67), (47, 17)])
-def test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok):
+def test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok, heads=3):
     """One to 127 kept values, fields of any width, runs that begin and end inside the four rows of a wave and the
     sixteen of a workgroup: the rows of the run bit for bit like the oracle's, every other byte of the pools as before;
     and the same from vectors that lie at odd multiples of two bytes."""
     torch, B, ctx = env
-    heads = 3
     rng = np.random.default_rng(keep + 7 * pos0 + ntok)
     K, V = (synth.kv_tensor(ntok, heads, 128, seed=s) for s in (31, 32))
     K[0, 0, :] = 0x3F81                                              # equal magnitudes: the first columns are kept
@@ -601,6 +600,15 @@ def test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok)
         B.cas_kv_append(ctx, kv, 0, 0, at(K), at(V))
         np.testing.assert_array_equal(kv.spec_pool.cpu().numpy(), spec)
         np.testing.assert_array_equal(kv.verif_pool.cpu().numpy(), verif)
+
+
+@pytest.mark.parametrize("keep,t,exp_mode", [(5, 0, 0), (117, 3, 0), (605, 5, 0), (631, 1, 0), (992, 7, 0), (996, 2, 0),
+                                             (5, 1, 2), (250, 6, 2), (605, 3, 2), (992, 0, 2)])
+@pytest.mark.parametrize("pos0,ntok,heads", [(14, 5, 310), (62, 67, 24), (47, 17, 92)])
+def test_online_encoder_of_many_vectors_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok, heads):
+    """The same with enough vectors that a wave takes four of them."""
+    assert 2 * ntok * heads > 12 * env[0].cuda.get_device_properties(0).multi_processor_count
+    test_online_encoder_at_any_row_of_a_page(env, keep, t, exp_mode, pos0, ntok, heads)
 
 
 @pytest.mark.parametrize("vocab", [1, 2, 63, 65, 1024, 1025, 4095, 4096, 4097, 9001])
