@@ -28,7 +28,7 @@ struct VerifyArgs {
 };
 
 constexpr int kFewGroups = 300;          // row groups below which a matrix gets more waves per row group
-constexpr int kOneEach = 256;            // row groups up to which every CU has one at most
+constexpr int kOneEach = 256;            // row groups up to which every CU of the whole card has one at most
 constexpr int kNowhere = 0x7FFFF000;     // a byte offset past the records of every stream: reads as 0, fetches nothing
 // A block of 16 rows x 128 columns in LDS: [1 + 32 positions][16 rows][4 words] values, position p of the four bitmap
 // words of a row side by side (row 0 takes what lanes without a value left write).  Whatever positions the lanes of a
@@ -281,19 +281,22 @@ static int launch_q(cas_ctx* ctx, const VerifyArgs& a, int t) {
 }
 
 // Waves per row group = parts that a row's columns are cut into.  The choice depends on the shape of the WHOLE matrix
-// (not on the number of columns or on the block of rows a launch covers): it fixes the order in which a row's partial
-// sums are added, and a column must get the same bits in every call.  Four where the row groups fill the chip (a step
-// is then shortest and the barrier waits for the fewest waves) and for rows that one step of theirs covers.  Else more, so
-// that each CU has waves to switch between: sixteen where a CU has one group and no half of a step is wasted, unless there
-// are four steps or more.  5 columns, matrices read in turn, 4 / 8 / 16 waves, us: 4096 rows of 512 columns 5.0 / 5.4 /
-// 7.0, 1024 6.0 / 5.4 / 7.2, 2048 9.0 / 7.7 / 7.0, 3072 12.8 / 10.4 / 12.2, 4096 15.8 / 12.6 / 12.3, 6144 22.3 / 17.0 /
-// 16.4; 1024 rows of 1024 5.5 / 5.0 / 6.9, 2048 8.6 / 7.0 / 6.6, 3072 11.8 / 9.2 / 10.4, 4096 14.8 / 11.3 / 10.0, 6144
-// 21.3 / 15.8 / 13.5; 4700 rows (294 groups) of 512 5.0 / 6.9 / 12.2, 4096 19.3 / 18.8 / 21.4, 6144 27.6 / 26.1 / 28.9;
-// 8192 rows of 512 5.3 / 7.0 / 12.5, 4096 20.3 / 20.0 / 23.1.
+// (not on the number of columns, on the form of the weights, on the block of rows a launch covers or on how many CUs a
+// partition of the card has): it fixes the order in which a row's partial sums are added, and a column must get the same
+// bits in every call.  Four where the row groups fill the chip (a step is then shortest and the barrier waits for the fewest
+// waves) and for rows that one step of theirs covers.  Else more, so that each CU has waves to switch between: sixteen where
+// a CU has one group and rounding up to whole steps costs a ninth at most, that is no half of one, or one half of five or more.
+// Matrices read in turn, 4 / 8 / 16 waves, us, for 5 and for 20 columns: 4096 rows of 512 columns 4.4 / 5.4 / 7.1, 4.8 / 6.6 /
+// 9.4; 1024 6.6 / 5.8 / 7.7, 7.1 / 6.9 / 10.2; 2048 10.2 / 8.7 / 8.3, 11.2 / 10.4 / 10.4; 3072 13.6 / 11.6 / 12.8, 15.6 / 13.8 /
+// 16.3; 4096 17.1 / 14.2 / 13.0, 18.8 / 16.3 / 16.0; 7168 27.3 / 21.6 / 21.8, 31.3 / 26.2 / 27.5; 14336 49.7 / 38.9 / 35.2, 58.7 /
+// 47.5 / 43.8; 1024 rows of 4096 15.5 / 12.0 / 11.3, 19.0 / 15.7 / 15.0, of 5120 18.8 / 14.3 / 15.3, 23.0 / 18.8 / 20.5; 4700 rows
+// (294 groups) of 4096 20.9 / 20.2 / 22.4, 26.1 / 25.7 / 28.8; 6144 rows of 4096 21.4 / 21.1 / 22.9, 26.0 / 25.9 / 29.0.  Two
+// sides on which the line does not lie best: 1025 to 1536 columns with 17 output columns or more (4096 x 1536, 20: 9.3 / 10.5
+// / 10.4), and shared exponents from kFewGroups on (8192 x 4096, 5: 26.6 / 23.9 / 26.0; 8192 x 8192 48.5 / 43.5 / 46.3).
 static inline int verify_parts(int64_t rows, int64_t cols) {
   const int64_t groups = (rows + 15) / 16, steps8 = (cols + 1023) / 1024, steps16 = (cols + 2047) / 2048;
   if (groups >= kFewGroups || cols <= 512) return 4;
-  return groups <= kOneEach && 17 * steps16 < 10 * steps8 ? 16 : 8;
+  return groups <= kOneEach && 9 * steps16 <= 5 * steps8 ? 16 : 8;
 }
 
 template <int NB, bool MX>
