@@ -8,10 +8,10 @@
 // are contiguous runs of the three streams.  The lane walks the set bits of its word (kept: leading
 // bits from spec, low bits from lo) and then the clear bits (pruned: verbatim word) and scatters the
 // bf16 values into a tile in LDS that the waves share.  After a barrier each wave multiplies the 16
-// rows of its own 128 columns with the matching part of X by four 16x16x32 bf16 MFMA operations,
+// rows of its own 128 columns with the matching part of X by four 16x16x32 bf16 MFMA operations per 16 columns of X,
 // accumulating in fp32, while the next step's values go to a second tile.  Each output column uses
-// the same sequence of operations whatever the number of columns is.  The four partial tiles of a
-// workgroup are added in wave order through LDS.
+// the same sequence of operations whatever the number of columns is.  The partial tiles of a
+// workgroup's waves (4, 8 or 16) are added through LDS, two by two and the pairs in wave order.
 #include "gemm_verify_kernel.inl"
 
 namespace cas {
