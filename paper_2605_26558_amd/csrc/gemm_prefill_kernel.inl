@@ -23,8 +23,8 @@ __host__ __device__ constexpr size_t wide_pre_bytes(int bw) {
 
 // One workgroup per CU (8 waves of up to 256 registers).  A step takes a run of KB blocks of 128 columns, one block of
 // each of KB parts: thread (row r, word j) places its 32 values in a tile in LDS, each wave multiplies all rows of the tile
-// with its own columns n and n + 128 of X, which it reads from memory (no other wave of the workgroup needs
-// them), a running sum per part.  Two tiles: while one is multiplied the next one is filled, with one barrier per step; the
+// with its own NB blocks of 16 columns of X, n and n + 128, which it reads from memory (no other wave of the workgroup needs
+// them), a running sum per part.  NB = 1 where the launch has no more than 128 columns (see launch_wide_rt).  Two tiles: while one is multiplied the next one is filled, with one barrier per step; the
 // waves w and w + 4, which share a SIMD, take the two halves of a step in opposite order, so that the decode of
 // the one runs under the matrix operations of the other.  Steps come by KB parts at a time (part p of Q has the blocks
 // p, p + Q, ...); the sums of parts that are complete lie in LDS, the counts of kept values in front of every run of
@@ -35,9 +35,10 @@ __host__ __device__ constexpr size_t wide_pre_bytes(int bw) {
 // through four layers, ms: 3.88 before; workgroups of a row group on one XCD 3.57 for 3.77; runs of KB blocks 3.47; loads
 // issued on every path and no copy of a value in flight, so that no wait is for more than its own load, 3.41; five fragments
 // ahead instead of three 3.40; 368 us are 317 then.  X of two blocks ahead instead of one is the same, products of 16 columns 3.57.
-template <int T, int RT, bool MX>
+template <int T, int RT, int NB, bool MX>
 __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a, int Q) {
   constexpr int ROWS = 16 * RT, KB = 128 / ROWS;
+  static_assert(NB == 1 || NB == 2, "a wave has one block of columns, or two");
   static_assert(KB == 2 || KB == 4, "the fragments of X alternate between two sets");
   constexpr int BLOCK = RT * kBlockVals + 64 / KB;  // values from a block of 128 columns to the next: in other banks
   constexpr int TILE = KB * BLOCK;
@@ -152,20 +153,20 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
     return __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, (int)(xrow * 2), kRawBufferFlags);
   };
   const __amdgpu_buffer_rsrc_t rs_x0 = rsrc_x(xp0), rs_x1 = rsrc_x(act1 ? xp0 + 8 * xrow : xp0);
-  f32x4 C[KB][RT][2];  // running sums of KB parts
+  f32x4 C[KB][RT][NB];  // running sums of KB parts
 #pragma unroll
   for (int jb = 0; jb < KB; ++jb)
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) C[jb][i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < NB; ++nb) C[jb][i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   // sum of the parts before them, in LDS: touched once in per_part steps
-  f32x4* const S = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(pre) + wide_pre_bytes<RT>(a.bw)) + wv * (RT * 2 * 64) + lane;
-  uint4 x[4][2];  // of one block; zeros for one past the end of the rows, whose tile holds zeros
+  f32x4* const S = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(pre) + wide_pre_bytes<RT>(a.bw)) + wv * (RT * NB * 64) + lane;
+  uint4 x[4][NB];  // of one block; zeros for one past the end of the rows, whose tile holds zeros
   auto load_x = [&](int blk, int kq) {
     const int off = lane * 16 + blk * 4096;
     x[kq][0] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs_x0, off + kq * 1024, 0, 0));
-    x[kq][1] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs_x1, off + kq * 1024, 0, 0));
+    if constexpr (NB == 2) x[kq][1] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs_x1, off + kq * 1024, 0, 0));
   };
   auto product = [&](int st) {
     const int blk0 = step_word(st) >> 2, blk_next = step_word(st + 1) >> 2;
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
       for (int n = 0; n < N; ++n) {
         if (n + kAhead < N) load_a(n + kAhead);
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
           C[jb][n % RT][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               av[n % (kAhead + 1)], __builtin_bit_cast(bf16x8, x[n / RT][nb]), C[jb][n % RT][nb], 0, 0, 0);
         if (n % RT == RT - 1) load_x(after, n / RT);
@@ -197,8 +198,8 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
 #pragma unroll
       for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          f32x4& sum = S[(i * 2 + nb) * 64];
+        for (int nb = 0; nb < NB; ++nb) {
+          f32x4& sum = S[(i * NB + nb) * 64];
           f32x4 t = C[0][i][nb] + C[1][i][nb];
           if (st + 1 > per_part) t = sum + t;
           if constexpr (KB == 4) t += C[2][i][nb] + C[3][i][nb];
@@ -238,13 +239,13 @@ __global__ __launch_bounds__(kWideThreads) void gemm_prefill_kernel(VerifyArgs a
 
   // ---- S[i][nb][e]: row 16 i + 4 mq + e, column cb0 + 128 nb + 16 wv + mi
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
+  for (int nb = 0; nb < NB; ++nb) {
     const int col = cb0 + 128 * nb + 16 * wv + mi;
     if (col >= a.ncols) continue;
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
       const int orow = row0 + 16 * i + 4 * mq;
-      const f32x4 s = S[(i * 2 + nb) * 64];
+      const f32x4 s = S[(i * NB + nb) * 64];
       if (a.epi == 0) {
         float* y = a.Y + (size_t)col * a.yld + orow;
         if (orow + 4 <= a.rows) {
@@ -282,17 +283,17 @@ static inline bool wide_shape_ok(const cas_ctx* ctx, int64_t rows, int64_t cols,
   return rows > 0 && cols < 65536 && wide_lds_bytes<2>(bw) <= (size_t)ctx->lds_max;
 }
 
-template <int RT, bool MX>
-static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
+template <int RT, int NB, bool MX>
+static int launch_wide_nb(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
   const size_t lds = wide_lds_bytes<RT>(a.bw);
   const int64_t groups = (a.rows + 16 * RT - 1) / (16 * RT);
   const int64_t grid = (groups + kXcds - 1) / kXcds * kXcds * ((a.ncols + kWideCols - 1) / kWideCols);
 #define CAS_LAUNCH(TV)                                                                                            \
   case TV: {                                                                                                      \
     static LdsLimit lim;                                                                                          \
-    const int rc = allow_lds(ctx, (const void*)gemm_prefill_kernel<TV, RT, MX>, lds, lim);                        \
+    const int rc = allow_lds(ctx, (const void*)gemm_prefill_kernel<TV, RT, NB, MX>, lds, lim);                        \
     if (rc != CAS_OK) return rc;                                                                                  \
-    hipLaunchKernelGGL((gemm_prefill_kernel<TV, RT, MX>), dim3((unsigned)grid), dim3(kWideThreads), lds, ctx->stream, a, q); \
+    hipLaunchKernelGGL((gemm_prefill_kernel<TV, RT, NB, MX>), dim3((unsigned)grid), dim3(kWideThreads), lds, ctx->stream, a, q); \
   } break;
   switch (t) {
     CAS_LAUNCH(0) CAS_LAUNCH(1) CAS_LAUNCH(2) CAS_LAUNCH(3) CAS_LAUNCH(4) CAS_LAUNCH(5) CAS_LAUNCH(6) CAS_LAUNCH(7)
@@ -303,12 +304,23 @@ static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
   return CAS_OK;
 }
 
+// Up to 128 columns no wave has a second block: the form with two would read the first one's X twice and multiply it twice
+// for sums that nobody stores.  A prompt through one layer, us, two blocks / one: 8B shape 48 tokens 380 / 348, 64 390 /
+// 354, 128 413 / 366, over shared exponents 64 399 / 359, 128 414 / 368; 70B shape 64 1087 / 975, 128 1146 / 973; hidden 256 (two
+// layers) 64 140 / 135.  The last 256 columns of a longer prompt still take two blocks, whatever is left for them: which
+// form it is has to be the same for a whole launch (a branch in the kernel makes loads of X conditional, see the loops).
+template <int RT, bool MX>
+static int launch_wide_rt(cas_ctx* ctx, const VerifyArgs& a, int t, int q) {
+  return a.ncols > kWideCols / 2 ? launch_wide_nb<RT, 2, MX>(ctx, a, t, q) : launch_wide_nb<RT, 1, MX>(ctx, a, t, q);
+}
+
 // The parts are those the verification GEMM cuts the rows of the WHOLE matrix (a.yld rows) into.  Rows per
 // workgroup: 64, or 32 where 64 would leave a third of the CUs or more without a workgroup (or rows of more than some
-// 61000 columns leave no room for the sums of 64).  Before the present order of blocks, a prompt through one
-// layer, us, by this rule / with 32 rows throughout / with 64: 8B shape 65 tokens 466 / 482 / 633, 257 tokens
-// 717 / 746 / 825, 513 tokens 940 / 975 / 1070; 70B shape 65 tokens 1335 / 1315 / 1574, 257 tokens 2249 / 2674 /
-// 2244, 513 tokens 3784 / 4268 / 4007.
+// 61000 columns leave no room for the sums of 64).  A prompt through one layer, us, by this rule / with 32 rows
+// throughout / with 64: 8B shape 64 tokens 355 / 363 / 499, 256 tokens 455 / 468 / 621, 508 tokens 648 / 662 / 780, over shared
+// exponents 358 / 378 / 483, 443 / 463 / 625, 658 / 664 / 802; hidden 2048, 508 tokens 271 / 283 / 369.  Not everywhere the
+// best: 70B shape 64 tokens 976 / 948 / 1178, 256 tokens 1257 / 1216 / 1506 (896 workgroups of 64 rows are three and a half
+// turns of the CUs, 1792 of 32 seven), 300 tokens 1960 / 2056 / 1959; hidden 5120, 508 tokens 949 / 962 / 902.
 template <bool MX>
 static int launch_wide(cas_ctx* ctx, const VerifyArgs& a, int t) {
   const int q = verify_parts(a.yld, a.cols);

@@ -454,12 +454,11 @@ static ActLayout act_layout(const cas_model_cfg& c) {
 // chunk's keys and values are appended to the cache, and attention runs over runs of some columns, each of
 // which reads the positions before it from the cache and its own uncompressed, exactly as a pass of
 // these columns does.  A chunk therefore leaves the bits in the cache that such passes leave.
-// 8B-shaped, 4 layers, 508 tokens: 4.2 ms (43.5 with passes of 16 columns, whose 32 readings of all weights
-// and 31 unread rows of logits it saves).
+// 8B-shaped, 4 layers, 508 tokens: 2.6 ms; passes of 16 columns, 32 readings of all weights, take more than 20.
 constexpr int kPrefillChunk = 512;
-// Fewer columns go through the passes.  A chunk and passes of 16 columns for the same prompt, one layer, us: 8B shape 49
-// tokens 642 / 929, 33 tokens 632 / 685, 21 tokens 630 / 633; 70B shape 33 tokens 1744 / 3181; hidden 256 (two
-// layers) 33 tokens 271 / 332.  So a chunk is the faster way at every length it takes (and would be from some 20 on).
+// Fewer columns go through the passes.  A chunk and passes of 16 columns for the same prompt, one layer, us: 8B shape 48
+// tokens 350 / 531, 64 tokens 357 / 713; 70B shape 48 tokens 960 / 2503; hidden 256 (two layers) 48 tokens 135, 47 by passes
+// 225.  So a chunk is the faster way at every length it takes (and would be from some 30 on).
 constexpr int kPrefillMin = 48;
 
 struct ChunkLayout {

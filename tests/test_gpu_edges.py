@@ -187,7 +187,7 @@ def wide_models(env):
 @pytest.mark.parametrize("shape,form,kv_form,keep,t", [("a", "raw", "raw", 600, 4), ("b", "raw", "raw", 600, 4),
                                                        ("a", "raw", "raw", 1000, 0), ("b", "shared", "shared", 400, 3),
                                                        ("a", "shared", "raw", 600, 5), ("b", "unary", "raw", 600, 4)])
-@pytest.mark.parametrize("before,n", [(0, 47), (0, 48), (5, 63), (0, 130), (70, 257), (3, 513)])
+@pytest.mark.parametrize("before,n", [(0, 47), (0, 48), (5, 63), (9, 128), (0, 130), (70, 257), (3, 513)])
 def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, shape, form, kv_form, keep, t, before, n):
     torch, B, _ = env
     tokens = torch.from_numpy(synth.token_ids(before + n + 1, 301, seed=3)).cuda()
@@ -209,9 +209,9 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
 
 
 @pytest.mark.parametrize("form,kv_form,keep,t", [("raw", "raw", 600, 4), ("shared", "raw", 700, 1)])
-@pytest.mark.parametrize("before,n", [(0, 129), (70, 257), (3, 500)])
+@pytest.mark.parametrize("before,n", [(0, 113), (0, 128), (0, 129), (70, 257), (3, 500)])
 def test_prompt_in_chunks_over_all_numbers_of_parts(env, wide_models, form, kv_form, keep, t, before, n):
-    """Rows cut into 4, 8 and 16 parts, two column blocks, workgroups of 32 and of 64 rows: the bits of narrow passes."""
+    """Rows cut into 4, 8 and 16 parts, one and two column blocks, workgroups of 32 and of 64 rows: the bits of narrow passes."""
     test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, "c", form, kv_form, keep, t, before, n)
 
 
