@@ -70,8 +70,9 @@ __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the 
 // operation where the search and the address took two, of four cycles each (same bits).  A lane that has run out writes 255, the row
 // of zeros at the end of the block.  The 55 KB between are free: the sums of the norm and the table of
 // magnitudes lie there, and not in static LDS: blocks begin at multiples of 64 KB only if the dynamic LDS begins at address
-// 0, which the launch checks (allow_lds).  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 19.98 -> 19.59
-// ms, over shared exponents (8 layers) 6.31 -> 6.14, 4096 x 4096 at 25 % 5.02 -> 4.94 us.
+// 0, which the launch checks (allow_lds).  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 20.02 -> 19.59
+// ms, over shared exponents (8 layers) 6.30 -> 6.05 (both sides timed in turn); 4096 x 4096 at 25 %, a launch and its
+// round trips for the most part, stays at 5.0 us.
 constexpr int kFarChunk = 64 << 10, kFarRed = 8 << 10, kFarTab = 16 << 10;  // bytes
 // Reads of x ahead of their products.  Left to itself the compiler waits for each read before it issues the next one,
 // which the waves of a full chip hide and those of a matrix of few rows do not, us, general form / FAR so / FAR with four
@@ -467,17 +468,9 @@ static inline size_t gemv_lds_bytes(int bw, int batch, bool half) {
   return (half ? sizeof(uint16_t) : sizeof(float)) * (size_t)((bw + 63) / 64 * 64) * kXRows * batch;
 }
 
-// one or two workgroups per CU (two fill its 32 wave slots), whichever leaves the most loaded
-// CU with fewer units (rows, or gate/up row pairs); all of them are resident at once
-static inline int gemv_grid(const cas_ctx* ctx, int64_t units) {
-  int64_t best_load = 0;
-  int grid = 1;
-  for (int g = 1; g <= 2; ++g) {
-    const int64_t wgs = std::min<int64_t>((int64_t)ctx->num_cu * g, units);
-    const int64_t load = (units + wgs - 1) / wgs * g;
-    if (g == 1 || load < best_load) { best_load = load; grid = (int)wgs; }
-  }
-  return grid;
-}
+// One workgroup per CU (16 waves), or one per row (gate/up row pair) of a matrix that has fewer: every workgroup stages x
+// once, and with FAR the blocks of x fill the LDS.  Two per CU for every matrix took a 28672 x 4096 product alone from 28.8 to
+// 26.9 us in the form with x side by side, but rounds from 19.9 to 20.2 ms and from 8.35 to 9.05 with four columns.
+static inline int gemv_grid(const cas_ctx* ctx, int64_t units) { return (int)std::min<int64_t>(ctx->num_cu, units); }
 
 }  // namespace cas
