@@ -136,6 +136,8 @@ WIDE_SHAPES = {  # hidden, query heads, kv heads, feed-forward: 4 parts per row,
     "b": (200, 14, 2, 8200, 1200 << 10),
     # 16 parts (qkv, out), 4 (gate/up, 64 rows a workgroup, 89 groups of them), 8 (down); the last run of a row is a part of one
     "c": (3900, 16, 4, 2840, 1600 << 10),
+    # down: groups of rows for 64 a workgroup, whose LDS does not hold the counts of 61000 columns beside the sums
+    "d": (5472, 4, 2, 61000, 8 << 20, 256 << 20),
 }
 
 
@@ -150,7 +152,7 @@ def wide_models(env):
         key = (shape, form, kv_form, keep, t)
         if key in cache:
             return cache[key]
-        hidden, n_q, n_kv, ffn, small = WIDE_SHAPES[shape]
+        hidden, n_q, n_kv, ffn, small, *big = WIDE_SHAPES[shape]
         gen = torch.Generator(device="cuda")
         gen.manual_seed(17)
         bits = lambda x: x.to(torch.bfloat16).view(torch.int16)  # noqa: E731
@@ -164,7 +166,7 @@ def wide_models(env):
         embed = bits(rnd(301, hidden))
         rope = torch.from_numpy(synth.rope_table(640, 128, 500000.0)).cuda()
         out = []
-        for ws in (small, 64 << 20):
+        for ws in (small, *(big or [64 << 20])):
             ctx = B.Context(workspace=torch.empty(ws, dtype=torch.uint8, device="cuda"))
             enc = [{n: B.cas_encode_weight(ctx, w, keep, t) for n, w in L.items()} for L in raw]
             layers = [dict(e, g_attn=gains[2 * i], g_ffn=gains[2 * i + 1]) for i, e in enumerate(enc)]
@@ -213,6 +215,10 @@ def test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, sha
 def test_prompt_in_chunks_over_all_numbers_of_parts(env, wide_models, form, kv_form, keep, t, before, n):
     """Rows cut into 4, 8 and 16 parts, one and two column blocks, workgroups of 32 and of 64 rows: the bits of narrow passes."""
     test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, "c", form, kv_form, keep, t, before, n)
+
+
+def test_prompt_in_chunks_over_rows_too_long_for_64_in_a_workgroup(env, wide_models):
+    test_prompt_in_chunks_leaves_the_bits_of_narrow_passes(env, wide_models, "d", "raw", "raw", 600, 4, 0, 300)
 
 
 @pytest.mark.parametrize("ws", [4 << 20, 5 << 20, 6 << 20, 8 << 20])
@@ -614,7 +620,8 @@ def test_online_encoder_of_many_vectors_at_any_row_of_a_page(env, keep, t, exp_m
 @pytest.mark.parametrize("vocab", [1, 2, 63, 65, 1024, 1025, 4095, 4096, 4097, 9001])
 def test_token_is_the_first_of_the_largest_logits(env, vocab):
     """One launch up to 4096 tokens, two above: with every row of the head present several times, the first of equal
-    maxima; rows of infinities (logits that are NaN are never chosen, token 0 where all are)."""
+    maxima, infinite ones too; logits that are NaN beside numbers and infinities are never chosen, nor where all others
+    are -Inf; token 0 where all are NaN."""
     from types import SimpleNamespace
     torch, B, _ = env
     hidden, n_q, n_kv, ffn = 256, 4, 2, 256
@@ -630,10 +637,17 @@ def test_token_is_the_first_of_the_largest_logits(env, vocab):
     rows = rnd(max(1, vocab // 3), hidden)
     rope = torch.from_numpy(synth.rope_table(64, 128, 500000.0)).cuda()
     embed, g = bits(rnd(vocab, hidden)), bits(1 + 0.1 * rnd(hidden))
-    for special in (False, True):
+    for special in ("none", "all", "mixed", "one +", "one -"):
         head = bits(rows[torch.arange(vocab, device="cuda") % rows.shape[0]] * hidden ** -0.5)
-        if special:
+        if special == "all":
             head[:] = 0x7F80  # infinities of one sign: products of either sign, sums that are NaN
+        elif special == "mixed":  # NaN, infinities of either sign (that of a hidden value) and numbers
+            head[1::4] = 0x7F80
+            for i in range(4):
+                head[4 * i + 2::16, i] = 0x7F80
+        elif special != "none":  # all logits infinities of one sign, -Inf with one of the two, but for a NaN in front
+            head[:, 5] = 0x7F80 if special == "one +" else -0x80  # 0xFF80
+            head[0] = 0x7F80
         head = B.cas_encode_weight(ctx, head.contiguous(), 1000, 0)
         model = B.Model(ctx, sh, [layer], head, embed, g, rope, max_cols=8)
         kv = B.KVCache(ctx, 1, n_kv, n_pages=1, max_seqs=1, max_pages_per_seq=1)
@@ -641,7 +655,16 @@ def test_token_is_the_first_of_the_largest_logits(env, vocab):
         out, logits = torch.full((3,), -7, dtype=torch.int32, device="cuda"), torch.empty((3, vocab), device="cuda")
         tokens = torch.tensor([0, vocab // 2, vocab - 1], dtype=torch.int32, device="cuda")
         B.cas_verify_step(ctx, model, kv, 0, tokens, 2, out, logits)
-        for lg, got in zip(logits.cpu().numpy(), out.cpu().numpy()):
+        seen = logits.cpu().numpy()
+        if special == "mixed" and vocab >= 63:
+            assert np.isnan(seen).any() and np.isfinite(seen).any() and (seen == np.inf).any() and (seen == -np.inf).any()
+        if special.startswith("one"):
+            assert np.isnan(seen[:, 0]).all() and np.isinf(seen[:, 1:]).all() and (seen[:, 1:] == seen[:, 1:2]).all()
+            if special == "one +":
+                first = seen[:, 1:2]
+            else:
+                np.testing.assert_array_equal(seen[:, 1:2], -first)
+        for lg, got in zip(seen, out.cpu().numpy()):
             ok = ~np.isnan(lg)
             want = int(np.flatnonzero(ok & (lg == lg[ok].max()))[0]) if ok.any() else 0
             assert got == want, (special, got, want)

@@ -25,7 +25,7 @@ def _dev(torch, a):
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda()
 
 
-def gpu_model(torch, B, ctx, weights, keep, t, max_cols, kv_exp_mode=0):
+def gpu_model(torch, B, ctx, weights, keep, t, max_cols, kv_exp_mode=0, SHAPE=SHAPE):
     layers = []
     for lw in weights["layers"]:
         L = {n: B.cas_encode_weight(ctx, _dev(torch, lw[n]), keep, t) for n in ("wqkv", "wo", "wgu", "wd")}
@@ -200,6 +200,30 @@ def test_model_steps_on_shared_exponent_weights(env, kv_mx):
     plain, _ = _gpu_generate(torch, B, ctx, model, kv, gen_prompt, 16, 0)
     spec, stats = _gpu_generate(torch, B, ctx, model, kv, gen_prompt, 16, 4)
     assert spec == plain, (spec, plain)
+
+
+@pytest.mark.parametrize("form", ["raw", "shared"])
+@pytest.mark.parametrize("hidden,ffn", [(1030, 264), (1032, 700), (2051, 1025)])
+def test_draft_step_of_one_column_whatever_form_its_x_has(env, hidden, ffn, form):
+    """The one-column form of the draft product with the norm, the residual add and SwiGLU fused, rows of one chunk and
+    two, multiples of 8 and not (x, gain and the sums of the norm are staged in another way): logits of the oracle."""
+    torch, B, ctx = env
+    shape = synth.LlamaShape("ragged", hidden, 1, 4, 2, 128, ffn, 300)
+    keep, t = 600, 4
+    weights = synth.model_weights(shape, seed=hidden)
+    model, kv = gpu_model(torch, B, ctx, weights, keep, t, max_cols=8, SHAPE=shape)
+    if form == "shared":
+        layers, head = model._keep[0], model._keep[1]
+        for which, name in enumerate(("wqkv", "wo", "wgu", "wd")):
+            model.use_mx(0, which, B.cas_mx_encode(ctx, layers[0][name]))
+        model.use_mx(-1, 0, B.cas_mx_encode(ctx, head))
+    om = O.OracleModel(shape, weights, synth.rope_table(MAX_POS, 128, shape.rope_theta), w_keep=keep, w_t=t, kv_keep=keep,
+                       kv_t=t, exp_mode="mx" if form == "shared" else "raw")
+    cur, nxt = torch.tensor([7], dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    logits = torch.empty((1, 300), dtype=torch.float32, device="cuda")
+    B.cas_draft_step(ctx, model, kv, 0, cur, 0, nxt, logits)
+    ref, _ = om.forward([7], draft=True, extra_kv=[(np.zeros((0, 2, 128), np.uint16),) * 2])
+    _check_logits(logits.cpu().numpy().astype(np.float64), ref, _logit_tol(om, True), f"draft, hidden {hidden}, {form}")
 
 
 def _gpu_generate(torch, B, ctx, model, kv, prompt, n_new, k):

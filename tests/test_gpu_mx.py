@@ -101,6 +101,25 @@ def test_gemv_draft_mx_matches_oracle(env, rows, cols, keep, t, special):
     assert err.max() < 2e-5, err.max()
 
 
+@pytest.mark.parametrize("cols", [1, 257, 1025, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("keep,t", [(600, 0), (1000, 1), (600, 3), (3, 4), (600, 7), (1000, 7)])
+def test_gemv_draft_mx_of_one_column_whatever_form_its_x_has(env, cols, keep, t):
+    """The form for up to 4096 columns, one chunk and two, with tables of 4 to 512 magnitudes, words with all, some and no
+    kept values, x from an aligned address and from the middle of a word (which is staged value by value)."""
+    torch, B, ctx = env
+    W = _matrix(37, cols, False, seed=cols + t)
+    x = synth.activations(cols, 1, seed=12)
+    mw = B.cas_mx_encode(ctx, B.cas_encode_weight(ctx, _dev(torch, W), keep, t))
+    y = B.cas_gemv_draft_mx(ctx, mw, _dev(torch, x))
+    odd = torch.empty(cols + 1, dtype=torch.int16, device="cuda")
+    odd[1:] = _dev(torch, x)[0]
+    assert torch.equal(B.cas_gemv_draft_mx(ctx, mw, odd[1:].view(1, cols)), y)
+    ref = O.gemv_draft_mx(O.to_mx(O.encode_weight(W, keep, t)), x[0])
+    tol = np.linalg.norm(O.bf16_to_f64(W), axis=1) * np.linalg.norm(O.bf16_to_f64(x[0])) + 1e-30
+    # fp32 sums of exact products, a word at a time: cols * 2^-24 |W| |x| at worst, twice that with the scaling of each word
+    assert (np.abs(y.cpu().numpy() - ref) <= 2 * cols * 2.0 ** -24 * tol).all()
+
+
 def test_gemv_draft_mx_tiny_magnitudes(env):
     """Blocks whose shared exponent is near the bottom of the range: the per-block scale is a
     subnormal float and must not be flushed."""
