@@ -58,11 +58,11 @@ constexpr int kBlockVals = 33 * kPosPitch;
 // Loads run half a step ahead: the pruned values of a step are fetched while its kept values are placed, the kept
 // fields of the next step while the pruned values are placed; X of a step before its decode.  All are issued on every
 // path: where a load may or may not have been issued, the wait for an older one waits for it as well.
-// Measured, matrices read from HBM, 1 / 7 / 20 columns, us (before: private tiles in column order, X through LDS): 28672
-// x 4096 59 / 67 / 84 (71 / 85 / 116), 4096 x 14336 35 / 36 / 45 (48 / 48 / 52), 6144 x 4096 20.7 / 21.1 / 26.0 (22.5 /
-// 25.4 / 34.0), 4096 x 4096 13.2 / 13.6 / 17.0 (15.9 / 17.4 / 20.4), 128256 x 4096 254 / 263 / 341 (308 / 332 / 422),
-// 11003 x 5001 39 / 42 / 53 (43 / 50 / 62).  28672 x 4096 with 7 columns is 3.7 TB/s; vector issue takes half of that
-// time, and the loads of X (sixteen columns, 64 bytes of each) the 8 us between 1 and 7 columns.  Tried: lanes side by
+// Measured, matrices read from HBM in turn, 1 / 7 / 20 columns, us: 28672 x 4096 59 / 63 / 79, 4096 x 14336 33 / 34 / 43, 6144 x
+// 4096 20.6 / 21.1 / 25.3, 4096 x 4096 13.1 / 13.3 / 15.8, 128256 x 4096 244 / 261 / 329 (private tiles in column order and X
+// through LDS: 71 / 85 / 116, 48 / 48 / 52, 22.5 / 25.4 / 34.0, 15.9 / 17.4 / 20.4, 308 / 332 / 422), 11003 x 5001 37 / 40 / 52
+// (43 / 50 / 62).  28672 x 4096 with 7 columns is 4.0 TB/s; vector issue takes half of that
+// time, and the loads of X (sixteen columns, 64 bytes of each) the 4 us between 1 and 7 columns.  Tried: lanes side by
 // side reading a column together and handing the pieces on through ds_bpermute, the same (67.5 / 82); one tile and a
 // second barrier instead of two tiles (five workgroups per CU instead of four), the same within 2 %.
 template <int T, int Q, int NB, bool MX = false>
