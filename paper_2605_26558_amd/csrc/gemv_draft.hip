@@ -23,7 +23,9 @@ namespace cas {
 template <int T, int NB>
 static int launch_nb(cas_ctx* ctx, const GemvArgs& a, int grid) {
   if constexpr (NB == 1) {
-    if (const size_t far = gemv_far_bytes(ctx, a.bw)) return launch_gemv_instance<T, 1, false, false, true>(ctx, a, grid, far);
+    const int far = gemv_far_chunks(ctx, a.bw);
+    if (far == 1) return launch_gemv_instance<T, 1, false, false, 1>(ctx, a, grid, gemv_far_bytes(1));
+    if (far == 2) return launch_gemv_instance<T, 1, false, false, 2>(ctx, a, grid, gemv_far_bytes(2));
   }
   const size_t lds = gemv_lds_bytes(a.bw, NB, false);
   if (lds <= (size_t)ctx->lds_max) return launch_gemv_instance<T, NB, false, false>(ctx, a, grid, lds);

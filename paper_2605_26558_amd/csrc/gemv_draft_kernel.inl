@@ -65,22 +65,23 @@ __device__ __forceinline__ int x_index(int col) {  // index of x[col][0] in the 
   const int w = col >> 5;
   return (((w >> 6) * kXRows + 1 + (col & 31)) * 64 + (w & 63)) * NB;
 }
-// FAR: one column of up to 4096 values, a block of 64 KB per chunk that begins at a multiple of 64 KB.  A position lies
-// 256 bytes from the next, so it is the second byte of the address, and the bit search writes it there itself: one
-// operation where the search and the address took two, of four cycles each (same bits).  A lane that has run out writes 255, the row
-// of zeros at the end of the block.  The 55 KB between are free: the sums of the norm and the table of
-// magnitudes lie there, and not in static LDS: blocks begin at multiples of 64 KB only if the dynamic LDS begins at address
+// FAR: one column of up to 4096 values, FAR chunks of 2048.  A position lies 256 bytes from the next, so it is the second
+// byte of the address, and the bit search writes it there itself: one operation where the search and the address took two,
+// of four cycles each (same bits).  The 8 KB of the second chunk lie behind those of the first, at an offset in the
+// instruction: the two items in flight of a wave are always one of each.  A lane that has run out writes 255, a row of zeros
+// that each chunk has at that distance.  What lies between is free: the sums of the norm and the table of
+// magnitudes lie there, and not in static LDS: the second byte is the position only if the dynamic LDS begins at address
 // 0, which the launch checks (allow_lds).  28672 x 4096 and its like are three quarters of a draft pass: a round of the 8B shape 20.02 -> 19.59
 // ms, over shared exponents (8 layers) 6.30 -> 6.05 (both sides timed in turn); 4096 x 4096 at 25 %, a launch and its
 // round trips for the most part, stays at 5.0 us.
-constexpr int kFarChunk = 64 << 10, kFarRed = 8 << 10, kFarTab = 16 << 10;  // bytes
+constexpr int kFarZero = 64 << 10, kFarChunk = 8 << 10, kFarRed = 24 << 10, kFarTab = 32 << 10;  // bytes
 // Reads of x ahead of their products.  Left to itself the compiler waits for each read before it issues the next one,
 // which the waves of a full chip hide and those of a matrix of few rows do not, us, general form / FAR so / FAR with four
 // ahead: 1024 x 4096 4.38 / 4.81 / 4.32, 2048 x 4096 5.1 / 5.3 / 4.9, 5120 x 2560 7.4 / 7.8 / 7.0, 6144 x 4096 8.3 / 8.6 /
 // 7.9, 14336 x 4096 15.7 / 14.0 / 14.1, 28672 x 4096 27.8 / 25.8 / 24.9; over shared exponents 1024 x 4096 4.8 / 5.0 / 4.7,
 // 5120 x 2560 7.6 / 8.2 / 7.5, 28672 x 4096 31.7 / 29.6 / 28.9.  Eight ahead, or groups of four or eight, are within 3 %.
 constexpr int kFarAhead = 4;
-__device__ __forceinline__ int far_row(int chunk, int row) { return chunk * (kFarChunk / 4) + row * 64; }
+__device__ __forceinline__ int far_row(int chunk, int row) { return chunk * (kFarChunk / 4) + row * 64; }  // of x
 __device__ __forceinline__ int far_index(int col) { return far_row(col >> 11, col & 31) + ((col >> 5) & 63); }
 // the position of the lowest set bit of m (255 if there is none) in the second byte of addr
 __device__ __forceinline__ void put_lowest_bit(uint32_t& addr, uint32_t m) {
@@ -108,12 +109,12 @@ struct XStage<true> {
 // descriptor as well).  The table of a small T is long enough for gathers of a wave to meet in a bank, which eats
 // some of the gain but not all: 28672 x 4096 33.1 -> 30.4 us at T = 0 (2.3 conflict cycles per LDS instruction),
 // 33.6 -> 28.7 at T = 2 (1.6), 33.6 -> 28.0 at T = 4 (none); 4096 x 4096 7.1 -> 7.1, 6.6, 6.5.
-template <int T, int NB, bool MX, bool XH, bool FAR = false>
+template <int T, int NB, bool MX, bool XH, int FAR = 0>
 __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   constexpr int FW = MX ? 9 - T : 16 - T;
   using XS = XStage<XH>;
   using XT = typename XS::type;
-  static_assert(!FAR || (NB == 1 && !XH), "one column as fp32");
+  static_assert(FAR == 0 || (FAR <= 2 && NB == 1 && !XH), "one column as fp32, a chunk for each item in flight");
   extern __shared__ __attribute__((aligned(16))) uint8_t xs_raw[];
   // shared-exponent form: the table of signed magnitudes in front of x
   uint8_t* const mag_tab = xs_raw + (FAR ? kFarTab : 0);
@@ -176,16 +177,17 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = gate[b] = 0.f;
 
-  auto compute = [&](const Cursor& c, const Window<FW>& w) {
+  // ITEM: which of the two items in flight
+  auto compute = [&](auto ITEM, const Cursor& c, const Window<FW>& w) {
     uint32_t win[FW];
 #pragma unroll
     for (int j = 0; j < FW; ++j) win[j] = __builtin_amdgcn_alignbit(w.d[j + 1], w.d[j], w.sh);
     uint32_t m = w.m;
     const XT* xb = xs + ((c.chunk * kXRows + 1) * 64 + lane) * NB;
     uint32_t far[kFarAhead];
-    if constexpr (FAR) {
+    if constexpr (FAR > 0) {
 #pragma unroll
-      for (int k = 0; k < kFarAhead; ++k) far[k] = (uint32_t)(c.chunk * kFarChunk + lane * 4);
+      for (int k = 0; k < kFarAhead; ++k) far[k] = (uint32_t)(lane * 4);
     }
     float accw[NB];  // shared-exponent form: unscaled sum of the lane's word
 #pragma unroll
@@ -194,10 +196,11 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
     // form), then the product
     auto fetch = [&](auto I, float (&xv)[NB], float& fv) {
       constexpr int i = decltype(I)::value;
-      if constexpr (FAR) {
+      if constexpr (FAR > 0) {
         put_lowest_bit(far[i % kFarAhead], m);
         m = drop_lowest(m);
-        xv[0] = *(const __attribute__((address_space(3))) float*)(uintptr_t)far[i % kFarAhead];
+        constexpr int chunk = FAR == 2 ? decltype(ITEM)::value : 0;
+        xv[0] = ((const __attribute__((address_space(3))) float*)(uintptr_t)far[i % kFarAhead])[far_row(chunk, 0)];
       } else {
         const XT* xp = xb + lowest_bit(m) * (64 * NB);
         m = drop_lowest(m);
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
       use(I, xv, fv);
     };
     // the first 16 set bits unconditionally, then pairs until every lane has run out
-    if constexpr (FAR) {
+    if constexpr (FAR > 0) {
       float xv[16][NB], fv[16] = {};
       static_for<0, 16 + kFarAhead>([&](auto I) {
         constexpr int i = decltype(I)::value, done = i - kFarAhead;
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
       if constexpr (i < 32) {
         if (__builtin_amdgcn_ballot_w64(m != 0u)) {
           std::integral_constant<int, i + 1> I1;
-          if constexpr (FAR) {
+          if constexpr (FAR > 0) {
             float xv[2][NB], fv[2] = {};
             fetch(I, xv[0], fv[0]);
             fetch(I1, xv[1], fv[1]);
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
         reinterpret_cast<float*>(mag_tab)[tid] = (tid >> (FW - 1)) ? -mag : mag;
       }
     }
-    if constexpr (FAR) {
+    if constexpr (FAR > 0) {
       for (int sgi = tid; sgi < nseg; sgi += kGemvThreads) xs[far_row(sgi >> 6, 255) + (sgi & 63)] = 0.f;
     }
     for (int sgi = tid; sgi < (FAR ? 0 : nseg); sgi += kGemvThreads) {
@@ -333,7 +336,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) rn[b] = 1.f;
     float* red;  // [NB][kGemvWaves]
-    if constexpr (FAR) {
+    if constexpr (FAR > 0) {
       red = reinterpret_cast<float*>(xs_raw + kFarRed);
     } else {
       __shared__ float red_[NB * kGemvWaves];
@@ -437,30 +440,36 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_draft_kernel(GemvArgs a) {
   while (true) {
     uint32_t m2 = load_bm(cb); cb.advance(nchunk, nwaves, pair);
     issue(ci, m1, w1); ci.advance(nchunk, nwaves, pair);
-    compute(cc, w0); cc.advance(nchunk, nwaves, pair);
+    compute(std::integral_constant<int, 0>{}, cc, w0); cc.advance(nchunk, nwaves, pair);
     if (cc.row >= a.rows) break;
     m1 = load_bm(cb); cb.advance(nchunk, nwaves, pair);
     issue(ci, m2, w0); ci.advance(nchunk, nwaves, pair);
-    compute(cc, w1); cc.advance(nchunk, nwaves, pair);
+    compute(std::integral_constant<int, 1>{}, cc, w1); cc.advance(nchunk, nwaves, pair);
     if (cc.row >= a.rows) break;
   }
 }
 
 // LDS allowance of the instantiation, then the launch
-template <int T, int NB, bool MX, bool XH, bool FAR = false>
+template <int T, int NB, bool MX, bool XH, int FAR = 0>
 static int launch_gemv_instance(cas_ctx* ctx, const GemvArgs& a, int grid, size_t lds) {
   static LdsLimit lim;
-  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH, FAR>, lds, lim, FAR);
+  const int rc = allow_lds(ctx, (const void*)gemv_draft_kernel<T, NB, MX, XH, FAR>, lds, lim, FAR > 0);
   if (rc != CAS_OK) return rc;
   hipLaunchKernelGGL((gemv_draft_kernel<T, NB, MX, XH, FAR>), dim3(grid), dim3(kGemvThreads), lds, ctx->stream, a);
   CAS_HIP(ctx, hipGetLastError());
   return CAS_OK;
 }
 
-// LDS bytes of the form with a block of 64 KB per chunk, 0 where they do not fit: more than 4096 columns
-static inline size_t gemv_far_bytes(const cas_ctx* ctx, int bw) {
-  const size_t lds = (size_t)((bw + 63) / 64) * kFarChunk;
-  return lds <= (size_t)ctx->lds_max ? lds : 0;
+// Chunks of the form with x far apart, 0 where it does not take the rows, and its LDS bytes: 64 KB, and 8 for a second chunk,
+// so that two workgroups, of two streams, share a CU.  With 64 KB per chunk they did not.  us a product, two / three streams with
+// a chain of them each, 64 KB per chunk / now / the form with x side by side: 4096 x 4096 5.4 / 5.1 / 5.3, 5.5 / 4.5 / 4.7; 28672
+// x 4096 24.2 / 21.9 / 22.8, 24.8 / 21.5 / 22.9, over shared exponents 23.9 / 17.9 / 20.2, 25.0 / 19.6 / 21.3; 1024 x 1024 2.85 /
+// 2.83 / 2.89, 2.15 / 2.13 / 2.18; one stream 26.3 / 26.5 / 28.4 (28672 x 4096).  More than two chunks would need as many items of a
+// wave in flight, or an operation for the address.
+static inline size_t gemv_far_bytes(int chunks) { return kFarZero + (size_t)(chunks - 1) * kFarChunk; }
+static inline int gemv_far_chunks(const cas_ctx* ctx, int bw) {
+  const int chunks = (bw + 63) / 64;
+  return chunks <= 2 && gemv_far_bytes(2) <= (size_t)ctx->lds_max ? chunks : 0;
 }
 
 // LDS bytes of the staged x
@@ -469,7 +478,7 @@ static inline size_t gemv_lds_bytes(int bw, int batch, bool half) {
 }
 
 // One workgroup per CU (16 waves), or one per row (gate/up row pair) of a matrix that has fewer: every workgroup stages x
-// once, and with FAR the blocks of x fill the LDS.  Two per CU for every matrix took a 28672 x 4096 product alone from 28.8 to
+// once.  Two per CU for every matrix took a 28672 x 4096 product alone from 28.8 to
 // 26.9 us in the form with x side by side, but rounds from 19.9 to 20.2 ms and from 8.35 to 9.05 with four columns.
 static inline int gemv_grid(const cas_ctx* ctx, int64_t units) { return (int)std::min<int64_t>(ctx->num_cu, units); }
 

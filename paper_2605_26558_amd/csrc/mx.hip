@@ -187,11 +187,12 @@ int launch_gemv_draft_mx_fused(cas_ctx* ctx, const cas_mxdesc& mx, const void* d
   if (lds > (size_t)ctx->lds_max) return CAS_ENOTSUP;
   const int grid = gemv_grid(ctx, epi == 2 ? d.rows / 2 : d.rows);  // a gate/up row pair stays in one wave
   a.nwaves = grid * kGemvWaves;
-  const size_t far = gemv_far_bytes(ctx, d.bw);
+  const int far = gemv_far_chunks(ctx, d.bw);
 #define CAS_T(TV)                                                                                   \
   case TV:                                                                                          \
-    return far ? launch_gemv_instance<TV, 1, true, false, true>(ctx, a, grid, far)                  \
-               : launch_gemv_instance<TV, 1, true, false>(ctx, a, grid, lds);
+    return far == 1   ? launch_gemv_instance<TV, 1, true, false, 1>(ctx, a, grid, gemv_far_bytes(1))   \
+           : far == 2 ? launch_gemv_instance<TV, 1, true, false, 2>(ctx, a, grid, gemv_far_bytes(2))   \
+                      : launch_gemv_instance<TV, 1, true, false>(ctx, a, grid, lds);
   switch (d.t) {
     CAS_T(0) CAS_T(1) CAS_T(2) CAS_T(3) CAS_T(4) CAS_T(5) CAS_T(6) CAS_T(7)
   }

@@ -190,6 +190,6 @@ def test_the_draft_product_that_counts_on_lds_address_0_has_no_static_lds():
     if not os.path.exists(B.LIB_PATH):
         import __graft_entry__ as g
         g.build()
-    far = {n: lds for n, lds in _kernels(B.LIB_PATH) if re.search(r"gemv_draft_kernelILi\dELi1ELb[01]ELb0ELb1E", n)}
-    assert len(far) == 16  # t = 0..7, raw and shared exponents
+    far = {n: lds for n, lds in _kernels(B.LIB_PATH) if re.search(r"gemv_draft_kernelILi\dELi1ELb[01]ELb0ELi[12]E", n)}
+    assert len(far) == 32  # t = 0..7, raw and shared exponents, one chunk of x and two
     assert all(lds == 0 for lds in far.values()), far
