@@ -294,7 +294,11 @@ static int launch_q(cas_ctx* ctx, const VerifyArgs& a, int t) {
 // 47.5 / 43.8; 1024 rows of 4096 15.5 / 12.0 / 11.3, 19.0 / 15.7 / 15.0, of 5120 18.8 / 14.3 / 15.3, 23.0 / 18.8 / 20.5; 4700 rows
 // (294 groups) of 4096 20.9 / 20.2 / 22.4, 26.1 / 25.7 / 28.8; 6144 rows of 4096 21.4 / 21.1 / 22.9, 26.0 / 25.9 / 29.0.  Two
 // sides on which the line does not lie best: 1025 to 1536 columns with 17 output columns or more (4096 x 1536, 20: 9.3 / 10.5
-// / 10.4), and shared exponents from kFewGroups on (8192 x 4096, 5: 26.6 / 23.9 / 26.0; 8192 x 8192 48.5 / 43.5 / 46.3).
+// / 10.4), and shared exponents from kFewGroups on (8192 x 4096, 5: 26.6 / 23.9 / 26.0; 8192 x 8192 48.5 / 43.5 / 46.3).  Sixteen
+// waves (128 registers each) are all that a CU holds of this kernel, two workgroups of eight the same: where several streams
+// verify at once, eight leave more to switch between.  us a product, one / two / three streams, 16 parts: 4096 x 4096 13.7 / 11.2 /
+// 11.5, with 8 14.1 / 9.5 / 9.5; 1024 x 4096 11.3 / 6.0 / 4.4, with 8 12.4 / 7.2 / 5.2.  A pass
+// that verifies several sequences is one launch, so the line is that of one stream.
 static inline int verify_parts(int64_t rows, int64_t cols) {
   const int64_t groups = (rows + 15) / 16, steps8 = (cols + 1023) / 1024, steps16 = (cols + 2047) / 2048;
   if (groups >= kFewGroups || cols <= 512) return 4;
